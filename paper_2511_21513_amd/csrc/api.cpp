@@ -621,17 +621,27 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
     if (variant == 5 && ctx->lut_bits > 5) variant = 4; // the pipelined sweep C holds 32-entry tables; same tiling otherwise
     if (a->scale_mode == 3) variant = 1;                // groups over the key axis: the single-launch kernel
     if (variant == 3 && a->scale_mode == 2) variant = 1; // the split-key single launch takes per-tensor / per-head parameters
-    const int rows_per_block = comparator ? 128 : fwd_rows_per_block(variant);
-    p.n_qtiles = fwd_row_tiles(p.row_lo, p.L, rows_per_block);
-    p.n_chunks = (p.Lk + rows_per_block - 1) / rows_per_block;
-    std::memcpy(p.lut, ctx->lut, 64);
-    p.dbg_row_max = a->dbg_row_max; p.dbg_row_sum = a->dbg_row_sum; p.dbg_acc = a->dbg_acc;
-
     // Few query rows against many keys: the split-key kernels (all query heads of a KV head, times
     // the query rows, packed into one MFMA operand of at most 31 rows).
     const int64_t packed_rows = (int64_t)p.group * p.L;
     const bool decode_ok = !comparator && stage == 0 && a->scale_mode < 2 && packed_rows <= 31 && (int64_t)a->B * a->Hkv <= 65535;
     const bool decode = decode_ok && (ctx->variant == 9 || ctx->variant == 10 || (ctx->variant == 0 && p.Lk >= 1024));
+
+    // Few query tiles against many keys: the tiled kernels with the keys split, where their cost model beats that of the
+    // single launch and the partial accumulators can be had
+    KeySplit ks = {0, 0};
+    const bool automatic = ctx->variant == 0 || ctx->variant == 9 || ctx->variant == 10;
+    if (automatic && !decode && (variant == 1 || variant == 3) && !comparator && stage == 0 && !rm.no_alloc && ctx->lut_bits <= 5 && a->scale_mode <= 2) {
+        ks = fwd_key_split(variant, a->B, a->Hq, a->L, p.Lk, a->d, a->causal);
+        const size_t rows = (size_t)a->B * a->Hq * a->L, n_chunks = ((size_t)p.Lk + 127) / 128;
+        if (ks.c > 0 && get_ws(rows * ((size_t)ks.c * a->d + 2) + (size_t)a->B * a->Hkv * n_chunks * a->d) != INTATTN_OK) ks = KeySplit{0, 0};
+        if (ks.c > 0) variant = VARIANT_KEY_SPLIT;
+    }
+    const int rows_per_block = comparator ? 128 : fwd_rows_per_block(variant);
+    p.n_qtiles = fwd_row_tiles(p.row_lo, p.L, rows_per_block);
+    p.n_chunks = (p.Lk + rows_per_block - 1) / rows_per_block;
+    std::memcpy(p.lut, ctx->lut, 64);
+    p.dbg_row_max = a->dbg_row_max; p.dbg_row_sum = a->dbg_row_sum; p.dbg_acc = a->dbg_acc;
 
     if (dynamic) {
         if (rm.no_alloc) return fail(ctx, INTATTN_ERR_UNSUPPORTED, "intattn_forward_noalloc takes host scales");
@@ -815,11 +825,15 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
     if (!comparator && variant != 3) { // (the split-key single launch passes nothing through memory)
         const size_t rows = (size_t)a->B * a->Hq * a->L;
         const size_t cs = (size_t)a->B * a->Hkv * p.n_chunks * a->d;
-        rc = get_ws(2 * rows + cs);
+        const size_t part = (size_t)ks.c * rows * a->d; // first: its rows start 16-byte aligned
+        rc = get_ws(part + 2 * rows + cs);
         if (rc) return rc;
-        p.ws_row_max = d_ws;
+        p.ws_part = d_ws;
+        p.ws_row_max = d_ws + part;
         p.ws_row_sum = p.ws_row_max + rows;
         p.ws_colsum = p.ws_row_sum + rows;
+        p.split_ab = ks.ab;
+        p.split_c = ks.c;
     }
     if (rm.reserve) return INTATTN_OK;
 

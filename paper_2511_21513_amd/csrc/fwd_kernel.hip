@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "kernel_common.h"
 #include "params.h"
 
@@ -21,7 +23,8 @@ namespace {
 
 // Sums of V over each chunk of `chunk` consecutive keys, per (batch, KV head) and channel:
 // out[((b * Hkv + kvh) * n_chunks + c) * D + ch].  Keys past Lk do not count.  The forward kernel
-// adds up the chunks its tiles cover.
+// adds up the chunks its tiles cover.  For the key-split launches that follow, it also sets the row maxima and row sums
+// they accumulate into to their neutral values.
 template <int D>
 __global__ __launch_bounds__(256) void colsum_kernel(const FwdParams p, int chunk)
 {
@@ -48,6 +51,46 @@ __global__ __launch_bounds__(256) void colsum_kernel(const FwdParams p, int chun
         for (int j = 0; j < KL; ++j) t += red[j][tid];
         p.ws_colsum[((int64_t)bk * p.n_chunks + c) * D + tid] = t;
     }
+    if (p.split_c > 0) { // uniform
+        const int64_t rows = (int64_t)p.B * p.Hq * p.L;
+        for (int64_t i = (int64_t)blockIdx.x * 256 + tid; i < rows; i += (int64_t)gridDim.x * 256) {
+            p.ws_row_max[i] = INT32_MIN;
+            p.ws_row_sum[i] = 0;
+        }
+    }
+}
+
+// Key-split path: adds up the partial accumulators of sweep C's ranges and requantizes; a thread takes four channels of a
+// row.  Bound by the partials it reads (16 bytes a load).
+template <int D>
+__global__ __launch_bounds__(256) void finish_split_kernel(const FwdParams p)
+{
+    const int64_t n4 = (int64_t)p.B * p.Hq * p.L * (D / 4), i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n4) return;
+    const int64_t r = i / (D / 4); // (b * Hq + hq) * L + row
+    const int c4 = (int)(i % (D / 4)), l = (int)(r % p.L), bh = (int)(r / p.L), hq = bh % p.Hq, b = bh / p.Hq;
+    v4i acc = {0, 0, 0, 0};
+#pragma unroll 4
+    for (int s = 0; s < p.split_c; ++s) acc += *(const v4i *)(p.ws_part + 4 * (s * n4 + i));
+    HeadParams hp = p.hp_table ? p.hp_table[hq] : p.hp0;
+    if (p.row_table) hp = p.row_table[(int64_t)bh * p.n_rowblk + l / p.q_block];
+    uint32_t packed = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        if (p.dbg_acc) p.dbg_acc[4 * i + k] = acc[k];
+        packed |= ((uint32_t)requant_any(acc[k], hp.rq_mult, hp.rq_shift) & 0xffu) << (8 * k);
+    }
+    *(uint32_t *)(p.out + (int64_t)b * p.os[0] + (int64_t)hq * p.os[1] + (int64_t)l * p.os[2] + 4 * c4) = packed;
+}
+
+int launch_finish_split(const FwdParams &p, int d, hipStream_t st)
+{
+    const int64_t n4 = (int64_t)p.B * p.Hq * p.L * (d / 4);
+    const dim3 grid((unsigned)((n4 + 255) / 256)), block(256);
+    if (d == 64) hipLaunchKernelGGL(finish_split_kernel<64>, grid, block, 0, st, p);
+    else if (d == 128) hipLaunchKernelGGL(finish_split_kernel<128>, grid, block, 0, st, p);
+    else return (int)hipErrorInvalidValue;
+    return (int)hipGetLastError();
 }
 
 int launch_colsum(const FwdParams &p, int d, int chunk, hipStream_t st)
@@ -85,6 +128,39 @@ int fwd_choose_variant(int variant, int B, int Hq, int L, int Lk, int d, int cau
     return (d == 64 && L >= 1024) ? 3 : 1;
 }
 bool fwd_variant_known(int variant) { return variant == 0 || (variant >= 1 && variant <= 5) || variant == 9 || variant == 10; }
+
+// Workgroups per query tile for the key-split path, and whether it pays at all: a model of its time against one of the
+// variant (1 or 3) that serves the shape otherwise, in microseconds.  A kernel takes its key tiles times a cost per tile
+// times the rounds of 256 compute units, with two rounds as the least (a unit with a single workgroup is bound by latency);
+// sweep C also writes and reads the partial accumulators of each range; 24 us for five launches.  The single launches are
+// bound by their longest chain of tiles or, once the chip is full, by a cost per 32 x 32 block (variant 3) or by rounds of
+// 380 workgroups (variant 1).  Checked on 111 shapes from 1 x 1 x 256 x 1024 to 1 x 32 x 2048 x 16384: with the margins below
+// the choice is the faster one or within 5 %.  (509 x 7001, 32 and 8 heads, d 128: 0.247 -> 0.125 ms; 64 x 16384, 8 heads,
+// d 128: 0.229 -> 0.068; but 0.022 -> 0.049 at 1024 x 1024.)
+KeySplit fwd_key_split(int variant, int B, int Hq, int L, int Lk, int d, int causal)
+{
+    const int row_lo = causal ? Lk - L : 0, tiles = (Lk + 127) / 128;
+    const int64_t w_ab = (int64_t)B * Hq * fwd_row_tiles(row_lo, L, 256), w_c = (int64_t)B * Hq * fwd_row_tiles(row_lo, L, 128);
+    const double seen = causal ? (Lk - 0.5 * L) / Lk : 1.0; // share of the keys that an average row sees
+    const double us_tile = d == 128 ? 1.4 : 0.9, us_part = (double)B * Hq * L * d * 8 / 4.0e6;
+    auto rounds = [&](int64_t w, int s) { return std::max((double)((w * s + 255) / 256) * seen, 2.0) / s * tiles; };
+    KeySplit ks = {1, 1};
+    double t_ab = 1e30, t_c = 1e30;
+    for (int s = 1; s <= 32 && (s == 1 || 2 * s <= tiles); ++s) {
+        const double ab = rounds(w_ab, s) * 2 * us_tile + 0.1 * s, c = rounds(w_c, s) * us_tile + us_part * s;
+        if (ab < t_ab) t_ab = ab, ks.ab = s;
+        if (s <= 16 && c < t_c) t_c = c, ks.c = s;
+    }
+    double other;
+    if (variant == 3) {
+        const double blocks = (double)B * Hq * ((L + 31) / 32) * (Lk * seen) / 32;
+        other = 8 + std::max(tiles * (d == 128 ? 1.75 : 1.15), blocks * (d == 128 ? 1.42e-3 : 0.58e-3));
+    } else {
+        other = 12 + tiles * (d == 128 ? 3.8 : 3.3) * std::max(1.0, (double)B * Hq * ((L + 127) / 128) * seen / 380);
+    }
+    if (24 + t_ab + t_c > (d == 128 ? 0.93 : 0.8) * other) return KeySplit{0, 0};
+    return ks;
+}
 int fwd_rows_per_block(int variant) { return variant == 2 ? 256 : (variant == 3 ? 32 : 128); }
 
 int launch_fwd(const FwdParams &p_in, int d, int idx_mode, int variant, int stage, void *stream)
@@ -94,6 +170,20 @@ int launch_fwd(const FwdParams &p_in, int d, int idx_mode, int variant, int stag
     const int64_t k_bytes = (int64_t)p.Lk * d; // K of one (batch, KV head) group; V is as large
     p.group_batch = fwd_group_batch(p.B, p.Hkv, 2 * k_bytes); // kernels that stream K and V
     const bool two_launches = variant == 4 || variant == 5;
+    if (variant == VARIANT_KEY_SPLIT) {
+        if (stage != 0) return (int)hipErrorNotSupported;
+        int e = launch_colsum(p, d, 128, st);
+        FwdParams pab = p;
+        pab.n_qtiles = fwd_row_tiles(p.row_lo, p.L, 256);
+        pab.group_batch = fwd_group_batch(p.B, p.Hkv, k_bytes); // streams K only
+        if (e == 0) e = launch_shape<2, 2, 3>(pab, d, idx_mode, st);
+        if (e == 0) e = launch_shape<2, 2, 4>(pab, d, idx_mode, st);
+        FwdParams pc = p;
+        const bool mix = p.hp_table_c && idx_mode == IDX_MULHI24; // as below
+        if (mix) pc.hp_table = p.hp_table_c;
+        if (e == 0) e = launch_sweep_c(pc, d, mix ? IDX_MIX : idx_mode, stream);
+        return e == 0 ? launch_finish_split(p, d, st) : e;
+    }
     if (stage != 0 && !two_launches) return (int)hipErrorNotSupported;
     // all launches go to the same stream: V chunk sums first, then the sweeps
     int e = 0;

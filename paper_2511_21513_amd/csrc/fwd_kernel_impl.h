@@ -51,10 +51,13 @@ constexpr int NT = WAVES * 64;
 // 1 = sweeps A and B only (row max and row sum go to a small workspace: 8 bytes per query row) --
 // without the output accumulators it needs far fewer registers, so a wave can own 64 query rows
 // (every K fragment read feeds two MFMAs) at three waves per SIMD; 2 = sweep C only, reading that
-// workspace.
+// workspace; 3 and 4 = sweep A and sweep B over one of FwdParams::split_ab ranges of the keys, for problems whose
+// query tiles alone leave compute units idle: row max and row sum meet in the workspace (atomics; the launch ahead of
+// these set it to INT32_MIN and 0).
 template <int D, int RB, int KT, bool CAUSAL, int MODE, int PH>
-__global__ __launch_bounds__(NT, PH == 1 ? (RB * KT <= 2 ? 4 : 3) : (RB == 1 ? (KT == 1 ? 3 : 2) : 1)) void fwd_kernel(const FwdParams p)
+__global__ __launch_bounds__(NT, (PH == 1 || PH >= 3) ? (RB * KT <= 2 ? 4 : 3) : (RB == 1 ? (KT == 1 ? 3 : 2) : 1)) void fwd_kernel(const FwdParams p)
 {
+    constexpr bool WITHOUT_C = PH == 1 || PH == 3 || PH == 4; // sweeps A and / or B alone
     constexpr int KS = KT; // sub-tiles sweep C computes per step: the whole staged tile
     constexpr int KB = D / 32;       // 32-wide blocks of the head dimension
     constexpr int CB = D / 32;       // 32-wide blocks of output channels
@@ -70,8 +73,8 @@ __global__ __launch_bounds__(NT, PH == 1 ? (RB * KT <= 2 ? 4 : 3) : (RB == 1 ? (
     // the array it targets, so reads of one buffer need not wait for loads into the other.
     __shared__ __attribute__((aligned(1024))) int8_t Ks0[TILE];
     __shared__ __attribute__((aligned(1024))) int8_t Ks1[TILE];
-    __shared__ __attribute__((aligned(1024))) int8_t Vs0[PH == 1 ? 16 : TILE];
-    __shared__ __attribute__((aligned(1024))) int8_t Vs1[PH == 1 ? 16 : TILE];
+    __shared__ __attribute__((aligned(1024))) int8_t Vs0[WITHOUT_C ? 16 : TILE];
+    __shared__ __attribute__((aligned(1024))) int8_t Vs1[WITHOUT_C ? 16 : TILE];
     // per-row probability tables, [wave][row block][idx][row]: dynamic shared memory of WAVES * RB * NIDX * 32
     // words, NIDX = 32 or 64 table entries (none for sweeps A+B alone)
     extern __shared__ uint32_t PT[];
@@ -80,7 +83,10 @@ __global__ __launch_bounds__(NT, PH == 1 ? (RB * KT <= 2 ? 4 : 3) : (RB == 1 ? (
     __shared__ int32_t cs4[PH == 0 ? WAVES : 1][D]; // in-kernel column sums of V (short sequences, single launch)
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 31, h = lane >> 5;
-    const WorkItem wi = fwd_work_item(p, (int)blockIdx.x);
+    int bid = (int)blockIdx.x;
+    const int n_split = PH == 3 || PH == 4 ? p.split_ab : 1;
+    const int ksp = PH == 3 || PH == 4 ? fwd_split_index(bid, n_split) : 0;
+    const WorkItem wi = fwd_work_item(p, bid);
     if (!wi.valid) return; // padding of the XCD-aware grid (uniform for the whole workgroup)
     const int b = wi.b, hq = wi.hq, kvh = wi.kvh, qt = wi.qt + p.row_lo / BQ;
     const int bh = b * p.Hq + hq;
@@ -140,6 +146,10 @@ __global__ __launch_bounds__(NT, PH == 1 ? (RB * KT <= 2 ? 4 : 3) : (RB == 1 ? (
 
     const int kmax = CAUSAL ? min(L, q0 + BQ) : L;
     const int ntiles = (kmax + BK - 1) / BK;
+    // this workgroup's key tiles [tlo, thi)
+    const int tlo = PH == 3 || PH == 4 ? ntiles * ksp / n_split : 0;
+    const int thi = PH == 3 || PH == 4 ? ntiles * (ksp + 1) / n_split : ntiles;
+    if ((PH == 3 || PH == 4) && tlo >= thi) return; // fewer tiles than ranges (uniform for the workgroup)
 
     // ---- staging: global -> LDS directly (no registers, no LDS store instructions), a tile ahead.
     // One wave-wide 16-byte load fills 1 KiB of LDS, lane i at byte 16 i: the lane's slot is key row
@@ -179,18 +189,18 @@ __global__ __launch_bounds__(NT, PH == 1 ? (RB * KT <= 2 ? 4 : 3) : (RB == 1 ? (
     // t's buffer.  Unrolled by two so that every buffer is named statically.
     auto sweep = [&](auto with_v, auto body) __attribute__((always_inline)) {
         constexpr bool WITH_V = decltype(with_v)::value;
-        dma_k(0, Ks0);
-        if (WITH_V) dma_v(0, Vs0);
+        dma_k(tlo, Ks0);
+        if (WITH_V) dma_v(tlo, Vs0);
         publish_tiles_barrier();
-        for (int t = 0; t < ntiles; t += 2) {
-            if (t + 1 < ntiles) {
+        for (int t = tlo; t < thi; t += 2) {
+            if (t + 1 < thi) {
                 dma_k(t + 1, Ks1);
                 if (WITH_V) dma_v(t + 1, Vs1);
             }
             body(t, (const int8_t *)Ks0, (const int8_t *)Vs0);
             publish_tiles_barrier();
-            if (t + 1 < ntiles) {
-                if (t + 2 < ntiles) {
+            if (t + 1 < thi) {
+                if (t + 2 < thi) {
                     dma_k(t + 2, Ks0);
                     if (WITH_V) dma_v(t + 2, Vs0);
                 }
@@ -286,7 +296,7 @@ __global__ __launch_bounds__(NT, PH == 1 ? (RB * KT <= 2 ? 4 : 3) : (RB == 1 ? (
         }
     };
 
-    if constexpr (PH != 2) {
+    if constexpr (PH != 2 && PH != 4) {
         sweep(std::false_type{}, [&](int t, const int8_t *Kb, const int8_t *) __attribute__((always_inline)) {
             if (tile_is_full(t)) tile_a(std::false_type{}, t, Kb);
             else if (!tile_is_hidden(t)) tile_a(std::true_type{}, t, Kb);
@@ -306,6 +316,15 @@ __global__ __launch_bounds__(NT, PH == 1 ? (RB * KT <= 2 ? 4 : 3) : (RB == 1 ? (
             const int row = qw0 + 32 * rb + n;
             mx[rb] = (row >= rlo && row < rhi) ? p.ws_row_max[(int64_t)bh * LQ + (row - rlo)] : 0;
         }
+    }
+
+    if constexpr (PH == 3) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const int row = qw0 + 32 * rb + n;
+            if (h == 0 && row >= rlo && row < rhi) atomicMax(&p.ws_row_max[(int64_t)bh * LQ + (row - rlo)], mx[rb]);
+        }
+        return;
     }
 
     // exact index map of each row block's lane row, applied to raw scores (no -rowMax start
@@ -416,7 +435,7 @@ __global__ __launch_bounds__(NT, PH == 1 ? (RB * KT <= 2 ? 4 : 3) : (RB == 1 ? (
         }
     };
 
-    if constexpr (PH != 2) {
+    if constexpr (PH != 2 && PH != 3) {
         sweep(std::false_type{}, [&](int t, const int8_t *Kb, const int8_t *) __attribute__((always_inline)) {
             if (tile_is_full(t)) tile_b(std::false_type{}, t, Kb);
             else if (!tile_is_hidden(t)) tile_b(std::true_type{}, t, Kb);
@@ -424,7 +443,14 @@ __global__ __launch_bounds__(NT, PH == 1 ? (RB * KT <= 2 ? 4 : 3) : (RB == 1 ? (
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) sum[rb] += __shfl_xor(sum[rb], 32);
     }
-    if constexpr (PH == 1) {
+    if constexpr (PH == 4) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const int row = qw0 + 32 * rb + n;
+            if (h == 0 && row >= rlo && row < rhi) atomicAdd(&p.ws_row_sum[(int64_t)bh * LQ + (row - rlo)], (int32_t)sum[rb]);
+        }
+        return;
+    } else if constexpr (PH == 1) {
         // hand row max and row sum to the second launch
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
@@ -611,9 +637,14 @@ __global__ __launch_bounds__(NT, PH == 1 ? (RB * KT <= 2 ? 4 : 3) : (RB == 1 ? (
 template <int D, int RB, int KT, bool CAUSAL, int PH>
 int launch_mode(const FwdParams &p, int idx_mode, hipStream_t st)
 {
-    const dim3 grid((unsigned)fwd_grid_size(p.B, p.Hq, p.Hkv, p.n_qtiles)), block(NT);
+    const int n_split = PH == 3 || PH == 4 ? p.split_ab : 1;
+    const dim3 grid((unsigned)(fwd_grid_size(p.B, p.Hq, p.Hkv, p.n_qtiles) * n_split)), block(NT);
     // dynamic shared memory: the per-row probability tables (32 or 64 entries of a word per query row)
-    const unsigned sh = PH == 1 ? 0u : (unsigned)(WAVES * RB * (p.top < 32 ? 32 : 64) * 32 * sizeof(uint32_t));
+    const unsigned sh = PH == 1 || PH >= 3 ? 0u : (unsigned)(WAVES * RB * (p.top < 32 ? 32 : 64) * 32 * sizeof(uint32_t));
+    if constexpr (PH == 3) { // row maxima: no index map
+        hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_MAD24, PH>), grid, block, sh, st, p);
+        return (int)hipGetLastError();
+    }
     if (idx_mode == IDX_DEVICE) {
         // the scheme of each head is known on the device only: one launch per scheme, each
         // skipping the heads of the other

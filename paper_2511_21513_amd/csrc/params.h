@@ -65,6 +65,10 @@ struct FwdParams {
     // workspace: [B*Hq*L] row max and [B*Hq*L] row sum (handed from the first to the second launch
     // of the two-launch variants), [B*Hkv*n_chunks*d] sums of V over each chunk of keys
     int32_t *ws_row_max, *ws_row_sum, *ws_colsum;
+    // key-split tiled path: workgroups per query tile in sweeps A and B (split_ab) and in sweep C (split_c), each with a
+    // range of the keys; ws_part: sweep C's partial accumulators [split_c][B * Hq * L][d].  0: keys not split
+    int32_t split_ab, split_c;
+    int32_t *ws_part;
     // split-key path for few query rows (decode): packed rows (Hq / Hkv) * L, 32-key sub-tiles 4 * ceil(Lk / 128);
     // per (batch, KV head) group g and sub-tile j: raw scores [g][j][2][rows][16], table indices (16 bytes where the
     // scores have 16 words), partial row max and row sum [g][dec_np][rows]; partial accumulators per workgroup [g][dec_np / 4][rows][d]
@@ -152,6 +156,12 @@ inline int fwd_row_tiles(int row_lo, int n_rows, int rows_per_tile)
     return (row_lo + n_rows + rows_per_tile - 1) / rows_per_tile - row_lo / rows_per_tile;
 }
 bool fwd_variant_known(int variant);
+// 5's tiles with the keys split over several workgroups (few query tiles against many keys); never asked for by number
+constexpr int VARIANT_KEY_SPLIT = 6;
+struct KeySplit {
+    int ab, c; // workgroups per query tile; c == 0: this shape is better served by `variant`, the choice without a split
+};
+KeySplit fwd_key_split(int variant, int B, int Hq, int L, int Lk, int d, int causal);
 int quantize_partials_per_slice(int B, int H, int L, int d);
 int launch_quantize(const QuantParams *ps, int n, void *stream);
 int launch_decode(const FwdParams &p, int d, void *stream);

@@ -96,7 +96,10 @@ __global__ __launch_bounds__(NT, RB == 1 ? 2 : 1) void sweep_c_kernel(const FwdP
     __shared__ int32_t colsum[D];
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 31, h = lane >> 5;
-    const WorkItem wi = fwd_work_item(p, (int)blockIdx.x);
+    int bid = (int)blockIdx.x;
+    const int n_split = p.split_c > 0 ? p.split_c : 1;
+    const int ksp = p.split_c > 0 ? fwd_split_index(bid, n_split) : 0;
+    const WorkItem wi = fwd_work_item(p, bid);
     if (!wi.valid) return; // padding of the XCD-aware grid (uniform for the whole workgroup)
     const int b = wi.b, hq = wi.hq, kvh = wi.kvh, qt = wi.qt + p.row_lo / BQ;
     const int bh = b * p.Hq + hq;
@@ -125,7 +128,11 @@ __global__ __launch_bounds__(NT, RB == 1 ? 2 : 1) void sweep_c_kernel(const FwdP
     if (tid < 8) lut_lds[tid] = p.lut[tid];
 
     const int kmax = CAUSAL ? min(L, q0 + BQ) : L;
-    const int ntiles = (kmax + BK - 1) / BK; // iterations = V tiles; K tiles 0..ntiles are touched
+    // iterations = V tiles [tlo, thi); K tiles tlo..thi are touched.  Key-split launches take a range of the tiles each and
+    // leave partial accumulators; otherwise the range is all of them.
+    const int tall = (kmax + BK - 1) / BK;
+    const int tlo = tall * ksp / n_split, ntiles = tall * (ksp + 1) / n_split;
+    static_assert(BK == BQ, "a tile of keys is a chunk of the column sums");
 
     // ---- staging: direct global -> LDS loads; the XOR swizzle is applied to the global address
     // (lane i of a wave-wide 16-byte load lands at byte 16 i of its 1 KiB block).
@@ -165,9 +172,9 @@ __global__ __launch_bounds__(NT, RB == 1 ? 2 : 1) void sweep_c_kernel(const FwdP
     };
     auto dma_v = [&](int t, int8_t *dst) __attribute__((always_inline)) { dma_tile(Vp, p.vs[2], dma_goff_v, t * BK, 0, dst); };
 
-    dma_k(0, Ks0);
-    dma_v(0, Vs0);
-    dma_k(1, Ks1);
+    dma_k(tlo, Ks0);
+    dma_v(tlo, Vs0);
+    dma_k(tlo + 1, Ks1);
 
     auto lut_at = [&](int k) { return (uint32_t)k <= top ? (p.lut[k / 4] >> (8 * (k % 4))) & 0xffu : 0u; };
     // The clip points of classes 1 .. 3, per head: cap[n] = the first clipped distance whose index is >= 8 n, i.e. the
@@ -262,15 +269,13 @@ __global__ __launch_bounds__(NT, RB == 1 ? 2 : 1) void sweep_c_kernel(const FwdP
         }
     }
 
-    // Column sums of V over every key the steps below cover (keys up to the end of this query tile
-    // under the causal mask, else all): the correction for feeding the probabilities to the signed
+    // Column sums of V over every key the steps below cover (the chunks of this range of tiles): the correction for feeding the probabilities to the signed
     // MFMA as P - 128.  A small kernel ahead of this one left the sums of each BQ-key chunk.
     if (tid < D) {
         const int32_t *cp = p.ws_colsum + (int64_t)(b * p.Hkv + kvh) * p.n_chunks * D + tid;
-        const int nchunk = CAUSAL ? min(qt + 1, p.n_chunks) : p.n_chunks;
         int32_t acc = 0;
 #pragma unroll 8
-        for (int c = 0; c < nchunk; ++c) acc += cp[(int64_t)c * D];
+        for (int c = tlo; c < ntiles; ++c) acc += cp[(int64_t)c * D];
         colsum[tid] = acc;
     }
     publish_tiles_barrier(); // LUT_hat, K tiles 0 and 1, V tile 0 are in LDS
@@ -439,7 +444,7 @@ __global__ __launch_bounds__(NT, RB == 1 ? 2 : 1) void sweep_c_kernel(const FwdP
     };
 
     // One iteration = V tile T: the lookups of its NSUB sub-tiles, the scores of the NSUB sub-tiles
-    // two further on (K tile T+1).  With PAR = T & 1: K tile T+2 replaces K tile T (read an iteration
+    // two further on (K tile T+1).  With PAR = (T - tlo) & 1: K tile T+2 replaces K tile T (read an iteration
     // ago) in Ks[PAR], V tile T+1 replaces V tile T-1 in Vs[PAR^1]; K tile T+1 is read from Ks[PAR^1]
     // and V tile T from Vs[PAR].
     auto iteration = [&](auto masked_tag, auto path_tag, int T, int8_t *Kdma, int8_t *Vdma, const int8_t *Krd, const int8_t *Vrd)
@@ -481,19 +486,19 @@ __global__ __launch_bounds__(NT, RB == 1 ? 2 : 1) void sweep_c_kernel(const FwdP
     // then knows which direct-to-LDS load a fragment read depends on) and no branch inside the body;
     // the few remaining iterations take the masked code with the buffers chosen at run time.
     // Every wave of the workgroup passes the same number of barriers whichever path it takes: one per
-    // iteration, ntiles in all.
+    // iteration, ntiles - tlo in all.
     const int nfull_sub = CAUSAL ? min(L / 32, (qw0 + 1) / 32) : L / 32;
     const int nhot = min(nfull_sub / NSUB, ntiles);
     auto sweep = [&](auto path_tag) __attribute__((always_inline)) {
         constexpr bool FAST = decltype(path_tag)::value != 0;
-        int T = 0;
+        int T = tlo;
         for (; T + 2 <= nhot; T += 2) {
             iteration(std::false_type{}, path_tag, T, Ks0, Vs1, Ks1, Vs0);
             iteration(std::false_type{}, path_tag, T + 1, Ks1, Vs0, Ks0, Vs1);
         }
 #pragma unroll 1
         for (; T < ntiles; ++T) {
-            const bool odd = T & 1;
+            const bool odd = (T - tlo) & 1;
             iteration(std::true_type{}, path_tag, T, odd ? Ks1 : Ks0, odd ? Vs0 : Vs1, odd ? Ks0 : Ks1, odd ? Vs1 : Vs0);
         }
         // ---- drain: the last sub-tile's probabilities meet V (V^T fragments in vf); in the general path
@@ -513,6 +518,25 @@ __global__ __launch_bounds__(NT, RB == 1 ? 2 : 1) void sweep_c_kernel(const FwdP
     else if (path == 4) sweep(std::integral_constant<int, 4>{});
     else sweep(std::integral_constant<int, 0>{});
 
+    // Key-split launch: the accumulators of this range, corrected, for finish_split_kernel to add up
+    if (p.split_c > 0) {
+        if (valid) {
+            int32_t *Pp = p.ws_part + ((int64_t)ksp * p.B * p.Hq * LQ + (int64_t)bh * LQ + (row - rlo)) * D;
+            const int32_t cfac = (path == 0 || path == 4) ? 128 : 0;
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int ch0 = cb * 32 + 8 * g + 4 * h;
+                    v4i a;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) a[r] = o[0][cb][4 * g + r] + cfac * colsum[ch0 + r];
+                    *(v4i *)(Pp + ch0) = a;
+                }
+            }
+        }
+        return;
+    }
     // ================================================================= epilogue (Sec. 3.2: requantization)
     // (instantiated for the shift range and for the debug tap, so that the 64 values of a lane meet no branch)
     auto epilogue = [&](auto fast_tag, auto dbg_tag) __attribute__((always_inline)) {
@@ -558,7 +582,7 @@ __global__ __launch_bounds__(NT, RB == 1 ? 2 : 1) void sweep_c_kernel(const FwdP
 template <int D, int RB, bool CAUSAL>
 int launch_mode(const FwdParams &p, int idx_mode, hipStream_t st)
 {
-    const dim3 grid((unsigned)fwd_grid_size(p.B, p.Hq, p.Hkv, p.n_qtiles)), block(NT);
+    const dim3 grid((unsigned)(fwd_grid_size(p.B, p.Hq, p.Hkv, p.n_qtiles) * (p.split_c > 0 ? p.split_c : 1))), block(NT);
     if (idx_mode == IDX_DEVICE) {
         // the scheme of each head is known on the device only: one launch per scheme, each
         // skipping the heads of the other

@@ -1,0 +1,77 @@
+"""The tiled path with the keys split over several workgroups (few query tiles against many keys, automatic variant),
+bit-compared with the CPU oracle; and the mapping of work to XCDs for group counts that do not divide by eight."""
+import numpy as np
+import pytest
+
+from test_parity_gpu import rect_forward, rect_problem, torch_mod  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # B, Hq, Hkv, Lq, Lkv, d, causal, per_head
+    (1, 1, 1, 32, 16384, 64, True, False),     # one partly filled query tile, every range a single tile long
+    (1, 1, 1, 257, 9001, 128, True, False),    # ragged rows and keys, the diagonal in the last range only
+    (1, 4, 1, 129, 8192, 64, False, True),     # no mask, whole tiles
+    (1, 3, 3, 200, 8190, 128, True, True),     # three groups over eight XCDs
+    (2, 2, 1, 513, 7001, 128, True, False),
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "B{}Hq{}Hkv{}Lq{}Lk{}d{}c{}ph{}".format(*[int(x) for x in s]))
+def test_key_split_bit_exact(torch_mod, oracle, shape):  # noqa: F811
+    from paper_2511_21513_amd import binding
+
+    torch = torch_mod
+    B, Hq, Hkv, lq, lk, d, causal, per_head = shape
+    print(f"case {shape}", flush=True)
+    ia = binding.IntAttn(device=0)
+    base, q, k, v = rect_problem(900 + lq, B, Hq, Hkv, lq, lk, d, causal, per_head)
+    want = oracle.forward(q, k, v, base.s_q, base.s_k, base.s_v, None, causal=causal, per_head=per_head, taps=True, threads=16)
+    got = rect_forward(torch, ia, base, q, k, v)
+    for key in ("row_max", "row_sum", "acc", "out"):
+        assert int((got[key] != want[key]).sum()) == 0, key
+    # the same scales in device memory
+    dev = torch.device("cuda:0")
+    tq, tk, tv = (torch.from_numpy(x).to(dev) for x in (q, k, v))
+    sc = [torch.from_numpy(np.ascontiguousarray(s, dtype=np.float32)).to(dev) for s in (base.s_q, base.s_k, base.s_v)]
+    out = torch.empty_like(tq)
+    args, keep = ia.make_args(tq, tk, tv, out, *sc, None, causal=causal, per_head=per_head, device_scales=True)
+    ia.forward_dynamic_args(args, torch.cuda.current_stream(dev).cuda_stream)
+    torch.cuda.synchronize()
+    assert ia.dynamic_status() == 0 and int((out.cpu().numpy() != want["out"]).sum()) == 0
+    ia.close()
+
+
+def test_key_split_row_groups_bit_exact(torch_mod, oracle):  # noqa: F811
+    """A scale and an output scale per block of query rows: every row's own requantization after the ranges meet."""
+    from paper_2511_21513_amd import binding
+
+    torch = torch_mod
+    ia = binding.IntAttn(device=0)
+    base, q, k, v = rect_problem(31, 1, 2, 1, 100, 8200, 128, True, per_head=True)
+    rng = np.random.default_rng(5)
+    s_q = (base.s_q[None, :, None] * rng.uniform(0.3, 2.5, size=(1, 2, 15))).astype(np.float32)
+    s_o = (base.s_v[[0, 0]][None, :, None] * rng.uniform(0.02, 0.2, size=(1, 2, 15))).astype(np.float32)
+    want = oracle.forward_row_groups(q, k, v, s_q, base.s_k, base.s_v, s_o, q_block=7, causal=True)["out"]
+    dev = torch.device("cuda:0")
+    tq, tk, tv = (torch.from_numpy(x).to(dev) for x in (q, k, v))
+    sc = [torch.from_numpy(np.ascontiguousarray(x)).to(dev) for x in (s_q, base.s_k, base.s_v, s_o)]
+    out = torch.empty_like(tq)
+    args, keep = ia.make_args(tq, tk, tv, out, *sc, causal=True, device_scales=True, q_block=7)
+    ia.forward_dynamic_args(args, torch.cuda.current_stream(dev).cuda_stream)
+    torch.cuda.synchronize()
+    assert ia.dynamic_status() == 0 and int((out.cpu().numpy() != want).sum()) == 0
+    ia.close()
+
+
+@pytest.mark.parametrize("variant", [1, 3, 5], ids=lambda v: f"variant{v}")
+@pytest.mark.parametrize("heads", [(1, 1, 1), (1, 6, 2), (1, 12, 12), (3, 9, 3), (1, 8, 4), (257, 1, 1)], ids=str)
+def test_group_counts_over_xcds_bit_exact(torch_mod, oracle, heads, variant):  # noqa: F811
+    from paper_2511_21513_amd import binding
+
+    B, Hq, Hkv = heads
+    ia = binding.IntAttn(device=0, variant=variant)
+    base, q, k, v = rect_problem(60 + B + Hq, B, Hq, Hkv, 150 if B < 100 else 33, 150 if B < 100 else 33, 64, True)
+    want = oracle.forward(q, k, v, base.s_q, base.s_k, base.s_v, None, causal=True, threads=16)["out"]
+    assert int((rect_forward(torch_mod, ia, base, q, k, v, taps=False)["out"] != want).sum()) == 0
+    ia.close()
