@@ -978,8 +978,6 @@ int intattn_index_softmax(intattn_ctx *ctx, const intattn_softmax_args *a, void 
     p.logits = a->logits; p.prob = a->prob;
     p.ls = a->logits_stride; p.ps = a->prob_stride;
     p.rows = a->rows; p.cols = a->cols;
-    p.vec_in = ((((uintptr_t)a->logits) & 15u) == 0 && (a->logits_stride & 15) == 0) ? 1 : 0;
-    p.vec_out = ((((uintptr_t)a->prob) & 3u) == 0 && (a->prob_stride & 3) == 0) ? 1 : 0;
     p.rows_per_matrix = a->causal ? a->rows_per_matrix : 1;
     p.causal = a->causal;
     p.top = (1 << ctx->lut_bits) - 1;

@@ -120,7 +120,6 @@ struct SoftmaxParams {
     int32_t cols;
     int32_t rows_per_matrix, causal; // causal: row r of each stacked matrix sees columns j <= r % rows_per_matrix + cols - rows_per_matrix
     int32_t top;           // 2^b - 1
-    int32_t vec_in, vec_out; // rows start 16-byte (logits) / 4-byte (prob) aligned: wide loads / stores
     HeadParams hp;         // c_int and the index-map constants, scheme in pad[0]
     uint32_t lut[16];
 };

@@ -21,6 +21,10 @@ __device__ __forceinline__ int32_t wave_max(int32_t v)
     for (int o = 32; o >= 1; o >>= 1) v = max(v, __shfl_xor(v, o));
     return v;
 }
+typedef int v4i_a4 __attribute__((ext_vector_type(4), aligned(4))); // 16 bytes at the alignment of a logit
+
+__device__ __forceinline__ bool in_row(int c, int end) { return (uint32_t)c < (uint32_t)end; }
+
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v)
 {
 #pragma unroll
@@ -51,13 +55,18 @@ __global__ __launch_bounds__(256) void index_softmax_kernel(const SoftmaxParams 
     const double negr = idx_fp64_factor(hp);
     const int mul = (int)hp.idx_mul;
 
+    // Groups of four columns start where the row's probabilities are 4-byte aligned: column 4 g - lead, the first and the
+    // last group partly outside the row.  Every store is then one aligned word whatever the strides are, and every load
+    // 16 bytes at the 4-byte alignment that logits have anyway.  (Rows of 6001 columns, whose starts fall on every
+    // alignment, took four loads and four byte stores a group: 8192 x 6001: 67.9 us, now 47.4, 5.2 TB/s.)
+    const int lead = (int)((uintptr_t)dst & 3u);
     auto load4 = [&](int c, int32_t (&x)[4]) __attribute__((always_inline)) {
-        if (p.vec_in && c + 3 < cols) {
-            const v4i q = *(const v4i *)(src + c);
+        if (c >= 0 && c + 3 < n_vis) {
+            const v4i_a4 q = *(const v4i_a4 *)(src + c);
             x[0] = q[0], x[1] = q[1], x[2] = q[2], x[3] = q[3];
         } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) x[e] = c + e < cols ? src[c + e] : 0;
+            for (int e = 0; e < 4; ++e) x[e] = in_row(c + e, n_vis) ? src[c + e] : 0;
         }
     };
     auto team_max = [&](int32_t v) __attribute__((always_inline)) {
@@ -86,12 +95,12 @@ __global__ __launch_bounds__(256) void index_softmax_kernel(const SoftmaxParams 
     // last table entry, which is 0 by Eq. lut16.  Groups that are visible as a whole skip the selects.
     auto index_word = [&](const int32_t (&x)[4], int32_t m, int c) __attribute__((always_inline)) {
         uint32_t w = 0;
-        if (c + 3 < n_vis) {
+        if (c >= 0 && c + 3 < n_vis) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) w |= index4(x[e], m) << (8 * e);
         } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) w |= (c + e < n_vis ? index4(x[e], m) : top4) << (8 * e);
+            for (int e = 0; e < 4; ++e) w |= (in_row(c + e, n_vis) ? index4(x[e], m) : top4) << (8 * e);
         }
         return w;
     };
@@ -109,11 +118,11 @@ __global__ __launch_bounds__(256) void index_softmax_kernel(const SoftmaxParams 
         return packed;
     };
     auto store4 = [&](int c, uint32_t packed) __attribute__((always_inline)) {
-        if (p.vec_out && c + 3 < cols) *(uint32_t *)(dst + c) = packed;
+        if (c >= 0 && c + 3 < cols) *(uint32_t *)(dst + c) = packed;
         else
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                if (c + e < cols) dst[c + e] = (uint8_t)(packed >> (8 * e));
+                if (in_row(c + e, cols)) dst[c + e] = (uint8_t)(packed >> (8 * e));
     };
 
     constexpr int NREG = NCH > 0 ? NCH : 1;
@@ -123,29 +132,29 @@ __global__ __launch_bounds__(256) void index_softmax_kernel(const SoftmaxParams 
     if (NCH > 0) {
 #pragma unroll
         for (int j = 0; j < NCH; ++j) {
-            const int c = (t + NTHR * j) * 4;
+            const int c = (t + NTHR * j) * 4 - lead;
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[j][e] = 0;
-            if (c < cols) load4(c, v[j]);
+            if (c < n_vis) load4(c, v[j]);
         }
 #pragma unroll
         for (int j = 0; j < NCH; ++j) {
-            const int c = (t + NTHR * j) * 4;
-            if (c + 3 < n_vis) {
+            const int c = (t + NTHR * j) * 4 - lead;
+            if (c >= 0 && c + 3 < n_vis) {
                 m = max(max(m, v[j][0]), max(v[j][1], max(v[j][2], v[j][3])));
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    if (c + e < n_vis) m = max(m, v[j][e]);
+                    if (in_row(c + e, n_vis)) m = max(m, v[j][e]);
             }
         }
     } else {
-        for (int c = t * 4; c < n_vis; c += NTHR * 4) {
+        for (int c = t * 4 - lead; c < n_vis; c += NTHR * 4) {
             int32_t x[4];
             load4(c, x);
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                if (c + e < n_vis) m = max(m, x[e]);
+                if (in_row(c + e, n_vis)) m = max(m, x[e]);
         }
     }
     m = team_max(m);
@@ -156,12 +165,16 @@ __global__ __launch_bounds__(256) void index_softmax_kernel(const SoftmaxParams 
     if (NCH > 0) {
 #pragma unroll
         for (int j = 0; j < NCH; ++j) {
-            w[j] = index_word(v[j], m, (t + NTHR * j) * 4);
-            sum += gather_sum(lutv, w[j]);
+            // a wave past the last visible column has nothing to look up (the last table entry is 0)
+            w[j] = top4 * 0x01010101u;
+            if ((t - lane + NTHR * j) * 4 - lead < n_vis) { // wave-uniform
+                w[j] = index_word(v[j], m, (t + NTHR * j) * 4 - lead);
+                sum += gather_sum(lutv, w[j]);
+            }
         }
     } else {
         // every lane takes part in every permute: the trip count is rounded up for the whole team
-        for (int c = t * 4; c - t * 4 < n_vis; c += NTHR * 4) {
+        for (int c = t * 4 - lead; c - t * 4 < n_vis; c += NTHR * 4) {
             int32_t x[4] = {0, 0, 0, 0};
             if (c < n_vis) load4(c, x);
             sum += gather_sum(lutv, index_word(x, m, c));
@@ -174,12 +187,13 @@ __global__ __launch_bounds__(256) void index_softmax_kernel(const SoftmaxParams 
     if (NCH > 0) {
 #pragma unroll
         for (int j = 0; j < NCH; ++j) {
-            const int c = (t + NTHR * j) * 4;
-            const uint32_t packed = gather_pack(ptv, w[j]);
+            const int c = (t + NTHR * j) * 4 - lead;
+            uint32_t packed = 0; // hidden columns
+            if ((t - lane + NTHR * j) * 4 - lead < n_vis) packed = gather_pack(ptv, w[j]); // wave-uniform
             if (c < cols) store4(c, packed);
         }
     } else {
-        for (int c = t * 4; c - t * 4 < cols; c += NTHR * 4) {
+        for (int c = t * 4 - lead; c - t * 4 < cols; c += NTHR * 4) {
             int32_t x[4] = {0, 0, 0, 0};
             if (c < n_vis) load4(c, x);
             const uint32_t packed = gather_pack(ptv, index_word(x, m, c));
@@ -200,13 +214,14 @@ template <int NTHR, int NCH> int launch_one(const SoftmaxParams &p, hipStream_t 
 
 } // namespace
 
-// rows <= 2^31 - 1 workgroups' worth, 1 <= cols <= 2^29; strides in bytes; vec_in / vec_out say whether
-// every row starts 16-byte (logits) / 4-byte (prob) aligned, which allows the wide accesses; p.hp holds
-// c_int and the index-map constants with the scheme in pad[0]: IDX_TOP24 or IDX_FP64.
+// rows <= 2^31 - 1 workgroups' worth, 1 <= cols <= 2^29; strides in bytes, logits and their stride multiples of 4; p.hp
+// holds c_int and the index-map constants with the scheme in pad[0]: IDX_TOP24 or IDX_FP64.  Rows whose probabilities may
+// start off a 4-byte boundary need room for up to three columns more (the lead of their first group).
 int launch_index_softmax(const SoftmaxParams &p, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
-    const int c = p.cols;
+    const int c = p.cols + ((((uintptr_t)p.prob | (uint64_t)p.ps) & 3u) != 0 ? 3 : 0);
+    if (p.cols <= 2048 && c > 2048) return launch_one<64, 9>(p, st); // api.cpp counts workgroups of four rows up to 2048 columns
     if (c <= 256) return launch_one<64, 1>(p, st);
     if (c <= 512) return launch_one<64, 2>(p, st);
     if (c <= 1024) return launch_one<64, 4>(p, st);
@@ -214,6 +229,7 @@ int launch_index_softmax(const SoftmaxParams &p, void *stream)
     if (c <= 4096) return launch_one<256, 4>(p, st);
     if (c <= 8192) return launch_one<256, 8>(p, st);
     if (c <= 16384) return launch_one<256, 16>(p, st);
+    if (p.cols <= 16384) return launch_one<256, 17>(p, st);
     return launch_one<256, 0>(p, st);
 }
 
