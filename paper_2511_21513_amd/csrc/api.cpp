@@ -4,6 +4,7 @@
 // fails, the error is returned.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -621,20 +622,46 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
     if (variant == 5 && ctx->lut_bits > 5) variant = 4; // the pipelined sweep C holds 32-entry tables; same tiling otherwise
     if (a->scale_mode == 3) variant = 1;                // groups over the key axis: the single-launch kernel
     if (variant == 3 && a->scale_mode == 2) variant = 1; // the split-key single launch takes per-tensor / per-head parameters
+    const bool automatic = ctx->variant == 0 || ctx->variant == 9 || ctx->variant == 10;
     // Few query rows against many keys: the split-key kernels (all query heads of a KV head, times
     // the query rows, packed into one MFMA operand of at most 31 rows).
     const int64_t packed_rows = (int64_t)p.group * p.L;
     const bool decode_ok = !comparator && stage == 0 && a->scale_mode < 2 && packed_rows <= 31 && (int64_t)a->B * a->Hkv <= 65535;
     const bool decode = decode_ok && (ctx->variant == 9 || ctx->variant == 10 || (ctx->variant == 0 && p.Lk >= 1024));
 
+    auto split_ws_words = [&](int c) {
+        const size_t rows = (size_t)a->B * a->Hq * a->L, n_chunks = ((size_t)p.Lk + 127) / 128;
+        return rows * ((size_t)c * a->d + 2) + (size_t)a->B * a->Hkv * n_chunks * a->d;
+    };
+    // A smaller problem than the one reserved for may split its keys where this one does not (an 8192-token prompt, then a
+    // chunk of 512 rows): room for the partial accumulators of any such problem.
+    auto reserve_split = [&]() -> int {
+        if (!automatic || comparator || ctx->lut_bits > 5 || a->scale_mode > 2) return INTATTN_OK;
+        const int64_t part = std::min<int64_t>(KEY_SPLIT_MAX_WORDS, (int64_t)KEY_SPLIT_MAX_RANGES * a->B * a->Hq * a->L * a->d);
+        if (get_ws(split_ws_words(0) + (size_t)part) != INTATTN_OK) {
+            (void)hipGetLastError(); // such a problem then runs unsplit
+            ctx->err.clear();
+        }
+        return INTATTN_OK;
+    };
     // Few query tiles against many keys: the tiled kernels with the keys split, where their cost model beats that of the
     // single launch and the partial accumulators can be had
     KeySplit ks = {0, 0};
-    const bool automatic = ctx->variant == 0 || ctx->variant == 9 || ctx->variant == 10;
     if (automatic && !decode && (variant == 1 || variant == 3) && !comparator && stage == 0 && !rm.no_alloc && ctx->lut_bits <= 5 && a->scale_mode <= 2) {
         ks = fwd_key_split(variant, a->B, a->Hq, a->L, p.Lk, a->d, a->causal);
-        const size_t rows = (size_t)a->B * a->Hq * a->L, n_chunks = ((size_t)p.Lk + 127) / 128;
-        if (ks.c > 0 && get_ws(rows * ((size_t)ks.c * a->d + 2) + (size_t)a->B * a->Hkv * n_chunks * a->d) != INTATTN_OK) ks = KeySplit{0, 0};
+        const size_t need = split_ws_words(ks.c);
+        if (ks.c > 0 && !rm.reserve && need > ctx->ws_cap) {
+            // a call that is being captured must not allocate: it runs as if the keys could not be split
+            hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+            if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+                (void)hipGetLastError();
+                ks = KeySplit{0, 0};
+            }
+        }
+        if (ks.c > 0 && get_ws(need) != INTATTN_OK) {
+            (void)hipGetLastError(); // the launches that follow report errors of their own
+            ks = KeySplit{0, 0};
+        }
         if (ks.c > 0) variant = VARIANT_KEY_SPLIT;
     }
     const int rows_per_block = comparator ? 128 : fwd_rows_per_block(variant);
@@ -795,7 +822,7 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
             const hipError_t e = hipMemset(ctx->d_dec_state, 0, ctx->dec_state_groups * DEC_STATE_WORDS * sizeof(uint32_t));
             if (e != hipSuccess) return hip_fail(ctx, e, "hipMemset(split-key group state)");
         }
-        if (rm.reserve) return INTATTN_OK;
+        if (rm.reserve) return reserve_split();
         p.dec_rows = (int32_t)R;
         p.dec_nt32 = (int32_t)nt32;
         p.dec_tpw = (int32_t)tpw;
@@ -835,7 +862,7 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
         p.split_ab = ks.ab;
         p.split_c = ks.c;
     }
-    if (rm.reserve) return INTATTN_OK;
+    if (rm.reserve) return reserve_split();
 
     const int herr = comparator ? launch_quantonly(p, a->d, ctx->variant, stream)
                                 : launch_fwd(p, a->d, dv.idx_mode, variant, stage, stream);

@@ -149,7 +149,7 @@ KeySplit fwd_key_split(int variant, int B, int Hq, int L, int Lk, int d, int cau
     for (int s = 1; s <= 32 && (s == 1 || 2 * s <= tiles); ++s) {
         const double ab = rounds(w_ab, s) * 2 * us_tile + 0.1 * s, c = rounds(w_c, s) * us_tile + us_part * s;
         if (ab < t_ab) t_ab = ab, ks.ab = s;
-        if (s <= 16 && c < t_c) t_c = c, ks.c = s;
+        if (s <= KEY_SPLIT_MAX_RANGES && (int64_t)s * B * Hq * L * d <= KEY_SPLIT_MAX_WORDS && c < t_c) t_c = c, ks.c = s;
     }
     double other;
     if (variant == 3) {

@@ -157,6 +157,8 @@ inline int fwd_row_tiles(int row_lo, int n_rows, int rows_per_tile)
 bool fwd_variant_known(int variant);
 // 5's tiles with the keys split over several workgroups (few query tiles against many keys); never asked for by number
 constexpr int VARIANT_KEY_SPLIT = 6;
+constexpr int KEY_SPLIT_MAX_RANGES = 16;          // ranges of sweep C: each writes and reads its partial accumulators
+constexpr int64_t KEY_SPLIT_MAX_WORDS = 32 << 20; // of partial accumulators (128 MB): what reserving ahead has to set aside
 struct KeySplit {
     int ab, c; // workgroups per query tile; c == 0: this shape is better served by `variant`, the choice without a split
 };

@@ -75,3 +75,39 @@ def test_group_counts_over_xcds_bit_exact(torch_mod, oracle, heads, variant):  #
     want = oracle.forward(q, k, v, base.s_q, base.s_k, base.s_v, None, causal=True, threads=16)["out"]
     assert int((rect_forward(torch_mod, ia, base, q, k, v, taps=False)["out"] != want).sum()) == 0
     ia.close()
+
+
+def test_key_split_workspace_reserved_ahead_and_under_capture(torch_mod, oracle):  # noqa: F811
+    """A chunk after a reservation for a longer prompt allocates nothing; a capture on a context without a workspace runs
+    (unsplit) instead of allocating."""
+    from paper_2511_21513_amd import binding
+
+    torch = torch_mod
+    base, q, k, v = rect_problem(77, 1, 2, 1, 129, 9001, 128, True)
+    want = oracle.forward(q, k, v, base.s_q, base.s_k, base.s_v, None, causal=True, threads=16)["out"]
+    tq, tk, tv = (torch.from_numpy(x).cuda() for x in (q, k, v))
+    out = torch.empty_like(tq)
+    ia = binding.IntAttn(device=0)
+    args, keep = ia.make_args(tq, tk, tv, out, base.s_q, base.s_k, base.s_v, None, causal=True)
+    longer = torch.zeros((1, 2, 9001, 128), dtype=torch.int8, device="cuda")
+    ia.reserve(ia.make_args(longer, tk, tv, torch.empty_like(longer), base.s_q, base.s_k, base.s_v, None, causal=True)[0])
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    ia.forward_args(args, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.cuda.mem_get_info()[0] == free
+    assert int((out.cpu().numpy() != want).sum()) == 0
+    ia.close()
+
+    ia = binding.IntAttn(device=0)
+    out.fill_(55)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ia.forward_args(args, torch.cuda.current_stream().cuda_stream)
+    for _ in range(3):
+        out.fill_(55)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert int((out.cpu().numpy() != want).sum()) == 0
+    ia.close()
