@@ -672,7 +672,7 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
 
     if (dynamic) {
         if (rm.no_alloc) return fail(ctx, INTATTN_ERR_UNSUPPORTED, "intattn_forward_noalloc takes host scales");
-        rc = get_tables(a->Hq);
+        rc = get_tables(2 * a->Hq); // the second half: sweep C's own table
         if (rc) return rc;
         if (a->Hq > ctx->status_cap) {
             int32_t *stw = nullptr;
@@ -736,6 +736,7 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
                     if (e != 0) return hip_fail(ctx, (hipError_t)e, "launch(derive head parameters)");
                 }
                 p.hp_table = d_hp;
+                p.hp_table_c = d_hp + a->Hq;
             }
         }
     } else if (decode) {

@@ -3,8 +3,11 @@
 // reading anything back:
 //   c_int = round(c * sqrt(d) / (s_Q s_K))                    (Sec. 3.1, Eq. clipping_thr)
 //   (M, sh) with M * 2^-sh ~ s_V / (255 s_O), M in [2^30, 2^31)   (output requantization)
-//   constants of an exact index map idx = round(x * top / c_int)  (Sec. 3.1, index map): the 24-bit
-//   multiply-add whose top byte is the index where it exists, else the fp64 map
+//   constants of an exact index map idx = round(x * top / c_int)  (Sec. 3.1, index map): the multiply-high of
+//   24-bit factors where it exists (nearly every threshold up to 60000, which covers what scales of activations
+//   give), with the cheaper multiply-add whose top byte is the index for sweep C of the heads that have it; else
+//   the fp64 map.  (With the top-byte and fp64 maps alone, thresholds above ten to twenty thousand, i.e. most
+//   layers, ran both sweeps on fp64 conversions: a layer of 2 x 2048 tokens, 32 / 8 heads, d 128: 184 us, now 180.)
 // The arithmetic is the host's, operation for operation, in IEEE double: products, quotients,
 // floor, frexp and the fma are exactly rounded on the GPU as on the CPU, and sqrt(d) comes from the
 // host.  One wave per query head, one check point of the index map per lane.
@@ -19,9 +22,11 @@ namespace {
 
 __device__ __forceinline__ bool good_scale(float s) { return s > 0.0f && s < __builtin_inff(); } // false for NaN
 
-__device__ __forceinline__ uint32_t exact_index(uint64_t x, uint64_t c_int, uint64_t top)
+// round(x top / c_int), exact: numerator and denominator are integers below 2^38, and a quotient that is no integer lies at
+// least 2^-31 from one (its rounding error is below 2^-46)
+__device__ __forceinline__ uint32_t exact_index(double x, double c_int, double top)
 {
-    return (uint32_t)((2 * top * x + c_int) / (2 * c_int));
+    return (uint32_t)(int)((2.0 * top * x + c_int) / (2.0 * c_int));
 }
 
 // c_int (capped at 2^30: beyond 62 * 2 * 128*128*128 every index is 0 anyway) and the requantization
@@ -73,73 +78,102 @@ __device__ __forceinline__ uint64_t set_fp64_factor(HeadParams &hp, uint32_t top
     return bits;
 }
 
-// One wave per query head.  Lane l computes two check points x of the index map (numbers l and l + 64):
-// x = 0, x = c_int, and both sides of each of the (at most 63) steps of the exact map; every map in
-// question is a monotone step function, so agreement at these points is agreement on all of [0, c_int].
-// The points go to LDS; then every lane tests one candidate multiplier of the top-byte scheme against
-// all of them (two rounds of 64 candidates at most), so the search costs the same few microseconds
-// whether or not constants exist.
-__global__ __launch_bounds__(64) void derive_kernel(const DeriveParams dp)
+// One wave per query head.  Every map in question is a monotone step function, so agreement at x = 0, x = c_int and on
+// both sides of each of the (at most 63) steps of the exact map is agreement on all of [0, c_int].  Lane l computes t_k, the
+// first x whose index is at least k = l + 1; then every lane tests one candidate of each scheme against all of the steps,
+// whose t_k it reads from lane k - 1.  Bound by the latency of one wave: quotients are IEEE double divisions (exact under
+// floor and ceil, see below) and the loops hold 32-bit integer operations only.  (With 64-bit integer divisions and
+// products, and the steps in LDS: 18.8 us for this kernel, now 8.0.)
+// `hp`: the parameters for every kernel (multiply-high scheme, or fp64); `hp_c`: for sweep C (top byte where it exists).
+__device__ __forceinline__ bool derive_head(const DeriveParams &dp, int h, int lane, HeadParams &hp, HeadParams &hp_c)
 {
-    __shared__ uint32_t px[128], pk[128];
-    const int h = blockIdx.x, lane = threadIdx.x;
     const int si = dp.per_head ? h : 0;
     const int kv = dp.per_head ? h / dp.group : 0;
     const float sq = dp.scale_q[si], sk = dp.scale_k[kv], sv = dp.scale_v[kv];
     const float so = dp.scale_out ? dp.scale_out[si] : sv;
-    HeadParams hp;
     bool ok = derive_scalars(sq, sk, sv, so, dp.clip, dp.sqrt_d, hp);
 
-    // this lane's check points
+    // t_k = ceil((2 k - 1) c_int / (2 top)): a quotient that is no integer lies at least 1 / 126 from one, its rounding
+    // error is below 2^-22.  Lanes past the last step hold c_int.
     const uint32_t c_int = (uint32_t)hp.c_int, top = (uint32_t)dp.top;
-    uint32_t x[2], want[2];
-    bool have[2];
+    const double cd = (double)c_int, topd = (double)top;
+    const int t = (uint32_t)lane < top ? (int)__builtin_ceil((2.0 * lane + 1.0) * cd / (2.0 * topd)) : (int)c_int;
+    const int at[3] = {t, t - 1, (int)c_int}; // this lane's check points (t >= 1); t_1 - 1 or 0 is checked by lane 0
+    uint32_t want[3];
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int id = lane + 64 * q;
-        x[q] = id == 0 ? 0u : c_int;
-        have[q] = id < 2;
-        if (id >= 2) {
-            const uint64_t k = (uint64_t)((id - 2) >> 1) + 1;
-            const uint64_t t = ((2 * k - 1) * (uint64_t)c_int + 2ull * top - 1) / (2ull * top); // first x whose index is >= k
-            const uint32_t below = (uint32_t)(id & 1);
-            have[q] = k <= top && t <= c_int && t >= below;
-            x[q] = (uint32_t)t - below;
-        }
-        if (!have[q]) x[q] = 0u; // a second copy of the point x = 0
-        want[q] = exact_index(x[q], c_int, top);
-        px[id] = x[q];
-        pk[id] = want[q];
-    }
-    __syncthreads();
+    for (int q = 0; q < 3; ++q) want[q] = exact_index((double)at[q], cd, topd);
 
-    // (x * mul + add) >> 24 with a 23-bit multiplier (the host's find_top24, candidate for candidate):
-    // a check point with exact index k confines add to [k 2^24 - x mul, (k + 1) 2^24 - 1 - x mul];
-    // the first multiplier around top 2^24 / c_int whose intervals intersect is taken
-    bool found = false;
+    HeadParams hp_top = hp;
+    bool found_top = false, found = false;
     if (ok && c_int < (1u << 23)) { // wave-uniform
-        const long long m0 = (long long)(((unsigned long long)top << 24) / c_int);
-        for (int round = 0; round < 2 && !found; ++round) {
-            const int cand = lane + 64 * round;
-            const long long dm = cand >> 1, mul = (cand & 1) ? m0 - dm : m0 + 1 + dm;
-            const bool valid = cand < 80 && mul >= 1 && mul < (1ll << 23);
-            long long lo = 0, hi = valid ? (1ll << 31) - 1 - (long long)c_int * mul : -1;
-            if (valid) {
-                for (int i = 0; i < 128; ++i) {
-                    const long long xm = (long long)px[i] * mul, k = (long long)pk[i];
-                    lo = max(lo, (k << 24) - xm);
-                    hi = min(hi, ((k + 1) << 24) - 1 - xm);
-                }
+        // (x * mul + add) >> 24 with a 23-bit multiplier (the host's find_top24, candidate for candidate): the step to
+        // index k, between x = t - 1 and x = t, confines add to k 2^24 - t mul <= add < k 2^24 - (t - 1) mul; the first
+        // multiplier around top 2^24 / c_int whose intervals intersect is taken.  Sums below 2^31: c_int mul is at most
+        // top 2^24 + 40 c_int.
+        const double m0 = __builtin_floor(topd * 16777216.0 / cd);
+        for (int round = 0; round < 2 && !found_top; ++round) {
+            const int cand = lane + 64 * round, dm = cand >> 1;
+            const double muld = (cand & 1) ? m0 - dm : m0 + 1.0 + dm;
+            const bool valid = cand < 80 && muld >= 1.0 && muld < 8388608.0;
+            const int mul = valid ? (int)muld : 0;
+            int lo = 0, hi = 0x7fffffff - (int)c_int * mul;
+            for (int k = 1; k <= (int)top; ++k) {
+                const int base = (k << 24) - __builtin_amdgcn_readlane(t, k - 1) * mul; // as a 32-bit product
+                lo = max(lo, base);
+                hi = min(hi, base + mul - 1);
             }
-            const unsigned long long good = __ballot(lo <= hi);
+            hi = min(hi, (int)(((top + 1u) << 24) - 1u) - (int)c_int * mul);
+            const unsigned long long good = __ballot(valid && lo <= hi);
             if (good != 0ull) {
                 const int src = __builtin_ctzll(good); // the first candidate in the host's order
-                const long long mul_s = __shfl(mul, src), lo_s = __shfl(lo, src), hi_s = __shfl(hi, src);
+                const int mul_s = __shfl(mul, src), lo_s = __shfl(lo, src), hi_s = __shfl(hi, src);
+                found_top = true;
+                hp_top.pad[0] = IDX_TOP24;
+                hp_top.idx_mul = (uint32_t)(-mul_s);
+                hp_top.idx_add = (uint32_t)(lo_s + (hi_s - lo_s) / 2);
+                hp_top.idx_shift = 24;
+            }
+        }
+
+        // (((x << pre) + off) * mul) >> 32 with factors below 2^23: a lane per shift and per one of the two multipliers
+        // around top 2^32 / (c_int << pre).  The step to index k confines off to
+        // ceil(k 2^32 / mul) - (t << pre) <= off < ceil(k 2^32 / mul) - ((t - 1) << pre); the quotients are kept as
+        // quotient and remainder, one addition per step (multipliers below 512 cannot reach the first step).
+        const int pre = lane >> 1;
+        const bool fits = pre < 23 && ((uint64_t)c_int << pre) < (1ull << 23);
+        const int span = fits ? (int)(c_int << pre) : 1;
+        const double muld = __builtin_floor(topd * 4294967296.0 / (double)span) + (double)(lane & 1);
+        const bool valid = fits && muld >= 512.0 && muld < 8388608.0;
+        const int mul = valid ? (int)muld : 512, sh = fits ? pre : 0;
+        const int q1 = (int)(4294967296.0 / (double)mul), r1 = (int)(0u - (uint32_t)q1 * (uint32_t)mul); // 2^32 = q1 mul + r1
+        int lo = 0, hi = (1 << 23) - 1 - span, quo = 0, rem = 0;
+        auto next_quotient = [&]() __attribute__((always_inline)) { // ceil of the next multiple of 2^32 over mul
+            quo += q1;
+            rem += r1;
+            if (rem >= mul) rem -= mul, quo += 1;
+            return quo + (rem > 0 ? 1 : 0);
+        };
+        for (int k = 1; k <= (int)top; ++k) {
+            const int base = next_quotient() - (__builtin_amdgcn_readlane(t, k - 1) << sh);
+            lo = max(lo, base);
+            hi = min(hi, base - 1 + (1 << sh));
+        }
+        hi = min(hi, next_quotient() - 1 - span);
+        const unsigned long long good = __ballot(valid && lo <= hi);
+        if (good != 0ull) {
+            const int src = __builtin_ctzll(good), pre_s = src >> 1;
+            const int lo_s = __shfl(lo, src), hi_s = __shfl(hi, src);
+            const uint32_t mul_s = (uint32_t)__shfl(mul, src), off_s = (uint32_t)(lo_s + (hi_s - lo_s) / 2);
+            bool match = true; // every check point, with the arithmetic of the kernels
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                if ((uint32_t)(((uint64_t)(((uint32_t)at[q] << pre_s) + off_s) * mul_s) >> 32) != want[q]) match = false;
+            if (__all(match)) {
                 found = true;
-                hp.pad[0] = IDX_TOP24;
-                hp.idx_mul = (uint32_t)(-(int32_t)mul_s);
-                hp.idx_add = (uint32_t)(lo_s + (hi_s - lo_s) / 2);
-                hp.idx_shift = 24;
+                hp.pad[0] = IDX_MULHI24;
+                hp.idx_mul = 0u - mul_s;
+                hp.idx_add = 0u - off_s;
+                hp.idx_shift = pre_s;
             }
         }
     }
@@ -147,42 +181,78 @@ __global__ __launch_bounds__(64) void derive_kernel(const DeriveParams dp)
         // fp64 with r the double after top / c_int: exact for every c_int (the excess of r is under
         // two units in the last place and the fma rounds once, monotonically; values of
         // x*top/c_int + 1/2 that are not integers stay 1/(2 c_int) away from the next integer)
-        const uint64_t bits = (uint64_t)__double_as_longlong((double)top / (double)c_int) + 1ull;
-        const double r = __longlong_as_double((long long)bits);
+        const double r = -__longlong_as_double((long long)(set_fp64_factor(hp, top)));
         bool match = true;
 #pragma unroll
-        for (int q = 0; q < 2; ++q)
-            if (have[q] && (uint32_t)(int)__builtin_fma(-(double)x[q], -r, 0.5) != want[q]) match = false;
+        for (int q = 0; q < 3; ++q)
+            if ((uint32_t)(int)__builtin_fma(-(double)at[q], r, 0.5) != want[q]) match = false;
         if (!__all(match)) ok = false;
-        const uint64_t neg = bits ^ 0x8000000000000000ull;
         hp.pad[0] = IDX_FP64;
-        hp.idx_mul = (uint32_t)neg;
-        hp.idx_add = (uint32_t)(neg >> 32);
-        hp.idx_shift = 0;
     }
     if (!ok) hp.rq_mult = 0; // (the fp64 check cannot fail; kept as the last line of defence)
-    if (lane == 0) {
-        dp.hp_table[h] = hp;
-        dp.status[h] = ok ? 0 : 1;
-    }
+    hp_c = found && found_top ? hp_top : hp; // (both were found only for usable scales)
+    return ok;
 }
 
-// All heads of a call run one index scheme: a launch that serves only some head indices leaves most of
-// the chip idle, because the workgroups of a head index share an XCD.  If any head lacks top-byte
-// constants, every head takes the fp64 map (exact for every threshold).  One wave.
-__global__ __launch_bounds__(64) void unify_schemes_kernel(HeadParams *table, int n_heads, uint32_t top)
+// All heads of a call run one index scheme (sweep C one kernel): a launch that serves only some head indices leaves most
+// of the chip idle, because the workgroups of a head index share an XCD.  If any head lacks multiply-high
+// constants, every head takes the fp64 map (exact for every threshold).
+__device__ __forceinline__ void unify_scheme(const DeriveParams &dp, int h)
+{
+    HeadParams hp = dp.hp_table[h];
+    if (hp.pad[0] != IDX_FP64) {
+        hp.pad[0] = IDX_FP64;
+        set_fp64_factor(hp, (uint32_t)dp.top);
+        dp.hp_table[h] = hp;
+    }
+    dp.hp_table[dp.Hq + h] = hp;
+}
+
+__device__ __forceinline__ void put_head(const DeriveParams &dp, int h, const HeadParams &hp, const HeadParams &hp_c, bool ok)
+{
+    dp.hp_table[h] = hp;
+    dp.hp_table[dp.Hq + h] = hp_c;
+    dp.status[h] = ok ? 0 : 1;
+}
+
+__global__ __launch_bounds__(64) void derive_kernel(const DeriveParams dp)
+{
+    HeadParams hp, hp_c;
+    const bool ok = derive_head(dp, blockIdx.x, threadIdx.x, hp, hp_c);
+    if (threadIdx.x == 0) put_head(dp, blockIdx.x, hp, hp_c, ok);
+}
+
+__global__ __launch_bounds__(64) void unify_schemes_kernel(const DeriveParams dp)
 {
     bool mixed = false;
-    for (int h = threadIdx.x; h < n_heads; h += 64) mixed |= table[h].pad[0] != IDX_TOP24;
+    for (int h = threadIdx.x; h < dp.Hq; h += 64) mixed |= dp.hp_table[h].pad[0] == IDX_FP64;
     if (!__any(mixed)) return;
-    for (int h = threadIdx.x; h < n_heads; h += 64) {
-        HeadParams hp = table[h];
-        if (hp.pad[0] == IDX_TOP24) {
-            hp.pad[0] = IDX_FP64;
-            set_fp64_factor(hp, top);
-            table[h] = hp;
-        }
+    for (int h = threadIdx.x; h < dp.Hq; h += 64) unify_scheme(dp, h);
+}
+
+// Per-tensor scales: one wave derives the one parameter set and writes it for every head.
+__global__ __launch_bounds__(64) void derive_one_kernel(const DeriveParams dp)
+{
+    HeadParams hp, hp_c;
+    const bool ok = derive_head(dp, 0, threadIdx.x, hp, hp_c);
+    for (int h = threadIdx.x; h < dp.Hq; h += 64) put_head(dp, h, hp, hp_c, ok);
+}
+
+// Per-head scales of up to 32 heads: one workgroup derives all of them, a wave per head and round, and settles the scheme.
+__global__ __launch_bounds__(1024) void derive_heads_kernel(const DeriveParams dp)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    bool mixed = false;
+    for (int h0 = 0; h0 < dp.Hq; h0 += nw) {
+        const int h = min(h0 + wave, dp.Hq - 1); // spare waves of the last round repeat the last head
+        HeadParams hp, hp_c;
+        const bool ok = derive_head(dp, h, lane, hp, hp_c);
+        mixed |= hp.pad[0] == IDX_FP64;
+        if (lane == 0 && h0 + wave < dp.Hq) put_head(dp, h, hp, hp_c, ok);
     }
+    if (!__syncthreads_or(mixed)) return;
+    __syncthreads(); // (the table written above is visible)
+    for (int h = threadIdx.x; h < dp.Hq; h += blockDim.x) unify_scheme(dp, h);
 }
 
 // Parameters per block of q_block query rows (finer quantization groups over the query rows,
@@ -238,10 +308,21 @@ int launch_derive_groups(const DeriveParams &dp, void *stream)
     return (int)hipGetLastError();
 }
 
+// One launch where the heads share their scales or fit two rounds of one workgroup (a launch is 2 to 4 us of the stream); more heads take a
+// workgroup each and a second launch for the scheme.
 int launch_derive(const DeriveParams &dp, void *stream)
 {
+    if (!dp.per_head) {
+        hipLaunchKernelGGL(derive_one_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, dp);
+        return (int)hipGetLastError();
+    }
+    if (dp.Hq <= 32) {
+        const int waves = dp.Hq < 16 ? dp.Hq : 16;
+        hipLaunchKernelGGL(derive_heads_kernel, dim3(1), dim3((unsigned)(64 * waves)), 0, (hipStream_t)stream, dp);
+        return (int)hipGetLastError();
+    }
     hipLaunchKernelGGL(derive_kernel, dim3((unsigned)dp.Hq), dim3(64), 0, (hipStream_t)stream, dp);
-    hipLaunchKernelGGL(unify_schemes_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, dp.hp_table, dp.Hq, (uint32_t)dp.top);
+    hipLaunchKernelGGL(unify_schemes_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, dp);
     return (int)hipGetLastError();
 }
 

@@ -161,6 +161,10 @@ KeySplit fwd_key_split(int variant, int B, int Hq, int L, int Lk, int d, int cau
     if (24 + t_ab + t_c > (d == 128 ? 0.93 : 0.8) * other) return KeySplit{0, 0};
     return ks;
 }
+// Sweep C with a table of its own (top-byte constants where a head has them, which cost it one vector instruction per score
+// less than the multiply-high scheme of the other kernels): the host's comes with the multiply-high scheme for all heads.
+static int sweep_c_mode(const FwdParams &p, int idx_mode) { return p.hp_table_c && idx_mode == IDX_MULHI24 ? IDX_MIX : idx_mode; }
+
 int fwd_rows_per_block(int variant) { return variant == 2 ? 256 : (variant == 3 ? 32 : 128); }
 
 int launch_fwd(const FwdParams &p_in, int d, int idx_mode, int variant, int stage, void *stream)
@@ -179,9 +183,8 @@ int launch_fwd(const FwdParams &p_in, int d, int idx_mode, int variant, int stag
         if (e == 0) e = launch_shape<2, 2, 3>(pab, d, idx_mode, st);
         if (e == 0) e = launch_shape<2, 2, 4>(pab, d, idx_mode, st);
         FwdParams pc = p;
-        const bool mix = p.hp_table_c && idx_mode == IDX_MULHI24; // as below
-        if (mix) pc.hp_table = p.hp_table_c;
-        if (e == 0) e = launch_sweep_c(pc, d, mix ? IDX_MIX : idx_mode, stream);
+        if (p.hp_table_c) pc.hp_table = p.hp_table_c; // as below
+        if (e == 0) e = launch_sweep_c(pc, d, sweep_c_mode(p, idx_mode), stream);
         return e == 0 ? launch_finish_split(p, d, st) : e;
     }
     if (stage != 0 && !two_launches) return (int)hipErrorNotSupported;
@@ -210,13 +213,9 @@ int launch_fwd(const FwdParams &p_in, int d, int idx_mode, int variant, int stag
             if (e != 0 || stage == 1) return e;
         }
         if (variant == 4) return launch_shape<1, 2, 2>(p, d, idx_mode, st);
-        if (p.hp_table_c && idx_mode == IDX_MULHI24) {
-            // most heads have top-byte constants, which cost sweep C one vector instruction per score less
-            FwdParams pc = p;
-            pc.hp_table = p.hp_table_c;
-            return launch_sweep_c(pc, d, IDX_MIX, stream);
-        }
-        return launch_sweep_c(p, d, idx_mode, stream);
+        FwdParams pc = p;
+        if (p.hp_table_c) pc.hp_table = p.hp_table_c;
+        return launch_sweep_c(pc, d, sweep_c_mode(p, idx_mode), stream);
     }
     return launch_shape<1, 2, 0>(p, d, idx_mode, st);
 }

@@ -92,8 +92,8 @@ __global__ __launch_bounds__(NT, (PH == 1 || PH >= 3) ? (RB * KT <= 2 ? 4 : 3) :
     const int bh = b * p.Hq + hq;
     const HeadParams hp = p.hp_table ? p.hp_table[hq] : p.hp0;
     // device-derived parameters: another launch of this pair serves the head when its scheme is not this
-    // kernel's (uniform for the workgroup); the top-byte scheme runs in the multiply-add code here
-    if (p.filter && (hp.pad[0] == IDX_TOP24 ? (int)IDX_MAD24 : hp.pad[0]) != MODE) return;
+    // kernel's (uniform for the workgroup)
+    if (p.filter && hp.pad[0] != MODE) return;
     const int L = p.Lk; // keys
     // query rows: [rlo, rhi) of the numbering in which row r sees keys <= r under the causal mask
     const int rlo = p.row_lo, rhi = p.row_lo + p.L, LQ = p.L;
@@ -650,7 +650,7 @@ int launch_mode(const FwdParams &p, int idx_mode, hipStream_t st)
         // skipping the heads of the other
         FwdParams pf = p;
         pf.filter = 1;
-        hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_MAD24, PH>), grid, block, sh, st, pf);
+        hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_MULHI24, PH>), grid, block, sh, st, pf);
         hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_FP64, PH>), grid, block, sh, st, pf);
         return (int)hipGetLastError();
     }

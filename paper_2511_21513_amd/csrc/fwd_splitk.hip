@@ -58,7 +58,7 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_splitk_kernel(const F
     const int b = wi.b, hq = wi.hq, kvh = wi.kvh, qt = wi.qt + p.row_lo / 32;
     const int bh = b * p.Hq + hq;
     const HeadParams hp = p.hp_table ? p.hp_table[hq] : p.hp0;
-    if (p.filter && (hp.pad[0] == IDX_TOP24 ? (int)IDX_MAD24 : hp.pad[0]) != MODE) return; // served by the other launch
+    if (p.filter && hp.pad[0] != MODE) return; // served by the other launch
     const int L = p.Lk;
     const int rlo = p.row_lo, rhi = p.row_lo + p.L, LQ = p.L;
     const uint32_t top = (uint32_t)p.top;
@@ -295,7 +295,7 @@ int launch_mode(const FwdParams &p, int idx_mode, hipStream_t st)
     if (idx_mode == IDX_DEVICE) {
         FwdParams pf = p;
         pf.filter = 1;
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_MAD24>), grid, block, sh, st, pf);
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_MULHI24>), grid, block, sh, st, pf);
         hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_FP64>), grid, block, sh, st, pf);
         return (int)hipGetLastError();
     }

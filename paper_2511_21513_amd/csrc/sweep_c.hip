@@ -60,7 +60,9 @@ namespace {
 constexpr int WAVES = 4;
 constexpr int NT = WAVES * 64;
 
-template <int D, int RB, bool CAUSAL, int MODE>
+// SPLIT: every work item is taken by p.split_c workgroups, each with a range of the key tiles.  (An instantiation of its own:
+// with the range decided at run time the launches that do not split were 1 % slower.)
+template <int D, int RB, bool CAUSAL, int MODE, bool SPLIT>
 __global__ __launch_bounds__(NT, RB == 1 ? 2 : 1) void sweep_c_kernel(const FwdParams p)
 {
     constexpr int KB = D / 32;       // 32-wide blocks of the head dimension
@@ -97,14 +99,14 @@ __global__ __launch_bounds__(NT, RB == 1 ? 2 : 1) void sweep_c_kernel(const FwdP
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 31, h = lane >> 5;
     int bid = (int)blockIdx.x;
-    const int n_split = p.split_c > 0 ? p.split_c : 1;
-    const int ksp = p.split_c > 0 ? fwd_split_index(bid, n_split) : 0;
+    const int n_split = SPLIT ? p.split_c : 1;
+    const int ksp = SPLIT ? fwd_split_index(bid, n_split) : 0;
     const WorkItem wi = fwd_work_item(p, bid);
     if (!wi.valid) return; // padding of the XCD-aware grid (uniform for the whole workgroup)
     const int b = wi.b, hq = wi.hq, kvh = wi.kvh, qt = wi.qt + p.row_lo / BQ;
     const int bh = b * p.Hq + hq;
     const HeadParams hp = p.hp_table ? p.hp_table[hq] : p.hp0;
-    if (MODE != IDX_MIX && p.filter && hp.pad[0] != MODE) return; // another launch of this pair serves the head (uniform for the workgroup)
+    if (p.filter && (MODE == IDX_MIX ? hp.pad[0] == IDX_FP64 : hp.pad[0] != MODE)) return; // another launch of this pair serves the head (uniform for the workgroup)
     // The rest of the kernel with the index scheme M as a compile-time constant: MODE itself, or, under IDX_MIX,
     // the scheme named in the head's own parameters (top-byte constants where the head has them, else the
     // multiply-high scheme that serves every head of the call).
@@ -519,7 +521,7 @@ __global__ __launch_bounds__(NT, RB == 1 ? 2 : 1) void sweep_c_kernel(const FwdP
     else sweep(std::integral_constant<int, 0>{});
 
     // Key-split launch: the accumulators of this range, corrected, for finish_split_kernel to add up
-    if (p.split_c > 0) {
+    if constexpr (SPLIT) {
         if (valid) {
             int32_t *Pp = p.ws_part + ((int64_t)ksp * p.B * p.Hq * LQ + (int64_t)bh * LQ + (row - rlo)) * D;
             const int32_t cfac = (path == 0 || path == 4) ? 128 : 0;
@@ -579,34 +581,42 @@ __global__ __launch_bounds__(NT, RB == 1 ? 2 : 1) void sweep_c_kernel(const FwdP
     }
 }
 
-template <int D, int RB, bool CAUSAL>
+template <int D, int RB, bool CAUSAL, bool SPLIT>
 int launch_mode(const FwdParams &p, int idx_mode, hipStream_t st)
 {
-    const dim3 grid((unsigned)(fwd_grid_size(p.B, p.Hq, p.Hkv, p.n_qtiles) * (p.split_c > 0 ? p.split_c : 1))), block(NT);
+    const dim3 grid((unsigned)(fwd_grid_size(p.B, p.Hq, p.Hkv, p.n_qtiles) * (SPLIT ? p.split_c : 1))), block(NT);
     if (idx_mode == IDX_DEVICE) {
         // the scheme of each head is known on the device only: one launch per scheme, each
         // skipping the heads of the other
         FwdParams pf = p;
         pf.filter = 1;
-        hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_TOP24>), grid, block, 0, st, pf);
-        hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_FP64>), grid, block, 0, st, pf);
+        hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_MIX, SPLIT>), grid, block, 0, st, pf);
+        hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_FP64, SPLIT>), grid, block, 0, st, pf);
         return (int)hipGetLastError();
     }
     if (idx_mode == IDX_MIX)
-        hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_MIX>), grid, block, 0, st, p);
+        hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_MIX, SPLIT>), grid, block, 0, st, p);
     else if (idx_mode == IDX_TOP24)
-        hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_TOP24>), grid, block, 0, st, p);
+        hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_TOP24, SPLIT>), grid, block, 0, st, p);
     else if (idx_mode == IDX_MAD24)
-        hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_MAD24>), grid, block, 0, st, p);
+        hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_MAD24, SPLIT>), grid, block, 0, st, p);
     else if (idx_mode == IDX_MULHI24)
-        hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_MULHI24>), grid, block, 0, st, p);
+        hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_MULHI24, SPLIT>), grid, block, 0, st, p);
     else if (idx_mode == IDX_FP32)
-        hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_FP32>), grid, block, 0, st, p);
+        hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_FP32, SPLIT>), grid, block, 0, st, p);
     else if (idx_mode == IDX_ROW64)
-        hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_ROW64>), grid, block, 0, st, p);
+        hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_ROW64, SPLIT>), grid, block, 0, st, p);
     else
-        hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_FP64>), grid, block, 0, st, p);
+        hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_FP64, SPLIT>), grid, block, 0, st, p);
     return (int)hipGetLastError();
+}
+
+template <bool SPLIT>
+int launch_split(const FwdParams &p, int d, int idx_mode, hipStream_t st)
+{
+    if (d == 64) return p.causal ? launch_mode<64, 1, true, SPLIT>(p, idx_mode, st) : launch_mode<64, 1, false, SPLIT>(p, idx_mode, st);
+    if (d == 128) return p.causal ? launch_mode<128, 1, true, SPLIT>(p, idx_mode, st) : launch_mode<128, 1, false, SPLIT>(p, idx_mode, st);
+    return (int)hipErrorInvalidValue;
 }
 
 } // namespace
@@ -616,9 +626,7 @@ int launch_mode(const FwdParams &p, int idx_mode, hipStream_t st)
 int launch_sweep_c(const FwdParams &p, int d, int idx_mode, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
-    if (d == 64) return p.causal ? launch_mode<64, 1, true>(p, idx_mode, st) : launch_mode<64, 1, false>(p, idx_mode, st);
-    if (d == 128) return p.causal ? launch_mode<128, 1, true>(p, idx_mode, st) : launch_mode<128, 1, false>(p, idx_mode, st);
-    return (int)hipErrorInvalidValue;
+    return p.split_c > 0 ? launch_split<true>(p, d, idx_mode, st) : launch_split<false>(p, d, idx_mode, st);
 }
 
 } // namespace intattn

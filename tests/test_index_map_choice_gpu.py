@@ -1,0 +1,73 @@
+"""The index map that the device picks for thresholds it learns from device-resident scales: the multiply-high and top-byte
+constants it searches, the fp64 map where a head has none, and the single-precision map of the group modes on both sides of
+its limit; bit-compared with the oracle."""
+import numpy as np
+import pytest
+
+from test_parity_gpu import key_group_forward, torch_mod  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+D = 64
+
+
+def scales_for(c_int):
+    """(s_q, s_k) whose threshold round(6.6 sqrt(64) / (s_q s_k)) is c_int."""
+    s_k = np.float32(0.03)
+    s_q = np.float32(6.6 * 8.0 / (float(s_k) * c_int))
+    got = int(np.floor(6.6 / ((float(s_q) * float(s_k)) / 8.0) + 0.5))
+    assert got == c_int
+    return s_q, s_k
+
+
+def qkv(rng, B, H, L):
+    return [rng.integers(-127, 128, (B, H, L, D), dtype=np.int8) for _ in range(3)]
+
+
+def without_multiply_high():
+    """A threshold that has no multiply-high constants at all (by the host's wider search)."""
+    from paper_2511_21513_amd import binding
+
+    host = binding.IntAttn(device=-1)
+    return next(c for c in range(70000, 90000) if host.derive_index_map(c, 2)[0] != 2)
+
+
+THRESHOLDS = [
+    [5203],                          # per tensor: one wave derives for every head
+    [47011],
+    [None],
+    [900, 5203, 33, 12000, 1],       # top byte for sweep C everywhere
+    [5203, 47011, 30011, 61, 55064], # some heads on multiply-high alone
+    [5203, None, 47011],             # one head without either: fp64 for all
+    [5203, 47011] * 9,               # a second round of the one workgroup
+    [5203, 47011] * 17,              # a workgroup per head
+    [5203] * 33 + [None],
+]
+
+
+@pytest.mark.parametrize("variant", [0, 1, 3, 4, 5, 9], ids=lambda v: f"variant{v}")
+@pytest.mark.parametrize("which", range(len(THRESHOLDS)))
+def test_device_scales_bit_exact(torch_mod, oracle, which, variant):  # noqa: F811
+    from paper_2511_21513_amd import binding
+
+    torch = torch_mod
+    c_ints = [without_multiply_high() if c is None else c for c in THRESHOLDS[which]]
+    per_head = len(c_ints) > 1
+    H, L, lq = (len(c_ints) if per_head else 2), 161, (1 if variant == 9 else 161)
+    print(f"case {c_ints} variant {variant}", flush=True)
+    rng = np.random.default_rng(which)
+    q, k, v = qkv(rng, 1, H, L)
+    q = np.ascontiguousarray(q[:, :, L - lq:])
+    s_q, s_k = (np.array(x, dtype=np.float32) for x in zip(*(scales_for(c) for c in c_ints)))
+    s_v = np.full(len(c_ints), 0.02, dtype=np.float32)
+    s_o = np.full(len(c_ints), 0.004, dtype=np.float32)
+    want = oracle.forward(q, k, v, s_q, s_k, s_v, s_o, causal=True, per_head=per_head)["out"]
+    assert np.abs(want).max() > 5
+    ia = binding.IntAttn(device=0, variant=variant)
+    tq, tk, tv, *sc = (torch.from_numpy(x).cuda() for x in (q, k, v, s_q, s_k, s_v, s_o))
+    out = torch.full_like(tq, 99)
+    args, keep = ia.make_args(tq, tk, tv, out, *sc, causal=True, per_head=per_head, device_scales=True)
+    ia.forward_dynamic_args(args, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert ia.dynamic_status() == 0 and int((out.cpu().numpy() != want).sum()) == 0
+    ia.close()
