@@ -620,9 +620,18 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
     p.top = (1 << ctx->lut_bits) - 1;
     int variant = fwd_choose_variant(ctx->variant, a->B, a->Hq, a->L, p.Lk, a->d, a->causal);
     if (variant == 5 && ctx->lut_bits > 5) variant = 4; // the pipelined sweep C holds 32-entry tables; same tiling otherwise
-    if (a->scale_mode == 3) variant = 1;                // groups over the key axis: the single-launch kernel
-    if (variant == 3 && a->scale_mode == 2) variant = 1; // the split-key single launch takes per-tensor / per-head parameters
+    // Groups (scale modes 2 and 3): up to 256 workgroups of 128 rows, and up to 512 with key groups, the keys split over
+    // the waves of a workgroup win (1024 tokens, 32 / 8 heads, d 128: 64 against 112 us with key groups, 50 against 55
+    // without; with key groups 2048 tokens, 32 / 8 heads, d 128: 170 against 203, 1500 tokens, 32 heads, d 64: 80 against
+    // 142), past that the 128-row kernel does (without key groups, 2 x 1024 tokens: 56 against 88; with them, 2 x 2048
+    // tokens, 32 heads, d 128: 289 against 327).  Key groups run in the single-launch kernels only.
     const bool automatic = ctx->variant == 0 || ctx->variant == 9 || ctx->variant == 10;
+    if (a->scale_mode >= 2) {
+        const int64_t wgs = (int64_t)a->B * a->Hq * ((a->L + 127) / 128);
+        if (automatic && a->scale_mode == 3) variant = wgs <= 512 ? 3 : 1;
+        else if (automatic && variant == 3 && wgs > 256) variant = 1;
+        else if (a->scale_mode == 3 && variant != 3) variant = 1;
+    }
     // Few query rows against many keys: the split-key kernels (all query heads of a KV head, times
     // the query rows, packed into one MFMA operand of at most 31 rows).
     const int64_t packed_rows = (int64_t)p.group * p.L;

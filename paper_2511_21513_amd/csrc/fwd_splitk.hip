@@ -34,7 +34,8 @@ constexpr int WAVES = 4;
 constexpr int NT = WAVES * 64;
 
 template <int D, bool CAUSAL, int MODE>
-__global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_splitk_kernel(const FwdParams p)
+// (key groups at d = 64: with 128 registers they spill)
+__global__ __launch_bounds__(NT, D == 64 && MODE != IDX_KGROUP ? 4 : 2) void fwd_splitk_kernel(const FwdParams p)
 {
     constexpr int KB = D / 32;  // 32-wide blocks of the head dimension
     constexpr int CB = D / 32;  // 32-wide blocks of output channels
@@ -49,6 +50,7 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_splitk_kernel(const F
     __shared__ __attribute__((aligned(1024))) int8_t Vw1[WAVES][SUB];
     __shared__ int32_t acc_lds[32][D + 1]; // output accumulators, summed over the waves (rows padded: one bank per row)
     __shared__ int32_t red[2][WAVES][32];                               // per-wave row max / row sum
+    __shared__ double red_m[MODE == IDX_KGROUP ? WAVES : 1][32];        // per-wave maximum of the dequantized logits
     __shared__ uint32_t lut_lds[16];
     extern __shared__ uint32_t PT[]; // [idx][row], NIDX * 32 words
 
@@ -63,12 +65,29 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_splitk_kernel(const F
     const int rlo = p.row_lo, rhi = p.row_lo + p.L, LQ = p.L;
     const uint32_t top = (uint32_t)p.top;
     const int NIDX = top < 32 ? 32 : 64;
+    // Finer quantization groups (Sec. 3.3).  RG: parameters per block of query rows, from the row table; KG: each key block
+    // has a scale of its own too, so that the row maximum is taken over the dequantized logits (fp64) and a lane forms the
+    // constants of its row for each key block (once per 32-key sub-tile where a sub-tile lies in one block).
+    constexpr bool KG = MODE == IDX_KGROUP, RG = KG || MODE == IDX_ROW64;
+    const float *skp = KG ? p.sk_blocks + (int64_t)(b * p.Hkv + kvh) * p.n_kblk : nullptr;
+    const bool kg_blocks = KG && (p.k_block % 32) == 0; // uniform
+    auto row_hp = [&](int r) __attribute__((always_inline)) {
+        const int lr = (r >= p.row_lo && r < p.row_lo + p.L) ? r - p.row_lo : 0;
+        return p.row_table[(int64_t)bh * p.n_rowblk + lr / p.q_block];
+    };
 
     const int q0 = qt * 32, row = q0 + n; // the lane's query row (numbering in which row r sees keys <= r)
     const bool row_ok = row >= rlo && row < rhi;
     const int8_t *Qp = p.q + (int64_t)b * p.qs[0] + (int64_t)hq * p.qs[1];
     const int8_t *Kp = p.k + (int64_t)b * p.ks[0] + (int64_t)kvh * p.ks[1];
     const int8_t *Vp = p.v + (int64_t)b * p.vs[0] + (int64_t)kvh * p.vs[1];
+
+    double sq_row = 0.0, Mreal = -__builtin_inf();
+    if constexpr (KG) sq_row = (double)p.sq_rows[(int64_t)bh * p.n_rowblk + (row_ok ? row - rlo : 0) / p.q_block];
+    // alpha^(g) of the logit (lane's row, key); keys past the end take the last block's scale
+    auto kg_alpha = [&](int key) __attribute__((always_inline)) {
+        return (sq_row * (double)skp[min(key, L - 1) / p.k_block]) / p.sqrt_d;
+    };
 
     if (tid < 16) lut_lds[tid] = p.lut[tid];
     for (int i = tid; i < 32 * (D + 1); i += NT) (&acc_lds[0][0])[i] = 0;
@@ -129,7 +148,28 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_splitk_kernel(const F
     int mx = INT32_MIN;
     walk(no_prefetch, [&](int j, const v4i (&kf)[KB], int) __attribute__((always_inline)) {
         const v16i s = scores(kf);
-        if (sub_is_full(j)) {
+        if constexpr (KG) {
+            const bool full = sub_is_full(j);
+            if (kg_blocks) {
+                int lmax = INT32_MIN; // no score is INT32_MIN
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (full || visible(32 * j + acc_key(i, h))) lmax = max(lmax, s[i]);
+                if (lmax != INT32_MIN) {
+                    const double x = kg_alpha(32 * j) * (double)lmax; // alpha > 0: the block's largest logit
+                    Mreal = x > Mreal ? x : Mreal;
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int key = 32 * j + acc_key(i, h);
+                    if (full || visible(key)) {
+                        const double x = kg_alpha(key) * (double)s[i];
+                        Mreal = x > Mreal ? x : Mreal;
+                    }
+                }
+            }
+        } else if (sub_is_full(j)) {
 #pragma unroll
             for (int i = 0; i < 16; i += 2) mx = max(max(s[i], s[i + 1]), mx);
         } else {
@@ -142,25 +182,90 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_splitk_kernel(const F
     __syncthreads(); // (also: lut_lds and the zeroed accumulators are visible)
     mx = max(max(red[0][0][n], red[0][1][n]), max(red[0][2][n], red[0][3][n]));
     if (!row_ok) mx = 0; // rows outside the problem: zero scores, never stored
+    if constexpr (KG) {
+        double o = __shfl_xor(Mreal, 32);
+        Mreal = o > Mreal ? o : Mreal;
+        if (h == 0) red_m[wave][n] = Mreal;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            o = red_m[w][n];
+            Mreal = o > Mreal ? o : Mreal;
+        }
+    }
 
     RowIndex<MODE> ri;
-    ri.init(hp, mx, top);
+    ri.init(MODE == IDX_ROW64 ? row_hp(row) : hp, KG ? 0 : mx, top);
+    if constexpr (KG) ri.shift = (int)top; // bound of the index (see RowIndex)
+    // Group modes: where every lane's threshold is small enough, the index map runs in fp32 (see RowIndex32), the choice
+    // uniform for the wave.
+    RowIndex32 ri32;
+    bool single = false;
+    auto pick_map = [&](int c_int) __attribute__((always_inline)) {
+        single = __all(ri32.init(c_int, ri.mx, top));
+    };
+    if constexpr (MODE == IDX_ROW64) pick_map(ri.mx - ri.bound);
+    // Key groups: the constants of the lane's row for the key block of `key`, as in the tiled kernel: c_int^(g) =
+    // round(c / alpha^(g)) capped at 2^30, m^(g) = round(M / alpha^(g)) clamped to [-2^22, 2^30 + 2^22], which changes no
+    // result (comparisons written so that a NaN from an unusable scale lands on a bound).
+    auto kg_index = [&](int key) __attribute__((always_inline)) {
+        const double al = kg_alpha(key);
+        double cd = __builtin_floor(p.clip / al + 0.5);
+        cd = cd >= 1.0 ? cd : 1.0;
+        cd = cd < 1073741824.0 ? cd : 1073741824.0;
+        double md = __builtin_floor(Mreal / al + 0.5);
+        md = md < 1077936128.0 ? md : 1077936128.0;
+        md = md > -4194304.0 ? md : -4194304.0;
+        ri.mx = (int)md;
+        ri.bound = ri.mx - (int)cd;
+        pick_map((int)cd);
+        if (!single) {
+            const uint64_t bits = (uint64_t)__double_as_longlong((double)top / cd) + 1ull; // the double after top / c_int
+            ri.negr = __longlong_as_double((long long)(bits ^ 0x8000000000000000ull));
+        }
+    };
+    // table indices of the sixteen scores of sub-tile j (in place); hidden keys and, with key groups, logits above their
+    // block's image of the maximum are brought to it
+    auto indices = [&](int j, v16i &s, bool clamp_max) __attribute__((always_inline)) {
+        if constexpr (!RG) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[i] = (int)ri(clamp_max ? min(max(s[i], ri.bound), ri.mx) : max(s[i], ri.bound));
+        } else if (KG && !kg_blocks) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                kg_index(32 * j + acc_key(i, h));
+                const int sc = min(max(s[i], ri.bound), ri.mx);
+                s[i] = (int)(single ? ri32(sc) : ri(sc));
+            }
+        } else {
+            if (KG) kg_index(32 * j);
+            if (single) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) s[i] = (int)ri32(min(max(s[i], ri.bound), ri.mx));
+            } else {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) s[i] = (int)ri(min(max(s[i], ri.bound), ri.mx));
+            }
+        }
+    };
 
     // ================================================================= sweep B: row sum of E_hat
     const uint8_t *lut_b = (const uint8_t *)lut_lds;
     uint32_t sum = 0;
     walk(no_prefetch, [&](int j, const v4i (&kf)[KB], int) __attribute__((always_inline)) {
-        const v16i s = scores(kf);
+        v16i s = scores(kf);
         if (sub_is_full(j)) {
             uint32_t e[16];
+            indices(j, s, false);
 #pragma unroll
-            for (int i = 0; i < 16; ++i) e[i] = lut_b[ri(max(s[i], ri.bound))];
+            for (int i = 0; i < 16; ++i) e[i] = lut_b[s[i]];
 #pragma unroll
             for (int i = 0; i < 16; ++i) sum += e[i];
         } else {
+            indices(j, s, true); // hidden keys may exceed the row max
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const uint32_t e = lut_b[ri(min(max(s[i], ri.bound), ri.mx))]; // hidden keys may exceed the row max
+                const uint32_t e = lut_b[s[i]];
                 sum += visible(32 * j + acc_key(i, h)) ? e : 0u;
             }
         }
@@ -171,7 +276,7 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_splitk_kernel(const F
     sum = (uint32_t)red[1][0][n] + (uint32_t)red[1][1][n] + (uint32_t)red[1][2][n] + (uint32_t)red[1][3][n];
     if (sum == 0) sum = 1; // only rows outside [rlo, rhi); never stored
     if (wave == 0 && h == 0 && row_ok) {
-        if (p.dbg_row_max) p.dbg_row_max[(int64_t)bh * LQ + (row - rlo)] = mx;
+        if (!KG && p.dbg_row_max) p.dbg_row_max[(int64_t)bh * LQ + (row - rlo)] = mx;
         if (p.dbg_row_sum) p.dbg_row_sum[(int64_t)bh * LQ + (row - rlo)] = (int32_t)sum;
     }
     // per-row probability table, once per workgroup: PT[idx][row] = round(255 LUT_hat[idx] / S) - 128 as a byte
@@ -233,11 +338,9 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_splitk_kernel(const F
     walk(stage_v, [&](int j, const v4i (&kf)[KB], int buf) __attribute__((always_inline)) {
         v16i s = scores(kf);
         const bool full = sub_is_full(j);
+        indices(j, s, !full);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int sc = full ? max(s[i], ri.bound) : min(max(s[i], ri.bound), ri.mx);
-            s[i] = (int)pt[ri(sc) * 32];
-        }
+        for (int i = 0; i < 16; ++i) s[i] = (int)pt[s[i] * 32];
         v4i pf;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -272,6 +375,8 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_splitk_kernel(const F
     const int er = tid >> 3, ec0 = (tid & 7) * CPT, erow = q0 + er;
     if (erow >= rlo && erow < rhi) {
         int8_t *Op = p.out + (int64_t)b * p.os[0] + (int64_t)hq * p.os[1] + (int64_t)(erow - rlo) * p.os[2];
+        HeadParams he = RG ? row_hp(erow) : hp;
+        if (KG && p.head_status[hq] != 0) he.rq_mult = 0; // an unusable scale somewhere in the head: all zeros
 #pragma unroll
         for (int c4 = 0; c4 < CPT; c4 += 4) {
             uint32_t packed = 0;
@@ -280,7 +385,7 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_splitk_kernel(const F
                 const int ch = ec0 + c4 + r;
                 const int32_t acc = acc_lds[er][ch];
                 if (p.dbg_acc) p.dbg_acc[((int64_t)bh * LQ + (erow - rlo)) * D + ch] = acc;
-                packed |= ((uint32_t)requant_any(acc, hp.rq_mult, hp.rq_shift) & 0xffu) << (8 * r);
+                packed |= ((uint32_t)requant_any(acc, he.rq_mult, he.rq_shift) & 0xffu) << (8 * r);
             }
             *(uint32_t *)(Op + ec0 + c4) = packed;
         }
@@ -305,6 +410,10 @@ int launch_mode(const FwdParams &p, int idx_mode, hipStream_t st)
         hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_MULHI24>), grid, block, sh, st, p);
     else if (idx_mode == IDX_FP32)
         hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_FP32>), grid, block, sh, st, p);
+    else if (idx_mode == IDX_ROW64)
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_ROW64>), grid, block, sh, st, p);
+    else if (idx_mode == IDX_KGROUP)
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_KGROUP>), grid, block, sh, st, p);
     else if (idx_mode == IDX_FP64)
         hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_FP64>), grid, block, sh, st, p);
     else
@@ -314,7 +423,7 @@ int launch_mode(const FwdParams &p, int idx_mode, hipStream_t st)
 
 } // namespace
 
-// p.n_qtiles counts 32-row blocks; per-tensor and per-head parameters only (hp0 / hp_table); no workspace.
+// p.n_qtiles counts 32-row blocks; every parameter mode; no workspace.
 int launch_fwd_splitk(const FwdParams &p, int d, int idx_mode, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;

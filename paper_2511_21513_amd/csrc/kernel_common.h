@@ -204,6 +204,24 @@ template <int MODE> struct RowIndex {
     }
 };
 
+// The index map in single precision for parameters that a lane forms itself: trunc(fma(t, -r, 0.5)), t = -Delta' in
+// [-c_int, 0], r the float after fl(top / c_int).  Exact where init() says so, without a search: r exceeds top / c_int by
+// more than 0 and less than 3 * 2^-24 of it, so the exact value of the fma is at least v = -t top / c_int + 1/2 and above it
+// by less than 3 top 2^-24; its rounding adds at most half a unit in the last place of a value below top + 1 (2^-20 for
+// top <= 31, 2^-19 for 63) and is monotone, so an integer v stays on or above itself; any other v lies at least
+// 1 / (2 c_int) below the next integer, which is more than the sum of both up to 76900 (top = 31) and 37900 (top = 63).
+struct RowIndex32 {
+    int mx;
+    float negr;
+    __device__ __forceinline__ bool init(int c_int, int row_max, uint32_t top)
+    {
+        mx = row_max;
+        negr = -__uint_as_float(__float_as_uint((float)top / (float)c_int) + 1u); // one IEEE division
+        return c_int <= (top < 32 ? 75000 : 37000);
+    }
+    __device__ __forceinline__ uint32_t operator()(int sc) const { return (uint32_t)(int)__builtin_fmaf((float)(sc - mx), negr, 0.5f); }
+};
+
 // The barrier that publishes tiles filled by direct-to-LDS loads: a wave's own loads must have landed before
 // it signals, because the other waves read what it loaded.  (On this target the compiler also drains every
 // counter before s_barrier; the wait is spelled out so that correctness does not rest on that.)
