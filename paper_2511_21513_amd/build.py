@@ -1,6 +1,6 @@
 """Builds libintattn.so (the C-ABI library) in-tree with hipcc for gfx950.
 
-Every source is compiled to an object of its own, a few at a time, and the objects are linked into
+Every source is compiled to an object of its own, a few at a time (the slowest first), and the objects are linked into
 the shared library; the objects live in `_build/` next to this file (not tracked)."""
 from __future__ import annotations
 
@@ -13,8 +13,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libintattn.so")
-SOURCES = ["api.cpp", "fwd_kernel.hip", "fwd_single.hip", "fwd_split.hip", "fwd_splitk.hip", "sweep_c.hip",
-           "quantize_kernel.hip", "derive_kernel.hip", "decode_kernel.hip", "softmax_kernel.hip", "quantonly_kernel.hip"]
+SOURCES = ["sweep_c_128.hip", "sweep_c_split_128.hip", "sweep_c_64.hip", "sweep_c_split_64.hip", "fwd_single.hip", "fwd_split.hip",
+           "fwd_splitk.hip", "api.cpp", "fwd_kernel.hip", "quantize_kernel.hip", "derive_kernel.hip", "decode_kernel.hip",
+           "softmax_kernel.hip", "quantonly_kernel.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",

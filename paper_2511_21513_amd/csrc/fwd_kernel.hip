@@ -19,6 +19,18 @@ int launch_shape(const FwdParams &p, int d, int idx_mode, hipStream_t st);
 } // namespace fwdk
 using fwdk::launch_shape;
 
+namespace sweepc {
+template <int D, bool SPLIT>
+int launch(const FwdParams &p, int idx_mode, hipStream_t st); // instantiated explicitly in sweep_c_*.hip
+} // namespace sweepc
+
+static int launch_sweep_c(const FwdParams &p, int d, int idx_mode, hipStream_t st)
+{
+    if (d == 64) return p.split_c > 0 ? sweepc::launch<64, true>(p, idx_mode, st) : sweepc::launch<64, false>(p, idx_mode, st);
+    if (d == 128) return p.split_c > 0 ? sweepc::launch<128, true>(p, idx_mode, st) : sweepc::launch<128, false>(p, idx_mode, st);
+    return (int)hipErrorInvalidValue;
+}
+
 namespace {
 
 // Sums of V over each chunk of `chunk` consecutive keys, per (batch, KV head) and channel:
@@ -184,7 +196,7 @@ int launch_fwd(const FwdParams &p_in, int d, int idx_mode, int variant, int stag
         if (e == 0) e = launch_shape<2, 2, 4>(pab, d, idx_mode, st);
         FwdParams pc = p;
         if (p.hp_table_c) pc.hp_table = p.hp_table_c; // as below
-        if (e == 0) e = launch_sweep_c(pc, d, sweep_c_mode(p, idx_mode), stream);
+        if (e == 0) e = launch_sweep_c(pc, d, sweep_c_mode(p, idx_mode), st);
         return e == 0 ? launch_finish_split(p, d, st) : e;
     }
     if (stage != 0 && !two_launches) return (int)hipErrorNotSupported;
@@ -215,7 +227,7 @@ int launch_fwd(const FwdParams &p_in, int d, int idx_mode, int variant, int stag
         if (variant == 4) return launch_shape<1, 2, 2>(p, d, idx_mode, st);
         FwdParams pc = p;
         if (p.hp_table_c) pc.hp_table = p.hp_table_c;
-        return launch_sweep_c(pc, d, sweep_c_mode(p, idx_mode), stream);
+        return launch_sweep_c(pc, d, sweep_c_mode(p, idx_mode), st);
     }
     return launch_shape<1, 2, 0>(p, d, idx_mode, st);
 }

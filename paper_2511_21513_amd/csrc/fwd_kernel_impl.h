@@ -91,9 +91,10 @@ __global__ __launch_bounds__(NT, (PH == 1 || PH >= 3) ? (RB * KT <= 2 ? 4 : 3) :
     const int b = wi.b, hq = wi.hq, kvh = wi.kvh, qt = wi.qt + p.row_lo / BQ;
     const int bh = b * p.Hq + hq;
     const HeadParams hp = p.hp_table ? p.hp_table[hq] : p.hp0;
-    // device-derived parameters: another launch of this pair serves the head when its scheme is not this
-    // kernel's (uniform for the workgroup)
-    if (p.filter && hp.pad[0] != MODE) return;
+    // The rest of the kernel with the index scheme M as a compile-time constant: MODE itself, or, under IDX_DEVICE, the one
+    // that the device-derived parameters name (uniform for the workgroup).
+    auto body = [&](auto mode_tag) __attribute__((always_inline)) {
+    constexpr int M = decltype(mode_tag)::value;
     const int L = p.Lk; // keys
     // query rows: [rlo, rhi) of the numbering in which row r sees keys <= r under the causal mask
     const int rlo = p.row_lo, rhi = p.row_lo + p.L, LQ = p.L;
@@ -103,7 +104,7 @@ __global__ __launch_bounds__(NT, (PH == 1 || PH >= 3) ? (RB * KT <= 2 ? 4 : 3) :
     // of q_block rows, every key the scale of its block of k_block keys.  alpha^(g) = s_Q^(g) s_K^(g) / sqrt(d)
     // per logit; the row maximum is taken over the dequantized logits (fp64), and each key block measures
     // distances from the image of that maximum in its own integer units.
-    constexpr bool KG = MODE == IDX_KGROUP;
+    constexpr bool KG = M == IDX_KGROUP;
     const float *skp = KG ? p.sk_blocks + (int64_t)(b * p.Hkv + kvh) * p.n_kblk : nullptr;
     const bool kg_blocks = KG && (p.k_block % 32) == 0; // a 32-key sub-tile lies in one key block (uniform)
     double sq_row[RB], Mreal[RB];
@@ -334,9 +335,9 @@ __global__ __launch_bounds__(NT, (PH == 1 || PH >= 3) ? (RB * KT <= 2 ? 4 : 3) :
         const int lr = (row >= rlo && row < rhi) ? row - rlo : 0;
         return p.row_table[(int64_t)bh * p.n_rowblk + lr / p.q_block];
     };
-    RowIndex<MODE> ri[RB];
+    RowIndex<M> ri[RB];
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) ri[rb].init(MODE == IDX_ROW64 ? row_hp(qw0 + 32 * rb + n) : hp, KG ? 0 : mx[rb], top);
+    for (int rb = 0; rb < RB; ++rb) ri[rb].init(M == IDX_ROW64 ? row_hp(qw0 + 32 * rb + n) : hp, KG ? 0 : mx[rb], top);
     if constexpr (KG) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) ri[rb].shift = (int)top; // bound of the index (see RowIndex)
@@ -481,7 +482,7 @@ __global__ __launch_bounds__(NT, (PH == 1 || PH >= 3) ? (RB * KT <= 2 ? 4 : 3) :
             for (int c = 0; c < nchunk; ++c) acc += cp[(int64_t)c * D];
             colsum[tid] = acc;
         }
-    } else {
+    } else if constexpr (PH == 0) {
         // Short key sequences: the launch of the small kernel costs more than summing V over the
         // keys [0, kmax) here (thread = 16 channels of every KL-th key row, then the key lanes of
         // a wave by lane exchange, then the four waves through LDS).
@@ -614,7 +615,7 @@ __global__ __launch_bounds__(NT, (PH == 1 || PH >= 3) ? (RB * KT <= 2 ? 4 : 3) :
         const int row = qw0 + 32 * rb + n;
         if (row < rlo || row >= rhi) continue;
         int8_t *Op = p.out + (int64_t)b * p.os[0] + (int64_t)hq * p.os[1] + (int64_t)(row - rlo) * p.os[2];
-        HeadParams he = (MODE == IDX_ROW64 || KG) ? row_hp(row) : hp;
+        HeadParams he = (M == IDX_ROW64 || KG) ? row_hp(row) : hp;
         if (KG && p.head_status[hq] != 0) he.rq_mult = 0; // an unusable scale somewhere in the head: all zeros
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
@@ -632,6 +633,13 @@ __global__ __launch_bounds__(NT, (PH == 1 || PH >= 3) ? (RB * KT <= 2 ? 4 : 3) :
             }
         }
     }
+    };
+    if constexpr (MODE == IDX_DEVICE) {
+        if (hp.pad[0] == IDX_MULHI24) body(std::integral_constant<int, IDX_MULHI24>{});
+        else body(std::integral_constant<int, IDX_FP64>{});
+    } else {
+        body(std::integral_constant<int, MODE>{});
+    }
 }
 
 template <int D, int RB, int KT, bool CAUSAL, int PH>
@@ -645,13 +653,8 @@ int launch_mode(const FwdParams &p, int idx_mode, hipStream_t st)
         hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_MAD24, PH>), grid, block, sh, st, p);
         return (int)hipGetLastError();
     }
-    if (idx_mode == IDX_DEVICE) {
-        // the scheme of each head is known on the device only: one launch per scheme, each
-        // skipping the heads of the other
-        FwdParams pf = p;
-        pf.filter = 1;
-        hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_MULHI24, PH>), grid, block, sh, st, pf);
-        hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_FP64, PH>), grid, block, sh, st, pf);
+    if (idx_mode == IDX_DEVICE) { // the scheme is known on the device only
+        hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_DEVICE, PH>), grid, block, sh, st, p);
         return (int)hipGetLastError();
     }
     if constexpr (RB == 1 && KT == 2 && PH == 0) {

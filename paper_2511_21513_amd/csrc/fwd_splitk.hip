@@ -23,6 +23,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "kernel_common.h"
 #include "params.h"
 
@@ -60,7 +62,10 @@ __global__ __launch_bounds__(NT, D == 64 && MODE != IDX_KGROUP ? 4 : 2) void fwd
     const int b = wi.b, hq = wi.hq, kvh = wi.kvh, qt = wi.qt + p.row_lo / 32;
     const int bh = b * p.Hq + hq;
     const HeadParams hp = p.hp_table ? p.hp_table[hq] : p.hp0;
-    if (p.filter && hp.pad[0] != MODE) return; // served by the other launch
+    // The rest of the kernel with the index scheme M as a compile-time constant: MODE itself, or, under IDX_DEVICE, the one
+    // that the device-derived parameters name (uniform for the workgroup).
+    auto body = [&](auto mode_tag) __attribute__((always_inline)) {
+    constexpr int M = decltype(mode_tag)::value;
     const int L = p.Lk;
     const int rlo = p.row_lo, rhi = p.row_lo + p.L, LQ = p.L;
     const uint32_t top = (uint32_t)p.top;
@@ -68,7 +73,7 @@ __global__ __launch_bounds__(NT, D == 64 && MODE != IDX_KGROUP ? 4 : 2) void fwd
     // Finer quantization groups (Sec. 3.3).  RG: parameters per block of query rows, from the row table; KG: each key block
     // has a scale of its own too, so that the row maximum is taken over the dequantized logits (fp64) and a lane forms the
     // constants of its row for each key block (once per 32-key sub-tile where a sub-tile lies in one block).
-    constexpr bool KG = MODE == IDX_KGROUP, RG = KG || MODE == IDX_ROW64;
+    constexpr bool KG = M == IDX_KGROUP, RG = KG || M == IDX_ROW64;
     const float *skp = KG ? p.sk_blocks + (int64_t)(b * p.Hkv + kvh) * p.n_kblk : nullptr;
     const bool kg_blocks = KG && (p.k_block % 32) == 0; // uniform
     auto row_hp = [&](int r) __attribute__((always_inline)) {
@@ -194,8 +199,8 @@ __global__ __launch_bounds__(NT, D == 64 && MODE != IDX_KGROUP ? 4 : 2) void fwd
         }
     }
 
-    RowIndex<MODE> ri;
-    ri.init(MODE == IDX_ROW64 ? row_hp(row) : hp, KG ? 0 : mx, top);
+    RowIndex<M> ri;
+    ri.init(M == IDX_ROW64 ? row_hp(row) : hp, KG ? 0 : mx, top);
     if constexpr (KG) ri.shift = (int)top; // bound of the index (see RowIndex)
     // Group modes: where every lane's threshold is small enough, the index map runs in fp32 (see RowIndex32), the choice
     // uniform for the wave.
@@ -204,7 +209,7 @@ __global__ __launch_bounds__(NT, D == 64 && MODE != IDX_KGROUP ? 4 : 2) void fwd
     auto pick_map = [&](int c_int) __attribute__((always_inline)) {
         single = __all(ri32.init(c_int, ri.mx, top));
     };
-    if constexpr (MODE == IDX_ROW64) pick_map(ri.mx - ri.bound);
+    if constexpr (M == IDX_ROW64) pick_map(ri.mx - ri.bound);
     // Key groups: the constants of the lane's row for the key block of `key`, as in the tiled kernel: c_int^(g) =
     // round(c / alpha^(g)) capped at 2^30, m^(g) = round(M / alpha^(g)) clamped to [-2^22, 2^30 + 2^22], which changes no
     // result (comparisons written so that a NaN from an unusable scale lands on a bound).
@@ -390,6 +395,13 @@ __global__ __launch_bounds__(NT, D == 64 && MODE != IDX_KGROUP ? 4 : 2) void fwd
             *(uint32_t *)(Op + ec0 + c4) = packed;
         }
     }
+    };
+    if constexpr (MODE == IDX_DEVICE) {
+        if (hp.pad[0] == IDX_MULHI24) body(std::integral_constant<int, IDX_MULHI24>{});
+        else body(std::integral_constant<int, IDX_FP64>{});
+    } else {
+        body(std::integral_constant<int, MODE>{});
+    }
 }
 
 template <int D, bool CAUSAL>
@@ -397,11 +409,8 @@ int launch_mode(const FwdParams &p, int idx_mode, hipStream_t st)
 {
     const dim3 grid((unsigned)fwd_grid_size(p.B, p.Hq, p.Hkv, p.n_qtiles)), block(NT);
     const unsigned sh = (unsigned)((p.top < 32 ? 32 : 64) * 32 * sizeof(uint32_t)); // the per-row probability table
-    if (idx_mode == IDX_DEVICE) {
-        FwdParams pf = p;
-        pf.filter = 1;
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_MULHI24>), grid, block, sh, st, pf);
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_FP64>), grid, block, sh, st, pf);
+    if (idx_mode == IDX_DEVICE) { // the scheme is known on the device only
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_DEVICE>), grid, block, sh, st, p);
         return (int)hipGetLastError();
     }
     if (idx_mode == IDX_MAD24 || idx_mode == IDX_TOP24) // the top-byte scheme is the multiply-add with the shift at 24

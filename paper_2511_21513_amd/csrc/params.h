@@ -13,7 +13,7 @@ enum IdxMode : int32_t {
     IDX_MAD24 = 1,  // (Delta' * mul + add) >> shift, 24-bit operands, 32-bit result
     IDX_MULHI24 = 2,// high 32 bits of the 48-bit product ((Delta' << pre) + add) * mul
     IDX_FP32 = 3,   // trunc(fma(Delta', top/c_int, 0.5)) in IEEE fp32 (idx_mul holds the bits of -top/c_int)
-    IDX_DEVICE = 4, // launchers only: the scheme (MULHI24 or FP64, one for all heads of the call; sweep C: MIX or FP64) is in the HeadParams, written on the device
+    IDX_DEVICE = 4, // the scheme (MULHI24 or FP64, one for all heads of the call) is in the HeadParams, written on the device; sweep C: MIX
     IDX_ROW64 = 5,  // the fp64 scheme with parameters per block of query rows (FwdParams::row_table): finer
                     // quantization groups over the query rows, Sec. 3.3
     IDX_KGROUP = 7, // per-logit parameters: quantization groups over the key axis (Sec. 3.3), fp64 map per key block
@@ -57,7 +57,6 @@ struct FwdParams {
     int32_t k_block, n_kblk;
     double clip, sqrt_d;
     const int32_t *head_status;
-    int32_t filter;             // 1: a workgroup whose head's HeadParams name another scheme than the kernel's returns at once
     int32_t group_batch;        // (batch, KV head) groups of an XCD whose query tiles are interleaved; 0: all of them
     HeadParams hp0;             // the single parameter set when hp_table == nullptr
     uint32_t lut[16];           // LUT_hat, up to 64 bytes packed little-endian (unused tail is 0)
@@ -145,7 +144,6 @@ struct DeriveParams {
 // Launchers implemented in the .hip files.  Return a hipError_t cast to int.
 // stage 0: everything; 1: V column sums + sweeps A+B; 2: sweep C (two-launch variants only; else hipErrorNotSupported)
 int launch_fwd(const FwdParams &p, int d, int idx_mode, int variant, int stage, void *stream);
-int launch_sweep_c(const FwdParams &p, int d, int idx_mode, void *stream);
 int launch_fwd_splitk(const FwdParams &p, int d, int idx_mode, void *stream);
 int fwd_choose_variant(int variant, int B, int Hq, int L, int Lk, int d, int causal); // resolves 0 (automatic) to a concrete variant
 int fwd_rows_per_block(int variant);

@@ -45,6 +45,7 @@
 // sub-tiles earlier than V tiles (K tile t covers sub-tiles [NSUB (t-1) + 2, NSUB t + 2)), so that
 // iteration T reads exactly K tile T+1 and V tile T, and at its top requests K tile T+2 and V
 // tile T+1 into the buffers that were read an iteration ago.
+#pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -55,7 +56,7 @@
 
 namespace intattn {
 
-namespace {
+namespace sweepc {
 
 constexpr int WAVES = 4;
 constexpr int NT = WAVES * 64;
@@ -106,10 +107,9 @@ __global__ __launch_bounds__(NT, RB == 1 ? 2 : 1) void sweep_c_kernel(const FwdP
     const int b = wi.b, hq = wi.hq, kvh = wi.kvh, qt = wi.qt + p.row_lo / BQ;
     const int bh = b * p.Hq + hq;
     const HeadParams hp = p.hp_table ? p.hp_table[hq] : p.hp0;
-    if (p.filter && (MODE == IDX_MIX ? hp.pad[0] == IDX_FP64 : hp.pad[0] != MODE)) return; // another launch of this pair serves the head (uniform for the workgroup)
     // The rest of the kernel with the index scheme M as a compile-time constant: MODE itself, or, under IDX_MIX,
     // the scheme named in the head's own parameters (top-byte constants where the head has them, else the
-    // multiply-high scheme that serves every head of the call).
+    // multiply-high scheme that serves every head of the call; parameters derived on the device may name the fp64 map).
     auto body = [&](auto mode_tag) __attribute__((always_inline)) {
     constexpr int M = decltype(mode_tag)::value;
     const int L = p.Lk; // keys
@@ -575,7 +575,8 @@ __global__ __launch_bounds__(NT, RB == 1 ? 2 : 1) void sweep_c_kernel(const FwdP
     };
     if constexpr (MODE == IDX_MIX) {
         if (hp.pad[0] == IDX_TOP24) body(std::integral_constant<int, IDX_TOP24>{}); // uniform for the workgroup
-        else body(std::integral_constant<int, IDX_MULHI24>{});
+        else if (hp.pad[0] == IDX_MULHI24) body(std::integral_constant<int, IDX_MULHI24>{});
+        else body(std::integral_constant<int, IDX_FP64>{});
     } else {
         body(std::integral_constant<int, MODE>{});
     }
@@ -585,16 +586,7 @@ template <int D, int RB, bool CAUSAL, bool SPLIT>
 int launch_mode(const FwdParams &p, int idx_mode, hipStream_t st)
 {
     const dim3 grid((unsigned)(fwd_grid_size(p.B, p.Hq, p.Hkv, p.n_qtiles) * (SPLIT ? p.split_c : 1))), block(NT);
-    if (idx_mode == IDX_DEVICE) {
-        // the scheme of each head is known on the device only: one launch per scheme, each
-        // skipping the heads of the other
-        FwdParams pf = p;
-        pf.filter = 1;
-        hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_MIX, SPLIT>), grid, block, 0, st, pf);
-        hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_FP64, SPLIT>), grid, block, 0, st, pf);
-        return (int)hipGetLastError();
-    }
-    if (idx_mode == IDX_MIX)
+    if (idx_mode == IDX_MIX || idx_mode == IDX_DEVICE)
         hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_MIX, SPLIT>), grid, block, 0, st, p);
     else if (idx_mode == IDX_TOP24)
         hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_TOP24, SPLIT>), grid, block, 0, st, p);
@@ -611,22 +603,15 @@ int launch_mode(const FwdParams &p, int idx_mode, hipStream_t st)
     return (int)hipGetLastError();
 }
 
-template <bool SPLIT>
-int launch_split(const FwdParams &p, int d, int idx_mode, hipStream_t st)
+// 32 query rows per wave: p.n_qtiles must count tiles of 128 query rows, and the V chunk sums in p.ws_colsum must be over
+// chunks of as many keys; p.ws_row_max / ws_row_sum filled.  Instantiated in a source of its own for each D and SPLIT (these
+// kernels take minutes to compile).
+template <int D, bool SPLIT>
+int launch(const FwdParams &p, int idx_mode, hipStream_t st)
 {
-    if (d == 64) return p.causal ? launch_mode<64, 1, true, SPLIT>(p, idx_mode, st) : launch_mode<64, 1, false, SPLIT>(p, idx_mode, st);
-    if (d == 128) return p.causal ? launch_mode<128, 1, true, SPLIT>(p, idx_mode, st) : launch_mode<128, 1, false, SPLIT>(p, idx_mode, st);
-    return (int)hipErrorInvalidValue;
+    return p.causal ? launch_mode<D, 1, true, SPLIT>(p, idx_mode, st) : launch_mode<D, 1, false, SPLIT>(p, idx_mode, st);
 }
 
-} // namespace
-
-// 32 query rows per wave: p.n_qtiles must count tiles of 128 query rows, and the V chunk sums in
-// p.ws_colsum must be over chunks of as many keys; p.ws_row_max / ws_row_sum filled.
-int launch_sweep_c(const FwdParams &p, int d, int idx_mode, void *stream)
-{
-    hipStream_t st = (hipStream_t)stream;
-    return p.split_c > 0 ? launch_split<true>(p, d, idx_mode, st) : launch_split<false>(p, d, idx_mode, st);
-}
+} // namespace sweepc
 
 } // namespace intattn
