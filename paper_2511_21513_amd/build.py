@@ -14,7 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libintattn.so")
 SOURCES = ["sweep_c_128.hip", "sweep_c_split_128.hip", "sweep_c_64.hip", "sweep_c_split_64.hip", "fwd_single.hip", "fwd_split.hip",
-           "fwd_splitk.hip", "api.cpp", "fwd_kernel.hip", "quantize_kernel.hip", "derive_kernel.hip", "decode_kernel.hip",
+           "fwd_splitk.hip", "fwd_short.hip", "api.cpp", "fwd_kernel.hip", "quantize_kernel.hip", "derive_kernel.hip", "decode_kernel.hip",
            "softmax_kernel.hip", "quantonly_kernel.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

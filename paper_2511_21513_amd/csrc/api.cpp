@@ -673,8 +673,13 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
         }
         if (ks.c > 0) variant = VARIANT_KEY_SPLIT;
     }
+    // Short key sequences at d = 64 with the integer index maps: all scores in registers (fwd_short.hip)
+    const bool integer_map = dv.idx_mode == IDX_MAD24 || dv.idx_mode == IDX_TOP24 || dv.idx_mode == IDX_MULHI24;
+    if (automatic && !decode && !comparator && stage == 0 && !dynamic && !rm.reserve && integer_map && a->scale_mode < 2 &&
+        ctx->lut_bits <= 5 && fwd_short_serves(a->B, a->Hq, p.Lk, a->d))
+        variant = VARIANT_SHORT;
     const int rows_per_block = comparator ? 128 : fwd_rows_per_block(variant);
-    p.n_qtiles = fwd_row_tiles(p.row_lo, p.L, rows_per_block);
+    p.n_qtiles = variant == VARIANT_SHORT ? (p.L + 127) / 128 : fwd_row_tiles(p.row_lo, p.L, rows_per_block);
     p.n_chunks = (p.Lk + rows_per_block - 1) / rows_per_block;
     std::memcpy(p.lut, ctx->lut, 64);
     p.dbg_row_max = a->dbg_row_max; p.dbg_row_sum = a->dbg_row_sum; p.dbg_acc = a->dbg_acc;
@@ -859,7 +864,7 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
         ctx->err.clear();
         return INTATTN_OK;
     }
-    if (!comparator && variant != 3) { // (the split-key single launch passes nothing through memory)
+    if (!comparator && variant != 3 && variant != VARIANT_SHORT) { // (those pass nothing through memory)
         const size_t rows = (size_t)a->B * a->Hq * a->L;
         const size_t cs = (size_t)a->B * a->Hkv * p.n_chunks * a->d;
         const size_t part = (size_t)ks.c * rows * a->d; // first: its rows start 16-byte aligned

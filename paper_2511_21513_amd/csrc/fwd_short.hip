@@ -1,0 +1,246 @@
+// Fused IntAttention forward for short key sequences (at most 256 keys, d = 64: image encoders, short prompts) on gfx950
+// (MI355X), where throughput counts: one workgroup per (batch, query head) and 128 query rows, a wave per 32 rows.
+//
+// All scores of a wave's rows fit its registers (16 per 32 keys), so Q.K^T is computed once and the three reductions of
+// IndexSoftmax (Sec. 3.1-3.2) run on registers: the score becomes its table index, then its probability, in place.  K and V of
+// the head are staged in LDS once, one barrier in all.  What bounds it is vector instructions per score: against the tiled
+// kernel it saves two of three score computations and one of two index computations, and pads rows and keys to 32 only
+// (197 x 197: 224 x 224 scores instead of 256 x 256).  Measured: 128 x 12 heads of 197 x 197 75.1 -> 49.6 us, 256 x 32 heads
+// of 64 x 64 98 -> 46, 128 x 12 heads of 256 x 256 under the mask 78 -> 49.  Workgroups of up to eight waves, a whole head
+// each, took 60.5 us on the first: 148 registers leave a compute unit 12 waves, so only one workgroup of seven.
+//
+// Probabilities go to the signed MFMA as P - 128; the correction comes from an operand of all ones, as in fwd_splitk.hip.
+// Hidden keys take the last table index, whose entry is 0 by Eq. lut16: no part in the sum, probability 0.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "kernel_common.h"
+#include "params.h"
+
+namespace intattn {
+
+namespace {
+
+constexpr int D = 64;
+constexpr int MAX_WAVES = 4; // 12 waves fit a compute unit: three workgroups of four, but only one of seven
+constexpr int KB = D / 32, CB = D / 32;
+constexpr int CPR = D / 16;   // 16-byte chunks per key row
+constexpr int RPB = 1024 / D; // key rows per 1 KiB block
+
+// NS: 32-key sub-tiles held (Lk <= 32 NS)
+template <int NS, bool CAUSAL, int MODE>
+__global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdParams p)
+{
+    __shared__ __attribute__((aligned(1024))) int8_t Ks[NS * 32 * D];
+    __shared__ __attribute__((aligned(1024))) int8_t Vs[NS * 32 * D];
+    __shared__ uint32_t lut_lds[8];
+    extern __shared__ __attribute__((aligned(16))) uint32_t PT_all[]; // a wave's probability table [idx][row], 32 x 32 words; then its output rows
+
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 31, h = lane >> 5;
+    const int n_waves = __builtin_amdgcn_readfirstlane((int)blockDim.x >> 6);
+    const WorkItem wi = fwd_work_item(p, (int)blockIdx.x);
+    if (!wi.valid) return; // padding of the XCD-aware grid (uniform for the whole workgroup)
+    const int b = wi.b, hq = wi.hq, kvh = wi.kvh, bh = b * p.Hq + hq;
+    const HeadParams hp = p.hp_table ? p.hp_table[hq] : p.hp0;
+    const int L = p.Lk, LQ = p.L;
+    const uint32_t top = (uint32_t)p.top;
+    const int l0 = (wi.qt * MAX_WAVES + wave) * 32, lr = l0 + n; // the lane's row of Q
+    const int row = p.row_lo + lr;                               // it sees keys <= row under the causal mask
+    const bool row_ok = lr < LQ;
+    const int8_t *Qp = p.q + (int64_t)b * p.qs[0] + (int64_t)hq * p.qs[1];
+
+    // K and V straight into LDS; the XOR swizzle is applied to the global address, rows at or past L arrive as zeros from the
+    // range check of the buffer descriptor
+    auto stage = [&](const int8_t *base, int64_t stride, int8_t *dst, int first, bool is_v) __attribute__((always_inline)) {
+        const int64_t bytes = (int64_t)(L - 1) * stride + D; // below 2^32: L <= 256, stride <= 2^24
+        const int nblk = ((L + 31) / 32) * 32 / RPB;
+#if defined(__HIP_DEVICE_COMPILE__) // the host pass has neither the descriptor type nor the builtins
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)(uint32_t)bytes, 0x00020000);
+        for (int blk = first; blk < nblk; blk += n_waves) {
+            const int key = blk * RPB + lane / CPR, cpos = lane % CPR;
+            const int swz = is_v ? swz_v<D>(key) : swz_k<D>(key);
+            const int goff = (int)((uint32_t)key * (uint32_t)stride + (uint32_t)((cpos ^ swz) << 4));
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(dst + blk * 1024), 16, goff, 0, 0, 0);
+        }
+#else
+        (void)base, (void)bytes, (void)nblk, (void)dst, (void)first, (void)is_v;
+#endif
+    };
+    stage(p.k + (int64_t)b * p.ks[0] + (int64_t)kvh * p.ks[1], p.ks[2], Ks, wave, false);
+    stage(p.v + (int64_t)b * p.vs[0] + (int64_t)kvh * p.vs[1], p.vs[2], Vs, wave, true);
+    if (tid < 8) lut_lds[tid] = p.lut[tid];
+    v4i qf[KB];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+        qf[kb] = v4i{0, 0, 0, 0};
+        if (row_ok) qf[kb] = *(const v4i *)(Qp + (int64_t)lr * p.qs[2] + kb * 32 + h * 16);
+    }
+    publish_tiles_barrier();
+    if (l0 >= LQ) return; // no barrier below
+
+    // wave-uniform: sub-tiles that hold keys some row of the wave sees, and whether every row sees all of a sub-tile
+    const int kmax = CAUSAL ? min(L, p.row_lo + l0 + 32) : L;
+    auto live = [&](int st) { return 32 * st < kmax; };
+    auto full = [&](int st) { return 32 * st + 32 <= L && (!CAUSAL || 32 * st + 31 <= p.row_lo + l0); };
+    auto visible = [&](int key) { return key < L && (!CAUSAL || key <= row); };
+
+    // ---- scores and row max
+    v16i s[NS];
+    int mx = INT32_MIN;
+#pragma unroll
+    for (int st = 0; st < NS; ++st) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[st][i] = 0;
+        if (!live(st)) continue;
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+            const int key = 32 * st + n;
+            const v4i kf = *(const v4i *)(Ks + key * D + (((2 * kb + h) ^ swz_k<D>(key)) << 4));
+            s[st] = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf, qf[kb], s[st], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int st = 0; st < NS; ++st) {
+        if (!live(st)) continue;
+        if (full(st)) {
+#pragma unroll
+            for (int i = 0; i < 16; i += 2) mx = max(max(s[st][i], s[st][i + 1]), mx);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) mx = visible(32 * st + acc_key(i, h)) ? max(mx, s[st][i]) : mx;
+        }
+    }
+    mx = max(mx, __shfl_xor(mx, 32));
+    if (!row_ok) mx = 0; // rows outside the problem: zero scores, never stored
+
+    // ---- table indices and row sum
+    RowIndex<MODE> ri;
+    ri.init(hp, mx, top);
+    const uint8_t *lut_b = (const uint8_t *)lut_lds;
+    uint32_t sum = 0;
+#pragma unroll
+    for (int st = 0; st < NS; ++st) {
+        if (!live(st)) continue;
+        if (full(st)) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[st][i] = (int)ri(max(s[st][i], ri.bound));
+        } else {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int idx = (int)ri(min(max(s[st][i], ri.bound), ri.mx)); // hidden keys may exceed the row max
+                s[st][i] = visible(32 * st + acc_key(i, h)) ? idx : (int)top;
+            }
+        }
+        uint32_t e[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) e[i] = lut_b[s[st][i]];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sum += e[i];
+    }
+    sum += __shfl_xor(sum, 32);
+    if (sum == 0) sum = 1; // only rows outside the problem
+    if (h == 0 && row_ok) {
+        if (p.dbg_row_max) p.dbg_row_max[(int64_t)bh * LQ + lr] = mx;
+        if (p.dbg_row_sum) p.dbg_row_sum[(int64_t)bh * LQ + lr] = (int32_t)sum;
+    }
+
+    // ---- the row's probabilities as bytes P - 128 (Eq. uint8-prob); the LDS executes one wave's instructions in order
+    uint32_t *PT = PT_all + wave * 1024;
+    const float inv_2s = __builtin_amdgcn_rcpf((float)(2u * sum));
+#pragma unroll 4
+    for (int j = 0; j < 16; ++j) {
+        const int idx = 16 * h + j;
+        PT[idx * 32 + n] = (prob_u8(lut_b[idx], sum, inv_2s) ^ 0x80u) & 0xffu; // lut is 0 past the table
+    }
+    v4i pf[NS];
+#pragma unroll
+    for (int st = 0; st < NS; ++st) {
+        pf[st] = v4i{0, 0, 0, 0};
+        if (!live(st)) continue;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[st][i] = (int)PT[s[st][i] * 32 + n];
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            pf[st][g] = (int)((((uint32_t)s[st][4 * g + 1] << 8) | (uint32_t)s[st][4 * g]) |
+                              ((((uint32_t)s[st][4 * g + 3] << 8) | (uint32_t)s[st][4 * g + 2]) << 16));
+    }
+
+    // ---- P_hat.V_hat and the column sums of V over the same keys
+    const int tr_i = lane & 15, tr_g = (lane >> 4) & 1, jj = tr_i >> 1;
+    const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
+    v16i o[CB], ocs[CB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[cb][i] = 0, ocs[cb][i] = 0;
+#pragma unroll
+    for (int st = 0; st < NS; ++st) {
+        if (!live(st)) continue;
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+            v4i vf;
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const int key = 32 * st + 8 * (2 * r + (jj >> 2)) + 4 * h + (jj & 3);
+                const int8_t *ptr = Vs + key * D + (((2 * cb + tr_g) ^ swz_v<D>(key)) << 4) + 8 * (tr_i & 1);
+                const v2i x = __builtin_amdgcn_ds_read_tr8_b64_v2i32((v2i __attribute__((address_space(3))) *)ptr);
+                vf[2 * r] = x[0];
+                vf[2 * r + 1] = x[1];
+            }
+            o[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf, pf[st], o[cb], 0, 0, 0);
+            ocs[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf, ones, ocs[cb], 0, 0, 0);
+        }
+    }
+
+    // ---- requantize (Sec. 3.2); the wave's 32 rows of 64 bytes meet in its LDS part, so that stores are 16 bytes a lane.
+    // Words of a row are rotated by half the row number, which spreads the rows over the banks.
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int ch0 = cb * 32 + 8 * g + 4 * h;
+            uint32_t packed = 0;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int32_t acc = o[cb][4 * g + r] + 128 * ocs[cb][4 * g + r];
+                if (p.dbg_acc && row_ok) p.dbg_acc[((int64_t)bh * LQ + lr) * D + ch0 + r] = acc;
+                packed |= ((uint32_t)requant_any(acc, hp.rq_mult, hp.rq_shift) & 0xffu) << (8 * r);
+            }
+            PT[n * 16 + ((ch0 / 4) ^ (((n >> 2) & 3) << 2))] = packed;
+        }
+    }
+    int8_t *Op = p.out + (int64_t)b * p.os[0] + (int64_t)hq * p.os[1];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int r = q * 16 + lane / 4, c = lane % 4;
+        const v4i x = *(const v4i *)(PT + r * 16 + 4 * (c ^ ((r >> 2) & 3)));
+        if (l0 + r < LQ) *(v4i *)(Op + (int64_t)(l0 + r) * p.os[2] + c * 16) = x;
+    }
+}
+
+template <int NS, bool CAUSAL>
+int launch_mode(const FwdParams &p, int idx_mode, hipStream_t st)
+{
+    const int waves = p.L >= MAX_WAVES * 32 ? MAX_WAVES : (p.L + 31) / 32;
+    const dim3 grid((unsigned)fwd_grid_size(p.B, p.Hq, p.Hkv, p.n_qtiles)), block((unsigned)(64 * waves));
+    const unsigned sh = (unsigned)waves * 4096u;
+    if (idx_mode == IDX_MULHI24) hipLaunchKernelGGL((fwd_short_kernel<NS, CAUSAL, IDX_MULHI24>), grid, block, sh, st, p);
+    else hipLaunchKernelGGL((fwd_short_kernel<NS, CAUSAL, IDX_MAD24>), grid, block, sh, st, p);
+    return (int)hipGetLastError();
+}
+
+} // namespace
+
+// d = 64, Lk <= 256, tables of at most 32 entries, the integer index maps (TOP24 is MAD24 with the shift at 24), parameters per
+// tensor or per head; p.n_qtiles counts tiles of 128 query rows from row 0; no workspace.
+int launch_fwd_short(const FwdParams &p, int d, int idx_mode, void *stream)
+{
+    hipStream_t st = (hipStream_t)stream;
+    if (d != D || p.Lk > 256 || p.top > 31 || (idx_mode != IDX_MAD24 && idx_mode != IDX_TOP24 && idx_mode != IDX_MULHI24))
+        return (int)hipErrorInvalidValue;
+    if (p.Lk <= 128) return p.causal ? launch_mode<4, true>(p, idx_mode, st) : launch_mode<4, false>(p, idx_mode, st);
+    if (p.Lk <= 224) return p.causal ? launch_mode<7, true>(p, idx_mode, st) : launch_mode<7, false>(p, idx_mode, st);
+    return p.causal ? launch_mode<8, true>(p, idx_mode, st) : launch_mode<8, false>(p, idx_mode, st);
+}
+
+} // namespace intattn

@@ -155,6 +155,10 @@ inline int fwd_row_tiles(int row_lo, int n_rows, int rows_per_tile)
 bool fwd_variant_known(int variant);
 // 5's tiles with the keys split over several workgroups (few query tiles against many keys); never asked for by number
 constexpr int VARIANT_KEY_SPLIT = 6;
+// the kernel for short key sequences (fwd_short.hip); never asked for by number
+constexpr int VARIANT_SHORT = 7;
+bool fwd_short_serves(int B, int Hq, int Lk, int d);
+int launch_fwd_short(const FwdParams &p, int d, int idx_mode, void *stream);
 constexpr int KEY_SPLIT_MAX_RANGES = 16;          // ranges of sweep C: each writes and reads its partial accumulators
 constexpr int64_t KEY_SPLIT_MAX_WORDS = 32 << 20; // of partial accumulators (128 MB): what reserving ahead has to set aside
 struct KeySplit {
