@@ -134,8 +134,9 @@ INTATTN_API int intattn_create(intattn_ctx **out, const intattn_config *cfg);
 
 /* Enqueues the fused IntAttention forward (Sec. 3) on hip_stream (a hipStream_t; NULL is
  * the default stream) and returns without waiting for it.  The context owns a device workspace
- * (8 bytes per query row plus d int32 per 128 keys and KV head) that the first call allocates and
- * a later, larger call re-allocates (hipMalloc / hipFree wait for the device and are not for use
+ * (8 bytes per query row plus d int32 per 128 keys and KV head; for few query tiles against many keys also
+ * partial accumulators of key ranges, at most 128 MB, which intattn_reserve sets aside and without which a
+ * captured call runs unsplit) that the first call allocates and a later, larger call re-allocates (hipMalloc / hipFree wait for the device and are not for use
  * under graph capture: call intattn_reserve first, or use intattn_forward_noalloc); the
  * kernels of a call pass intermediate results through it, so calls on ONE context must not
  * overlap in time (same stream, or ordered by the caller); use one context per concurrent stream.

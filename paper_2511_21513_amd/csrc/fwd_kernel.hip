@@ -155,6 +155,15 @@ KeySplit fwd_key_split(int variant, int B, int Hq, int L, int Lk, int d, int cau
     const int64_t w_ab = (int64_t)B * Hq * fwd_row_tiles(row_lo, L, 256), w_c = (int64_t)B * Hq * fwd_row_tiles(row_lo, L, 128);
     const double seen = causal ? (Lk - 0.5 * L) / Lk : 1.0; // share of the keys that an average row sees
     const double us_tile = d == 128 ? 1.4 : 0.9, us_part = (double)B * Hq * L * d * 8 / 4.0e6;
+    double other;
+    if (variant == 3) {
+        const double blocks = (double)B * Hq * ((L + 31) / 32) * (Lk * seen) / 32;
+        other = 8 + std::max(tiles * (d == 128 ? 1.75 : 1.15), blocks * (d == 128 ? 1.42e-3 : 0.58e-3));
+    } else {
+        other = 12 + tiles * (d == 128 ? 3.8 : 3.3) * std::max(1.0, (double)B * Hq * ((L + 127) / 128) * seen / 380);
+    }
+    const double worth = (d == 128 ? 0.93 : 0.8) * other;
+    if (24 > worth) return KeySplit{0, 0}; // the launches alone take longer
     auto rounds = [&](int64_t w, int s) { return std::max((double)((w * s + 255) / 256) * seen, 2.0) / s * tiles; };
     KeySplit ks = {1, 1};
     double t_ab = 1e30, t_c = 1e30;
@@ -163,14 +172,7 @@ KeySplit fwd_key_split(int variant, int B, int Hq, int L, int Lk, int d, int cau
         if (ab < t_ab) t_ab = ab, ks.ab = s;
         if (s <= KEY_SPLIT_MAX_RANGES && (int64_t)s * B * Hq * L * d <= KEY_SPLIT_MAX_WORDS && c < t_c) t_c = c, ks.c = s;
     }
-    double other;
-    if (variant == 3) {
-        const double blocks = (double)B * Hq * ((L + 31) / 32) * (Lk * seen) / 32;
-        other = 8 + std::max(tiles * (d == 128 ? 1.75 : 1.15), blocks * (d == 128 ? 1.42e-3 : 0.58e-3));
-    } else {
-        other = 12 + tiles * (d == 128 ? 3.8 : 3.3) * std::max(1.0, (double)B * Hq * ((L + 127) / 128) * seen / 380);
-    }
-    if (24 + t_ab + t_c > (d == 128 ? 0.93 : 0.8) * other) return KeySplit{0, 0};
+    if (24 + t_ab + t_c > worth) return KeySplit{0, 0};
     return ks;
 }
 // Sweep C with a table of its own (top-byte constants where a head has them, which cost it one vector instruction per score

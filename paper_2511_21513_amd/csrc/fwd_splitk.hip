@@ -23,8 +23,6 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <type_traits>
-
 #include "kernel_common.h"
 #include "params.h"
 
@@ -37,7 +35,7 @@ constexpr int NT = WAVES * 64;
 
 template <int D, bool CAUSAL, int MODE>
 // (key groups at d = 64: with 128 registers they spill)
-__global__ __launch_bounds__(NT, D == 64 && MODE != IDX_KGROUP ? 4 : 2) void fwd_splitk_kernel(const FwdParams p)
+__global__ __launch_bounds__(NT, D == 64 && MODE != IDX_KGROUP ? 4 : 2) void fwd_splitk_kernel(const FwdParams p, int one_scheme, int fold)
 {
     constexpr int KB = D / 32;  // 32-wide blocks of the head dimension
     constexpr int CB = D / 32;  // 32-wide blocks of output channels
@@ -57,15 +55,17 @@ __global__ __launch_bounds__(NT, D == 64 && MODE != IDX_KGROUP ? 4 : 2) void fwd
     extern __shared__ uint32_t PT[]; // [idx][row], NIDX * 32 words
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 31, h = lane >> 5;
-    const WorkItem wi = fwd_work_item(p, (int)blockIdx.x);
+    int bid = (int)blockIdx.x;
+    if (fold > 0) { // every other round of an XCD's 32 compute units in reverse order
+        const int xcd = bid % NUM_XCD, slot = bid / NUM_XCD, r0 = slot / 32 * 32;
+        if ((r0 / 32) & 1) bid = (r0 + min(32, fold - r0) - 1 - (slot - r0)) * NUM_XCD + xcd;
+    }
+    const WorkItem wi = fwd_work_item(p, bid);
     if (!wi.valid) return; // padding of the XCD-aware grid (uniform for the whole workgroup)
     const int b = wi.b, hq = wi.hq, kvh = wi.kvh, qt = wi.qt + p.row_lo / 32;
     const int bh = b * p.Hq + hq;
     const HeadParams hp = p.hp_table ? p.hp_table[hq] : p.hp0;
-    // The rest of the kernel with the index scheme M as a compile-time constant: MODE itself, or, under IDX_DEVICE, the one
-    // that the device-derived parameters name (uniform for the workgroup).
-    auto body = [&](auto mode_tag) __attribute__((always_inline)) {
-    constexpr int M = decltype(mode_tag)::value;
+    if (one_scheme && hp.pad[0] != MODE) return; // served by the other launch
     const int L = p.Lk;
     const int rlo = p.row_lo, rhi = p.row_lo + p.L, LQ = p.L;
     const uint32_t top = (uint32_t)p.top;
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(NT, D == 64 && MODE != IDX_KGROUP ? 4 : 2) void fwd
     // Finer quantization groups (Sec. 3.3).  RG: parameters per block of query rows, from the row table; KG: each key block
     // has a scale of its own too, so that the row maximum is taken over the dequantized logits (fp64) and a lane forms the
     // constants of its row for each key block (once per 32-key sub-tile where a sub-tile lies in one block).
-    constexpr bool KG = M == IDX_KGROUP, RG = KG || M == IDX_ROW64;
+    constexpr bool KG = MODE == IDX_KGROUP, RG = KG || MODE == IDX_ROW64;
     const float *skp = KG ? p.sk_blocks + (int64_t)(b * p.Hkv + kvh) * p.n_kblk : nullptr;
     const bool kg_blocks = KG && (p.k_block % 32) == 0; // uniform
     auto row_hp = [&](int r) __attribute__((always_inline)) {
@@ -199,8 +199,8 @@ __global__ __launch_bounds__(NT, D == 64 && MODE != IDX_KGROUP ? 4 : 2) void fwd
         }
     }
 
-    RowIndex<M> ri;
-    ri.init(M == IDX_ROW64 ? row_hp(row) : hp, KG ? 0 : mx, top);
+    RowIndex<MODE> ri;
+    ri.init(MODE == IDX_ROW64 ? row_hp(row) : hp, KG ? 0 : mx, top);
     if constexpr (KG) ri.shift = (int)top; // bound of the index (see RowIndex)
     // Group modes: where every lane's threshold is small enough, the index map runs in fp32 (see RowIndex32), the choice
     // uniform for the wave.
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(NT, D == 64 && MODE != IDX_KGROUP ? 4 : 2) void fwd
     auto pick_map = [&](int c_int) __attribute__((always_inline)) {
         single = __all(ri32.init(c_int, ri.mx, top));
     };
-    if constexpr (M == IDX_ROW64) pick_map(ri.mx - ri.bound);
+    if constexpr (MODE == IDX_ROW64) pick_map(ri.mx - ri.bound);
     // Key groups: the constants of the lane's row for the key block of `key`, as in the tiled kernel: c_int^(g) =
     // round(c / alpha^(g)) capped at 2^30, m^(g) = round(M / alpha^(g)) clamped to [-2^22, 2^30 + 2^22], which changes no
     // result (comparisons written so that a NaN from an unusable scale lands on a bound).
@@ -395,36 +395,44 @@ __global__ __launch_bounds__(NT, D == 64 && MODE != IDX_KGROUP ? 4 : 2) void fwd
             *(uint32_t *)(Op + ec0 + c4) = packed;
         }
     }
-    };
-    if constexpr (MODE == IDX_DEVICE) {
-        if (hp.pad[0] == IDX_MULHI24) body(std::integral_constant<int, IDX_MULHI24>{});
-        else body(std::integral_constant<int, IDX_FP64>{});
-    } else {
-        body(std::integral_constant<int, MODE>{});
-    }
+}
+
+// Slots of an XCD whose order is folded, or 0.  Where all workgroups of a causal launch are resident at once, a compute unit
+// takes one from each round of 32 and nothing is dealt later: with the longest blocks of rows first in every round, the unit
+// with the longest block of the first round also gets the longest of the others (2048 rows, two heads an XCD: 156 sub-tile
+// columns against 126 on average).  Reversing every other round evens that out: 1024 rows, 16 heads, d 128: 28.5 -> 25.2 us;
+// 4096 rows, 8 heads, d 64: 60.1 -> 56.0; 2048 rows, 16 heads, d 64: 31.2 -> 30.6.  (Sweeps A+B of 512 workgroups gained nothing from it.)
+inline int fold_slots(int64_t grid, bool causal, int workgroups_per_cu)
+{
+    return causal && grid > 256 && grid <= (int64_t)256 * workgroups_per_cu ? (int)(grid / NUM_XCD) : 0;
 }
 
 template <int D, bool CAUSAL>
 int launch_mode(const FwdParams &p, int idx_mode, hipStream_t st)
 {
-    const dim3 grid((unsigned)fwd_grid_size(p.B, p.Hq, p.Hkv, p.n_qtiles)), block(NT);
+    const int64_t n_wg = fwd_grid_size(p.B, p.Hq, p.Hkv, p.n_qtiles);
+    const int fold = fold_slots(n_wg, CAUSAL, D == 64 && idx_mode != IDX_KGROUP ? 4 : 2);
+    const dim3 grid((unsigned)n_wg), block(NT);
     const unsigned sh = (unsigned)((p.top < 32 ? 32 : 64) * 32 * sizeof(uint32_t)); // the per-row probability table
-    if (idx_mode == IDX_DEVICE) { // the scheme is known on the device only
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_DEVICE>), grid, block, sh, st, p);
+    if (idx_mode == IDX_DEVICE) {
+        // the scheme is known on the device only: one launch per scheme, the other returns at once (a kernel that holds both
+        // took 6 % longer on host scales, 2048 x 2048, 16 heads, d 64, for the same registers)
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_MULHI24>), grid, block, sh, st, p, 1, fold);
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_FP64>), grid, block, sh, st, p, 1, fold);
         return (int)hipGetLastError();
     }
     if (idx_mode == IDX_MAD24 || idx_mode == IDX_TOP24) // the top-byte scheme is the multiply-add with the shift at 24
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_MAD24>), grid, block, sh, st, p);
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_MAD24>), grid, block, sh, st, p, 0, fold);
     else if (idx_mode == IDX_MULHI24)
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_MULHI24>), grid, block, sh, st, p);
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_MULHI24>), grid, block, sh, st, p, 0, fold);
     else if (idx_mode == IDX_FP32)
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_FP32>), grid, block, sh, st, p);
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_FP32>), grid, block, sh, st, p, 0, fold);
     else if (idx_mode == IDX_ROW64)
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_ROW64>), grid, block, sh, st, p);
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_ROW64>), grid, block, sh, st, p, 0, fold);
     else if (idx_mode == IDX_KGROUP)
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_KGROUP>), grid, block, sh, st, p);
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_KGROUP>), grid, block, sh, st, p, 0, fold);
     else if (idx_mode == IDX_FP64)
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_FP64>), grid, block, sh, st, p);
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_FP64>), grid, block, sh, st, p, 0, fold);
     else
         return (int)hipErrorInvalidValue;
     return (int)hipGetLastError();
