@@ -643,10 +643,11 @@ __global__ __launch_bounds__(NT, (PH == 1 || PH >= 3) ? (RB * KT <= 2 ? 4 : 3) :
 }
 
 template <int D, int RB, int KT, bool CAUSAL, int PH>
-int launch_mode(const FwdParams &p, int idx_mode, hipStream_t st)
+int launch_mode(const FwdParams &p_in, int idx_mode, hipStream_t st)
 {
+    FwdParams p = p_in;
     const int n_split = PH == 3 || PH == 4 ? p.split_ab : 1;
-    const dim3 grid((unsigned)(fwd_grid_size(p.B, p.Hq, p.Hkv, p.n_qtiles) * n_split)), block(NT);
+    const dim3 grid((unsigned)fwd_map_work(p, n_split)), block(NT);
     // dynamic shared memory: the per-row probability tables (32 or 64 entries of a word per query row)
     const unsigned sh = PH == 1 || PH >= 3 ? 0u : (unsigned)(WAVES * RB * (p.top < 32 ? 32 : 64) * 32 * sizeof(uint32_t));
     if constexpr (PH == 3) { // row maxima: no index map

@@ -219,10 +219,11 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
 }
 
 template <int NS, bool CAUSAL>
-int launch_mode(const FwdParams &p, int idx_mode, hipStream_t st)
+int launch_mode(const FwdParams &p_in, int idx_mode, hipStream_t st)
 {
+    FwdParams p = p_in;
     const int waves = p.L >= MAX_WAVES * 32 ? MAX_WAVES : (p.L + 31) / 32;
-    const dim3 grid((unsigned)fwd_grid_size(p.B, p.Hq, p.Hkv, p.n_qtiles)), block((unsigned)(64 * waves));
+    const dim3 grid((unsigned)fwd_map_work(p)), block((unsigned)(64 * waves));
     const unsigned sh = (unsigned)waves * 4096u;
     if (idx_mode == IDX_MULHI24) hipLaunchKernelGGL((fwd_short_kernel<NS, CAUSAL, IDX_MULHI24>), grid, block, sh, st, p);
     else hipLaunchKernelGGL((fwd_short_kernel<NS, CAUSAL, IDX_MAD24>), grid, block, sh, st, p);

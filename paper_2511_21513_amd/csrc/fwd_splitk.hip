@@ -35,7 +35,7 @@ constexpr int NT = WAVES * 64;
 
 template <int D, bool CAUSAL, int MODE>
 // (key groups at d = 64: with 128 registers they spill)
-__global__ __launch_bounds__(NT, D == 64 && MODE != IDX_KGROUP ? 4 : 2) void fwd_splitk_kernel(const FwdParams p, int one_scheme, int fold)
+__global__ __launch_bounds__(NT, D == 64 && MODE != IDX_KGROUP ? 4 : 2) void fwd_splitk_kernel(const FwdParams p)
 {
     constexpr int KB = D / 32;  // 32-wide blocks of the head dimension
     constexpr int CB = D / 32;  // 32-wide blocks of output channels
@@ -55,17 +55,12 @@ __global__ __launch_bounds__(NT, D == 64 && MODE != IDX_KGROUP ? 4 : 2) void fwd
     extern __shared__ uint32_t PT[]; // [idx][row], NIDX * 32 words
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 31, h = lane >> 5;
-    int bid = (int)blockIdx.x;
-    if (fold > 0) { // every other round of an XCD's 32 compute units in reverse order
-        const int xcd = bid % NUM_XCD, slot = bid / NUM_XCD, r0 = slot / 32 * 32;
-        if ((r0 / 32) & 1) bid = (r0 + min(32, fold - r0) - 1 - (slot - r0)) * NUM_XCD + xcd;
-    }
-    const WorkItem wi = fwd_work_item(p, bid);
+    const WorkItem wi = fwd_work_item(p, (int)blockIdx.x);
     if (!wi.valid) return; // padding of the XCD-aware grid (uniform for the whole workgroup)
     const int b = wi.b, hq = wi.hq, kvh = wi.kvh, qt = wi.qt + p.row_lo / 32;
     const int bh = b * p.Hq + hq;
     const HeadParams hp = p.hp_table ? p.hp_table[hq] : p.hp0;
-    if (one_scheme && hp.pad[0] != MODE) return; // served by the other launch
+    if (p.one_scheme && hp.pad[0] != MODE) return; // served by the other launch
     const int L = p.Lk;
     const int rlo = p.row_lo, rhi = p.row_lo + p.L, LQ = p.L;
     const uint32_t top = (uint32_t)p.top;
@@ -408,31 +403,33 @@ inline int fold_slots(int64_t grid, bool causal, int workgroups_per_cu)
 }
 
 template <int D, bool CAUSAL>
-int launch_mode(const FwdParams &p, int idx_mode, hipStream_t st)
+int launch_mode(const FwdParams &p_in, int idx_mode, hipStream_t st)
 {
-    const int64_t n_wg = fwd_grid_size(p.B, p.Hq, p.Hkv, p.n_qtiles);
-    const int fold = fold_slots(n_wg, CAUSAL, D == 64 && idx_mode != IDX_KGROUP ? 4 : 2);
+    FwdParams p = p_in;
+    const int64_t n_wg = fwd_map_work(p);
+    p.map.fold = fold_slots(n_wg, CAUSAL, D == 64 && idx_mode != IDX_KGROUP ? 4 : 2);
     const dim3 grid((unsigned)n_wg), block(NT);
     const unsigned sh = (unsigned)((p.top < 32 ? 32 : 64) * 32 * sizeof(uint32_t)); // the per-row probability table
     if (idx_mode == IDX_DEVICE) {
         // the scheme is known on the device only: one launch per scheme, the other returns at once (a kernel that holds both
         // took 6 % longer on host scales, 2048 x 2048, 16 heads, d 64, for the same registers)
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_MULHI24>), grid, block, sh, st, p, 1, fold);
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_FP64>), grid, block, sh, st, p, 1, fold);
+        p.one_scheme = 1;
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_MULHI24>), grid, block, sh, st, p);
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_FP64>), grid, block, sh, st, p);
         return (int)hipGetLastError();
     }
     if (idx_mode == IDX_MAD24 || idx_mode == IDX_TOP24) // the top-byte scheme is the multiply-add with the shift at 24
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_MAD24>), grid, block, sh, st, p, 0, fold);
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_MAD24>), grid, block, sh, st, p);
     else if (idx_mode == IDX_MULHI24)
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_MULHI24>), grid, block, sh, st, p, 0, fold);
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_MULHI24>), grid, block, sh, st, p);
     else if (idx_mode == IDX_FP32)
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_FP32>), grid, block, sh, st, p, 0, fold);
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_FP32>), grid, block, sh, st, p);
     else if (idx_mode == IDX_ROW64)
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_ROW64>), grid, block, sh, st, p, 0, fold);
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_ROW64>), grid, block, sh, st, p);
     else if (idx_mode == IDX_KGROUP)
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_KGROUP>), grid, block, sh, st, p, 0, fold);
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_KGROUP>), grid, block, sh, st, p);
     else if (idx_mode == IDX_FP64)
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_FP64>), grid, block, sh, st, p, 0, fold);
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_FP64>), grid, block, sh, st, p);
     else
         return (int)hipErrorInvalidValue;
     return (int)hipGetLastError();

@@ -1,103 +1,17 @@
-// Device helpers shared by the forward kernels: vector types, the exact index map of Sec. 3.1,
+// Device helpers shared by the forward kernels: vector types, the mapping of workgroups to work, the exact index map of Sec. 3.1,
 // the MFMA accumulator-to-key map and the LDS chunk swizzles.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include "params.h"
+#include "work_map.h"
 
 namespace intattn {
 
 typedef int v2i __attribute__((ext_vector_type(2)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
-
-// ------------------------------------------------------------------ workgroup -> work mapping
-// Workgroups are dealt round-robin to the 8 XCDs (workgroup id mod 8), and each XCD has its
-// own L2.  All query heads that share one KV head -- i.e. one (batch, KV head) group -- are
-// therefore sent to the same XCD, so that K and V of the group are fetched into one L2 only.
-// Within an XCD the groups are taken in batches of FwdParams::group_batch groups: inside a batch the longest
-// (latest) causal query tiles of all its groups come first, which balances the compute units; the batch is sized
-// so that the K and V its workgroups read at the same time fit the XCD's L2 (with the tiles of all 64 groups of
-// an XCD interleaved, and no sharing between query heads, sweep C of the batched prefill workload streamed
-// 4.3 TB/s of K and V from HBM and was bound by it).
-constexpr int NUM_XCD = 8;
-constexpr int64_t XCD_L2_BUDGET = 4 << 20; // bytes of K (and V) that a batch of groups may hold in flight: the L2 of an XCD
-                                           // (1 to 16 MiB measured within 3 % of each other on the batched prefill workload)
-
-// Where B * Hkv is not a multiple of 8, each group is dealt to several XCDs instead: its units (query tile, query head)
-// are cut into `fwd_xcd_split` residue classes, so that groups times classes is a multiple of 8 and every XCD gets as much
-// work.  (With whole groups only, 2 groups left six XCDs idle: 2048 x 16384, 8 query and 2 KV heads, d 128: 1371 us on the
-// key-split-over-waves kernel; 12 groups gave four XCDs twice the work of the others.)  K and V then pass the L2 of each of
-// them, which costs less than the idle compute units: they hold no more than 1 / classes of the work each.
-__host__ __device__ inline int fwd_xcd_split(int groups)
-{
-    if (groups >= 256) return 1; // at most one group in 32 too many for an XCD
-    return groups % 8 == 0 ? 1 : (groups % 4 == 0 ? 2 : (groups % 2 == 0 ? 4 : 8)); // 8 / gcd(groups, 8)
-}
-
-// groups per batch for kernels that stream `bytes_per_group` of K (and V) per (batch, KV head) group
-inline int fwd_group_batch(int B, int Hkv, int64_t bytes_per_group)
-{
-    const int64_t gpx = ((int64_t)B * Hkv * fwd_xcd_split(B * Hkv) + NUM_XCD - 1) / NUM_XCD;
-    const int64_t fit = bytes_per_group > 0 ? XCD_L2_BUDGET / bytes_per_group : gpx;
-    return (int)(fit < 1 ? 1 : (fit > gpx ? gpx : fit));
-}
-
-__host__ __device__ inline int64_t fwd_grid_size(int B, int Hq, int Hkv, int n_qtiles)
-{
-    const int groups = B * Hkv, m = fwd_xcd_split(groups);
-    const int64_t units = ((int64_t)(Hq / Hkv) * n_qtiles + m - 1) / m;
-    return ((int64_t)groups * m + NUM_XCD - 1) / NUM_XCD * NUM_XCD * units;
-}
-
-struct WorkItem {
-    int b, hq, kvh, qt;
-    bool valid;
-};
-
-__device__ __forceinline__ WorkItem fwd_work_item(const FwdParams &p, int bid)
-{
-    const int g = p.group, groups = p.B * p.Hkv, m = fwd_xcd_split(groups);
-    const int units = (g * p.n_qtiles + m - 1) / m;   // of a class, the longest (latest) query tiles first
-    const int classes_per_xcd = (groups * m + NUM_XCD - 1) / NUM_XCD;
-    const int xcd = bid % NUM_XCD, slot = bid / NUM_XCD;
-    const int gb = p.group_batch > 0 ? min(p.group_batch, classes_per_xcd) : classes_per_xcd;
-    const int per_batch = gb * units; // slots of a full batch; the last batch may hold fewer groups
-    const int batch = slot / per_batch, rem = slot - batch * per_batch;
-    const int gbb = min(gb, classes_per_xcd - batch * gb);
-    WorkItem w;
-    int gi, hg, qt_rev;
-    if (m == 1) {
-        // within a batch: query heads of a group fastest (they share K and V), then the groups, then the tiles
-        const int rest = rem / g;
-        hg = rem - rest * g;
-        qt_rev = rest / gbb;
-        gi = (batch * gb + rest - qt_rev * gbb) * NUM_XCD + xcd;
-        w.valid = gi < groups;
-    } else {
-        // a class takes every m-th unit of its group, query head fastest
-        const int u = rem / gbb, ci = (batch * gb + rem - u * gbb) * NUM_XCD + xcd, unit = u * m + (ci & (m - 1));
-        gi = ci / m;
-        qt_rev = unit / g;
-        hg = unit - qt_rev * g;
-        w.valid = gi < groups && qt_rev < p.n_qtiles;
-    }
-    w.b = gi / p.Hkv;
-    w.kvh = gi - w.b * p.Hkv;
-    w.hq = w.kvh * g + hg;
-    w.qt = p.n_qtiles - 1 - qt_rev;
-    return w;
-}
-
-// Key-split launches: every work item is taken by n_split consecutive workgroups of one XCD, each with a range of the
-// item's key tiles.  Returns the range's number and replaces bid by the item's.
-__device__ __forceinline__ int fwd_split_index(int &bid, int n_split)
-{
-    const int xcd = bid % NUM_XCD, slot = bid / NUM_XCD;
-    bid = (slot / n_split) * NUM_XCD + xcd;
-    return slot % n_split;
-}
 
 // ------------------------------------------------------------------ index map (Sec. 3.1)
 // The fp64 scheme's factor -r (its bits are split over idx_mul, low word, and idx_add).

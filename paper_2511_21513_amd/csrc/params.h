@@ -33,21 +33,42 @@ struct HeadParams {
     int32_t pad[2];    // pad[0]: this head's IdxMode when the table was derived on the device
 };
 
+// A divisor known on the host, for n / d without a division (work_map.h).
+struct FastDiv {
+    uint32_t mul, shift;
+};
+
+// What fwd_work_item (work_map.h) needs beyond the shape: filled for each launch by fwd_map_work.
+struct WorkMap {
+    int32_t groups;      // (batch, KV head) groups
+    int32_t whole, left; // groups of each XCD, and groups dealt out to all of them
+    int32_t units;       // query tiles of all query heads of a group
+    uint32_t dealt_mul;  // dealt-out slots of an XCD per slot, times 2^32
+    FastDiv by_left, by_group, by_hkv;   // left, group, Hkv
+    FastDiv by_batch, by_full, by_last;  // slots of a full batch, groups of a full / the last batch
+    int32_t fold;        // slots of an XCD whose order is folded (fwd_splitk.hip); 0: not folded
+};
+
 struct FwdParams {
+    // first, and the map before all: every workgroup starts with these, which a few loads issued together bring
+    WorkMap map;
+    int32_t group;       // Hq / Hkv
+    int32_t group_batch; // (batch, KV head) groups of an XCD whose query tiles are interleaved (at least 1)
+    int32_t n_qtiles;    // tiles of (rows per workgroup) rows that [row_lo, row_lo + L) touches
+    int32_t Hkv;
+    int32_t one_scheme;  // 1: a workgroup whose head's HeadParams name another index scheme than the kernel's returns at once
+    const HeadParams *hp_table; // device [Hq] when per-head or derived on the device, else nullptr
     const int8_t *q, *k, *v;
     int8_t *out;
     int64_t qs[3], ks[3], vs[3], os[3]; // byte strides of B, H, L
-    int32_t B, Hq, Hkv;
+    int32_t B, Hq;
     int32_t L;           // query rows
     int32_t Lk;          // keys
     int32_t row_lo;      // number of the first query row in the numbering where row r sees keys <= r under the
                          // causal mask: Lk - L when causal, else 0; tiles are aligned to this numbering
     int32_t causal;
-    int32_t group;       // Hq / Hkv
     int32_t top;         // 2^b - 1
-    int32_t n_qtiles;    // tiles of (rows per workgroup) rows that [row_lo, row_lo + L) touches
     int32_t n_chunks;    // ceil(Lk / rows per workgroup of sweep C): chunks of V the column sums are kept for
-    const HeadParams *hp_table; // device [Hq] when per-head or derived on the device, else nullptr
     const HeadParams *hp_table_c; // device [Hq] or nullptr: sweep C's own table (IDX_MIX) where some heads have top-byte constants
     const HeadParams *row_table; // IDX_ROW64: device [B * Hq][n_rowblk], parameters of every block of q_block query rows
     int32_t q_block, n_rowblk;
@@ -57,7 +78,6 @@ struct FwdParams {
     int32_t k_block, n_kblk;
     double clip, sqrt_d;
     const int32_t *head_status;
-    int32_t group_batch;        // (batch, KV head) groups of an XCD whose query tiles are interleaved; 0: all of them
     HeadParams hp0;             // the single parameter set when hp_table == nullptr
     uint32_t lut[16];           // LUT_hat, up to 64 bytes packed little-endian (unused tail is 0)
     int32_t *dbg_row_max, *dbg_row_sum, *dbg_acc;

@@ -583,9 +583,10 @@ __global__ __launch_bounds__(NT, RB == 1 ? 2 : 1) void sweep_c_kernel(const FwdP
 }
 
 template <int D, int RB, bool CAUSAL, bool SPLIT>
-int launch_mode(const FwdParams &p, int idx_mode, hipStream_t st)
+int launch_mode(const FwdParams &p_in, int idx_mode, hipStream_t st)
 {
-    const dim3 grid((unsigned)(fwd_grid_size(p.B, p.Hq, p.Hkv, p.n_qtiles) * (SPLIT ? p.split_c : 1))), block(NT);
+    FwdParams p = p_in;
+    const dim3 grid((unsigned)fwd_map_work(p, SPLIT ? p.split_c : 1)), block(NT);
     if (idx_mode == IDX_MIX || idx_mode == IDX_DEVICE)
         hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_MIX, SPLIT>), grid, block, 0, st, p);
     else if (idx_mode == IDX_TOP24)
