@@ -47,17 +47,15 @@ namespace fwdk {
 constexpr int WAVES = 4;
 constexpr int NT = WAVES * 64;
 
-// PH selects which part of the path this instantiation runs: 0 = all three sweeps in one launch;
-// 1 = sweeps A and B only (row max and row sum go to a small workspace: 8 bytes per query row) --
-// without the output accumulators it needs far fewer registers, so a wave can own 64 query rows
-// (every K fragment read feeds two MFMAs) at three waves per SIMD; 2 = sweep C only, reading that
-// workspace; 3 and 4 = sweep A and sweep B over one of FwdParams::split_ab ranges of the keys, for problems whose
-// query tiles alone leave compute units idle: row max and row sum meet in the workspace (atomics; the launch ahead of
-// these set it to INT32_MIN and 0).
-template <int D, int RB, int KT, bool CAUSAL, int MODE, int PH>
-__global__ __launch_bounds__(NT, (PH == 1 || PH >= 3) ? (RB * KT <= 2 ? 4 : 3) : (RB == 1 ? (KT == 1 ? 3 : 2) : 1)) void fwd_kernel(const FwdParams p)
+// The kernel for one work item with the index scheme M as a compile-time constant; the LDS arrays are the kernel's (see
+// there), ksp is the number of this workgroup's range of key tiles out of n_split.  A function rather than a lambda in the
+// kernel: as a lambda it cost the instantiations with sweep C 13 (d = 64) to 28 (d = 128) registers and 5 to 9 % more
+// vector instructions (135 and 217 registers as it is, causal, one launch).
+template <int D, int RB, int KT, bool CAUSAL, int M, int PH>
+__device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi, const HeadParams &hp, const int ksp, const int n_split,
+                                         int8_t *Ks0, int8_t *Ks1, int8_t *Vs0, int8_t *Vs1, uint32_t *PT, uint32_t *lut_lds,
+                                         int32_t *colsum, int32_t (*cs4)[D])
 {
-    constexpr bool WITHOUT_C = PH == 1 || PH == 3 || PH == 4; // sweeps A and / or B alone
     constexpr int KS = KT; // sub-tiles sweep C computes per step: the whole staged tile
     constexpr int KB = D / 32;       // 32-wide blocks of the head dimension
     constexpr int CB = D / 32;       // 32-wide blocks of output channels
@@ -69,32 +67,9 @@ __global__ __launch_bounds__(NT, (PH == 1 || PH >= 3) ? (RB * KT <= 2 ? 4 : 3) :
     constexpr int CPR = D / 16;                      // 16-byte chunks per key row
     constexpr int RPB = 1024 / D;                    // key rows per block
 
-    // Two buffers per operand, as separate arrays: the compiler tracks each direct-to-LDS load by
-    // the array it targets, so reads of one buffer need not wait for loads into the other.
-    __shared__ __attribute__((aligned(1024))) int8_t Ks0[TILE];
-    __shared__ __attribute__((aligned(1024))) int8_t Ks1[TILE];
-    __shared__ __attribute__((aligned(1024))) int8_t Vs0[WITHOUT_C ? 16 : TILE];
-    __shared__ __attribute__((aligned(1024))) int8_t Vs1[WITHOUT_C ? 16 : TILE];
-    // per-row probability tables, [wave][row block][idx][row]: dynamic shared memory of WAVES * RB * NIDX * 32
-    // words, NIDX = 32 or 64 table entries (none for sweeps A+B alone)
-    extern __shared__ uint32_t PT[];
-    __shared__ uint32_t lut_lds[16];
-    __shared__ int32_t colsum[D];
-    __shared__ int32_t cs4[PH == 0 ? WAVES : 1][D]; // in-kernel column sums of V (short sequences, single launch)
-
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 31, h = lane >> 5;
-    int bid = (int)blockIdx.x;
-    const int n_split = PH == 3 || PH == 4 ? p.split_ab : 1;
-    const int ksp = PH == 3 || PH == 4 ? fwd_split_index(bid, n_split) : 0;
-    const WorkItem wi = fwd_work_item(p, bid);
-    if (!wi.valid) return; // padding of the XCD-aware grid (uniform for the whole workgroup)
     const int b = wi.b, hq = wi.hq, kvh = wi.kvh, qt = wi.qt + p.row_lo / BQ;
     const int bh = b * p.Hq + hq;
-    const HeadParams hp = p.hp_table ? p.hp_table[hq] : p.hp0;
-    // The rest of the kernel with the index scheme M as a compile-time constant: MODE itself, or, under IDX_DEVICE, the one
-    // that the device-derived parameters name (uniform for the workgroup).
-    auto body = [&](auto mode_tag) __attribute__((always_inline)) {
-    constexpr int M = decltype(mode_tag)::value;
     const int L = p.Lk; // keys
     // query rows: [rlo, rhi) of the numbering in which row r sees keys <= r under the causal mask
     const int rlo = p.row_lo, rhi = p.row_lo + p.L, LQ = p.L;
@@ -633,12 +608,46 @@ __global__ __launch_bounds__(NT, (PH == 1 || PH >= 3) ? (RB * KT <= 2 ? 4 : 3) :
             }
         }
     }
-    };
+}
+
+// PH selects which part of the path this instantiation runs: 0 = all three sweeps in one launch;
+// 1 = sweeps A and B only (row max and row sum go to a small workspace: 8 bytes per query row) --
+// without the output accumulators it needs far fewer registers, so a wave can own 64 query rows
+// (every K fragment read feeds two MFMAs) at three waves per SIMD; 2 = sweep C only, reading that
+// workspace; 3 and 4 = sweep A and sweep B over one of FwdParams::split_ab ranges of the keys, for problems whose
+// query tiles alone leave compute units idle: row max and row sum meet in the workspace (atomics; the launch ahead of
+// these set it to INT32_MIN and 0).
+template <int D, int RB, int KT, bool CAUSAL, int MODE, int PH>
+__global__ __launch_bounds__(NT, (PH == 1 || PH >= 3) ? (RB * KT <= 2 ? 4 : 3) : (RB == 1 ? (KT == 1 ? 3 : 2) : 1)) void fwd_kernel(const FwdParams p)
+{
+    constexpr bool WITHOUT_C = PH == 1 || PH == 3 || PH == 4; // sweeps A and / or B alone
+    constexpr int TILE = 32 * KT * D; // bytes of a tile of keys
+
+    // Two buffers per operand, as separate arrays: the compiler tracks each direct-to-LDS load by
+    // the array it targets, so reads of one buffer need not wait for loads into the other.
+    __shared__ __attribute__((aligned(1024))) int8_t Ks0[TILE];
+    __shared__ __attribute__((aligned(1024))) int8_t Ks1[TILE];
+    __shared__ __attribute__((aligned(1024))) int8_t Vs0[WITHOUT_C ? 16 : TILE];
+    __shared__ __attribute__((aligned(1024))) int8_t Vs1[WITHOUT_C ? 16 : TILE];
+    // per-row probability tables, [wave][row block][idx][row]: dynamic shared memory of WAVES * RB * NIDX * 32
+    // words, NIDX = 32 or 64 table entries (none for sweeps A+B alone)
+    extern __shared__ uint32_t PT[];
+    __shared__ uint32_t lut_lds[16];
+    __shared__ int32_t colsum[D];
+    __shared__ int32_t cs4[PH == 0 ? WAVES : 1][D]; // in-kernel column sums of V (short sequences, single launch)
+
+    int bid = (int)blockIdx.x;
+    const int n_split = PH == 3 || PH == 4 ? p.split_ab : 1;
+    const int ksp = PH == 3 || PH == 4 ? fwd_split_index(bid, n_split) : 0;
+    const WorkItem wi = fwd_work_item(p, bid);
+    if (!wi.valid) return; // padding of the XCD-aware grid (uniform for the whole workgroup)
+    const HeadParams hp = p.hp_table ? p.hp_table[wi.hq] : p.hp0;
+    // MODE, or, under IDX_DEVICE, the scheme that the device-derived parameters name (uniform for the workgroup)
     if constexpr (MODE == IDX_DEVICE) {
-        if (hp.pad[0] == IDX_MULHI24) body(std::integral_constant<int, IDX_MULHI24>{});
-        else body(std::integral_constant<int, IDX_FP64>{});
+        if (hp.pad[0] == IDX_MULHI24) fwd_body<D, RB, KT, CAUSAL, IDX_MULHI24, PH>(p, wi, hp, ksp, n_split, Ks0, Ks1, Vs0, Vs1, PT, lut_lds, colsum, cs4);
+        else fwd_body<D, RB, KT, CAUSAL, IDX_FP64, PH>(p, wi, hp, ksp, n_split, Ks0, Ks1, Vs0, Vs1, PT, lut_lds, colsum, cs4);
     } else {
-        body(std::integral_constant<int, MODE>{});
+        fwd_body<D, RB, KT, CAUSAL, MODE, PH>(p, wi, hp, ksp, n_split, Ks0, Ks1, Vs0, Vs1, PT, lut_lds, colsum, cs4);
     }
 }
 
