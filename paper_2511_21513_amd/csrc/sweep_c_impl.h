@@ -64,7 +64,7 @@ constexpr int NT = WAVES * 64;
 // SPLIT: every work item is taken by p.split_c workgroups, each with a range of the key tiles.  (An instantiation of its own:
 // with the range decided at run time the launches that do not split were 1 % slower.)
 template <int D, int RB, bool CAUSAL, int MODE, bool SPLIT>
-__global__ __launch_bounds__(NT, RB == 1 ? 2 : 1) void sweep_c_kernel(const FwdParams p)
+__global__ __launch_bounds__(NT, RB == 1 ? (D == 64 && MODE == IDX_DEVICE ? 3 : 2) : 1) void sweep_c_kernel(const FwdParams p)
 {
     constexpr int KB = D / 32;       // 32-wide blocks of the head dimension
     constexpr int CB = D / 32;       // 32-wide blocks of output channels
@@ -107,9 +107,12 @@ __global__ __launch_bounds__(NT, RB == 1 ? 2 : 1) void sweep_c_kernel(const FwdP
     const int b = wi.b, hq = wi.hq, kvh = wi.kvh, qt = wi.qt + p.row_lo / BQ;
     const int bh = b * p.Hq + hq;
     const HeadParams hp = p.hp_table ? p.hp_table[hq] : p.hp0;
-    // The rest of the kernel with the index scheme M as a compile-time constant: MODE itself, or, under IDX_MIX,
-    // the scheme named in the head's own parameters (top-byte constants where the head has them, else the
+    // The rest of the kernel with the index scheme M as a compile-time constant: MODE itself, or, under IDX_MIX and
+    // IDX_DEVICE, the scheme named in the head's own parameters (top-byte constants where the head has them, else the
     // multiply-high scheme that serves every head of the call; parameters derived on the device may name the fp64 map).
+    // With the fp64 map among them the kernel takes 170 registers instead of 162 at d = 64 with the mask, i.e. two waves a
+    // SIMD instead of three (2 x 4096 tokens, 32 / 8 heads: 245 us against 234): host parameters, which never mix it in, have
+    // an instantiation without it, and the other is held to three waves (168 registers, nothing spilled).
     auto body = [&](auto mode_tag) __attribute__((always_inline)) {
     constexpr int M = decltype(mode_tag)::value;
     const int L = p.Lk; // keys
@@ -573,9 +576,9 @@ __global__ __launch_bounds__(NT, RB == 1 ? 2 : 1) void sweep_c_kernel(const FwdP
         }
     }
     };
-    if constexpr (MODE == IDX_MIX) {
+    if constexpr (MODE == IDX_MIX || MODE == IDX_DEVICE) {
         if (hp.pad[0] == IDX_TOP24) body(std::integral_constant<int, IDX_TOP24>{}); // uniform for the workgroup
-        else if (hp.pad[0] == IDX_MULHI24) body(std::integral_constant<int, IDX_MULHI24>{});
+        else if (MODE == IDX_MIX || hp.pad[0] == IDX_MULHI24) body(std::integral_constant<int, IDX_MULHI24>{});
         else body(std::integral_constant<int, IDX_FP64>{});
     } else {
         body(std::integral_constant<int, MODE>{});
@@ -587,8 +590,10 @@ int launch_mode(const FwdParams &p_in, int idx_mode, hipStream_t st)
 {
     FwdParams p = p_in;
     const dim3 grid((unsigned)fwd_map_work(p, SPLIT ? p.split_c : 1)), block(NT);
-    if (idx_mode == IDX_MIX || idx_mode == IDX_DEVICE)
+    if (idx_mode == IDX_MIX)
         hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_MIX, SPLIT>), grid, block, 0, st, p);
+    else if (idx_mode == IDX_DEVICE)
+        hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_DEVICE, SPLIT>), grid, block, 0, st, p);
     else if (idx_mode == IDX_TOP24)
         hipLaunchKernelGGL((sweep_c_kernel<D, RB, CAUSAL, IDX_TOP24, SPLIT>), grid, block, 0, st, p);
     else if (idx_mode == IDX_MAD24)

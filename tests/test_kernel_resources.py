@@ -68,3 +68,8 @@ def test_tiled_kernels_with_sweep_c_on_known_schemes(kernels, d, most):
     """All sweeps, and sweep C alone, of 32 rows a wave on host scales (index schemes 0 to 3)."""
     for phase in (0, 2):
         assert registers(kernels, rf"fwd_kernelILi{d}ELi1ELi2ELb[01]ELi[0-3]ELi{phase}E") <= most
+
+
+def test_sweep_c_at_head_dimension_64_runs_three_waves(kernels):
+    """168 registers a lane let three waves share a SIMD."""
+    assert registers(kernels, r"sweep_c_kernelILi64E") <= 168
