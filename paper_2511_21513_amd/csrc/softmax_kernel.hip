@@ -37,8 +37,20 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v)
 // byte of a 24-bit multiply-add; thresholds up to several thousand) or IDX_FP64 (every threshold).
 // Table indices travel as idx * 4, the byte offset the lane permute takes, so that a lookup is one
 // permute: LUT_hat[idx] and later P[idx] live in lane idx.
-template <int NTHR, int NCH, int MODE>
-__global__ __launch_bounds__(256) void index_softmax_kernel(const SoftmaxParams p)
+// ROWS_ANY: any row.  ROWS_WHOLE: no mask, rows of a multiple of four columns, probabilities that start on a word: a group of
+// columns lies in the row as a whole or not at all, so that there is no test per column, and the loads of a row have no branch
+// between them and are all in flight at once.  (As ROWS_ANY: 8192 rows of 2048 columns 17.4 us, now 14.6; of 8192 columns 62.8
+// and 59.2; of 6000 columns 39.5 and 35.4.)  ROWS_SHORT: up to 256 columns, groups from column 0, words or bytes stored as
+// the alignment has it; for rows where the lead costs more than it gives (see the launcher).
+enum Rows { ROWS_ANY, ROWS_WHOLE, ROWS_SHORT };
+
+// Waves a SIMD that ROWS_WHOLE of long rows is held to: fewer rows in flight stream faster (4096 rows of 16384 columns: 66.7 us
+// at five, 63.4 at three; 8192 rows of 7168 columns: 44.6 at eight, 42.8 at five; ROWS_ANY is slower with the limit, 81 against
+// 67 us at 8190 columns).
+constexpr int max_waves(int nthr, int nch, int rows) { return rows != ROWS_WHOLE || nthr < 256 || nch < 8 ? 8 : (nch < 16 ? 5 : 3); }
+
+template <int NTHR, int NCH, int MODE, int ROWS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, max_waves(NTHR, NCH, ROWS)))) void index_softmax_kernel(const SoftmaxParams p)
 {
     __shared__ int32_t red[2][4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -59,9 +71,11 @@ __global__ __launch_bounds__(256) void index_softmax_kernel(const SoftmaxParams 
     // last group partly outside the row.  Every store is then one aligned word whatever the strides are, and every load
     // 16 bytes at the 4-byte alignment that logits have anyway.  (Rows of 6001 columns, whose starts fall on every
     // alignment, took four loads and four byte stores a group: 8192 x 6001: 67.9 us, now 47.4, 5.2 TB/s.)
-    const int lead = (int)((uintptr_t)dst & 3u);
+    constexpr bool whole = ROWS == ROWS_WHOLE;
+    const int lead = ROWS == ROWS_ANY ? (int)((uintptr_t)dst & 3u) : 0;
+    [[maybe_unused]] const bool words = ((uintptr_t)dst & 3u) == 0;
     auto load4 = [&](int c, int32_t (&x)[4]) __attribute__((always_inline)) {
-        if (c >= 0 && c + 3 < n_vis) {
+        if (whole || (c >= 0 && c + 3 < n_vis)) {
             const v4i_a4 q = *(const v4i_a4 *)(src + c);
             x[0] = q[0], x[1] = q[1], x[2] = q[2], x[3] = q[3];
         } else {
@@ -95,7 +109,7 @@ __global__ __launch_bounds__(256) void index_softmax_kernel(const SoftmaxParams 
     // last table entry, which is 0 by Eq. lut16.  Groups that are visible as a whole skip the selects.
     auto index_word = [&](const int32_t (&x)[4], int32_t m, int c) __attribute__((always_inline)) {
         uint32_t w = 0;
-        if (c >= 0 && c + 3 < n_vis) {
+        if (whole || (c >= 0 && c + 3 < n_vis)) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) w |= index4(x[e], m) << (8 * e);
         } else {
@@ -118,7 +132,7 @@ __global__ __launch_bounds__(256) void index_softmax_kernel(const SoftmaxParams 
         return packed;
     };
     auto store4 = [&](int c, uint32_t packed) __attribute__((always_inline)) {
-        if (c >= 0 && c + 3 < cols) *(uint32_t *)(dst + c) = packed;
+        if (whole || ((ROWS == ROWS_ANY || words) && c >= 0 && c + 3 < cols)) *(uint32_t *)(dst + c) = packed;
         else
 #pragma unroll
             for (int e = 0; e < 4; ++e)
@@ -135,12 +149,13 @@ __global__ __launch_bounds__(256) void index_softmax_kernel(const SoftmaxParams 
             const int c = (t + NTHR * j) * 4 - lead;
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[j][e] = 0;
-            if (c < n_vis) load4(c, v[j]);
+            if (whole) load4(min(c, cols - 4), v[j]); // (a hidden group: the row's last one again)
+            else if (c < n_vis) load4(c, v[j]);
         }
 #pragma unroll
         for (int j = 0; j < NCH; ++j) {
             const int c = (t + NTHR * j) * 4 - lead;
-            if (c >= 0 && c + 3 < n_vis) {
+            if (whole || (c >= 0 && c + 3 < n_vis)) {
                 m = max(max(m, v[j][0]), max(v[j][1], max(v[j][2], v[j][3])));
             } else {
 #pragma unroll
@@ -166,9 +181,11 @@ __global__ __launch_bounds__(256) void index_softmax_kernel(const SoftmaxParams 
 #pragma unroll
         for (int j = 0; j < NCH; ++j) {
             // a wave past the last visible column has nothing to look up (the last table entry is 0)
+            const int c = (t + NTHR * j) * 4 - lead;
             w[j] = top4 * 0x01010101u;
-            if ((t - lane + NTHR * j) * 4 - lead < n_vis) { // wave-uniform
-                w[j] = index_word(v[j], m, (t + NTHR * j) * 4 - lead);
+            if (whole || c - 4 * lane < n_vis) { // wave-uniform
+                const uint32_t x = index_word(v[j], m, c);
+                if (!whole || c < cols) w[j] = x;
                 sum += gather_sum(lutv, w[j]);
             }
         }
@@ -189,7 +206,7 @@ __global__ __launch_bounds__(256) void index_softmax_kernel(const SoftmaxParams 
         for (int j = 0; j < NCH; ++j) {
             const int c = (t + NTHR * j) * 4 - lead;
             uint32_t packed = 0; // hidden columns
-            if ((t - lane + NTHR * j) * 4 - lead < n_vis) packed = gather_pack(ptv, w[j]); // wave-uniform
+            if (whole || c - 4 * lane < n_vis) packed = gather_pack(ptv, w[j]); // wave-uniform
             if (c < cols) store4(c, packed);
         }
     } else {
@@ -202,14 +219,21 @@ __global__ __launch_bounds__(256) void index_softmax_kernel(const SoftmaxParams 
     }
 }
 
-template <int NTHR, int NCH> int launch_one(const SoftmaxParams &p, hipStream_t st)
+template <int NTHR, int NCH, int ROWS> int launch_rows(const SoftmaxParams &p, hipStream_t st)
 {
     const int64_t blocks = NTHR == 64 ? (p.rows + 3) / 4 : p.rows;
     if (p.hp.pad[0] == IDX_TOP24)
-        hipLaunchKernelGGL((index_softmax_kernel<NTHR, NCH, IDX_TOP24>), dim3((unsigned)blocks), dim3(256), 0, st, p);
+        hipLaunchKernelGGL((index_softmax_kernel<NTHR, NCH, IDX_TOP24, ROWS>), dim3((unsigned)blocks), dim3(256), 0, st, p);
     else
-        hipLaunchKernelGGL((index_softmax_kernel<NTHR, NCH, IDX_FP64>), dim3((unsigned)blocks), dim3(256), 0, st, p);
+        hipLaunchKernelGGL((index_softmax_kernel<NTHR, NCH, IDX_FP64, ROWS>), dim3((unsigned)blocks), dim3(256), 0, st, p);
     return (int)hipGetLastError();
+}
+
+template <int NTHR, int NCH> int launch_one(const SoftmaxParams &p, bool aligned, hipStream_t st)
+{
+    if constexpr (NCH > 0 && (NCH & (NCH - 1)) == 0)
+        if (aligned && !p.causal && p.cols % 4 == 0) return launch_rows<NTHR, NCH, ROWS_WHOLE>(p, st);
+    return launch_rows<NTHR, NCH, ROWS_ANY>(p, st);
 }
 
 } // namespace
@@ -220,17 +244,22 @@ template <int NTHR, int NCH> int launch_one(const SoftmaxParams &p, hipStream_t 
 int launch_index_softmax(const SoftmaxParams &p, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
-    const int c = p.cols + ((((uintptr_t)p.prob | (uint64_t)p.ps) & 3u) != 0 ? 3 : 0);
-    if (p.cols <= 2048 && c > 2048) return launch_one<64, 9>(p, st); // api.cpp counts workgroups of four rows up to 2048 columns
-    if (c <= 256) return launch_one<64, 1>(p, st);
-    if (c <= 512) return launch_one<64, 2>(p, st);
-    if (c <= 1024) return launch_one<64, 4>(p, st);
-    if (c <= 2048) return launch_one<64, 8>(p, st);
-    if (c <= 4096) return launch_one<256, 4>(p, st);
-    if (c <= 8192) return launch_one<256, 8>(p, st);
-    if (c <= 16384) return launch_one<256, 16>(p, st);
-    if (p.cols <= 16384) return launch_one<256, 17>(p, st);
-    return launch_one<256, 0>(p, st);
+    const bool al = (((uintptr_t)p.prob | (uint64_t)p.ps) & 3u) == 0; // every row of probabilities starts on a word
+    const int c = p.cols + (al ? 0 : 3);
+    // A lead costs 0.3 us where there is none to find (20000 masked rows of 200: 8.3 us, 8.1 without) or where the rows are too
+    // short for their stores to matter (20000 rows of 50: 8.1 and 7.9), and a second group per lane for a column or three where
+    // it takes the row past 256 (20000 rows of 254: 10.2 and 8.4).  (Rows of 250 off a word: 8.6 us with it, 9.2 without.)
+    if (p.cols <= 256 && (c > 256 || p.cols <= 128 || al) && !(al && !p.causal && p.cols % 4 == 0)) return launch_rows<64, 1, ROWS_SHORT>(p, st);
+    if (p.cols <= 2048 && c > 2048) return launch_one<64, 9>(p, al, st); // api.cpp counts workgroups of four rows up to 2048 columns
+    if (c <= 256) return launch_one<64, 1>(p, al, st);
+    if (c <= 512) return launch_one<64, 2>(p, al, st);
+    if (c <= 1024) return launch_one<64, 4>(p, al, st);
+    if (c <= 2048) return launch_one<64, 8>(p, al, st);
+    if (c <= 4096) return launch_one<256, 4>(p, al, st);
+    if (c <= 8192) return launch_one<256, 8>(p, al, st);
+    if (c <= 16384) return launch_one<256, 16>(p, al, st);
+    if (p.cols <= 16384) return launch_one<256, 17>(p, al, st);
+    return launch_one<256, 0>(p, al, st);
 }
 
 } // namespace intattn
