@@ -73,3 +73,7 @@ def test_tiled_kernels_with_sweep_c_on_known_schemes(kernels, d, most):
 def test_sweep_c_at_head_dimension_64_runs_three_waves(kernels):
     """168 registers a lane let three waves share a SIMD."""
     assert registers(kernels, r"sweep_c_kernelILi64E") <= 168
+
+
+def test_derivation_kernels_use_no_scratch(kernels):
+    assert all(k[".private_segment_fixed_size"] == 0 for k in pick(kernels, r"derive_").values())
