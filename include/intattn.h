@@ -289,6 +289,14 @@ INTATTN_API int intattn_derive_params(const intattn_ctx *ctx, float s_q, float s
 INTATTN_API int intattn_derive_index_map(const intattn_ctx *ctx, int64_t c_int, int32_t *mode, uint32_t *mul,
                                          uint32_t *add, int32_t *shift);
 
+/* Host-only, exposed for tests: the kernels that intattn_forward (dynamic != 0: intattn_forward_dynamic,
+ * whose scale pointers are not read) would run for args on this context, room for split keys assumed.
+ * *kernel is a number of intattn_config.variant, 6 (4 or 5 with the keys split over *split_rows
+ * workgroups per query tile for row maxima and row sums and over *split_pv for the rest; both 0
+ * otherwise) or 7 (all scores in registers).  Tensors are not read. */
+INTATTN_API int intattn_kernel_choice(intattn_ctx *ctx, const intattn_args *args, int32_t dynamic, int32_t *kernel,
+                                      int32_t *split_rows, int32_t *split_pv);
+
 /* Copies the 2^b bytes of LUT_hat to dst (HOST); cap is dst's capacity in bytes.
  * Returns the number of bytes written, or a negative error. */
 INTATTN_API int intattn_get_lut(const intattn_ctx *ctx, uint8_t *dst, int32_t cap);

@@ -31,6 +31,7 @@ SYMBOLS = (
     "intattn_index_softmax",
     "intattn_derive_params",
     "intattn_derive_index_map",
+    "intattn_kernel_choice",
     "intattn_get_lut",
     "intattn_last_error",
     "intattn_destroy",
@@ -134,6 +135,8 @@ def load() -> ctypes.CDLL:
             ctypes.POINTER(ctypes.c_uint32), ctypes.POINTER(i32),
         ]
         lib.intattn_derive_index_map.restype = i32
+        lib.intattn_kernel_choice.argtypes = [vp, ctypes.POINTER(Args), i32, ctypes.POINTER(i32), ctypes.POINTER(i32), ctypes.POINTER(i32)]
+        lib.intattn_kernel_choice.restype = i32
         lib.intattn_get_lut.argtypes = [vp, vp, i32]
         lib.intattn_get_lut.restype = i32
         lib.intattn_last_error.argtypes = [vp]
@@ -202,6 +205,14 @@ class IntAttn:
         if rc != OK:
             raise IntAttnError(rc, "intattn_derive_index_map")
         return int(mode.value), int(mul.value), int(add.value), int(sh.value)
+
+    def kernel_choice(self, args: Args, dynamic: bool = False):
+        """intattn_kernel_choice: (kernel, split_rows, split_pv) for a call with these arguments."""
+        out = [ctypes.c_int32(0) for _ in range(3)]
+        rc = self._lib.intattn_kernel_choice(self._ctx, ctypes.byref(args), int(bool(dynamic)), *(ctypes.byref(x) for x in out))
+        if rc != OK:
+            raise IntAttnError(rc, self.last_error())
+        return tuple(int(x.value) for x in out)
 
     def make_args(self, q, k, v, out, s_q, s_k, s_v, s_o=None, *, causal=False, per_head=False,
                   row_max=None, row_sum=None, acc=None, device_scales=False, q_block=0, k_block=0):

@@ -504,6 +504,58 @@ struct RunMode {
     bool reserve = false;    // allocate what the call would need and return without deriving or launching
 };
 
+// int32 words of a key-split launch: c partial accumulators, row maxima and row sums, V column sums
+int64_t split_words(const intattn_args *a, int c)
+{
+    const int64_t rows = (int64_t)a->B * a->Hq * a->L, n_chunks = ((a->Lkv ? a->Lkv : a->L) + 127) / 128;
+    return rows * ((int64_t)c * a->d + 2) + (int64_t)a->B * a->Hkv * n_chunks * a->d;
+}
+
+// The kernels that serve a call.
+struct Choice {
+    int variant;
+    bool decode; // the split-key kernels for few query rows
+    KeySplit ks; // variant VARIANT_KEY_SPLIT: workgroups per query tile
+};
+
+// idx_mode: the index map of the call's scales; may_split: room for a key split can be had.
+Choice choose_kernels(const intattn_ctx *ctx, const intattn_args *a, const RunMode &rm, int idx_mode, bool may_split)
+{
+    const int Lk = a->Lkv ? a->Lkv : a->L;
+    Choice ch = {fwd_choose_variant(ctx->variant, a->B, a->Hq, a->L, Lk, a->d, a->causal), false, {0, 0}};
+    if (ch.variant == 5 && ctx->lut_bits > 5) ch.variant = 4; // the pipelined sweep C holds 32-entry tables; same tiling otherwise
+    const bool automatic = ctx->variant == 0 || ctx->variant == 9 || ctx->variant == 10;
+    // Groups (scale modes 2 and 3): up to 256 workgroups of 128 rows, and up to 512 with key groups, the keys split over
+    // the waves of a workgroup win (1024 tokens, 32 / 8 heads, d 128: 64 against 112 us with key groups, 50 against 55
+    // without; with key groups 2048 tokens, 32 / 8 heads, d 128: 170 against 203, 1500 tokens, 32 heads, d 64: 80 against
+    // 142), past that the 128-row kernel does (without key groups, 2 x 1024 tokens: 56 against 88; with them, 2 x 2048
+    // tokens, 32 heads, d 128: 289 against 327).  Key groups run in the single-launch kernels only.
+    if (a->scale_mode >= 2) {
+        const int64_t wgs = (int64_t)a->B * a->Hq * ((a->L + 127) / 128);
+        if (automatic && a->scale_mode == 3) ch.variant = wgs <= 512 ? 3 : 1;
+        else if (automatic && ch.variant == 3 && wgs > 256) ch.variant = 1;
+        else if (a->scale_mode == 3 && ch.variant != 3) ch.variant = 1;
+    }
+    // Few query rows against many keys: the split-key kernels (all query heads of a KV head, times
+    // the query rows, packed into one MFMA operand of at most 31 rows).
+    const int64_t packed_rows = (int64_t)(a->Hq / a->Hkv) * a->L;
+    const bool plain = !rm.comparator && rm.stage == 0;
+    if (plain && a->scale_mode < 2 && packed_rows <= 31 && (int64_t)a->B * a->Hkv <= 65535)
+        ch.decode = ctx->variant == 9 || ctx->variant == 10 || (ctx->variant == 0 && Lk >= 1024);
+    if (!automatic || !plain || ch.decode || ctx->lut_bits > 5) return ch;
+    // Few query tiles against many keys: the tiled kernels with the keys split, where their cost model beats that of the
+    // single launch
+    if (may_split && (ch.variant == 1 || ch.variant == 3) && !rm.no_alloc && a->scale_mode <= 2) {
+        ch.ks = fwd_key_split(ch.variant, a->B, a->Hq, a->Hkv, a->L, Lk, a->d, a->causal);
+        if (ch.ks.c > 0) ch.variant = VARIANT_KEY_SPLIT;
+    }
+    // Short key sequences at d = 64 with the integer index maps: all scores in registers (fwd_short.hip)
+    const bool integer_map = idx_mode == IDX_MAD24 || idx_mode == IDX_TOP24 || idx_mode == IDX_MULHI24;
+    if (!rm.dynamic && integer_map && a->scale_mode < 2 && fwd_short_serves(ch.variant, a->B, a->Hq, a->L, Lk, a->d, a->causal))
+        ch.variant = VARIANT_SHORT;
+    return ch;
+}
+
 int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm)
 {
     const bool comparator = rm.comparator, dynamic = rm.dynamic;
@@ -618,66 +670,38 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
     p.causal = a->causal;
     p.group = a->Hq / a->Hkv;
     p.top = (1 << ctx->lut_bits) - 1;
-    int variant = fwd_choose_variant(ctx->variant, a->B, a->Hq, a->L, p.Lk, a->d, a->causal);
-    if (variant == 5 && ctx->lut_bits > 5) variant = 4; // the pipelined sweep C holds 32-entry tables; same tiling otherwise
-    // Groups (scale modes 2 and 3): up to 256 workgroups of 128 rows, and up to 512 with key groups, the keys split over
-    // the waves of a workgroup win (1024 tokens, 32 / 8 heads, d 128: 64 against 112 us with key groups, 50 against 55
-    // without; with key groups 2048 tokens, 32 / 8 heads, d 128: 170 against 203, 1500 tokens, 32 heads, d 64: 80 against
-    // 142), past that the 128-row kernel does (without key groups, 2 x 1024 tokens: 56 against 88; with them, 2 x 2048
-    // tokens, 32 heads, d 128: 289 against 327).  Key groups run in the single-launch kernels only.
-    const bool automatic = ctx->variant == 0 || ctx->variant == 9 || ctx->variant == 10;
-    if (a->scale_mode >= 2) {
-        const int64_t wgs = (int64_t)a->B * a->Hq * ((a->L + 127) / 128);
-        if (automatic && a->scale_mode == 3) variant = wgs <= 512 ? 3 : 1;
-        else if (automatic && variant == 3 && wgs > 256) variant = 1;
-        else if (a->scale_mode == 3 && variant != 3) variant = 1;
+    Choice ch = choose_kernels(ctx, a, rm, dv.idx_mode, !rm.reserve);
+    if (ch.ks.c > 0) {
+        bool room = true;
+        if ((size_t)split_words(a, ch.ks.c) > ctx->ws_cap) {
+            // a call that is being captured must not allocate: it runs as if the keys could not be split
+            hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+            room = hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+            if (!room) (void)hipGetLastError();
+            else if (get_ws((size_t)split_words(a, ch.ks.c)) != INTATTN_OK) {
+                (void)hipGetLastError(); // the launches that follow report errors of their own
+                room = false;
+            }
+        }
+        if (!room) ch = choose_kernels(ctx, a, rm, dv.idx_mode, false);
     }
-    // Few query rows against many keys: the split-key kernels (all query heads of a KV head, times
-    // the query rows, packed into one MFMA operand of at most 31 rows).
+    const int variant = ch.variant;
+    const bool decode = ch.decode;
     const int64_t packed_rows = (int64_t)p.group * p.L;
-    const bool decode_ok = !comparator && stage == 0 && a->scale_mode < 2 && packed_rows <= 31 && (int64_t)a->B * a->Hkv <= 65535;
-    const bool decode = decode_ok && (ctx->variant == 9 || ctx->variant == 10 || (ctx->variant == 0 && p.Lk >= 1024));
-
-    auto split_ws_words = [&](int c) {
-        const size_t rows = (size_t)a->B * a->Hq * a->L, n_chunks = ((size_t)p.Lk + 127) / 128;
-        return rows * ((size_t)c * a->d + 2) + (size_t)a->B * a->Hkv * n_chunks * a->d;
-    };
-    // A smaller problem than the one reserved for may split its keys where this one does not (an 8192-token prompt, then a
-    // chunk of 512 rows): room for the partial accumulators of any such problem.
-    auto reserve_split = [&]() -> int {
-        if (!automatic || comparator || ctx->lut_bits > 5 || a->scale_mode > 2) return INTATTN_OK;
-        const int64_t part = std::min<int64_t>(KEY_SPLIT_MAX_WORDS, (int64_t)KEY_SPLIT_MAX_RANGES * a->B * a->Hq * a->L * a->d);
-        if (get_ws(split_ws_words(0) + (size_t)part) != INTATTN_OK) {
+    // What a problem no larger than this one may need besides: it may split its keys where this one does not (an 8192-token
+    // prompt, then a chunk of 512 rows), or run on the 128-row kernels where this one needs no workspace.
+    auto reserve_rest = [&]() -> int {
+        const int r = get_ws((size_t)split_words(a, 0));
+        if (r) return r;
+        if (ctx->variant != 0 && ctx->variant != 9 && ctx->variant != 10) return INTATTN_OK;
+        if (comparator || ctx->lut_bits > 5 || a->scale_mode > 2) return INTATTN_OK;
+        const int64_t most = std::min<int64_t>(KEY_SPLIT_MAX_WORDS, split_words(a, KEY_SPLIT_MAX_RANGES));
+        if (get_ws((size_t)most) != INTATTN_OK) {
             (void)hipGetLastError(); // such a problem then runs unsplit
             ctx->err.clear();
         }
         return INTATTN_OK;
     };
-    // Few query tiles against many keys: the tiled kernels with the keys split, where their cost model beats that of the
-    // single launch and the partial accumulators can be had
-    KeySplit ks = {0, 0};
-    if (automatic && !decode && (variant == 1 || variant == 3) && !comparator && stage == 0 && !rm.no_alloc && ctx->lut_bits <= 5 && a->scale_mode <= 2) {
-        ks = fwd_key_split(variant, a->B, a->Hq, a->L, p.Lk, a->d, a->causal);
-        const size_t need = split_ws_words(ks.c);
-        if (ks.c > 0 && !rm.reserve && need > ctx->ws_cap) {
-            // a call that is being captured must not allocate: it runs as if the keys could not be split
-            hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-            if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-                (void)hipGetLastError();
-                ks = KeySplit{0, 0};
-            }
-        }
-        if (ks.c > 0 && get_ws(need) != INTATTN_OK) {
-            (void)hipGetLastError(); // the launches that follow report errors of their own
-            ks = KeySplit{0, 0};
-        }
-        if (ks.c > 0) variant = VARIANT_KEY_SPLIT;
-    }
-    // Short key sequences at d = 64 with the integer index maps: all scores in registers (fwd_short.hip)
-    const bool integer_map = dv.idx_mode == IDX_MAD24 || dv.idx_mode == IDX_TOP24 || dv.idx_mode == IDX_MULHI24;
-    if (automatic && !decode && !comparator && stage == 0 && !dynamic && !rm.reserve && integer_map && a->scale_mode < 2 &&
-        ctx->lut_bits <= 5 && fwd_short_serves(a->B, a->Hq, p.Lk, a->d))
-        variant = VARIANT_SHORT;
     const int rows_per_block = comparator ? 128 : fwd_rows_per_block(variant);
     p.n_qtiles = variant == VARIANT_SHORT ? (p.L + 127) / 128 : fwd_row_tiles(p.row_lo, p.L, rows_per_block);
     p.n_chunks = (p.Lk + rows_per_block - 1) / rows_per_block;
@@ -837,7 +861,7 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
             const hipError_t e = hipMemset(ctx->d_dec_state, 0, ctx->dec_state_groups * DEC_STATE_WORDS * sizeof(uint32_t));
             if (e != hipSuccess) return hip_fail(ctx, e, "hipMemset(split-key group state)");
         }
-        if (rm.reserve) return reserve_split();
+        if (rm.reserve) return reserve_rest();
         p.dec_rows = (int32_t)R;
         p.dec_nt32 = (int32_t)nt32;
         p.dec_tpw = (int32_t)tpw;
@@ -867,17 +891,18 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
     if (!comparator && variant != 3 && variant != VARIANT_SHORT) { // (those pass nothing through memory)
         const size_t rows = (size_t)a->B * a->Hq * a->L;
         const size_t cs = (size_t)a->B * a->Hkv * p.n_chunks * a->d;
-        const size_t part = (size_t)ks.c * rows * a->d; // first: its rows start 16-byte aligned
+        const size_t part = (size_t)ch.ks.c * rows * a->d; // first: its rows start 16-byte aligned
         rc = get_ws(part + 2 * rows + cs);
         if (rc) return rc;
         p.ws_part = d_ws;
-        p.ws_row_max = d_ws + part;
+        p.split_ab = ch.ks.ab;
+        p.split_c = ch.ks.c;
+        int32_t *base = d_ws + part;
+        p.ws_row_max = base;
         p.ws_row_sum = p.ws_row_max + rows;
         p.ws_colsum = p.ws_row_sum + rows;
-        p.split_ab = ks.ab;
-        p.split_c = ks.c;
     }
-    if (rm.reserve) return reserve_split();
+    if (rm.reserve) return reserve_rest();
 
     const int herr = comparator ? launch_quantonly(p, a->d, ctx->variant, stream)
                                 : launch_fwd(p, a->d, dv.idx_mode, variant, stage, stream);
@@ -1163,6 +1188,29 @@ int intattn_derive_index_map(const intattn_ctx *ctx, int64_t c_int, int32_t *mod
     *mul = (uint32_t)(-(int32_t)hp.idx_mul);
     *add = *mode == IDX_MULHI24 ? (uint32_t)(-(int32_t)hp.idx_add) : hp.idx_add;
     *shift = hp.idx_shift;
+    return INTATTN_OK;
+}
+
+int intattn_kernel_choice(intattn_ctx *ctx, const intattn_args *a, int32_t dynamic, int32_t *kernel, int32_t *split_rows, int32_t *split_pv)
+{
+    const int rc = validate(ctx, a);
+    if (rc) return rc;
+    if (!kernel || !split_rows || !split_pv) return fail(ctx, INTATTN_ERR_INVALID_ARG, "kernel, split_rows, split_pv must be non-NULL");
+    RunMode rm;
+    rm.dynamic = dynamic != 0;
+    Derived dv;
+    if (rm.dynamic) {
+        dv.idx_mode = a->scale_mode == 3 ? IDX_KGROUP : (a->scale_mode == 2 ? IDX_ROW64 : IDX_DEVICE);
+    } else {
+        if (a->scale_mode >= 2) return fail(ctx, INTATTN_ERR_UNSUPPORTED, "scale_mode 2 and 3 are served by intattn_forward_dynamic only");
+        const int rd = derive_all(ctx, a, &dv);
+        if (rd) return rd;
+    }
+    const Choice ch = choose_kernels(ctx, a, rm, dv.idx_mode, true);
+    *kernel = ch.decode ? (ctx->variant == 10 ? 10 : 9) : ch.variant;
+    *split_rows = ch.ks.ab;
+    *split_pv = ch.ks.c;
+    ctx->err.clear();
     return INTATTN_OK;
 }
 

@@ -149,9 +149,10 @@ bool fwd_variant_known(int variant) { return variant == 0 || (variant >= 1 && va
 // 380 workgroups (variant 1).  Checked on 111 shapes from 1 x 1 x 256 x 1024 to 1 x 32 x 2048 x 16384: with the margins below
 // the choice is the faster one or within 5 %.  (509 x 7001, 32 and 8 heads, d 128: 0.247 -> 0.125 ms; 64 x 16384, 8 heads,
 // d 128: 0.229 -> 0.068; but 0.022 -> 0.049 at 1024 x 1024.)
-KeySplit fwd_key_split(int variant, int B, int Hq, int L, int Lk, int d, int causal)
+KeySplit fwd_key_split(int variant, int B, int Hq, int Hkv, int L, int Lk, int d, int causal)
 {
     const int row_lo = causal ? Lk - L : 0, tiles = (Lk + 127) / 128;
+    const int64_t rows = (int64_t)B * Hq * L, fixed = 2 * rows + (int64_t)B * Hkv * tiles * d; // row maxima and sums, V column sums
     const int64_t w_ab = (int64_t)B * Hq * fwd_row_tiles(row_lo, L, 256), w_c = (int64_t)B * Hq * fwd_row_tiles(row_lo, L, 128);
     const double seen = causal ? (Lk - 0.5 * L) / Lk : 1.0; // share of the keys that an average row sees
     const double us_tile = d == 128 ? 1.4 : 0.9, us_part = (double)B * Hq * L * d * 8 / 4.0e6;
@@ -170,7 +171,7 @@ KeySplit fwd_key_split(int variant, int B, int Hq, int L, int Lk, int d, int cau
     for (int s = 1; s <= 32 && (s == 1 || 2 * s <= tiles); ++s) {
         const double ab = rounds(w_ab, s) * 2 * us_tile + 0.1 * s, c = rounds(w_c, s) * us_tile + us_part * s;
         if (ab < t_ab) t_ab = ab, ks.ab = s;
-        if (s <= KEY_SPLIT_MAX_RANGES && (int64_t)s * B * Hq * L * d <= KEY_SPLIT_MAX_WORDS && c < t_c) t_c = c, ks.c = s;
+        if (s <= KEY_SPLIT_MAX_RANGES && s * rows * d + fixed <= KEY_SPLIT_MAX_WORDS && c < t_c) t_c = c, ks.c = s;
     }
     if (24 + t_ab + t_c > worth) return KeySplit{0, 0};
     return ks;
@@ -181,7 +182,7 @@ static int sweep_c_mode(const FwdParams &p, int idx_mode) { return p.hp_table_c 
 
 // All scores in registers (fwd_short.hip): up to 256 keys at d = 64, from 128 heads on (16 x 12 heads of 197 x 197: 12.3 us
 // against 17.0 with the keys split over waves; 8 x 12 heads would take 11.6 against 10.6).
-bool fwd_short_serves(int B, int Hq, int Lk, int d) { return d == 64 && Lk <= 256 && (int64_t)B * Hq >= 128; }
+bool fwd_short_serves(int, int B, int Hq, int, int Lk, int d, int) { return d == 64 && Lk <= 256 && (int64_t)B * Hq >= 128; }
 
 int fwd_rows_per_block(int variant) { return variant == 2 ? 256 : (variant == 3 ? 32 : 128); }
 

@@ -177,14 +177,14 @@ bool fwd_variant_known(int variant);
 constexpr int VARIANT_KEY_SPLIT = 6;
 // the kernel for short key sequences (fwd_short.hip); never asked for by number
 constexpr int VARIANT_SHORT = 7;
-bool fwd_short_serves(int B, int Hq, int Lk, int d);
+bool fwd_short_serves(int variant, int B, int Hq, int L, int Lk, int d, int causal); // instead of `variant`
 int launch_fwd_short(const FwdParams &p, int d, int idx_mode, void *stream);
 constexpr int KEY_SPLIT_MAX_RANGES = 16;          // ranges of sweep C: each writes and reads its partial accumulators
-constexpr int64_t KEY_SPLIT_MAX_WORDS = 32 << 20; // of partial accumulators (128 MB): what reserving ahead has to set aside
+constexpr int64_t KEY_SPLIT_MAX_WORDS = 32 << 20; // that a launch may need (128 MiB): what reserving ahead has to set aside
 struct KeySplit {
     int ab, c; // workgroups per query tile; c == 0: this shape is better served by `variant`, the choice without a split
 };
-KeySplit fwd_key_split(int variant, int B, int Hq, int L, int Lk, int d, int causal);
+KeySplit fwd_key_split(int variant, int B, int Hq, int Hkv, int L, int Lk, int d, int causal);
 int quantize_partials_per_slice(int B, int H, int L, int d);
 int launch_quantize(const QuantParams *ps, int n, void *stream);
 int launch_decode(const FwdParams &p, int d, void *stream);

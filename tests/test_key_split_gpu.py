@@ -3,6 +3,8 @@ bit-compared with the CPU oracle; and the mapping of work to XCDs for group coun
 import numpy as np
 import pytest
 
+from test_index_map_choice_gpu import scales_for, without_multiply_high
+from test_kernel_choice import SPLIT
 from test_parity_gpu import rect_forward, rect_problem, torch_mod  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -14,6 +16,8 @@ SHAPES = [
     (1, 4, 1, 129, 8192, 64, False, True),     # no mask, whole tiles
     (1, 3, 3, 200, 8190, 128, True, True),     # three groups over eight XCDs
     (2, 2, 1, 513, 7001, 128, True, False),
+    (1, 1, 1, 4096, 4096, 128, True, False),   # the first query tiles have fewer key tiles than there are ranges: empty ranges
+    (1, 1, 1, 8192, 8192, 64, True, False),
 ]
 
 
@@ -27,18 +31,49 @@ def test_key_split_bit_exact(torch_mod, oracle, shape):  # noqa: F811
     ia = binding.IntAttn(device=0)
     base, q, k, v = rect_problem(900 + lq, B, Hq, Hkv, lq, lk, d, causal, per_head)
     want = oracle.forward(q, k, v, base.s_q, base.s_k, base.s_v, None, causal=causal, per_head=per_head, taps=True, threads=16)
+    dev = torch.device("cuda:0")
+    tq, tk, tv = (torch.from_numpy(x).to(dev) for x in (q, k, v))
+    kernel, split_rows, split_pv = ia.kernel_choice(ia.make_args(tq, tk, tv, torch.empty_like(tq), base.s_q, base.s_k, base.s_v, None, causal=causal,
+                                                                 per_head=per_head)[0])
+    assert kernel == SPLIT and split_rows > 1 and split_pv > 1
     got = rect_forward(torch, ia, base, q, k, v)
     for key in ("row_max", "row_sum", "acc", "out"):
         assert int((got[key] != want[key]).sum()) == 0, key
     # the same scales in device memory
-    dev = torch.device("cuda:0")
-    tq, tk, tv = (torch.from_numpy(x).to(dev) for x in (q, k, v))
     sc = [torch.from_numpy(np.ascontiguousarray(s, dtype=np.float32)).to(dev) for s in (base.s_q, base.s_k, base.s_v)]
     out = torch.empty_like(tq)
     args, keep = ia.make_args(tq, tk, tv, out, *sc, None, causal=causal, per_head=per_head, device_scales=True)
+    assert ia.kernel_choice(args, dynamic=True)[0] == SPLIT
     ia.forward_dynamic_args(args, torch.cuda.current_stream(dev).cuda_stream)
     torch.cuda.synchronize()
     assert ia.dynamic_status() == 0 and int((out.cpu().numpy() != want["out"]).sum()) == 0
+    ia.close()
+
+
+@pytest.mark.parametrize("lut_bits, scheme", [(3, 6), (5, 2), (5, 3), (5, 0)], ids=["table of 8", "multiply-high", "fp32", "fp64"])
+def test_key_split_tables_and_index_maps_bit_exact(torch_mod, oracle, lut_bits, scheme):  # noqa: F811
+    """Tables of fewer than 32 entries, and every index map; the fp64 map also as the device picks it."""
+    from paper_2511_21513_amd import binding
+
+    torch = torch_mod
+    host = binding.IntAttn(device=-1, lut_bits=lut_bits)
+    c_int = {6: 5203, 2: 47011, 3: without_multiply_high(), 0: 2**25 + 1}[scheme]
+    assert host.derive_index_map(c_int, scheme)[0] == scheme
+    assert scheme == 6 or host.derive_index_map(c_int, 6)[0] == 0
+    base, q, k, v = rect_problem(77, 1, 2, 1, 129, 9001, 64, True)
+    s_q, s_k = (np.array([x], dtype=np.float32) for x in scales_for(c_int))
+    s_v, s_o = np.array([0.02], dtype=np.float32), np.array([0.004], dtype=np.float32)
+    want = oracle.forward(q, k, v, s_q, s_k, s_v, s_o, causal=True, lut_bits=lut_bits, threads=16)["out"]
+    ia = binding.IntAttn(device=0, lut_bits=lut_bits)
+    tq, tk, tv = (torch.from_numpy(x).cuda() for x in (q, k, v))
+    for device_scales in (False, True):
+        out = torch.full_like(tq, 99)
+        sc = [torch.from_numpy(x).cuda() if device_scales else x for x in (s_q, s_k, s_v, s_o)]
+        args, keep = ia.make_args(tq, tk, tv, out, *sc, causal=True, device_scales=device_scales)
+        assert ia.kernel_choice(args, dynamic=device_scales)[0] == SPLIT
+        (ia.forward_dynamic_args if device_scales else ia.forward_args)(args, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert int((out.cpu().numpy() != want).sum()) == 0, device_scales
     ia.close()
 
 

@@ -4,6 +4,7 @@ row maxima, row sums, accumulators and bytes of the oracle."""
 import numpy as np
 import pytest
 
+from test_kernel_choice import SHORT
 from test_parity_gpu import rect_forward, rect_problem, torch_mod  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -29,6 +30,10 @@ def test_short_keys_bit_exact(torch_mod, oracle, shape):  # noqa: F811
     q, k, v = (np.ascontiguousarray(np.tile(x, (B // 2, 1, 1, 1))) for x in (q, k, v))
     want = oracle.forward(q[:2], k[:2], v[:2], base.s_q, base.s_k, base.s_v, None, causal=causal, per_head=per_head, taps=True, threads=16)
     ia = binding.IntAttn(device=0)
+    tensors = [torch_mod.from_numpy(x) for x in (q, k, v)]
+    args, _ = ia.make_args(*tensors, torch_mod.empty_like(tensors[0]), base.s_q, base.s_k, base.s_v, None, causal=causal, per_head=per_head)
+    args.q, args.k, args.v, args.out = 16, 32, 48, 64  # (not read)
+    assert ia.kernel_choice(args)[0] == SHORT
     got = rect_forward(torch_mod, ia, base, q, k, v)
     ia.close()
     for key in ("row_max", "row_sum", "acc", "out"):
@@ -48,8 +53,10 @@ def test_short_keys_fused_projection_layout_bit_exact(torch_mod, oracle, lut_bit
     qkv = torch.from_numpy(np.stack([np.tile(x, (B // 2, 1, 1, 1)).transpose(0, 2, 1, 3) for x in (q, k, v)], axis=2)).cuda()
     out = torch.full((B, L, H, 96), 7, dtype=torch.int8, device="cuda")
     ia = binding.IntAttn(device=0, lut_bits=lut_bits)
-    ia.forward(*(qkv[:, :, i].permute(0, 2, 1, 3) for i in range(3)), base.s_q, base.s_k, base.s_v, None, causal=False,
-               out=out[..., 16:80].permute(0, 2, 1, 3))
+    q, k, v = (qkv[:, :, i].permute(0, 2, 1, 3) for i in range(3))
+    dst = out[..., 16:80].permute(0, 2, 1, 3)
+    assert ia.kernel_choice(ia.make_args(q, k, v, dst, base.s_q, base.s_k, base.s_v, None, causal=False)[0])[0] == SHORT
+    ia.forward(q, k, v, base.s_q, base.s_k, base.s_v, None, causal=False, out=dst)
     torch.cuda.synchronize()
     ia.close()
     got = out.cpu().numpy()
