@@ -134,12 +134,17 @@ INTATTN_API int intattn_create(intattn_ctx **out, const intattn_config *cfg);
 
 /* Enqueues the fused IntAttention forward (Sec. 3) on hip_stream (a hipStream_t; NULL is
  * the default stream) and returns without waiting for it.  The context owns a device workspace
- * (8 bytes per query row plus d int32 per 128 keys and KV head; for few query tiles against many keys also
- * partial accumulators of key ranges, at most 128 MB, which intattn_reserve sets aside and without which a
- * captured call runs unsplit) that the first call allocates and a later, larger call re-allocates (hipMalloc / hipFree wait for the device and are not for use
- * under graph capture: call intattn_reserve first, or use intattn_forward_noalloc); the
+ * (8 bytes per query row plus d int32 per 128 keys and KV head) that the first call allocates and a
+ * later, larger call re-allocates (hipMalloc / hipFree wait for the device and are not for use under
+ * graph capture: call intattn_reserve first, or use intattn_forward_noalloc); the
  * kernels of a call pass intermediate results through it, so calls on ONE context must not
  * overlap in time (same stream, or ordered by the caller); use one context per concurrent stream.
+ * Few query tiles against many keys run with the keys split over workgroups, whose partial results
+ * take room of their own, at most 128 MiB a call.  It grows apart from the workspace and is never
+ * given back or moved before intattn_destroy (what it outgrows, in all less than its last size, stays
+ * too), so captured launches stay valid whatever is called later.  A captured call that lacks the room
+ * allocates nothing for it and runs unsplit; what the unsplit kernels need of the workspace has to
+ * be there, as for any captured call.
  * The one-launch split-key path (few query rows; see intattn_config.variant) lets the workgroups of a
  * (batch, KV head) group wait for each other at a counter in device memory.  Alone on the GPU a group's
  * workgroups are always scheduled together (they have consecutive ids).  The wait is bounded (a few
@@ -154,13 +159,15 @@ INTATTN_API int intattn_forward(intattn_ctx *ctx, const intattn_args *args, void
 
 /* Pre-sizes the context's device memory (workspace, per-head tables) for a problem of the shape and
  * scale mode of `args`, so that later forward calls with problems no larger allocate nothing and
- * never wait for the device.  dynamic != 0: for intattn_forward_dynamic (scale pointers are not read
- * either way).  May call hipMalloc / hipFree; launches nothing. */
+ * never wait for the device.  That includes the room for split keys; where this cannot be had, the
+ * reservation succeeds all the same, and no later call on the context asks for more of it: those it
+ * does not suffice for run unsplit.  dynamic != 0: for intattn_forward_dynamic (scale pointers are not
+ * read either way).  May call hipMalloc / hipFree; launches nothing. */
 INTATTN_API int intattn_reserve(intattn_ctx *ctx, const intattn_args *args, int32_t dynamic);
 
 /* intattn_forward for callers that cannot allocate device memory (code under HIP graph capture, tight
- * serving loops, harnesses that forbid hipMalloc): same arguments (host scales), same kernels, same
- * bytes out, but the workspace -- row maxima and row sums between the launches, V column sums, the
+ * serving loops, harnesses that forbid hipMalloc): same arguments (host scales), same kernels (but for
+ * split keys, which it never uses), same bytes out, but the workspace -- row maxima and row sums between the launches, V column sums, the
  * partial results of the split-key kernels -- and the per-head parameter table live in a static
  * device array of INTATTN_NOALLOC_SCRATCH_BYTES that the library's image holds on every GPU it runs
  * on.  Calls no hipMalloc / hipFree.  A problem that needs more workspace than the array holds (8

@@ -51,6 +51,12 @@ struct intattn_ctx {
     // kernel workspace (row max and row sum between the two launches, V chunk sums), grown on demand
     int32_t *d_ws = nullptr;
     size_t ws_cap = 0; // in int32 elements
+    // room of the key-split launches, apart from the workspace: a smaller problem may need more of it than a larger one, and
+    // captured launches keep the pointers they were recorded with, so an outgrown piece stays until the context goes
+    int32_t *d_split = nullptr, *split_outgrown[KEY_SPLIT_PIECES] = {nullptr};
+    int n_split_outgrown = 0;
+    size_t split_cap = 0; // in int32 elements
+    bool split_fixed = false; // a reservation could not have it all: what is there now is all there will be
     HeadParams *d_rowtab = nullptr; // parameters per block of query rows (scale_mode 2), grown on demand
     uint32_t *d_dec_state = nullptr; // fused split-key kernel: DEC_STATE_WORDS per (batch, KV head) group, zero between launches
     size_t dec_state_groups = 0;
@@ -495,6 +501,25 @@ int ensure_workspace(intattn_ctx *ctx, size_t n_int32)
     return INTATTN_OK;
 }
 
+// Room for the key-split launches, at most KEY_SPLIT_MAX_WORDS; never frees (see intattn_ctx).  Sizes double, so the outgrown
+// pieces together hold less than the last one.
+int ensure_split(intattn_ctx *ctx, size_t n_int32)
+{
+    if (n_int32 <= ctx->split_cap) return INTATTN_OK;
+    if (ctx->split_fixed || n_int32 > (size_t)KEY_SPLIT_MAX_WORDS) return INTATTN_ERR_NOMEM;
+    size_t cap = KEY_SPLIT_MAX_WORDS >> KEY_SPLIT_PIECES;
+    while (cap < n_int32) cap *= 2;
+    int32_t *room = nullptr;
+    if (hipMalloc((void **)&room, cap * sizeof(int32_t)) != hipSuccess) {
+        (void)hipGetLastError(); // the launches that follow report errors of their own
+        return INTATTN_ERR_NOMEM;
+    }
+    if (ctx->d_split) ctx->split_outgrown[ctx->n_split_outgrown++] = ctx->d_split;
+    ctx->d_split = room;
+    ctx->split_cap = cap;
+    return INTATTN_OK;
+}
+
 // What a call may do beyond the plain forward.
 struct RunMode {
     bool comparator = false; // the conventional INT8 pipeline instead of the integer one
@@ -673,15 +698,12 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
     Choice ch = choose_kernels(ctx, a, rm, dv.idx_mode, !rm.reserve);
     if (ch.ks.c > 0) {
         bool room = true;
-        if ((size_t)split_words(a, ch.ks.c) > ctx->ws_cap) {
+        if ((size_t)split_words(a, ch.ks.c) > ctx->split_cap) {
             // a call that is being captured must not allocate: it runs as if the keys could not be split
             hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
             room = hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
             if (!room) (void)hipGetLastError();
-            else if (get_ws((size_t)split_words(a, ch.ks.c)) != INTATTN_OK) {
-                (void)hipGetLastError(); // the launches that follow report errors of their own
-                room = false;
-            }
+            else room = ensure_split(ctx, (size_t)split_words(a, ch.ks.c)) == INTATTN_OK;
         }
         if (!room) ch = choose_kernels(ctx, a, rm, dv.idx_mode, false);
     }
@@ -696,10 +718,7 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
         if (ctx->variant != 0 && ctx->variant != 9 && ctx->variant != 10) return INTATTN_OK;
         if (comparator || ctx->lut_bits > 5 || a->scale_mode > 2) return INTATTN_OK;
         const int64_t most = std::min<int64_t>(KEY_SPLIT_MAX_WORDS, split_words(a, KEY_SPLIT_MAX_RANGES));
-        if (get_ws((size_t)most) != INTATTN_OK) {
-            (void)hipGetLastError(); // such a problem then runs unsplit
-            ctx->err.clear();
-        }
+        if (ensure_split(ctx, (size_t)most) != INTATTN_OK) ctx->split_fixed = true; // later calls run unsplit rather than allocate
         return INTATTN_OK;
     };
     const int rows_per_block = comparator ? 128 : fwd_rows_per_block(variant);
@@ -891,13 +910,17 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
     if (!comparator && variant != 3 && variant != VARIANT_SHORT) { // (those pass nothing through memory)
         const size_t rows = (size_t)a->B * a->Hq * a->L;
         const size_t cs = (size_t)a->B * a->Hkv * p.n_chunks * a->d;
-        const size_t part = (size_t)ch.ks.c * rows * a->d; // first: its rows start 16-byte aligned
-        rc = get_ws(part + 2 * rows + cs);
-        if (rc) return rc;
-        p.ws_part = d_ws;
-        p.split_ab = ch.ks.ab;
-        p.split_c = ch.ks.c;
-        int32_t *base = d_ws + part;
+        int32_t *base = nullptr;
+        if (variant == VARIANT_KEY_SPLIT) {
+            p.ws_part = ctx->d_split; // first: its rows start 16-byte aligned
+            p.split_ab = ch.ks.ab;
+            p.split_c = ch.ks.c;
+            base = p.ws_part + (size_t)ch.ks.c * rows * a->d;
+        } else {
+            rc = get_ws(2 * rows + cs);
+            if (rc) return rc;
+            base = d_ws;
+        }
         p.ws_row_max = base;
         p.ws_row_sum = p.ws_row_max + rows;
         p.ws_colsum = p.ws_row_sum + rows;
@@ -1234,6 +1257,8 @@ void intattn_destroy(intattn_ctx *ctx)
         if (ctx->d_alpha) (void)hipFree(ctx->d_alpha);
         if (ctx->d_svso) (void)hipFree(ctx->d_svso);
         if (ctx->d_ws) (void)hipFree(ctx->d_ws);
+        if (ctx->d_split) (void)hipFree(ctx->d_split);
+        for (int i = 0; i < ctx->n_split_outgrown; ++i) (void)hipFree(ctx->split_outgrown[i]);
         if (ctx->d_amax) (void)hipFree(ctx->d_amax);
         if (ctx->d_status) (void)hipFree(ctx->d_status);
         if (ctx->d_rowtab) (void)hipFree(ctx->d_rowtab);

@@ -181,6 +181,7 @@ bool fwd_short_serves(int variant, int B, int Hq, int L, int Lk, int d, int caus
 int launch_fwd_short(const FwdParams &p, int d, int idx_mode, void *stream);
 constexpr int KEY_SPLIT_MAX_RANGES = 16;          // ranges of sweep C: each writes and reads its partial accumulators
 constexpr int64_t KEY_SPLIT_MAX_WORDS = 32 << 20; // that a launch may need (128 MiB): what reserving ahead has to set aside
+constexpr int KEY_SPLIT_PIECES = 5;               // doublings of the context's room for it up to that
 struct KeySplit {
     int ab, c; // workgroups per query tile; c == 0: this shape is better served by `variant`, the choice without a split
 };

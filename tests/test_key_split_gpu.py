@@ -146,3 +146,45 @@ def test_key_split_workspace_reserved_ahead_and_under_capture(torch_mod, oracle)
         torch.cuda.synchronize()
         assert int((out.cpu().numpy() != want).sum()) == 0
     ia.close()
+
+
+def test_captured_launches_stay_valid_when_the_room_for_split_keys_grows(torch_mod, oracle):  # noqa: F811
+    """Graphs captured after an eager call, of a problem that splits its keys and of one that uses the workspace; then eager
+    calls that split and need more room: what the graphs were recorded with is still theirs."""
+    from paper_2511_21513_amd import binding
+
+    torch = torch_mod
+    ia = binding.IntAttn(device=0)
+    stream = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
+
+    def call(B, Hq, Hkv, lq, lk, d, kernel):
+        base, q, k, v = rect_problem(lq, B, Hq, Hkv, lq, lk, d, True)
+        tq, tk, tv = (torch.from_numpy(x).cuda() for x in (q, k, v))
+        out = torch.empty_like(tq)
+        args, keep = ia.make_args(tq, tk, tv, out, base.s_q, base.s_k, base.s_v, None, causal=True)
+        assert ia.kernel_choice(args)[0] == kernel
+        ia.forward_args(args, stream())
+        torch.cuda.synchronize()
+        return args, out, out.cpu().numpy(), (tq, tk, tv, keep), (base, q, k, v)
+
+    graphs = []
+    for shape in ((1, 2, 1, 129, 9001, 128, SPLIT), (1, 40, 40, 900, 900, 128, 1)):
+        args, out, want, keep, problem = call(*shape)
+        if shape[-1] == SPLIT:
+            base, q, k, v = problem
+            assert int((want != oracle.forward(q, k, v, base.s_q, base.s_k, base.s_v, None, causal=True, threads=16)["out"]).sum()) == 0
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            ia.forward_args(args, stream())
+        graphs.append((graph, out, want, keep))
+    for shape in ((1, 2, 1, 513, 9001, 128, SPLIT), (1, 8, 2, 513, 12000, 128, SPLIT)):
+        call(*shape)
+        filler = [torch.full((1 << 20,), 77, dtype=torch.int32, device="cuda") for _ in range(8)]
+        for graph, out, want, _ in graphs:
+            out.fill_(55)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert int((out.cpu().numpy() != want).sum()) == 0
+        assert all(int((x != 77).sum()) == 0 for x in filler)
+    ia.close()
