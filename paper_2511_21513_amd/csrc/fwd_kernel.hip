@@ -180,9 +180,16 @@ KeySplit fwd_key_split(int variant, int B, int Hq, int Hkv, int L, int Lk, int d
 // less than the multiply-high scheme of the other kernels): the host's comes with the multiply-high scheme for all heads.
 static int sweep_c_mode(const FwdParams &p, int idx_mode) { return p.hp_table_c && idx_mode == IDX_MULHI24 ? IDX_MIX : idx_mode; }
 
-// All scores in registers (fwd_short.hip): up to 256 keys at d = 64, from 128 heads on (16 x 12 heads of 197 x 197: 12.3 us
-// against 17.0 with the keys split over waves; 8 x 12 heads would take 11.6 against 10.6).
-bool fwd_short_serves(int, int B, int Hq, int, int Lk, int d, int) { return d == 64 && Lk <= 256 && (int64_t)B * Hq >= 128; }
+// All scores in registers (fwd_short.hip): up to 256 keys at d = 64, from 128 heads on.  Against variant 3, whose chain is a
+// quarter as long, only where more blocks of 32 rows than three for each compute unit are in flight, or, as its waves pad the
+// masked half, one under a square mask: 160 heads of 160 x 160 10.2 us against 10.4, 128 of 197 x 197 10.5 against 11.2, masked
+// 128 of 96 x 96 8.5 against 8.8, but 128 heads of 96 x 96 8.0 against 7.1 and of 64 x 200, masked, 11.1 against 10.0.  Against
+// the 128-row kernels always: 384 heads of 32 x 32 7.2 us against 10.9, 1536 of 197 x 197 48.5 against 74.
+bool fwd_short_serves(int variant, int B, int Hq, int L, int Lk, int d, int causal)
+{
+    if (d != 64 || Lk > 256 || (int64_t)B * Hq < 128) return false;
+    return variant != 3 || (int64_t)B * Hq * ((L + 31) / 32) > (causal && L == Lk ? 256 : 768);
+}
 
 int fwd_rows_per_block(int variant) { return variant == 2 ? 256 : (variant == 3 ? 32 : 128); }
 

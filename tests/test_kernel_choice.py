@@ -36,9 +36,14 @@ CASES = [
     (1, 32, 8, 509, 7001, 128, True, SPLIT),
     (1, 1, 1, 8192, 8192, 64, True, SPLIT),
     (1, 16, 16, 1024, 1024, 128, True, 3),
-    # all scores in registers
+    # all scores in registers: enough heads, and enough blocks of 32 rows against variant 3
     (16, 8, 8, 197, 197, 64, False, SHORT),
     (15, 8, 8, 197, 197, 64, False, 3),
+    (16, 8, 8, 192, 192, 64, False, 3),
+    (16, 8, 8, 96, 96, 64, True, SHORT),
+    (16, 8, 8, 64, 64, 64, True, 3),
+    (16, 8, 8, 96, 200, 64, True, 3),
+    (48, 8, 8, 32, 32, 64, False, SHORT),
     (128, 12, 12, 256, 256, 64, False, SHORT),
     (128, 12, 12, 257, 257, 64, False, 1),
     (128, 12, 12, 256, 256, 128, False, 1),
