@@ -661,29 +661,22 @@ int launch_mode(const FwdParams &p_in, int idx_mode, hipStream_t st)
     const unsigned sh = PH == 1 || PH >= 3 ? 0u : (unsigned)(WAVES * RB * (p.top < 32 ? 32 : 64) * 32 * sizeof(uint32_t));
     if constexpr (PH == 3) { // row maxima: no index map
         hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_MAD24, PH>), grid, block, sh, st, p);
-        return (int)hipGetLastError();
-    }
-    if (idx_mode == IDX_DEVICE) { // the scheme is known on the device only
+    } else if (idx_mode == IDX_DEVICE) { // the scheme is known on the device only
         hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_DEVICE, PH>), grid, block, sh, st, p);
-        return (int)hipGetLastError();
-    }
-    if constexpr (RB == 1 && KT == 2 && PH == 0) {
-        if (idx_mode == IDX_KGROUP) { // groups over the key axis: single-launch kernel only
-            hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_KGROUP, PH>), grid, block, sh, st, p);
-            return (int)hipGetLastError();
-        }
-    }
-    if (idx_mode == IDX_KGROUP) return (int)hipErrorInvalidValue;
-    if (idx_mode == IDX_MAD24 || idx_mode == IDX_TOP24) // TOP24 is MAD24 with the shift at 24: same code here
+    } else if (idx_mode == IDX_KGROUP) { // groups over the key axis: single-launch kernel only
+        if constexpr (RB == 1 && KT == 2 && PH == 0) hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_KGROUP, PH>), grid, block, sh, st, p);
+        else return (int)hipErrorInvalidValue;
+    } else if (idx_mode == IDX_MAD24 || idx_mode == IDX_TOP24) { // TOP24 is MAD24 with the shift at 24: same code here
         hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_MAD24, PH>), grid, block, sh, st, p);
-    else if (idx_mode == IDX_MULHI24)
+    } else if (idx_mode == IDX_MULHI24) {
         hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_MULHI24, PH>), grid, block, sh, st, p);
-    else if (idx_mode == IDX_FP32)
+    } else if (idx_mode == IDX_FP32) {
         hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_FP32, PH>), grid, block, sh, st, p);
-    else if (idx_mode == IDX_ROW64)
+    } else if (idx_mode == IDX_ROW64) {
         hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_ROW64, PH>), grid, block, sh, st, p);
-    else
+    } else {
         hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_FP64, PH>), grid, block, sh, st, p);
+    }
     return (int)hipGetLastError();
 }
 

@@ -24,7 +24,7 @@ namespace {
 constexpr int D = 64;
 constexpr int MAX_WAVES = 4; // 12 waves fit a compute unit: three workgroups of four, but only one of seven
 constexpr int KB = D / 32, CB = D / 32;
-constexpr int CPR = D / 16;   // 16-byte chunks per key row
+[[maybe_unused]] constexpr int CPR = D / 16; // 16-byte chunks per key row
 constexpr int RPB = 1024 / D; // key rows per 1 KiB block
 
 // NS: 32-key sub-tiles held (Lk <= 32 NS)
@@ -37,7 +37,7 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
     extern __shared__ __attribute__((aligned(16))) uint32_t PT_all[]; // a wave's probability table [idx][row], 32 x 32 words; then its output rows
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 31, h = lane >> 5;
-    const int n_waves = __builtin_amdgcn_readfirstlane((int)blockDim.x >> 6);
+    [[maybe_unused]] const int n_waves = __builtin_amdgcn_readfirstlane((int)blockDim.x >> 6);
     const WorkItem wi = fwd_work_item(p, (int)blockIdx.x);
     if (!wi.valid) return; // padding of the XCD-aware grid (uniform for the whole workgroup)
     const int b = wi.b, hq = wi.hq, kvh = wi.kvh, bh = b * p.Hq + hq;
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
     }
 
     // ---- requantize (Sec. 3.2); the wave's 32 rows of 64 bytes meet in its LDS part, so that stores are 16 bytes a lane.
-    // Words of a row are rotated by half the row number, which spreads the rows over the banks.
+    // Bits 2 and 3 of a word's number are XORed with bits 2 and 3 of the row's, which spreads the rows over the banks.
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
 #pragma unroll

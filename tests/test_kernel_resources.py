@@ -77,3 +77,8 @@ def test_sweep_c_at_head_dimension_64_runs_three_waves(kernels):
 
 def test_derivation_kernels_use_no_scratch(kernels):
     assert all(k[".private_segment_fixed_size"] == 0 for k in pick(kernels, r"derive_").values())
+
+
+def test_row_maxima_alone_have_no_index_map(kernels):
+    """Sweep A over a range of the keys: one kernel for each head dimension and mask."""
+    assert len(pick(kernels, r"fwd_kernelILi\d+ELi2ELi2ELb[01]ELi\d+ELi3E")) == 4
