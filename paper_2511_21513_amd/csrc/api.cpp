@@ -550,15 +550,16 @@ Choice choose_kernels(const intattn_ctx *ctx, const intattn_args *a, const RunMo
     Choice ch = {fwd_choose_variant(ctx->variant, a->B, a->Hq, a->L, Lk, a->d, a->causal), false, {0, 0}};
     if (ch.variant == 5 && ctx->lut_bits > 5) ch.variant = 4; // the pipelined sweep C holds 32-entry tables; same tiling otherwise
     const bool automatic = ctx->variant == 0 || ctx->variant == 9 || ctx->variant == 10;
-    // Groups (scale modes 2 and 3): up to 256 workgroups of 128 rows, and up to 512 with key groups, the keys split over
-    // the waves of a workgroup win (1024 tokens, 32 / 8 heads, d 128: 64 against 112 us with key groups, 50 against 55
-    // without; with key groups 2048 tokens, 32 / 8 heads, d 128: 170 against 203, 1500 tokens, 32 heads, d 64: 80 against
-    // 142), past that the 128-row kernel does (without key groups, 2 x 1024 tokens: 56 against 88; with them, 2 x 2048
-    // tokens, 32 heads, d 128: 289 against 327).  Key groups run in the single-launch kernels only.
+    // Groups (scale modes 2 and 3): the keys split over the waves of a workgroup win up to 256 workgroups of 128 rows, up to
+    // 512 with key groups and under the mask at d = 64 (1024 tokens, 32 / 8 heads, d 128: 64 against 112 us with key groups,
+    // 49 against 54 without; with key groups 2048 tokens, 32 / 8 heads, d 128: 170 against 203; without, 32 heads of 1500
+    // tokens, d 64: 47 against 60, of 2048: 65 against 71).  Past that the 128-row kernel does (with key groups, 2 x 2048
+    // tokens, 32 heads, d 128: 289 against 327; without, d 64, 40 / 8 heads of 2048 tokens: 76 against 78, and without a
+    // mask 3 x 16 / 8 heads of 1030: 57 against 61).  Key groups run in the single-launch kernels only.
     if (a->scale_mode >= 2) {
         const int64_t wgs = (int64_t)a->B * a->Hq * ((a->L + 127) / 128);
         if (automatic && a->scale_mode == 3) ch.variant = wgs <= 512 ? 3 : 1;
-        else if (automatic && ch.variant == 3 && wgs > 256) ch.variant = 1;
+        else if (automatic && ch.variant == 3 && wgs > (a->causal && a->d == 64 ? 512 : 256)) ch.variant = 1;
         else if (a->scale_mode == 3 && ch.variant != 3) ch.variant = 1;
     }
     // Few query rows against many keys: the split-key kernels (all query heads of a KV head, times

@@ -33,9 +33,13 @@ namespace {
 constexpr int WAVES = 4;
 constexpr int NT = WAVES * 64;
 
+// Waves a SIMD (and workgroups a compute unit): at d = 64 four, i.e. 128 registers (six spill under the mask).  Row groups,
+// which hold constants per lane, spill 45 then, and run with three (32 heads of 1500 tokens: 51.8 -> 46.7 us; 512 tokens:
+// 20.2 -> 17.5); key groups hold yet more and run with two.
+constexpr int splitk_waves(int d, int mode) { return d != 64 || mode == IDX_KGROUP ? 2 : (mode == IDX_ROW64 ? 3 : 4); }
+
 template <int D, bool CAUSAL, int MODE>
-// (key groups at d = 64: with 128 registers they spill)
-__global__ __launch_bounds__(NT, D == 64 && MODE != IDX_KGROUP ? 4 : 2) void fwd_splitk_kernel(const FwdParams p)
+__global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(const FwdParams p)
 {
     constexpr int KB = D / 32;  // 32-wide blocks of the head dimension
     constexpr int CB = D / 32;  // 32-wide blocks of output channels
@@ -407,7 +411,7 @@ int launch_mode(const FwdParams &p_in, int idx_mode, hipStream_t st)
 {
     FwdParams p = p_in;
     const int64_t n_wg = fwd_map_work(p);
-    p.map.fold = fold_slots(n_wg, CAUSAL, D == 64 && idx_mode != IDX_KGROUP ? 4 : 2);
+    p.map.fold = fold_slots(n_wg, CAUSAL, splitk_waves(D, idx_mode));
     const dim3 grid((unsigned)n_wg), block(NT);
     const unsigned sh = (unsigned)((p.top < 32 ? 32 : 64) * 32 * sizeof(uint32_t)); // the per-row probability table
     if (idx_mode == IDX_DEVICE) {

@@ -65,6 +65,8 @@ def test_forms_that_a_rule_does_not_take(ia):
     chunk, short = (1, 32, 8, 509, 7001, 128, True), (128, 12, 12, 197, 197, 64, False)
     assert choice(ia, *chunk, scale_mode=1, dynamic=True)[0] == SPLIT
     assert choice(ia, *chunk, scale_mode=2, dynamic=True, q_block=64)[0] == SPLIT
+    for L, causal, want in ((1500, True, 3), (2048, True, 3), (2049, True, 1), (1024, False, 3), (1025, False, 1)):
+        assert choice(ia, 1, 32, 32, L, L, 64, causal, scale_mode=2, dynamic=True, q_block=1)[0] == want, (L, causal)
     assert choice(ia, *chunk, scale_mode=3, dynamic=True, q_block=64, k_block=64)[0] == 3
     assert choice(ia, *short, scale_mode=1)[0] == SHORT
     assert choice(ia, *short, dynamic=True)[0] == 1  # device-resident scales

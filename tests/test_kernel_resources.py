@@ -82,3 +82,8 @@ def test_derivation_kernels_use_no_scratch(kernels):
 def test_row_maxima_alone_have_no_index_map(kernels):
     """Sweep A over a range of the keys: one kernel for each head dimension and mask."""
     assert len(pick(kernels, r"fwd_kernelILi\d+ELi2ELi2ELb[01]ELi\d+ELi3E")) == 4
+
+
+def test_kernels_with_the_keys_split_over_waves_spill_little(kernels):
+    """Row groups and host scales (key groups at d = 128 are at the limit of 256 registers)."""
+    assert all(k[".vgpr_spill_count"] <= 8 for k in pick(kernels, r"fwd_splitk_kernelILi\d+ELb[01]ELi[0-6]E").values())
