@@ -33,7 +33,7 @@ namespace {
 constexpr int WAVES = 4;
 constexpr int NT = WAVES * 64;
 
-// Waves a SIMD (and workgroups a compute unit): at d = 64 four, i.e. 128 registers (six spill under the mask).  Row groups,
+// Waves a SIMD (and workgroups a compute unit): at d = 64 four, i.e. 128 registers (eight spill under the mask).  Row groups,
 // which hold constants per lane, spill 45 then, and run with three (32 heads of 1500 tokens: 51.8 -> 46.7 us; 512 tokens:
 // 20.2 -> 17.5); key groups hold yet more and run with two.
 constexpr int splitk_waves(int d, int mode) { return d != 64 || mode == IDX_KGROUP ? 2 : (mode == IDX_ROW64 ? 3 : 4); }
@@ -59,11 +59,17 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
     extern __shared__ uint32_t PT[]; // [idx][row], NIDX * 32 words
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 31, h = lane >> 5;
+    HeadParams hp = p.hp0;
+    // asked for with the rest of the work item's parameters, not with vector loads through a selected pointer, whose wait is 0.1
+    // to 0.2 us of a small launch
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+s"(hp.c_int), "+s"(hp.idx_mul), "+s"(hp.idx_add), "+s"(hp.idx_shift), "+s"(hp.rq_mult), "+s"(hp.rq_shift), "+s"(hp.pad[0]));
+#endif
     const WorkItem wi = fwd_work_item(p, (int)blockIdx.x);
     if (!wi.valid) return; // padding of the XCD-aware grid (uniform for the whole workgroup)
     const int b = wi.b, hq = wi.hq, kvh = wi.kvh, qt = wi.qt + p.row_lo / 32;
     const int bh = b * p.Hq + hq;
-    const HeadParams hp = p.hp_table ? p.hp_table[hq] : p.hp0;
+    if (p.hp_table) hp = p.hp_table[hq];
     if (p.one_scheme && hp.pad[0] != MODE) return; // served by the other launch
     const int L = p.Lk;
     const int rlo = p.row_lo, rhi = p.row_lo + p.L, LQ = p.L;

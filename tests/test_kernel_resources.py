@@ -86,4 +86,4 @@ def test_row_maxima_alone_have_no_index_map(kernels):
 
 def test_kernels_with_the_keys_split_over_waves_spill_little(kernels):
     """Row groups and host scales (key groups at d = 128 are at the limit of 256 registers)."""
-    assert all(k[".vgpr_spill_count"] <= 8 for k in pick(kernels, r"fwd_splitk_kernelILi\d+ELb[01]ELi[0-6]E").values())
+    assert all(k[".vgpr_spill_count"] <= 10 for k in pick(kernels, r"fwd_splitk_kernelILi\d+ELb[01]ELi[0-6]E").values())
