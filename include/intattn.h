@@ -166,11 +166,12 @@ INTATTN_API int intattn_forward(intattn_ctx *ctx, const intattn_args *args, void
 INTATTN_API int intattn_reserve(intattn_ctx *ctx, const intattn_args *args, int32_t dynamic);
 
 /* intattn_forward for callers that cannot allocate device memory (code under HIP graph capture, tight
- * serving loops, harnesses that forbid hipMalloc): same arguments (host scales), same kernels (but for
- * split keys, which it never uses), same bytes out, but the workspace -- row maxima and row sums between the launches, V column sums, the
- * partial results of the split-key kernels -- and the per-head parameter table live in a static
- * device array of INTATTN_NOALLOC_SCRATCH_BYTES that the library's image holds on every GPU it runs
- * on.  Calls no hipMalloc / hipFree.  A problem that needs more workspace than the array holds (8
+ * serving loops, harnesses that forbid hipMalloc): same arguments (host scales), same bytes out.  Same
+ * kernels, except that tiled launches never split their keys over workgroups and that the split-key
+ * path takes its four launches.  The workspace -- row maxima and row sums between the launches, V
+ * column sums, the partial results of the split-key path -- and the per-head parameter table live in a
+ * static device array of INTATTN_NOALLOC_SCRATCH_BYTES that the library's image holds on every GPU it
+ * runs on.  Calls no hipMalloc / hipFree.  A problem that needs more workspace than the array holds (8
  * bytes per query row of every (batch, head) plus 4 d bytes per 128 keys of every (batch, KV head),
  * or more than 512 query heads with per-head scales) is rejected with INTATTN_ERR_UNSUPPORTED and a
  * message naming both sizes.  The array is shared by every context on the GPU and keeps the last
@@ -226,8 +227,8 @@ typedef struct {
     const int32_t *logits;   /* DEVICE [rows, cols]                                           */
     uint8_t *prob;           /* DEVICE [rows, cols]; must not alias logits                    */
     int64_t logits_stride;   /* BYTES between rows, >= 4 * cols, multiple of 4                */
-    int64_t prob_stride;     /* BYTES between rows, >= cols.  Rows that all start 16-byte
-                                (logits) and 4-byte (prob) aligned take the wide accesses     */
+    int64_t prob_stride;     /* BYTES between rows, >= cols.  Any; without mask, 4 | cols and
+                                all rows of prob 4-byte aligned take the fastest form         */
     int32_t causal;          /* 0, or 1: the rows are stacked [rows_per_matrix, cols] matrices
                                 with the attention mask: row r of a matrix sees columns
                                 j <= r + cols - rows_per_matrix; hidden columns get 0          */

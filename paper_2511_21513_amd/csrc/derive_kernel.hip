@@ -7,7 +7,8 @@
 //   24-bit factors where it exists (nearly every threshold up to 60000, which covers what scales of activations
 //   give), with the cheaper multiply-add whose top byte is the index for sweep C of the heads that have it; else
 //   the fp64 map.  (With the top-byte and fp64 maps alone, thresholds above ten to twenty thousand, i.e. most
-//   layers, ran both sweeps on fp64 conversions: a layer of 2 x 2048 tokens, 32 / 8 heads, d 128: 184 us, now 180.)
+//   layers, ran both sweeps on fp64 conversions: a layer of 2 x 2048 tokens, 32 / 8 heads, d 128, 187.7 us; with this search,
+//   whose kernel takes 8.0 instead of 18.8 us, 171.2.)
 // The arithmetic is the host's, operation for operation, in IEEE double: products, quotients,
 // floor, frexp and the fma are exactly rounded on the GPU as on the CPU, and sqrt(d) comes from the
 // host.  One wave per query head, one check point of the index map per lane.

@@ -146,9 +146,13 @@ bool fwd_variant_known(int variant) { return variant == 0 || (variant >= 1 && va
 // times the rounds of 256 compute units, with two rounds as the least (a unit with a single workgroup is bound by latency);
 // sweep C also writes and reads the partial accumulators of each range; 24 us for five launches.  The single launches are
 // bound by their longest chain of tiles or, once the chip is full, by a cost per 32 x 32 block (variant 3) or by rounds of
-// 380 workgroups (variant 1).  Checked on 111 shapes from 1 x 1 x 256 x 1024 to 1 x 32 x 2048 x 16384: with the margins below
-// the choice is the faster one or within 5 %.  (509 x 7001, 32 and 8 heads, d 128: 0.247 -> 0.125 ms; 64 x 16384, 8 heads,
-// d 128: 0.229 -> 0.068; but 0.022 -> 0.049 at 1024 x 1024.)
+// 380 workgroups (variant 1).  It is made to rank the two and errs where a launch is a little over a whole number of rounds
+// (509 x 7001, 32 / 8 heads, d 128: 544 workgroups of variant 3, two rounds of 512; it says 161 us, measured 247), for the
+// single launch then, as the margins below do.  KV heads enter through the room for column sums only: 32 / 32 and 32 / 8 heads
+// measure within 6 % of each other (one pair of 25: 11 %).  Timed on 286 shapes of 1 to 128 heads, 40
+// to 8192 rows and 600 to 16384 keys: the 105 that it splits take 0.23 to 0.94 of the time of the better of variants 1 and 3
+// (509 x 7001: 247 -> 120 us; 128 x 12000, 8 heads, d 64: 128 -> 47; 3000 square, 12 heads, d 128: 94.9 -> 88.8); what else a
+// split would serve was not timed.  Small problems lose by it (1024 square, 16 heads, d 128: 22 us unsplit, 49 split).
 KeySplit fwd_key_split(int variant, int B, int Hq, int Hkv, int L, int Lk, int d, int causal)
 {
     const int row_lo = causal ? Lk - L : 0, tiles = (Lk + 127) / 128;
