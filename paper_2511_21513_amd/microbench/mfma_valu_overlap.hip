@@ -146,6 +146,7 @@ int main()
     if (run<4, 48>("MFMA only", 512, d_out)) return 1;
     if (run<5, 48>("vector only", 256, d_out)) return 1;
     if (run<5, 48>("vector only", 512, d_out)) return 1;
+    if (run<5, 96>("vector only", 256, d_out)) return 1;
     if (run<5, 96>("vector only", 512, d_out)) return 1;
     if (run<6, 48>("split: MFMA wave + vector wave", 512, d_out)) return 1;
     if (run<6, 96>("split: MFMA wave + vector wave", 512, d_out)) return 1;
