@@ -69,7 +69,7 @@ struct intattn_ctx {
     // microseconds per head; serving loops pass the same scales again and again)
     std::vector<uint32_t> dv_key;
     std::vector<HeadParams> dv_hp;
-    std::vector<HeadParams> dv_hp_c;
+    bool dv_fma = false;
     std::vector<float> dv_alpha, dv_svso;
     int dv_mode = 0;
     std::vector<HeadParams> hp_host;  // what d_hp currently holds
@@ -346,9 +346,45 @@ bool find_fp64(uint32_t c_int, uint32_t top, HeadParams *hp)
     return true;
 }
 
+// The factor of the IDX_FMA map (ScoreIndex, kernel_common.h): a float r near top / c_int for which x r, x = c_int - Delta',
+// rounded to a float and then to the nearest integer (ties to even) is top - round(Delta' top / c_int) for every integer x in
+// [0, c_int].  Ties of top x / c_int must go down, so r lies below the quotient: one unit in the last place serves 99 % of
+// thresholds up to 65 000, two nearly all others; some r exists for every threshold up to about 130 000 (b <= 5) and for
+// 95 % of those up to 400 000.  The accumulators that carry x hold thresholds below 2^22.
+bool find_fma(uint32_t c_int, uint32_t top, HeadParams *hp)
+{
+    if (c_int >= (1u << 22)) return false;
+    const std::vector<uint32_t> pts = check_points(c_int, top);
+    const float quotient = (float)((double)top / (double)c_int);
+    const int ulps[6] = {1, 2, 0, 3, 4, -1};
+    for (int u : ulps) {
+        uint32_t bits;
+        std::memcpy(&bits, &quotient, 4);
+        bits -= (uint32_t)u;
+        float r;
+        std::memcpy(&r, &bits, 4);
+        bool ok = true;
+        for (uint32_t t : pts) {
+            const uint32_t acc = 0x4b000000u + c_int - t;
+            float f;
+            std::memcpy(&f, &acc, 4);
+            const float y = std::nearbyintf(std::fmaf(f, r, -8388608.0f * r));
+            if ((uint32_t)(int)y != top - true_index(t, c_int, top)) {
+                ok = false;
+                break;
+            }
+        }
+        if (ok) {
+            hp->fma_r = bits;
+            return true;
+        }
+    }
+    return false;
+}
+
 struct Derived {
     std::vector<HeadParams> hp;
-    std::vector<HeadParams> hp_c; // per head, for sweep C alone: top-byte constants where they exist (pad[0] names the scheme); empty: as hp
+    bool fma = false; // every head has a factor of the IDX_FMA map
     std::vector<float> alpha, svso;
     int idx_mode = IDX_MAD24;
 };
@@ -412,7 +448,7 @@ int derive_all(intattn_ctx *ctx, const intattn_args *a, Derived *out)
     bool all_ok[5] = {true, true, true, true, true};
     std::vector<HeadParams> cand[5];
     for (auto &c : cand) c.assign((size_t)n, HeadParams{});
-    std::vector<char> top_ok((size_t)n, 0);
+    out->fma = true;
     for (int h = 0; h < n; ++h) {
         const int kv = a->scale_mode ? h / g : 0;
         const float sq = a->scale_q[h], sk = a->scale_k[kv], sv = a->scale_v[kv];
@@ -423,34 +459,18 @@ int derive_all(intattn_ctx *ctx, const intattn_args *a, Derived *out)
         hp.c_int = (int32_t)derive_c_int(ctx->clip, sq, sk, a->d);
         if (!derive_requant(sv, so, &hp.rq_mult, &hp.rq_shift))
             return fail(ctx, INTATTN_ERR_INVALID_ARG, "s_V / (255 s_O) is outside the representable range");
-        for (int m = 0; m < 5; ++m) {
+        out->fma = out->fma && find_fma((uint32_t)hp.c_int, top, &hp);
+        for (int m = out->fma ? 0 : 4; m < 5; ++m) {
             cand[m][(size_t)h] = hp;
-            if (m == 0) { // the top-byte scheme: per head, for the mixed table of sweep C
-                top_ok[(size_t)h] = finders[0]((uint32_t)hp.c_int, top, &cand[0][(size_t)h]);
-                if (!top_ok[(size_t)h]) all_ok[0] = false;
-            } else if (all_ok[m] && !finders[m]((uint32_t)hp.c_int, top, &cand[m][(size_t)h])) {
-                all_ok[m] = false;
-            }
+            if (all_ok[m] && !finders[m]((uint32_t)hp.c_int, top, &cand[m][(size_t)h])) all_ok[m] = false;
         }
         out->alpha[(size_t)h] = (float)(((double)sq * (double)sk) / std::sqrt((double)a->d));
         out->svso[(size_t)h] = (float)((double)sv / (double)so);
     }
-    for (int m = 0; m < 5; ++m) {
+    for (int m = out->fma ? 0 : 4; m < 5; ++m) { // without the factor somewhere every kernel takes the fp64 map
         if (all_ok[m]) {
             out->idx_mode = modes[m];
             out->hp = cand[m];
-            out->hp_c.clear();
-            // Some heads only lack top-byte constants (thresholds below 62 or of many thousands): sweep C, where that
-            // scheme saves a vector instruction per score, then takes each head's own scheme from a table of its own.
-            int n_top = 0;
-            for (int h = 0; h < n; ++h) n_top += top_ok[(size_t)h] ? 1 : 0;
-            if (modes[m] == IDX_MULHI24 && n > 1 && n_top > 0) {
-                out->hp_c = cand[m];
-                for (int h = 0; h < n; ++h) {
-                    if (top_ok[(size_t)h]) out->hp_c[(size_t)h] = cand[0][(size_t)h];
-                    out->hp_c[(size_t)h].pad[0] = top_ok[(size_t)h] ? IDX_TOP24 : IDX_MULHI24;
-                }
-            }
             return INTATTN_OK;
         }
     }
@@ -616,7 +636,7 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
         if (a->scale_out) add(a->scale_out, n_q);
         if (!ctx->dv_key.empty() && key == ctx->dv_key) {
             dv.hp = ctx->dv_hp;
-            dv.hp_c = ctx->dv_hp_c;
+            dv.fma = ctx->dv_fma;
             dv.alpha = ctx->dv_alpha;
             dv.svso = ctx->dv_svso;
             dv.idx_mode = ctx->dv_mode;
@@ -625,7 +645,7 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
             if (rc) return rc;
             ctx->dv_key = key;
             ctx->dv_hp = dv.hp;
-            ctx->dv_hp_c = dv.hp_c;
+            ctx->dv_fma = dv.fma;
             ctx->dv_alpha = dv.alpha;
             ctx->dv_svso = dv.svso;
             ctx->dv_mode = dv.idx_mode;
@@ -696,6 +716,7 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
     p.causal = a->causal;
     p.group = a->Hq / a->Hkv;
     p.top = (1 << ctx->lut_bits) - 1;
+    p.fma = dv.fma ? 1 : 0;
     Choice ch = choose_kernels(ctx, a, rm, dv.idx_mode, !rm.reserve);
     if (ch.ks.c > 0) {
         bool room = true;
@@ -730,7 +751,7 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
 
     if (dynamic) {
         if (rm.no_alloc) return fail(ctx, INTATTN_ERR_UNSUPPORTED, "intattn_forward_noalloc takes host scales");
-        rc = get_tables(2 * a->Hq); // the second half: sweep C's own table
+        rc = get_tables(a->Hq);
         if (rc) return rc;
         if (a->Hq > ctx->status_cap) {
             int32_t *stw = nullptr;
@@ -794,7 +815,6 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
                     if (e != 0) return hip_fail(ctx, (hipError_t)e, "launch(derive head parameters)");
                 }
                 p.hp_table = d_hp;
-                p.hp_table_c = d_hp + a->Hq;
             }
         }
     } else if (decode) {
@@ -819,18 +839,10 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
             p.sv_over_so0 = dv.svso[0];
         }
     } else {
-        // (twice the heads: a second table for sweep C may follow the first)
-        rc = get_tables(rm.no_alloc ? a->Hq : 2 * a->Hq);
+        rc = get_tables(a->Hq);
         if (rc) return rc;
         if (!rm.reserve) {
-            if (!dv.hp_c.empty() && !rm.no_alloc && !comparator) {
-                std::vector<HeadParams> both(dv.hp);
-                both.insert(both.end(), dv.hp_c.begin(), dv.hp_c.end());
-                rc = put_table(both);
-                p.hp_table_c = d_hp + a->Hq;
-            } else {
-                rc = put_table(dv.hp);
-            }
+            rc = put_table(dv.hp);
             if (rc) return rc;
             if (comparator && !(ctx->alpha_host == dv.alpha && ctx->svso_host == dv.svso)) {
                 const size_t n = (size_t)a->Hq;

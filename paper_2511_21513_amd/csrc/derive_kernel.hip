@@ -3,18 +3,16 @@
 // reading anything back:
 //   c_int = round(c * sqrt(d) / (s_Q s_K))                    (Sec. 3.1, Eq. clipping_thr)
 //   (M, sh) with M * 2^-sh ~ s_V / (255 s_O), M in [2^30, 2^31)   (output requantization)
-//   constants of an exact index map idx = round(x * top / c_int)  (Sec. 3.1, index map): the multiply-high of
-//   24-bit factors where it exists (nearly every threshold up to 60000, which covers what scales of activations
-//   give), with the cheaper multiply-add whose top byte is the index for sweep C of the heads that have it; else
-//   the fp64 map.  (With the top-byte and fp64 maps alone, thresholds above ten to twenty thousand, i.e. most
-//   layers, ran both sweeps on fp64 conversions: a layer of 2 x 2048 tokens, 32 / 8 heads, d 128, 187.7 us; with this search,
-//   whose kernel takes 8.0 instead of 18.8 us, 171.2.)
+//   constants of an exact index map idx = round(x * top / c_int)  (Sec. 3.1, index map): the factor of the fma map
+//   (ScoreIndex) for the tiled kernels, and, for those that do not take it, the multiply-high of 24-bit factors where it
+//   exists (nearly every threshold up to 60000); else the fp64 map for all.
 // The arithmetic is the host's, operation for operation, in IEEE double: products, quotients,
 // floor, frexp and the fma are exactly rounded on the GPU as on the CPU, and sqrt(d) comes from the
 // host.  One wave per query head, one check point of the index map per lane.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "kernel_common.h"
 #include "params.h"
 
 namespace intattn {
@@ -35,7 +33,7 @@ __device__ __forceinline__ uint32_t exact_index(double x, double c_int, double t
 __device__ __forceinline__ bool derive_scalars(float sq, float sk, float sv, float so, double clip, double sqrt_d, HeadParams &hp)
 {
     hp.pad[0] = IDX_FP64;
-    hp.pad[1] = 0;
+    hp.fma_r = 0;
     bool ok = good_scale(sq) && good_scale(sk) && good_scale(sv) && good_scale(so);
     double c = 1.0;
     if (ok) {
@@ -85,8 +83,7 @@ __device__ __forceinline__ uint64_t set_fp64_factor(HeadParams &hp, uint32_t top
 // whose t_k it reads from lane k - 1.  Bound by the latency of one wave: quotients are IEEE double divisions (exact under
 // floor and ceil, see below) and the loops hold 32-bit integer operations only.  (With 64-bit integer divisions and
 // products, and the steps in LDS: 18.8 us for this kernel, now 8.0.)
-// `hp`: the parameters for every kernel (multiply-high scheme, or fp64); `hp_c`: for sweep C (top byte where it exists).
-__device__ __forceinline__ bool derive_head(const DeriveParams &dp, int h, int lane, HeadParams &hp, HeadParams &hp_c)
+__device__ __forceinline__ bool derive_head(const DeriveParams &dp, int h, int lane, HeadParams &hp)
 {
     const int si = dp.per_head ? h : 0;
     const int kv = dp.per_head ? h / dp.group : 0;
@@ -104,36 +101,23 @@ __device__ __forceinline__ bool derive_head(const DeriveParams &dp, int h, int l
 #pragma unroll
     for (int q = 0; q < 3; ++q) want[q] = exact_index((double)at[q], cd, topd);
 
-    uint32_t top_mul = 0, top_add = 0;
-    bool found_top = false, found = false;
-    if (ok && c_int < (1u << 23)) { // wave-uniform
-        // (x * mul + add) >> 24 with a 23-bit multiplier (the host's find_top24, candidate for candidate): the step to
-        // index k, between x = t - 1 and x = t, confines add to k 2^24 - t mul <= add < k 2^24 - (t - 1) mul; the first
-        // multiplier around top 2^24 / c_int whose intervals intersect is taken.  Sums below 2^31: c_int mul is at most
-        // top 2^24 + 40 c_int.
-        const double m0 = __builtin_floor(topd * 16777216.0 / cd);
-        for (int round = 0; round < 2 && !found_top; ++round) {
-            const int cand = lane + 64 * round, dm = cand >> 1;
-            const double muld = (cand & 1) ? m0 - dm : m0 + 1.0 + dm;
-            const bool valid = cand < 80 && muld >= 1.0 && muld < 8388608.0;
-            const int mul = valid ? (int)muld : 0;
-            int lo = 0, hi = 0x7fffffff - (int)c_int * mul;
-            for (int k = 1; k <= (int)top; ++k) {
-                const int base = (k << 24) - __builtin_amdgcn_readlane(t, k - 1) * mul; // as a 32-bit product
-                lo = max(lo, base);
-                hi = min(hi, base + mul - 1);
-            }
-            hi = min(hi, (int)(((top + 1u) << 24) - 1u) - (int)c_int * mul);
-            const unsigned long long good = __ballot(valid && lo <= hi);
-            if (good != 0ull) {
-                const int src = __builtin_ctzll(good); // the first candidate in the host's order
-                const int mul_s = __shfl(mul, src), lo_s = __shfl(lo, src), hi_s = __shfl(hi, src);
-                found_top = true;
-                top_mul = (uint32_t)(-mul_s);
-                top_add = (uint32_t)(lo_s + (hi_s - lo_s) / 2);
-            }
+    // the factor of the IDX_FMA map: the host's candidates with the arithmetic of the kernels
+    if (ok && c_int < (1u << 22)) {
+        const uint32_t quotient = __float_as_uint((float)(topd / cd));
+#pragma unroll 1
+        for (int u = 0; u < 6 && hp.fma_r == 0; ++u) {
+            hp.fma_r = quotient - (uint32_t)(u == 0 ? 1 : u == 1 ? 2 : u == 2 ? 0 : u == 3 ? 3 : u == 4 ? 4 : -1);
+            ScoreIndex<IDX_FMA> si;
+            si.init(hp, 0, top);
+            bool match = true;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) match = match && si.index(si.start() - at[q]) == top - want[q];
+            if (!__all(match)) hp.fma_r = 0;
         }
+    }
 
+    bool found = false;
+    if (ok && hp.fma_r != 0) { // wave-uniform
         // (((x << pre) + off) * mul) >> 32 with factors below 2^23: a lane per shift and per one of the two multipliers
         // around top 2^32 / (c_int << pre).  The step to index k confines off to
         // ceil(k 2^32 / mul) - (t << pre) <= off < ceil(k 2^32 / mul) - ((t - 1) << pre); the quotients are kept as
@@ -189,13 +173,6 @@ __device__ __forceinline__ bool derive_head(const DeriveParams &dp, int h, int l
         hp.pad[0] = IDX_FP64;
     }
     if (!ok) hp.rq_mult = 0; // (the fp64 check cannot fail; kept as the last line of defence)
-    hp_c = hp;
-    if (found && found_top) { // (both were found only for usable scales)
-        hp_c.pad[0] = IDX_TOP24;
-        hp_c.idx_mul = top_mul;
-        hp_c.idx_add = top_add;
-        hp_c.idx_shift = 24;
-    }
     return ok;
 }
 
@@ -210,21 +187,19 @@ __device__ __forceinline__ void unify_scheme(const DeriveParams &dp, int h)
         set_fp64_factor(hp, (uint32_t)dp.top);
         dp.hp_table[h] = hp;
     }
-    dp.hp_table[dp.Hq + h] = hp;
 }
 
-__device__ __forceinline__ void put_head(const DeriveParams &dp, int h, const HeadParams &hp, const HeadParams &hp_c, bool ok)
+__device__ __forceinline__ void put_head(const DeriveParams &dp, int h, const HeadParams &hp, bool ok)
 {
     dp.hp_table[h] = hp;
-    dp.hp_table[dp.Hq + h] = hp_c;
     dp.status[h] = ok ? 0 : 1;
 }
 
 __global__ __launch_bounds__(64) void derive_kernel(const DeriveParams dp)
 {
-    HeadParams hp, hp_c;
-    const bool ok = derive_head(dp, blockIdx.x, threadIdx.x, hp, hp_c);
-    if (threadIdx.x == 0) put_head(dp, blockIdx.x, hp, hp_c, ok);
+    HeadParams hp;
+    const bool ok = derive_head(dp, blockIdx.x, threadIdx.x, hp);
+    if (threadIdx.x == 0) put_head(dp, blockIdx.x, hp, ok);
 }
 
 __global__ __launch_bounds__(64) void unify_schemes_kernel(const DeriveParams dp)
@@ -238,9 +213,9 @@ __global__ __launch_bounds__(64) void unify_schemes_kernel(const DeriveParams dp
 // Per-tensor scales: one wave derives the one parameter set and writes it for every head.
 __global__ __launch_bounds__(64) void derive_one_kernel(const DeriveParams dp)
 {
-    HeadParams hp, hp_c;
-    const bool ok = derive_head(dp, 0, threadIdx.x, hp, hp_c);
-    for (int h = threadIdx.x; h < dp.Hq; h += 64) put_head(dp, h, hp, hp_c, ok);
+    HeadParams hp;
+    const bool ok = derive_head(dp, 0, threadIdx.x, hp);
+    for (int h = threadIdx.x; h < dp.Hq; h += 64) put_head(dp, h, hp, ok);
 }
 
 // Per-head scales of few heads: one workgroup derives all of them, a wave per head, and settles the scheme.
@@ -248,9 +223,9 @@ constexpr int FEW_HEADS = 8;
 __global__ __launch_bounds__(64 * FEW_HEADS) void derive_heads_kernel(const DeriveParams dp)
 {
     const int lane = threadIdx.x & 63, h = threadIdx.x >> 6;
-    HeadParams hp, hp_c;
-    const bool ok = derive_head(dp, h, lane, hp, hp_c);
-    if (lane == 0) put_head(dp, h, hp, hp_c, ok);
+    HeadParams hp;
+    const bool ok = derive_head(dp, h, lane, hp);
+    if (lane == 0) put_head(dp, h, hp, ok);
     if (!__syncthreads_or(hp.pad[0] == IDX_FP64)) return;
     __syncthreads(); // (the table written above is visible)
     for (int h = threadIdx.x; h < dp.Hq; h += blockDim.x) unify_scheme(dp, h);

@@ -180,9 +180,9 @@ KeySplit fwd_key_split(int variant, int B, int Hq, int Hkv, int L, int Lk, int d
     if (24 + t_ab + t_c > worth) return KeySplit{0, 0};
     return ks;
 }
-// Sweep C with a table of its own (top-byte constants where a head has them, which cost it one vector instruction per score
-// less than the multiply-high scheme of the other kernels): the host's comes with the multiply-high scheme for all heads.
-static int sweep_c_mode(const FwdParams &p, int idx_mode) { return p.hp_table_c && idx_mode == IDX_MULHI24 ? IDX_MIX : idx_mode; }
+// The index map of the kernels that take IDX_FMA or IDX_FP64 (and the group and device modes): without a factor for every
+// head the parameters hold the fp64 map.
+static int fma_mode(const FwdParams &p, int idx_mode) { return p.fma ? IDX_FMA : idx_mode; }
 
 // All scores in registers (fwd_short.hip): up to 256 keys at d = 64, from 128 heads on.  Against variant 3, whose chain is a
 // quarter as long, only where more blocks of 32 rows than three for each compute unit are in flight, or, as its waves pad the
@@ -204,6 +204,7 @@ int launch_fwd(const FwdParams &p_in, int d, int idx_mode, int variant, int stag
     const int64_t k_bytes = (int64_t)p.Lk * d; // K of one (batch, KV head) group; V is as large
     p.group_batch = fwd_group_batch(p.B, p.Hkv, 2 * k_bytes); // kernels that stream K and V
     const bool two_launches = variant == 4 || variant == 5;
+    const int mode = fma_mode(p, idx_mode);
     if (variant == VARIANT_SHORT) return stage != 0 ? (int)hipErrorNotSupported : launch_fwd_short(p, d, idx_mode, stream);
     if (variant == VARIANT_KEY_SPLIT) {
         if (stage != 0) return (int)hipErrorNotSupported;
@@ -211,11 +212,9 @@ int launch_fwd(const FwdParams &p_in, int d, int idx_mode, int variant, int stag
         FwdParams pab = p;
         pab.n_qtiles = fwd_row_tiles(p.row_lo, p.L, 256);
         pab.group_batch = fwd_group_batch(p.B, p.Hkv, k_bytes); // streams K only
-        if (e == 0) e = launch_shape<2, 2, 3>(pab, d, idx_mode, st);
-        if (e == 0) e = launch_shape<2, 2, 4>(pab, d, idx_mode, st);
-        FwdParams pc = p;
-        if (p.hp_table_c) pc.hp_table = p.hp_table_c; // as below
-        if (e == 0) e = launch_sweep_c(pc, d, sweep_c_mode(p, idx_mode), st);
+        if (e == 0) e = launch_shape<2, 2, 3>(pab, d, mode, st);
+        if (e == 0) e = launch_shape<2, 2, 4>(pab, d, mode, st);
+        if (e == 0) e = launch_sweep_c(p, d, mode, st);
         return e == 0 ? launch_finish_split(p, d, st) : e;
     }
     if (stage != 0 && !two_launches) return (int)hipErrorNotSupported;
@@ -228,27 +227,25 @@ int launch_fwd(const FwdParams &p_in, int d, int idx_mode, int variant, int stag
         // short key sequences: the single-launch kernels sum V themselves (one launch less)
         FwdParams ps = p;
         ps.ws_colsum = nullptr;
-        if (variant == 2) return launch_shape<2, 2, 0>(ps, d, idx_mode, st);
-        return launch_shape<1, 2, 0>(ps, d, idx_mode, st);
+        if (variant == 2) return launch_shape<2, 2, 0>(ps, d, mode, st);
+        return launch_shape<1, 2, 0>(ps, d, mode, st);
     }
     if (stage != 2) e = launch_colsum(p, d, fwd_rows_per_block(variant), st);
     if (e != 0) return e;
-    if (variant == 2) return launch_shape<2, 2, 0>(p, d, idx_mode, st);
+    if (variant == 2) return launch_shape<2, 2, 0>(p, d, mode, st);
     if (two_launches) {
         // sweeps A+B leave row max and row sum in the workspace for sweep C
         if (stage != 2) {
             FwdParams pab = p;
             pab.n_qtiles = fwd_row_tiles(p.row_lo, p.L, 256); // 64 query rows per wave in the first launch
             pab.group_batch = fwd_group_batch(p.B, p.Hkv, k_bytes); // streams K only
-            e = launch_shape<2, 2, 1>(pab, d, idx_mode, st);
+            e = launch_shape<2, 2, 1>(pab, d, mode, st);
             if (e != 0 || stage == 1) return e;
         }
-        if (variant == 4) return launch_shape<1, 2, 2>(p, d, idx_mode, st);
-        FwdParams pc = p;
-        if (p.hp_table_c) pc.hp_table = p.hp_table_c;
-        return launch_sweep_c(pc, d, sweep_c_mode(p, idx_mode), st);
+        if (variant == 4) return launch_shape<1, 2, 2>(p, d, mode, st);
+        return launch_sweep_c(p, d, mode, st);
     }
-    return launch_shape<1, 2, 0>(p, d, idx_mode, st);
+    return launch_shape<1, 2, 0>(p, d, mode, st);
 }
 
 } // namespace intattn

@@ -30,7 +30,9 @@
 // Within a tile the work is ordered in phases (all fragment reads, all MFMAs, all index
 // arithmetic with every table lookup in flight, then the consumers).  This is the kernel for
 // small problems (all three sweeps in one launch) and for sweeps A+B of large ones; sweep C of
-// large problems has a software-pipelined kernel of its own.
+// large problems has a kernel of its own.  Sweep B takes a tile sub-tile by sub-tile, which leaves room for the start values
+// of the IDX_FMA map at three waves a SIMD, and costs two vector instructions, half an addition and a lookup a score
+// (1 x 8192, 32 / 8 heads, d 128: sweeps A and B 292 -> 262 us; A alone 118).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -94,7 +96,11 @@ __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi,
     const int8_t *Kp = p.k + (int64_t)b * p.ks[0] + (int64_t)kvh * p.ks[1];
     const int8_t *Vp = p.v + (int64_t)b * p.vs[0] + (int64_t)kvh * p.vs[1];
 
-    if (tid < 16) lut_lds[tid] = p.lut[tid];
+    // LUT_hat by place (see ScoreIndex)
+    if (tid < 64) {
+        const int idx = ScoreIndex<M>::place(tid, (int)top);
+        ((uint8_t *)lut_lds)[tid] = idx >= 0 ? (uint8_t)(p.lut[idx / 4] >> (8 * (idx % 4))) : (uint8_t)0;
+    }
     if constexpr (KG) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
@@ -213,6 +219,22 @@ __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi,
         }
         __builtin_amdgcn_sched_barrier(0);
     };
+    auto read_kf = [&](const int8_t *Kb, int st, v4i (&kf)[KB]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+            const int key = 32 * st + n;
+            kf[kb] = *(const v4i *)(Kb + key * D + (((2 * kb + h) ^ swz_k<D>(key)) << 4));
+        }
+    };
+    // the scores of one sub-tile, added to `start`
+    auto qk_sub = [&](const v4i (&kf)[KB], const v16i (&start)[RB], v16i (&s)[RB]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+                s[rb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf[kb], qf[rb][kb], kb == 0 ? start[rb] : s[rb], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
     auto visible = [&](int key, int row) { return key < L && (!CAUSAL || key <= row); };
     // wave-uniform: every key of tile t is visible to every row of this wave (no mask needed)
     auto tile_is_full = [&](int t) { return (t + 1) * BK <= L && (!CAUSAL || (t + 1) * BK - 1 <= qw0); };
@@ -310,12 +332,12 @@ __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi,
         const int lr = (row >= rlo && row < rhi) ? row - rlo : 0;
         return p.row_table[(int64_t)bh * p.n_rowblk + lr / p.q_block];
     };
-    RowIndex<M> ri[RB];
+    ScoreIndex<M> si[RB];
 #pragma unroll
-    for (int rb = 0; rb < RB; ++rb) ri[rb].init(M == IDX_ROW64 ? row_hp(qw0 + 32 * rb + n) : hp, KG ? 0 : mx[rb], top);
+    for (int rb = 0; rb < RB; ++rb) si[rb].init(M == IDX_ROW64 ? row_hp(qw0 + 32 * rb + n) : hp, KG ? 0 : mx[rb], top);
     if constexpr (KG) {
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) ri[rb].shift = (int)top; // bound of the index (see RowIndex)
+        for (int rb = 0; rb < RB; ++rb) si[rb].ri.shift = (int)top; // bound of the index (see RowIndex)
     }
     // Key groups: the index constants of the lane's row for the key block of `key` (Sec. 3.3):
     // c_int^(g) = round(c / alpha^(g)) capped at 2^30, m^(g) = round(M / alpha^(g)), the fp64 index map's
@@ -331,10 +353,10 @@ __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi,
         md = md < 1077936128.0 ? md : 1077936128.0;
         md = md > -4194304.0 ? md : -4194304.0;
         const int c_int = (int)cd;
-        ri[rb].mx = (int)md;
-        ri[rb].bound = ri[rb].mx - c_int;
+        si[rb].ri.mx = (int)md;
+        si[rb].ri.bound = si[rb].ri.mx - c_int;
         const uint64_t bits = (uint64_t)__double_as_longlong((double)top / cd) + 1ull; // the double after top / c_int
-        ri[rb].negr = __longlong_as_double((long long)(bits ^ 0x8000000000000000ull));
+        si[rb].ri.negr = __longlong_as_double((long long)(bits ^ 0x8000000000000000ull));
     };
 
     // ================================================================= sweep B: row sum of E_hat
@@ -357,58 +379,57 @@ __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi,
     };
 
     const uint8_t *lut_b = (const uint8_t *)lut_lds;
+    v16i start[RB]; // what the scores are added to
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) start[rb][i] = si[rb].start();
     uint32_t sum[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) sum[rb] = 0;
 
+    // One tile of sweep B, sub-tile by sub-tile: the scores, their table lookups (in place, all in flight), and, behind the
+    // MFMAs of the next sub-tile, their sum.
     auto tile_b = [&](auto masked_tag, int t, const int8_t *Kb) __attribute__((always_inline)) {
         constexpr bool MASKED = decltype(masked_tag)::value;
-        v16i s[KT][RB];
+        v4i kf[KT][KB];
 #pragma unroll
-        for (int st = 0; st < KT; ++st)
+        for (int st = 0; st < KT; ++st) read_kf(Kb, st, kf[st]);
+        __builtin_amdgcn_sched_barrier(0);
+        v16i s[KT][RB];
+        auto add_up = [&](int st) __attribute__((always_inline)) {
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) s[st][rb][i] = 0;
-        qk_tile(Kb, 0, s);
+                for (int i = 0; i < 16; ++i) sum[rb] += (uint32_t)s[st][rb][i];
+            __builtin_amdgcn_sched_barrier(0);
+        };
 #pragma unroll
         for (int st = 0; st < KT; ++st) {
+            qk_sub(kf[st], start, s[st]);
+            if (st > 0 && !KG) add_up(st - 1);
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
-                if constexpr (KG) {
-                    const int klo = t * BK + 32 * st, row = qw0 + 32 * rb + n;
-                    if (kg_blocks) kg_index(rb, klo);
+                const int klo = t * BK + 32 * st, row = qw0 + 32 * rb + n;
+                if (KG && kg_blocks) kg_index(rb, klo);
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int key = klo + acc_key(i, h);
+                for (int i = 0; i < 16; ++i) {
+                    const int key = klo + acc_key(i, h);
+                    if constexpr (KG) {
                         if (!kg_blocks) kg_index(rb, key);
-                        const uint32_t e = lut_b[ri[rb](min(max(s[st][rb][i], ri[rb].bound), ri[rb].mx))];
+                        const RowIndex<M> &ri = si[rb].ri;
+                        const uint32_t e = lut_b[ri(min(max(s[st][rb][i], ri.bound), ri.mx))];
                         sum[rb] += (!MASKED || visible(key, row)) ? e : 0u;
+                    } else {
+                        // a hidden key takes the table's last entry, which is 0
+                        const int sc = !MASKED || visible(key, row) ? s[st][rb][i] : si[rb].hidden();
+                        s[st][rb][i] = (int)lut_b[si[rb].index(sc)];
                     }
-                } else if (MASKED) {
-                    const int klo = t * BK + 32 * st, row = qw0 + 32 * rb + n;
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        // hidden keys may exceed the row max
-                        const uint32_t e = lut_b[ri[rb](min(max(s[st][rb][i], ri[rb].bound), ri[rb].mx))];
-                        sum[rb] += visible(klo + acc_key(i, h), row) ? e : 0u;
-                    }
-                } else {
-                    // every lookup of the block is issued before the first one is consumed
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) s[st][rb][i] = (int)lut_b[ri[rb](max(s[st][rb][i], ri[rb].bound))];
                 }
             }
-        }
-        if (!MASKED && !KG) {
             __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int st = 0; st < KT; ++st)
-#pragma unroll
-                for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) sum[rb] += (uint32_t)s[st][rb][i];
         }
+        if (!KG) add_up(KT - 1);
     };
 
     if constexpr (PH != 2 && PH != 3) {
@@ -489,7 +510,7 @@ __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi,
         const float inv_2s = __builtin_amdgcn_rcpf((float)(2u * sum[rb]));
         for (int j = 0; j < NIDX / 2; ++j) {
             const int kidx = (NIDX / 2) * h + j;
-            pt[kidx * 32 + n] = (prob_u8(lut_b[kidx], sum[rb], inv_2s) ^ 0x80u) & 0xffu;
+            pt[kidx * 32 + n] = (prob_u8(lut_b[kidx], sum[rb], inv_2s) ^ 0x80u) & 0xffu; // by place, like LUT_hat
         }
         const int row = qw0 + 32 * rb + n;
         if (!KG && p.dbg_row_max && h == 0 && row >= rlo && row < rhi) p.dbg_row_max[(int64_t)bh * LQ + (row - rlo)] = mx[rb];
@@ -516,9 +537,7 @@ __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi,
 #pragma unroll
         for (int st = 0; st < KS; ++st)
 #pragma unroll
-            for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) s[st][rb][i] = 0;
+            for (int rb = 0; rb < RB; ++rb) s[st][rb] = start[rb];
         qk_tile(Kb, st0, s);
 #pragma unroll
         for (int st = 0; st < KS; ++st) {
@@ -528,9 +547,16 @@ __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi,
                 if (kg_blocks) kg_index(rb, t * BK + 32 * (st0 + st));
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    if (KG && !kg_blocks) kg_index(rb, t * BK + 32 * (st0 + st) + acc_key(i, h));
-                    const int sc = (MASKED || KG) ? min(max(s[st][rb][i], ri[rb].bound), ri[rb].mx) : max(s[st][rb][i], ri[rb].bound);
-                    s[st][rb][i] = (int)pt[ri[rb](sc) * 32];
+                    const int key = t * BK + 32 * (st0 + st) + acc_key(i, h);
+                    if constexpr (KG) {
+                        if (!kg_blocks) kg_index(rb, key);
+                        const RowIndex<M> &ri = si[rb].ri;
+                        s[st][rb][i] = (int)pt[ri(min(max(s[st][rb][i], ri.bound), ri.mx)) * 32];
+                        if (MASKED) s[st][rb][i] = visible(key, qw0 + 32 * rb + n) ? s[st][rb][i] : 0x80;
+                    } else { // a hidden key takes the table's last entry, whose probability is 0
+                        const int sc = !MASKED || visible(key, qw0 + 32 * rb + n) ? s[st][rb][i] : si[rb].hidden();
+                        s[st][rb][i] = (int)pt[si[rb].index(sc) * 32];
+                    }
                 }
             }
         }
@@ -543,16 +569,11 @@ __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi,
         for (int st = 0; st < KS; ++st) {
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
-                const int klo = t * BK + 32 * (st0 + st), row = qw0 + 32 * rb + n;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     uint32_t pb4[4];
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int i = 4 * g + r;
-                        pb4[r] = (uint32_t)s[st][rb][i];
-                        if (MASKED) pb4[r] = visible(klo + acc_key(i, h), row) ? pb4[r] : 0x80u;
-                    }
+                    for (int r = 0; r < 4; ++r) pb4[r] = (uint32_t)s[st][rb][4 * g + r];
                     pf[st][rb][g] = (int)(((pb4[1] << 8) | pb4[0]) | (((pb4[3] << 8) | pb4[2]) << 16));
                 }
             }
@@ -644,7 +665,7 @@ __global__ __launch_bounds__(NT, (PH == 1 || PH >= 3) ? (RB * KT <= 2 ? 4 : 3) :
     const HeadParams hp = p.hp_table ? p.hp_table[wi.hq] : p.hp0;
     // MODE, or, under IDX_DEVICE, the scheme that the device-derived parameters name (uniform for the workgroup)
     if constexpr (MODE == IDX_DEVICE) {
-        if (hp.pad[0] == IDX_MULHI24) fwd_body<D, RB, KT, CAUSAL, IDX_MULHI24, PH>(p, wi, hp, ksp, n_split, Ks0, Ks1, Vs0, Vs1, PT, lut_lds, colsum, cs4);
+        if (hp.fma_r != 0) fwd_body<D, RB, KT, CAUSAL, IDX_FMA, PH>(p, wi, hp, ksp, n_split, Ks0, Ks1, Vs0, Vs1, PT, lut_lds, colsum, cs4);
         else fwd_body<D, RB, KT, CAUSAL, IDX_FP64, PH>(p, wi, hp, ksp, n_split, Ks0, Ks1, Vs0, Vs1, PT, lut_lds, colsum, cs4);
     } else {
         fwd_body<D, RB, KT, CAUSAL, MODE, PH>(p, wi, hp, ksp, n_split, Ks0, Ks1, Vs0, Vs1, PT, lut_lds, colsum, cs4);
@@ -660,18 +681,14 @@ int launch_mode(const FwdParams &p_in, int idx_mode, hipStream_t st)
     // dynamic shared memory: the per-row probability tables (32 or 64 entries of a word per query row)
     const unsigned sh = PH == 1 || PH >= 3 ? 0u : (unsigned)(WAVES * RB * (p.top < 32 ? 32 : 64) * 32 * sizeof(uint32_t));
     if constexpr (PH == 3) { // row maxima: no index map
-        hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_MAD24, PH>), grid, block, sh, st, p);
+        hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_FP64, PH>), grid, block, sh, st, p);
     } else if (idx_mode == IDX_DEVICE) { // the scheme is known on the device only
         hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_DEVICE, PH>), grid, block, sh, st, p);
     } else if (idx_mode == IDX_KGROUP) { // groups over the key axis: single-launch kernel only
         if constexpr (RB == 1 && KT == 2 && PH == 0) hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_KGROUP, PH>), grid, block, sh, st, p);
         else return (int)hipErrorInvalidValue;
-    } else if (idx_mode == IDX_MAD24 || idx_mode == IDX_TOP24) { // TOP24 is MAD24 with the shift at 24: same code here
-        hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_MAD24, PH>), grid, block, sh, st, p);
-    } else if (idx_mode == IDX_MULHI24) {
-        hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_MULHI24, PH>), grid, block, sh, st, p);
-    } else if (idx_mode == IDX_FP32) {
-        hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_FP32, PH>), grid, block, sh, st, p);
+    } else if (idx_mode == IDX_FMA) {
+        hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_FMA, PH>), grid, block, sh, st, p);
     } else if (idx_mode == IDX_ROW64) {
         hipLaunchKernelGGL((fwd_kernel<D, RB, KT, CAUSAL, IDX_ROW64, PH>), grid, block, sh, st, p);
     } else {

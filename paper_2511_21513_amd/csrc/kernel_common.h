@@ -85,17 +85,6 @@ template <int MODE> struct RowIndex {
         else if (MODE == IDX_MAD24 || MODE == IDX_TOP24) addc = hp.idx_add - (uint32_t)__mul24(row_max, (int)hp.idx_mul);
         else addc = 0;
     }
-    // Delta' * mul + add of the clipped score sc (IDX_TOP24: the index is its top byte)
-    __device__ __forceinline__ uint32_t scaled(int sc) const { return (uint32_t)__mul24(sc, mul) + addc; }
-    // Address of the score's entry in a table whose rows (one per index) are 256 bytes apart.  lane_base =
-    // the table's address, which must be a multiple of 65536, plus the lane's offset (< 256) inside a
-    // row.  IDX_TOP24: one byte permute puts the top byte of the scaled score into byte 1 of lane_base;
-    // the other schemes shift the index up and add.
-    __device__ __forceinline__ uint32_t row_addr(int sc, uint32_t lane_base) const
-    {
-        if (MODE == IDX_TOP24) return __builtin_amdgcn_perm(scaled(sc), lane_base, 0x03020700u);
-        return ((*this)(sc) << 8) + lane_base;
-    }
     __device__ __forceinline__ uint32_t operator()(int sc) const
     {
         if (MODE == IDX_MULHI24) {
@@ -106,7 +95,7 @@ template <int MODE> struct RowIndex {
         } else if (MODE == IDX_MAD24) {
             return ((uint32_t)__mul24(sc, mul) + addc) >> shift;
         } else if (MODE == IDX_TOP24) {
-            return scaled(sc) >> 24;
+            return ((uint32_t)__mul24(sc, mul) + addc) >> 24;
         } else if (MODE == IDX_FP32) {
             return (uint32_t)(int)__builtin_fmaf((float)(sc - mx), __uint_as_float((uint32_t)mul), 0.5f);
         } else if (MODE == IDX_KGROUP) {
@@ -134,6 +123,49 @@ struct RowIndex32 {
         return c_int <= (top < 32 ? 75000 : 37000);
     }
     __device__ __forceinline__ uint32_t operator()(int sc) const { return (uint32_t)(int)__builtin_fmaf((float)(sc - mx), negr, 0.5f); }
+};
+
+// The map of a score to its place in a table of 2^b entries, for kernels that start the score's MFMAs at start().
+//
+// IDX_FMA counts entries from the end of the table (place = top - idx, 0 where a key is clipped or hidden) and needs neither the clip nor a conversion of the score.  The accumulators of the score's MFMAs start at the bits of
+// the float 2^23 + c_int - rowMax, so that a finished one, read as a float f, is 2^23 + x with x = c_int - Delta exactly
+// where x >= 0, and below 2^23 where the distance Delta exceeds c_int (|score - rowMax| <= 2^22, c_int < 2^22).  One fma gives
+// f r - 2^23 r = x r, rounded once (2^23 r is exact), and the conversion to a byte rounds it to the nearest integer and takes
+// negative values to 0.  r is a float just below top / c_int, so that ties (top x / c_int = k + 1/2) go down, as
+// top - round-half-up(top Delta / c_int) does; the host (find_fma) or the derivation kernel has proved it at both sides of
+// every step.  Rounding and saturation of v_cvt_pk_u8_f32: nearest even, [0, 255].
+template <int MODE> struct ScoreIndex {
+    RowIndex<MODE> ri;
+    float r, b;
+    int add0;
+    // place of entry idx of the table, and the entry at a place (top = 2^b - 1)
+    static __device__ __forceinline__ int place(int idx, int top) { return MODE == IDX_FMA ? top - idx : idx; }
+    __device__ __forceinline__ void init(const HeadParams &hp, int row_max, uint32_t top_)
+    {
+        if constexpr (MODE == IDX_FMA) {
+            r = __uint_as_float(hp.fma_r);
+            b = r * -8388608.0f;
+            add0 = 0x4b000000 + hp.c_int - row_max;
+        } else {
+            ri.init(hp, row_max, top_);
+            add0 = 0;
+        }
+    }
+    __device__ __forceinline__ int start() const { return add0; }                             // of the score's accumulator
+    __device__ __forceinline__ int hidden() const { return MODE == IDX_FMA ? 0 : INT32_MIN; } // the score of a hidden key
+    __device__ __forceinline__ float steps(int sc) const { return __builtin_fmaf(__uint_as_float((uint32_t)sc), r, b); }
+    __device__ __forceinline__ uint32_t index(int sc) const
+    {
+        if constexpr (MODE == IDX_FMA) return __builtin_amdgcn_cvt_pk_u8_f32(steps(sc), 0, 0);
+        else return ri(max(sc, ri.bound));
+    }
+    // Offset of the score's entry in a table whose rows (one per place) are 256 bytes apart; lane_base = the lane's offset
+    // (< 256) inside a row: the conversion writes the place into byte 1.
+    __device__ __forceinline__ uint32_t address(int sc, uint32_t lane_base) const
+    {
+        if constexpr (MODE == IDX_FMA) return __builtin_amdgcn_cvt_pk_u8_f32(steps(sc), 1, lane_base);
+        else return (index(sc) << 8) + lane_base;
+    }
 };
 
 // The barrier that publishes tiles filled by direct-to-LDS loads: a wave's own loads must have landed before

@@ -13,13 +13,13 @@ enum IdxMode : int32_t {
     IDX_MAD24 = 1,  // (Delta' * mul + add) >> shift, 24-bit operands, 32-bit result
     IDX_MULHI24 = 2,// high 32 bits of the 48-bit product ((Delta' << pre) + add) * mul
     IDX_FP32 = 3,   // trunc(fma(Delta', top/c_int, 0.5)) in IEEE fp32 (idx_mul holds the bits of -top/c_int)
-    IDX_DEVICE = 4, // the scheme (MULHI24 or FP64, one for all heads of the call) is in the HeadParams, written on the device; sweep C: one of TOP24, MULHI24 and FP64 for every head
+    IDX_DEVICE = 4, // the scheme (MULHI24 or FP64, one for all heads of the call; FMA or FP64 in the kernels that take those) is in the HeadParams, written on the device
     IDX_ROW64 = 5,  // the fp64 scheme with parameters per block of query rows (FwdParams::row_table): finer
                     // quantization groups over the query rows, Sec. 3.3
     IDX_KGROUP = 7, // per-logit parameters: quantization groups over the key axis (Sec. 3.3), fp64 map per key block
-    IDX_TOP24 = 6,  // MAD24 with shift 24: the index is the top byte of Delta' * mul + add, which one byte
-                    // permute turns into the address of a table row 256 bytes apart (sweep C)
-    IDX_MIX = 8     // launchers of sweep C only: every head's own scheme, IDX_TOP24 or IDX_MULHI24, is in its parameters
+    IDX_TOP24 = 6,  // MAD24 with shift 24: the index is the top byte of Delta' * mul + add
+    IDX_FMA = 9     // one fp32 fma on the accumulator read as a float and one conversion (ScoreIndex, kernel_common.h): every c_int up
+                    // to about 130 000 and most up to 400 000; HeadParams::fma_r
 };
 
 // Per query head: everything the kernel needs that depends on the scales.
@@ -30,7 +30,8 @@ struct HeadParams {
     int32_t idx_shift; // MAD24: right shift; MULHI24: left pre-shift of Delta'
     int32_t rq_mult;   // output requantization multiplier M in [2^30, 2^31)
     int32_t rq_shift;  // output requantization shift sh in [1, 62]
-    int32_t pad[2];    // pad[0]: this head's IdxMode when the table was derived on the device
+    int32_t pad[1];    // this head's IdxMode when the table was derived on the device
+    uint32_t fma_r;    // IDX_FMA: bits of the float factor r; 0: the head has none
 };
 
 // A divisor known on the host, for n / d without a division (work_map.h).
@@ -69,7 +70,7 @@ struct FwdParams {
     int32_t causal;
     int32_t top;         // 2^b - 1
     int32_t n_chunks;    // ceil(Lk / rows per workgroup of sweep C): chunks of V the column sums are kept for
-    const HeadParams *hp_table_c; // device [Hq] or nullptr: sweep C's own table (IDX_MIX) where some heads have top-byte constants
+    int32_t fma;         // host scales: every head has HeadParams::fma_r
     const HeadParams *row_table; // IDX_ROW64: device [B * Hq][n_rowblk], parameters of every block of q_block query rows
     int32_t q_block, n_rowblk;
     // IDX_KGROUP: scales per block of q_block query rows [B * Hq][n_rowblk] and per block of k_block keys
