@@ -119,8 +119,8 @@ int launch_colsum(const FwdParams &p, int d, int chunk, hipStream_t st)
 // Kernel variants (0 = automatic choice; the others are tuning knobs, all bit-identical):
 //   1  one launch, 32 query rows per wave, 64-key tiles     2  one launch, 64 rows per wave
 //   3  one launch, a workgroup per 32 query rows with the keys split over its four waves (fwd_splitk.hip)
-//   4  two launches: sweeps A+B (64 rows per wave), then sweep C (32 rows per wave), phase-ordered kernels
-//   5  as 4 with the software-pipelined sweep C kernel
+//   4  two launches: sweeps A+B (32 or 64 rows per wave), then sweep C (32 rows per wave), phase-ordered kernels
+//   5  as 4 with sweep C's kernel of its own
 //   9, 10  the split-key kernels of decode_kernel.hip (one launch / four launches) whenever the shape allows them, else as 0
 // Automatic choice among the tiled kernels, by measurement on shapes from 8 x 12 x 197 to 2 x 32 x 4096 (W = workgroups
 // of 128 query rows): W >= 1024 fills the chip with the two-launch path (variant 5), short rows excepted; up to 256 the 128-row kernels
@@ -180,6 +180,14 @@ KeySplit fwd_key_split(int variant, int B, int Hq, int Hkv, int L, int Lk, int d
     if (24 + t_ab + t_c > worth) return KeySplit{0, 0};
     return ks;
 }
+// Blocks of 32 query rows of a wave of sweeps A+B.  Two share every K fragment, which saves LDS reads, and a tile is staged
+// for 256 rows; one leaves four waves a SIMD instead of three and half the masked work on the diagonal.  d = 64, where a
+// fragment is half as long: always one (4 x 4096, causal, 16 heads: 95 against 100 us; 8 x 1024: 30.5 against 38.4; 1 x 8192 the
+// same).  d = 128: one up to 2048 keys under the mask (8 x 1024, 32 heads: 47 against 55; 2 x 2048: 45 against 58; 8 x 2048: 160
+// against 163), two beyond (2 x 4096: 144 against 145; 1 x 8192: 265 against 276; 16 x 4096: 1020 against 1074) and without a
+// mask (1 x 4096: 138 against 142; 4 x 1024 the same).
+static int fwd_ab_row_blocks(int d, int causal, int Lk) { return d == 64 || (causal && Lk <= 2048) ? 1 : 2; }
+
 // The index map of the kernels that take IDX_FMA or IDX_FP64 (and the group and device modes): without a factor for every
 // head the parameters hold the fp64 map.
 static int fma_mode(const FwdParams &p, int idx_mode) { return p.fma ? IDX_FMA : idx_mode; }
@@ -237,9 +245,10 @@ int launch_fwd(const FwdParams &p_in, int d, int idx_mode, int variant, int stag
         // sweeps A+B leave row max and row sum in the workspace for sweep C
         if (stage != 2) {
             FwdParams pab = p;
-            pab.n_qtiles = fwd_row_tiles(p.row_lo, p.L, 256); // 64 query rows per wave in the first launch
             pab.group_batch = fwd_group_batch(p.B, p.Hkv, k_bytes); // streams K only
-            e = launch_shape<2, 2, 1>(pab, d, mode, st);
+            const int rb = fwd_ab_row_blocks(d, p.causal, p.Lk);
+            pab.n_qtiles = fwd_row_tiles(p.row_lo, p.L, 128 * rb);
+            e = rb == 1 ? launch_shape<1, 2, 1>(pab, d, mode, st) : launch_shape<2, 2, 1>(pab, d, mode, st);
             if (e != 0 || stage == 1) return e;
         }
         if (variant == 4) return launch_shape<1, 2, 2>(p, d, mode, st);

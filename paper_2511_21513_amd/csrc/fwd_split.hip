@@ -3,6 +3,7 @@
 
 namespace intattn {
 namespace fwdk {
+template int launch_shape<1, 2, 1>(const FwdParams &, int, int, hipStream_t);
 template int launch_shape<2, 2, 1>(const FwdParams &, int, int, hipStream_t);
 template int launch_shape<1, 2, 2>(const FwdParams &, int, int, hipStream_t);
 template int launch_shape<2, 2, 3>(const FwdParams &, int, int, hipStream_t);
