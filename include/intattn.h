@@ -134,7 +134,7 @@ INTATTN_API int intattn_create(intattn_ctx **out, const intattn_config *cfg);
 
 /* Enqueues the fused IntAttention forward (Sec. 3) on hip_stream (a hipStream_t; NULL is
  * the default stream) and returns without waiting for it.  The context owns a device workspace
- * (8 bytes per query row plus d int32 per 128 keys and KV head) that the first call allocates and a
+ * (8 bytes per query row) that the first call allocates and a
  * later, larger call re-allocates (hipMalloc / hipFree wait for the device and are not for use under
  * graph capture: call intattn_reserve first, or use intattn_forward_noalloc); the
  * kernels of a call pass intermediate results through it, so calls on ONE context must not
@@ -168,10 +168,10 @@ INTATTN_API int intattn_reserve(intattn_ctx *ctx, const intattn_args *args, int3
 /* intattn_forward for callers that cannot allocate device memory (code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc): same arguments (host scales), same bytes out.  Same
  * kernels, except that tiled launches never split their keys over workgroups and that the split-key
- * path takes its four launches.  The workspace -- row maxima and row sums between the launches, V
- * column sums, the partial results of the split-key path -- and the per-head parameter table live in a
+ * path takes its four launches.  The workspace -- row maxima and row sums between the launches,
+ * the partial results of the split-key path -- and the per-head parameter table live in a
  * static device array of INTATTN_NOALLOC_SCRATCH_BYTES that the library's image holds on every GPU it
- * runs on.  Calls no hipMalloc / hipFree.  A problem that needs more workspace than the array holds (8
+ * runs on.  Calls no hipMalloc / hipFree.  A problem past the array's bound (8
  * bytes per query row of every (batch, head) plus 4 d bytes per 128 keys of every (batch, KV head),
  * or more than 512 query heads with per-head scales) is rejected with INTATTN_ERR_UNSUPPORTED and a
  * message naming both sizes.  The array is shared by every context on the GPU and keeps the last
@@ -188,7 +188,7 @@ INTATTN_API int intattn_forward_noalloc(intattn_ctx *ctx, const intattn_args *ar
 /* Timing hook for benchmarks, not part of the serving interface: the forward cut at the point where
  * the row maxima and row sums of IndexSoftmax (Sec. 3.1-3.2) are complete, so that the two launches of
  * the tiled path can be timed separately.  stage 0: everything, as
- * intattn_forward.  stage 1: V column sums and sweeps A+B only (row max, row sum of E_hat go to
+ * intattn_forward.  stage 1: sweeps A+B only (row max, row sum of E_hat go to
  * the context's workspace; args->out is not written).  stage 2: sweep C only (P_hat, P_hat.V_hat,
  * requantization), reading what the last stage-1 call on this context left: it must have had the
  * same arguments, and nothing else may run on the context in between.  Returns

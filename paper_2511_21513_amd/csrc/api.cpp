@@ -69,7 +69,6 @@ struct intattn_ctx {
     // microseconds per head; serving loops pass the same scales again and again)
     std::vector<uint32_t> dv_key;
     std::vector<HeadParams> dv_hp;
-    bool dv_fma = false;
     std::vector<float> dv_alpha, dv_svso;
     int dv_mode = 0;
     std::vector<HeadParams> hp_host;  // what d_hp currently holds
@@ -384,9 +383,8 @@ bool find_fma(uint32_t c_int, uint32_t top, HeadParams *hp)
 
 struct Derived {
     std::vector<HeadParams> hp;
-    bool fma = false; // every head has a factor of the IDX_FMA map
     std::vector<float> alpha, svso;
-    int idx_mode = IDX_MAD24;
+    int idx_mode = IDX_FP64;
 };
 
 int validate(intattn_ctx *ctx, const intattn_args *a)
@@ -441,14 +439,8 @@ int derive_all(intattn_ctx *ctx, const intattn_args *a, Derived *out)
     out->hp.assign((size_t)n, HeadParams{});
     out->alpha.assign((size_t)n, 0.f);
     out->svso.assign((size_t)n, 0.f);
-    // candidate index-map schemes in order of preference; a launch uses one scheme for all heads
-    typedef bool (*finder)(uint32_t, uint32_t, HeadParams *);
-    const finder finders[5] = {find_top24, find_mulhi24, find_mad24, find_fp32, find_fp64};
-    const int modes[5] = {IDX_TOP24, IDX_MULHI24, IDX_MAD24, IDX_FP32, IDX_FP64};
-    bool all_ok[5] = {true, true, true, true, true};
-    std::vector<HeadParams> cand[5];
-    for (auto &c : cand) c.assign((size_t)n, HeadParams{});
-    out->fma = true;
+    // a launch uses one scheme for all heads
+    bool fma = true;
     for (int h = 0; h < n; ++h) {
         const int kv = a->scale_mode ? h / g : 0;
         const float sq = a->scale_q[h], sk = a->scale_k[kv], sv = a->scale_v[kv];
@@ -459,22 +451,15 @@ int derive_all(intattn_ctx *ctx, const intattn_args *a, Derived *out)
         hp.c_int = (int32_t)derive_c_int(ctx->clip, sq, sk, a->d);
         if (!derive_requant(sv, so, &hp.rq_mult, &hp.rq_shift))
             return fail(ctx, INTATTN_ERR_INVALID_ARG, "s_V / (255 s_O) is outside the representable range");
-        out->fma = out->fma && find_fma((uint32_t)hp.c_int, top, &hp);
-        for (int m = out->fma ? 0 : 4; m < 5; ++m) {
-            cand[m][(size_t)h] = hp;
-            if (all_ok[m] && !finders[m]((uint32_t)hp.c_int, top, &cand[m][(size_t)h])) all_ok[m] = false;
-        }
+        fma = fma && find_fma((uint32_t)hp.c_int, top, &hp);
         out->alpha[(size_t)h] = (float)(((double)sq * (double)sk) / std::sqrt((double)a->d));
         out->svso[(size_t)h] = (float)((double)sv / (double)so);
     }
-    for (int m = out->fma ? 0 : 4; m < 5; ++m) { // without the factor somewhere every kernel takes the fp64 map
-        if (all_ok[m]) {
-            out->idx_mode = modes[m];
-            out->hp = cand[m];
-            return INTATTN_OK;
-        }
-    }
-    return fail(ctx, INTATTN_ERR_UNSUPPORTED, "no exact index map for these scales");
+    out->idx_mode = fma ? IDX_FMA : IDX_FP64;
+    if (!fma)
+        for (HeadParams &hp : out->hp)
+            if (!find_fp64((uint32_t)hp.c_int, top, &hp)) return fail(ctx, INTATTN_ERR_UNSUPPORTED, "no exact index map for these scales");
+    return INTATTN_OK;
 }
 
 int ensure_tables(intattn_ctx *ctx, int n)
@@ -549,11 +534,10 @@ struct RunMode {
     bool reserve = false;    // allocate what the call would need and return without deriving or launching
 };
 
-// int32 words of a key-split launch: c partial accumulators, row maxima and row sums, V column sums
+// int32 words of a key-split launch: c partial accumulators, row maxima and row sums
 int64_t split_words(const intattn_args *a, int c)
 {
-    const int64_t rows = (int64_t)a->B * a->Hq * a->L, n_chunks = ((a->Lkv ? a->Lkv : a->L) + 127) / 128;
-    return rows * ((int64_t)c * a->d + 2) + (int64_t)a->B * a->Hkv * n_chunks * a->d;
+    return (int64_t)a->B * a->Hq * a->L * ((int64_t)c * a->d + 2);
 }
 
 // The kernels that serve a call.
@@ -592,12 +576,11 @@ Choice choose_kernels(const intattn_ctx *ctx, const intattn_args *a, const RunMo
     // Few query tiles against many keys: the tiled kernels with the keys split, where their cost model beats that of the
     // single launch
     if (may_split && (ch.variant == 1 || ch.variant == 3) && !rm.no_alloc && a->scale_mode <= 2) {
-        ch.ks = fwd_key_split(ch.variant, a->B, a->Hq, a->Hkv, a->L, Lk, a->d, a->causal);
+        ch.ks = fwd_key_split(ch.variant, a->B, a->Hq, a->L, Lk, a->d, a->causal);
         if (ch.ks.c > 0) ch.variant = VARIANT_KEY_SPLIT;
     }
-    // Short key sequences at d = 64 with the integer index maps: all scores in registers (fwd_short.hip)
-    const bool integer_map = idx_mode == IDX_MAD24 || idx_mode == IDX_TOP24 || idx_mode == IDX_MULHI24;
-    if (!rm.dynamic && integer_map && a->scale_mode < 2 && fwd_short_serves(ch.variant, a->B, a->Hq, a->L, Lk, a->d, a->causal))
+    // Short key sequences at d = 64 with the fma map: all scores in registers (fwd_short.hip)
+    if (!rm.dynamic && idx_mode == IDX_FMA && a->scale_mode < 2 && fwd_short_serves(ch.variant, a->B, a->Hq, a->L, Lk, a->d, a->causal))
         ch.variant = VARIANT_SHORT;
     return ch;
 }
@@ -636,7 +619,6 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
         if (a->scale_out) add(a->scale_out, n_q);
         if (!ctx->dv_key.empty() && key == ctx->dv_key) {
             dv.hp = ctx->dv_hp;
-            dv.fma = ctx->dv_fma;
             dv.alpha = ctx->dv_alpha;
             dv.svso = ctx->dv_svso;
             dv.idx_mode = ctx->dv_mode;
@@ -645,7 +627,6 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
             if (rc) return rc;
             ctx->dv_key = key;
             ctx->dv_hp = dv.hp;
-            ctx->dv_fma = dv.fma;
             ctx->dv_alpha = dv.alpha;
             ctx->dv_svso = dv.svso;
             ctx->dv_mode = dv.idx_mode;
@@ -716,7 +697,6 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
     p.causal = a->causal;
     p.group = a->Hq / a->Hkv;
     p.top = (1 << ctx->lut_bits) - 1;
-    p.fma = dv.fma ? 1 : 0;
     Choice ch = choose_kernels(ctx, a, rm, dv.idx_mode, !rm.reserve);
     if (ch.ks.c > 0) {
         bool room = true;
@@ -745,7 +725,6 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
     };
     const int rows_per_block = comparator ? 128 : fwd_rows_per_block(variant);
     p.n_qtiles = variant == VARIANT_SHORT ? (p.L + 127) / 128 : fwd_row_tiles(p.row_lo, p.L, rows_per_block);
-    p.n_chunks = (p.Lk + rows_per_block - 1) / rows_per_block;
     std::memcpy(p.lut, ctx->lut, 64);
     p.dbg_row_max = a->dbg_row_max; p.dbg_row_sum = a->dbg_row_sum; p.dbg_acc = a->dbg_acc;
 
@@ -922,7 +901,8 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
     }
     if (!comparator && variant != 3 && variant != VARIANT_SHORT) { // (those pass nothing through memory)
         const size_t rows = (size_t)a->B * a->Hq * a->L;
-        const size_t cs = (size_t)a->B * a->Hkv * p.n_chunks * a->d;
+        // (the static array keeps the bound it has always had: d words per workgroup's worth of keys and KV head beside the rows)
+        const size_t kept = rm.no_alloc ? (size_t)a->B * a->Hkv * ((p.Lk + rows_per_block - 1) / rows_per_block) * a->d : 0;
         int32_t *base = nullptr;
         if (variant == VARIANT_KEY_SPLIT) {
             p.ws_part = ctx->d_split; // first: its rows start 16-byte aligned
@@ -930,13 +910,12 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
             p.split_c = ch.ks.c;
             base = p.ws_part + (size_t)ch.ks.c * rows * a->d;
         } else {
-            rc = get_ws(2 * rows + cs);
+            rc = get_ws(2 * rows + kept);
             if (rc) return rc;
             base = d_ws;
         }
         p.ws_row_max = base;
         p.ws_row_sum = p.ws_row_max + rows;
-        p.ws_colsum = p.ws_row_sum + rows;
     }
     if (rm.reserve) return reserve_rest();
 

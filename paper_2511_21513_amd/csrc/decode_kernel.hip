@@ -210,16 +210,14 @@ __global__ __launch_bounds__(NT) void decode_lookup_kernel(const FwdParams p)
             const int g = q & 3, rn = q >> 2, n = rn % R, sh = rn / R, h = sh & 1, t32l = sh >> 1;
             const int key0 = (t0 * 4 + t32l) * 32;
             const int mx = row_max[n], ri = row_i[n];
-            const HeadParams &hp = row_hp[n];
+            const AnyIndex index(row_hp[n], p.top);
             uint32_t w = 0, sum = 0;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 uint32_t idx = 64u; // hidden key: probability 0 (one past the largest table, 2^6 entries)
                 if (key_visible(p, key0 + acc_key(4 * g + j, h), ri)) {
                     // Delta = max - score (Sec. 3.1), clipped at c_int (Eq. int_clipping), index map, Eq. gather16
-                    const int64_t delta = (int64_t)mx - (int64_t)sc[j];
-                    const int dclip = delta < (int64_t)hp.c_int ? (int)delta : hp.c_int;
-                    idx = index_any(hp, -dclip, (uint32_t)p.top);
+                    idx = index(mx - sc[j]); // (scores are at most 2^21 in magnitude)
                     sum += lut_b[idx];
                 }
                 w |= idx << (8 * j);
@@ -580,7 +578,7 @@ __global__ __launch_bounds__(NT, 4) void decode_fused_kernel(const FwdParams p)
             // >= 0 and below 2^23 where the row sees a key of the sub-tile (meaningless, and unused, where it sees none)
             const int base = WIDE ? row_max[nn] : (int)((uint32_t)row_max[nn] - (uint32_t)sub_max[tl * R + nn]);
             const int ri = row_i[nn];
-            const HeadParams &hp = row_hp[nn];
+            const AnyIndex index(row_hp[nn], p.top);
             const bool full = key0 + 32 <= p.Lk && (!p.causal || key0 + 31 <= p.row_lo + ri);
             uint32_t w = 0, sum = 0;
 #pragma unroll
@@ -588,7 +586,7 @@ __global__ __launch_bounds__(NT, 4) void decode_fused_kernel(const FwdParams p)
                 uint32_t idx = 64u; // hidden key: probability 0
                 if (full || key_visible(p, key0 + acc_key(4 * g + j, hh), ri)) {
                     const int delta = WIDE ? base - (int)u[j] : base + (int)u[j]; // scores are below 2^22 in magnitude
-                    idx = index_any(hp, -min(delta, hp.c_int), (uint32_t)p.top);
+                    idx = index(delta);
                     sum += lut_b[idx];
                 }
                 w |= idx << (8 * j);

@@ -33,43 +33,13 @@ static int launch_sweep_c(const FwdParams &p, int d, int idx_mode, hipStream_t s
 
 namespace {
 
-// Sums of V over each chunk of `chunk` consecutive keys, per (batch, KV head) and channel:
-// out[((b * Hkv + kvh) * n_chunks + c) * D + ch].  Keys past Lk do not count.  The forward kernel
-// adds up the chunks its tiles cover.  For the key-split launches that follow, it also sets the row maxima and row sums
-// they accumulate into to their neutral values.
-template <int D>
-__global__ __launch_bounds__(256) void colsum_kernel(const FwdParams p, int chunk)
+// Key-split path: the row maxima and row sums that the launches of sweeps A and B accumulate into, at their neutral values.
+__global__ __launch_bounds__(256) void neutral_rows_kernel(const FwdParams p, int64_t rows)
 {
-    constexpr int G = D / 16;   // 16-byte column groups of a key row
-    constexpr int KL = 256 / G; // key lanes
-    __shared__ int32_t red[KL][D + 1];
-    const int tid = threadIdx.x, c16 = tid % G, kl = tid / G;
-    const int c = blockIdx.x % p.n_chunks, bk = blockIdx.x / p.n_chunks, kvh = bk % p.Hkv, b = bk / p.Hkv;
-    const int8_t *Vp = p.v + (int64_t)b * p.vs[0] + (int64_t)kvh * p.vs[1];
-    int32_t acc[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0;
-    const int kend = min(p.Lk, (c + 1) * chunk);
-    for (int key = c * chunk + kl; key < kend; key += KL) {
-        const v4i x = *(const v4i *)(Vp + (int64_t)key * p.vs[2] + c16 * 16);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[i] += (int32_t)(int8_t)((uint32_t)x[i / 4] >> (8 * (i % 4)));
-    }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) red[kl][c16 * 16 + i] = acc[i];
-    __syncthreads();
-    if (tid < D) {
-        int32_t t = 0;
-        for (int j = 0; j < KL; ++j) t += red[j][tid];
-        p.ws_colsum[((int64_t)bk * p.n_chunks + c) * D + tid] = t;
-    }
-    if (p.split_c > 0) { // uniform
-        const int64_t rows = (int64_t)p.B * p.Hq * p.L;
-        for (int64_t i = (int64_t)blockIdx.x * 256 + tid; i < rows; i += (int64_t)gridDim.x * 256) {
-            p.ws_row_max[i] = INT32_MIN;
-            p.ws_row_sum[i] = 0;
-        }
-    }
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= rows) return;
+    p.ws_row_max[i] = INT32_MIN;
+    p.ws_row_sum[i] = 0;
 }
 
 // Key-split path: adds up the partial accumulators of sweep C's ranges and requantizes; a thread takes four channels of a
@@ -105,12 +75,10 @@ int launch_finish_split(const FwdParams &p, int d, hipStream_t st)
     return (int)hipGetLastError();
 }
 
-int launch_colsum(const FwdParams &p, int d, int chunk, hipStream_t st)
+int launch_neutral_rows(const FwdParams &p, hipStream_t st)
 {
-    const dim3 grid((unsigned)(p.B * p.Hkv * p.n_chunks)), block(256);
-    if (d == 64) hipLaunchKernelGGL(colsum_kernel<64>, grid, block, 0, st, p, chunk);
-    else if (d == 128) hipLaunchKernelGGL(colsum_kernel<128>, grid, block, 0, st, p, chunk);
-    else return (int)hipErrorInvalidValue;
+    const int64_t rows = (int64_t)p.B * p.Hq * p.L;
+    hipLaunchKernelGGL(neutral_rows_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, st, p, rows);
     return (int)hipGetLastError();
 }
 
@@ -148,15 +116,15 @@ bool fwd_variant_known(int variant) { return variant == 0 || (variant >= 1 && va
 // bound by their longest chain of tiles or, once the chip is full, by a cost per 32 x 32 block (variant 3) or by rounds of
 // 380 workgroups (variant 1).  It is made to rank the two and errs where a launch is a little over a whole number of rounds
 // (509 x 7001, 32 / 8 heads, d 128: 544 workgroups of variant 3, two rounds of 512; it says 161 us, measured 247), for the
-// single launch then, as the margins below do.  KV heads enter through the room for column sums only: 32 / 32 and 32 / 8 heads
+// single launch then, as the margins below do.  KV heads do not enter: 32 / 32 and 32 / 8 heads
 // measure within 6 % of each other (one pair of 25: 11 %).  Timed on 286 shapes of 1 to 128 heads, 40
 // to 8192 rows and 600 to 16384 keys: the 105 that it splits take 0.23 to 0.94 of the time of the better of variants 1 and 3
 // (509 x 7001: 247 -> 120 us; 128 x 12000, 8 heads, d 64: 128 -> 47; 3000 square, 12 heads, d 128: 94.9 -> 88.8); what else a
 // split would serve was not timed.  Small problems lose by it (1024 square, 16 heads, d 128: 22 us unsplit, 49 split).
-KeySplit fwd_key_split(int variant, int B, int Hq, int Hkv, int L, int Lk, int d, int causal)
+KeySplit fwd_key_split(int variant, int B, int Hq, int L, int Lk, int d, int causal)
 {
     const int row_lo = causal ? Lk - L : 0, tiles = (Lk + 127) / 128;
-    const int64_t rows = (int64_t)B * Hq * L, fixed = 2 * rows + (int64_t)B * Hkv * tiles * d; // row maxima and sums, V column sums
+    const int64_t rows = (int64_t)B * Hq * L, fixed = 2 * rows; // row maxima and sums
     const int64_t w_ab = (int64_t)B * Hq * fwd_row_tiles(row_lo, L, 256), w_c = (int64_t)B * Hq * fwd_row_tiles(row_lo, L, 128);
     const double seen = causal ? (Lk - 0.5 * L) / Lk : 1.0; // share of the keys that an average row sees
     const double us_tile = d == 128 ? 1.4 : 0.9, us_part = (double)B * Hq * L * d * 8 / 4.0e6;
@@ -188,10 +156,6 @@ KeySplit fwd_key_split(int variant, int B, int Hq, int Hkv, int L, int Lk, int d
 // mask (1 x 4096: 138 against 142; 4 x 1024 the same).
 static int fwd_ab_row_blocks(int d, int causal, int Lk) { return d == 64 || (causal && Lk <= 2048) ? 1 : 2; }
 
-// The index map of the kernels that take IDX_FMA or IDX_FP64 (and the group and device modes): without a factor for every
-// head the parameters hold the fp64 map.
-static int fma_mode(const FwdParams &p, int idx_mode) { return p.fma ? IDX_FMA : idx_mode; }
-
 // All scores in registers (fwd_short.hip): up to 256 keys at d = 64, from 128 heads on.  Against variant 3, whose chain is a
 // quarter as long, only where more blocks of 32 rows than three for each compute unit are in flight, or, as its waves pad the
 // masked half, one under a square mask: 160 heads of 160 x 160 10.2 us against 10.4, 128 of 197 x 197 10.5 against 11.2, masked
@@ -212,35 +176,21 @@ int launch_fwd(const FwdParams &p_in, int d, int idx_mode, int variant, int stag
     const int64_t k_bytes = (int64_t)p.Lk * d; // K of one (batch, KV head) group; V is as large
     p.group_batch = fwd_group_batch(p.B, p.Hkv, 2 * k_bytes); // kernels that stream K and V
     const bool two_launches = variant == 4 || variant == 5;
-    const int mode = fma_mode(p, idx_mode);
     if (variant == VARIANT_SHORT) return stage != 0 ? (int)hipErrorNotSupported : launch_fwd_short(p, d, idx_mode, stream);
     if (variant == VARIANT_KEY_SPLIT) {
         if (stage != 0) return (int)hipErrorNotSupported;
-        int e = launch_colsum(p, d, 128, st);
+        int e = launch_neutral_rows(p, st);
         FwdParams pab = p;
         pab.n_qtiles = fwd_row_tiles(p.row_lo, p.L, 256);
         pab.group_batch = fwd_group_batch(p.B, p.Hkv, k_bytes); // streams K only
-        if (e == 0) e = launch_shape<2, 2, 3>(pab, d, mode, st);
-        if (e == 0) e = launch_shape<2, 2, 4>(pab, d, mode, st);
-        if (e == 0) e = launch_sweep_c(p, d, mode, st);
+        if (e == 0) e = launch_shape<2, 2, 3>(pab, d, idx_mode, st);
+        if (e == 0) e = launch_shape<2, 2, 4>(pab, d, idx_mode, st);
+        if (e == 0) e = launch_sweep_c(p, d, idx_mode, st);
         return e == 0 ? launch_finish_split(p, d, st) : e;
     }
     if (stage != 0 && !two_launches) return (int)hipErrorNotSupported;
-    // all launches go to the same stream: V chunk sums first, then the sweeps
-    int e = 0;
-    if (variant == 3) {
-        return launch_fwd_splitk(p, d, idx_mode, stream); // sums V itself
-    }
-    if (!two_launches && p.Lk <= 512) {
-        // short key sequences: the single-launch kernels sum V themselves (one launch less)
-        FwdParams ps = p;
-        ps.ws_colsum = nullptr;
-        if (variant == 2) return launch_shape<2, 2, 0>(ps, d, mode, st);
-        return launch_shape<1, 2, 0>(ps, d, mode, st);
-    }
-    if (stage != 2) e = launch_colsum(p, d, fwd_rows_per_block(variant), st);
-    if (e != 0) return e;
-    if (variant == 2) return launch_shape<2, 2, 0>(p, d, mode, st);
+    if (variant == 3) return launch_fwd_splitk(p, d, idx_mode, stream);
+    if (variant == 2) return launch_shape<2, 2, 0>(p, d, idx_mode, st);
     if (two_launches) {
         // sweeps A+B leave row max and row sum in the workspace for sweep C
         if (stage != 2) {
@@ -248,13 +198,13 @@ int launch_fwd(const FwdParams &p_in, int d, int idx_mode, int variant, int stag
             pab.group_batch = fwd_group_batch(p.B, p.Hkv, k_bytes); // streams K only
             const int rb = fwd_ab_row_blocks(d, p.causal, p.Lk);
             pab.n_qtiles = fwd_row_tiles(p.row_lo, p.L, 128 * rb);
-            e = rb == 1 ? launch_shape<1, 2, 1>(pab, d, mode, st) : launch_shape<2, 2, 1>(pab, d, mode, st);
+            const int e = rb == 1 ? launch_shape<1, 2, 1>(pab, d, idx_mode, st) : launch_shape<2, 2, 1>(pab, d, idx_mode, st);
             if (e != 0 || stage == 1) return e;
         }
-        if (variant == 4) return launch_shape<1, 2, 2>(p, d, mode, st);
-        return launch_sweep_c(p, d, mode, st);
+        if (variant == 4) return launch_shape<1, 2, 2>(p, d, idx_mode, st);
+        return launch_sweep_c(p, d, idx_mode, st);
     }
-    return launch_shape<1, 2, 0>(p, d, mode, st);
+    return launch_shape<1, 2, 0>(p, d, idx_mode, st);
 }
 
 } // namespace intattn

@@ -15,12 +15,7 @@
 // Scores are produced transposed (keys x queries) so that each lane owns one query row:
 // row max and row sum are in-lane plus one exchange between the two half-waves.
 //
-// The int8 MFMA is signed x signed while P_hat is unsigned (0..255).  The kernel feeds
-// P_hat - 128 and adds 128 * (column sums of the V rows of every processed tile) at the end;
-// hidden keys inside a processed tile carry P_hat = 0, i.e. the byte -128, so the correction
-// is the plain column sum.  colsum_kernel (below) leaves the sums of V over each chunk of as
-// many keys as a workgroup has query rows; sweep C adds up the chunks it covers.  All
-// intermediate magnitudes stay below 2^31 for L < 131072.
+// All intermediate magnitudes stay below 2^31 for L < 131072.
 //
 // LDS tiles are row-major [key][d] with the 16-byte chunks of each row XOR-swizzled so that
 // both access patterns are bank-conflict free: K fragments are read with 128-bit loads
@@ -55,8 +50,7 @@ constexpr int NT = WAVES * 64;
 // vector instructions (135 and 217 registers as it is, causal, one launch).
 template <int D, int RB, int KT, bool CAUSAL, int M, int PH>
 __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi, const HeadParams &hp, const int ksp, const int n_split,
-                                         int8_t *Ks0, int8_t *Ks1, int8_t *Vs0, int8_t *Vs1, uint32_t *PT, uint32_t *lut_lds,
-                                         int32_t *colsum, int32_t (*cs4)[D])
+                                         int8_t *Ks0, int8_t *Ks1, int8_t *Vs0, int8_t *Vs1, uint32_t *PT, uint32_t *lut_lds)
 {
     constexpr int KS = KT; // sub-tiles sweep C computes per step: the whole staged tile
     constexpr int KB = D / 32;       // 32-wide blocks of the head dimension
@@ -349,10 +343,6 @@ __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi,
     ScoreIndex<M> si[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) si[rb].init(M == IDX_ROW64 ? row_hp(qw0 + 32 * rb + n) : hp, KG ? 0 : mx[rb], top);
-    if constexpr (KG) {
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) si[rb].ri.shift = (int)top; // bound of the index (see RowIndex)
-    }
     // Key groups: the index constants of the lane's row for the key block of `key` (Sec. 3.3):
     // c_int^(g) = round(c / alpha^(g)) capped at 2^30, m^(g) = round(M / alpha^(g)), the fp64 index map's
     // factor for c_int^(g).  m^(g) is clamped to [-2^22, 2^30 + 2^22]: below every logit / far enough above
@@ -479,54 +469,17 @@ __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi,
             sum[rb] = (row >= rlo && row < rhi) ? (uint32_t)p.ws_row_sum[(int64_t)bh * LQ + (row - rlo)] : 0u;
         }
     }
-    // Column sums of V over every key that sweep C's tiles cover (keys up to the end of this query
-    // tile under the causal mask, else all): the correction for feeding the probabilities to the
-    // signed MFMA as P - 128.  A small kernel ahead of this one left the sums of each BQ-key chunk
-    // per (batch, KV head); visible to all waves after sweep C's barriers.
-    if (PH != 0 || p.ws_colsum) {
-        if (tid < D) {
-            const int32_t *cp = p.ws_colsum + (int64_t)(b * p.Hkv + kvh) * p.n_chunks * D + tid;
-            const int nchunk = CAUSAL ? min(qt + 1, p.n_chunks) : p.n_chunks;
-            int32_t acc = 0;
-#pragma unroll 8
-            for (int c = 0; c < nchunk; ++c) acc += cp[(int64_t)c * D];
-            colsum[tid] = acc;
-        }
-    } else if constexpr (PH == 0) {
-        // Short key sequences: the launch of the small kernel costs more than summing V over the
-        // keys [0, kmax) here (thread = 16 channels of every KL-th key row, then the key lanes of
-        // a wave by lane exchange, then the four waves through LDS).
-        constexpr int G = D / 16, KL = NT / G;
-        const int c16 = tid % G, kl = tid / G;
-        int32_t a16[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) a16[i] = 0;
-        for (int key = kl; key < kmax; key += KL) {
-            const v4i x = *(const v4i *)(Vp + (int64_t)key * p.vs[2] + c16 * 16);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) a16[i] += (int32_t)(int8_t)((uint32_t)x[i / 4] >> (8 * (i % 4)));
-        }
-#pragma unroll
-        for (int o = G; o < 64; o <<= 1)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) a16[i] += __shfl_xor(a16[i], o);
-        if (lane < G)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) cs4[wave][c16 * 16 + i] = a16[i];
-        __syncthreads();
-        if (tid < D) colsum[tid] = cs4[0][tid] + cs4[1][tid] + cs4[2][tid] + cs4[3][tid];
-    }
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-        if (sum[rb] == 0) sum[rb] = 1; // only rows outside [rlo, rhi); never stored
-        // per-row probability table: PT[idx] = round(255 * LUT_hat[idx] / sum) - 128 as a byte
+        const int row = qw0 + 32 * rb + n;
+        if (row < rlo || row >= rhi) sum[rb] = 1u << 24; // all probabilities 0, never stored
+        // per-row probability table: PT[place of idx] = round(255 * LUT_hat[idx] / sum)
         uint32_t *pt = PT + (wave * RB + rb) * NIDX * 32;
         const float inv_2s = __builtin_amdgcn_rcpf((float)(2u * sum[rb]));
         for (int j = 0; j < NIDX / 2; ++j) {
             const int kidx = (NIDX / 2) * h + j;
-            pt[kidx * 32 + n] = (prob_u8(lut_b[kidx], sum[rb], inv_2s) ^ 0x80u) & 0xffu; // by place, like LUT_hat
+            pt[kidx * 32 + n] = prob_u8(lut_b[kidx], sum[rb], inv_2s); // by place, like LUT_hat
         }
-        const int row = qw0 + 32 * rb + n;
         if (!KG && p.dbg_row_max && h == 0 && row >= rlo && row < rhi) p.dbg_row_max[(int64_t)bh * LQ + (row - rlo)] = mx[rb];
         if (p.dbg_row_sum && h == 0 && row >= rlo && row < rhi) p.dbg_row_sum[(int64_t)bh * LQ + (row - rlo)] = (int32_t)sum[rb];
     }
@@ -566,7 +519,7 @@ __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi,
                         if (!kg_blocks) kg_index(rb, key);
                         const RowIndex<M> &ri = si[rb].ri;
                         s[st][rb][i] = (int)pt[ri(min(max(s[st][rb][i], ri.bound), ri.mx)) * 32];
-                        if (MASKED) s[st][rb][i] = visible(key, qw0 + 32 * rb + n) ? s[st][rb][i] : 0x80;
+                        if (MASKED) s[st][rb][i] = visible(key, qw0 + 32 * rb + n) ? s[st][rb][i] : 0;
                     } else { // a hidden key takes the table's last entry, whose probability is 0
                         const int sc = !MASKED || visible(key, qw0 + 32 * rb + n) ? s[st][rb][i] : si[rb].hidden();
                         s[st][rb][i] = (int)pt[si[rb].index(sc) * 32];
@@ -594,10 +547,10 @@ __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi,
         }
     };
 
-    // every wave walks every tile of the workgroup here: the column-sum correction assumes it
     sweep(std::true_type{}, [&](int t, const int8_t *Kb, const int8_t *Vb) __attribute__((always_inline)) {
 #pragma unroll
         for (int st0 = 0; st0 < KT; st0 += KS) {
+            if (tile_is_hidden(t)) continue; // no P_hat of this wave's rows there
             // (the P_hat.V_hat MFMAs follow in one place for both instantiations, so that the output
             // accumulators have a single home)
             v4i pf[KS][RB], vf[KS][CB];
@@ -607,19 +560,13 @@ __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi,
             else tile_c(std::true_type{}, t, Kb, Vb, st0, pf, vf);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int st = 0; st < KS; ++st) {
+            for (int st = 0; st < KS; ++st)
 #pragma unroll
-                for (int cb = 0; cb < CB; ++cb) {
-#pragma unroll
-                    for (int rb = 0; rb < RB; ++rb)
-                        o[rb][cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf[st][cb], pf[st][rb], o[rb][cb], 0, 0, 0);
-                }
-            }
+                for (int rb = 0; rb < RB; ++rb) add_pv<true>(vf[st], pf[st][rb], o[rb]);
         }
     });
 
     // ================================================================= epilogue
-    // colsum was written after sweep B; sweep C's barriers made it visible
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
         const int row = qw0 + 32 * rb + n;
@@ -635,7 +582,7 @@ __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi,
                 uint32_t packed = 0;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int32_t acc = o[rb][cb][4 * g + r] + 128 * colsum[ch0 + r];
+                    const int32_t acc = o[rb][cb][4 * g + r];
                     if (p.dbg_acc) p.dbg_acc[((int64_t)bh * LQ + (row - rlo)) * D + ch0 + r] = acc;
                     packed |= ((uint32_t)requant_any(acc, he.rq_mult, he.rq_shift) & 0xffu) << (8 * r);
                 }
@@ -668,8 +615,6 @@ __global__ __launch_bounds__(NT, (PH == 1 || PH >= 3) ? (RB == 1 ? 4 : 3) : (RB 
     // words, NIDX = 32 or 64 table entries (none for sweeps A+B alone)
     extern __shared__ uint32_t PT[];
     __shared__ uint32_t lut_lds[16];
-    __shared__ int32_t colsum[D];
-    __shared__ int32_t cs4[PH == 0 ? WAVES : 1][D]; // in-kernel column sums of V (short sequences, single launch)
 
     int bid = (int)blockIdx.x;
     const int n_split = PH == 3 || PH == 4 ? p.split_ab : 1;
@@ -679,10 +624,10 @@ __global__ __launch_bounds__(NT, (PH == 1 || PH >= 3) ? (RB == 1 ? 4 : 3) : (RB 
     const HeadParams hp = p.hp_table ? p.hp_table[wi.hq] : p.hp0;
     // MODE, or, under IDX_DEVICE, the scheme that the device-derived parameters name (uniform for the workgroup)
     if constexpr (MODE == IDX_DEVICE) {
-        if (hp.fma_r != 0) fwd_body<D, RB, KT, CAUSAL, IDX_FMA, PH>(p, wi, hp, ksp, n_split, Ks0, Ks1, Vs0, Vs1, PT, lut_lds, colsum, cs4);
-        else fwd_body<D, RB, KT, CAUSAL, IDX_FP64, PH>(p, wi, hp, ksp, n_split, Ks0, Ks1, Vs0, Vs1, PT, lut_lds, colsum, cs4);
+        if (hp.fma_r != 0) fwd_body<D, RB, KT, CAUSAL, IDX_FMA, PH>(p, wi, hp, ksp, n_split, Ks0, Ks1, Vs0, Vs1, PT, lut_lds);
+        else fwd_body<D, RB, KT, CAUSAL, IDX_FP64, PH>(p, wi, hp, ksp, n_split, Ks0, Ks1, Vs0, Vs1, PT, lut_lds);
     } else {
-        fwd_body<D, RB, KT, CAUSAL, MODE, PH>(p, wi, hp, ksp, n_split, Ks0, Ks1, Vs0, Vs1, PT, lut_lds, colsum, cs4);
+        fwd_body<D, RB, KT, CAUSAL, MODE, PH>(p, wi, hp, ksp, n_split, Ks0, Ks1, Vs0, Vs1, PT, lut_lds);
     }
 }
 

@@ -11,7 +11,6 @@
 // each, took 60.5 us on the first: 148 to 167 registers (five to eight sub-tiles; 103 up to four) leave a compute unit 12
 // waves, so only one workgroup of seven.
 //
-// Probabilities go to the signed MFMA as P - 128; the correction comes from an operand of all ones, as in fwd_splitk.hip.
 // Hidden keys take the last table index, whose entry is 0 by Eq. lut16: no part in the sum, probability 0.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -30,7 +29,7 @@ constexpr int KB = D / 32, CB = D / 32;
 constexpr int RPB = 1024 / D; // key rows per 1 KiB block
 
 // NS: 32-key sub-tiles held (Lk <= 32 NS)
-template <int NS, bool CAUSAL, int MODE>
+template <int NS, bool CAUSAL>
 __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdParams p)
 {
     __shared__ __attribute__((aligned(1024))) int8_t Ks[NS * 32 * D];
@@ -70,7 +69,11 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
     };
     stage(p.k + (int64_t)b * p.ks[0] + (int64_t)kvh * p.ks[1], p.ks[2], Ks, wave, false);
     stage(p.v + (int64_t)b * p.vs[0] + (int64_t)kvh * p.vs[1], p.vs[2], Vs, wave, true);
-    if (tid < 8) lut_lds[tid] = p.lut[tid];
+    // LUT_hat by place (see ScoreIndex)
+    if (tid < 32) {
+        const int idx = ScoreIndex<IDX_FMA>::place(tid, (int)top);
+        ((uint8_t *)lut_lds)[tid] = idx >= 0 ? (uint8_t)(p.lut[idx / 4] >> (8 * (idx % 4))) : (uint8_t)0;
+    }
     v4i qf[KB];
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
@@ -115,9 +118,10 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
     mx = max(mx, __shfl_xor(mx, 32));
     if (!row_ok) mx = 0; // rows outside the problem: zero scores, never stored
 
-    // ---- table indices and row sum
-    RowIndex<MODE> ri;
-    ri.init(hp, mx, top);
+    // ---- table places and row sum; the row maximum is known only now, so the start value is added here
+    ScoreIndex<IDX_FMA> si;
+    si.init(hp, mx, top);
+    const int last = CAUSAL ? min(L - 1, row) : L - 1; // last key the lane's row sees
     const uint8_t *lut_b = (const uint8_t *)lut_lds;
     uint32_t sum = 0;
 #pragma unroll
@@ -125,13 +129,11 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
         if (!live(st)) continue;
         if (full(st)) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) s[st][i] = (int)ri(max(s[st][i], ri.bound));
+            for (int i = 0; i < 16; ++i) s[st][i] = (int)si.index(s[st][i] + si.start());
         } else {
+            const int lim = last - 32 * st - 4 * h;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int idx = (int)ri(min(max(s[st][i], ri.bound), ri.mx)); // hidden keys may exceed the row max
-                s[st][i] = visible(32 * st + acc_key(i, h)) ? idx : (int)top;
-            }
+            for (int i = 0; i < 16; ++i) s[st][i] = (int)si.index(acc_key(i, 0) <= lim ? s[st][i] + si.start() : si.hidden());
         }
         uint32_t e[16];
 #pragma unroll
@@ -140,19 +142,24 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
         for (int i = 0; i < 16; ++i) sum += e[i];
     }
     sum += __shfl_xor(sum, 32);
-    if (sum == 0) sum = 1; // only rows outside the problem
+    const bool big = __any(row_ok && sum <= BIG_ROW_SUM); // wave-uniform
+    if (!row_ok) sum = 1u << 24;                          // rows outside the problem: all probabilities 0
     if (h == 0 && row_ok) {
         if (p.dbg_row_max) p.dbg_row_max[(int64_t)bh * LQ + lr] = mx;
         if (p.dbg_row_sum) p.dbg_row_sum[(int64_t)bh * LQ + lr] = (int32_t)sum;
     }
 
-    // ---- the row's probabilities as bytes P - 128 (Eq. uint8-prob); the LDS executes one wave's instructions in order
+    // ---- the row's probabilities (Eq. uint8-prob) by place; the LDS executes one wave's instructions in order
+    // Where a probability may exceed 127 (BIG_ROW_SUM) the wave feeds P - 128 and takes the column sums of V from an operand of
+    // all ones.  (Rows this short mostly have a key of that size in every sub-tile or none at all, so taking the top bits
+    // apart as add_pv does costs more here: 128 x 12 heads of 197 x 197 with outlier channels 50.3 us.)
+    const uint32_t flip = big ? 0x80u : 0u;
     uint32_t *PT = PT_all + wave * 1024;
     const float inv_2s = __builtin_amdgcn_rcpf((float)(2u * sum));
 #pragma unroll 4
     for (int j = 0; j < 16; ++j) {
         const int idx = 16 * h + j;
-        PT[idx * 32 + n] = (prob_u8(lut_b[idx], sum, inv_2s) ^ 0x80u) & 0xffu; // lut is 0 past the table
+        PT[idx * 32 + n] = prob_u8(lut_b[idx], sum, inv_2s) ^ flip; // lut is 0 past the table
     }
     v4i pf[NS];
 #pragma unroll
@@ -167,7 +174,7 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
                               ((((uint32_t)s[st][4 * g + 3] << 8) | (uint32_t)s[st][4 * g + 2]) << 16));
     }
 
-    // ---- P_hat.V_hat and the column sums of V over the same keys
+    // ---- P_hat.V_hat
     const int tr_i = lane & 15, tr_g = (lane >> 4) & 1, jj = tr_i >> 1;
     const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
     v16i o[CB], ocs[CB];
@@ -178,20 +185,20 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
 #pragma unroll
     for (int st = 0; st < NS; ++st) {
         if (!live(st)) continue;
+        v4i vf[CB];
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
-            v4i vf;
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
                 const int key = 32 * st + 8 * (2 * r + (jj >> 2)) + 4 * h + (jj & 3);
                 const int8_t *ptr = Vs + key * D + (((2 * cb + tr_g) ^ swz_v<D>(key)) << 4) + 8 * (tr_i & 1);
                 const v2i x = __builtin_amdgcn_ds_read_tr8_b64_v2i32((v2i __attribute__((address_space(3))) *)ptr);
-                vf[2 * r] = x[0];
-                vf[2 * r + 1] = x[1];
+                vf[cb][2 * r] = x[0];
+                vf[cb][2 * r + 1] = x[1];
             }
-            o[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf, pf[st], o[cb], 0, 0, 0);
-            ocs[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf, ones, ocs[cb], 0, 0, 0);
         }
+        add_pv<false>(vf, pf[st], o);
+        if (big) add_pv<false>(vf, ones, ocs);
     }
 
     // ---- requantize (Sec. 3.2); the wave's 32 rows of 64 bytes meet in its LDS part, so that stores are 16 bytes a lane.
@@ -221,29 +228,28 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
 }
 
 template <int NS, bool CAUSAL>
-int launch_mode(const FwdParams &p_in, int idx_mode, hipStream_t st)
+int launch_shape(const FwdParams &p_in, hipStream_t st)
 {
     FwdParams p = p_in;
     const int waves = p.L >= MAX_WAVES * 32 ? MAX_WAVES : (p.L + 31) / 32;
     const dim3 grid((unsigned)fwd_map_work(p)), block((unsigned)(64 * waves));
     const unsigned sh = (unsigned)waves * 4096u;
-    if (idx_mode == IDX_MULHI24) hipLaunchKernelGGL((fwd_short_kernel<NS, CAUSAL, IDX_MULHI24>), grid, block, sh, st, p);
-    else hipLaunchKernelGGL((fwd_short_kernel<NS, CAUSAL, IDX_MAD24>), grid, block, sh, st, p);
+    hipLaunchKernelGGL((fwd_short_kernel<NS, CAUSAL>), grid, block, sh, st, p);
     return (int)hipGetLastError();
 }
 
 } // namespace
 
-// d = 64, Lk <= 256, tables of at most 32 entries, the integer index maps (TOP24 is MAD24 with the shift at 24), parameters per
+// d = 64, Lk <= 256, tables of at most 32 entries, host scales with the fma map, parameters per
 // tensor or per head; p.n_qtiles counts tiles of 128 query rows from row 0; no workspace.
 int launch_fwd_short(const FwdParams &p, int d, int idx_mode, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
-    if (d != D || p.Lk > 256 || p.top > 31 || (idx_mode != IDX_MAD24 && idx_mode != IDX_TOP24 && idx_mode != IDX_MULHI24))
+    if (d != D || p.Lk > 256 || p.top > 31 || idx_mode != IDX_FMA)
         return (int)hipErrorInvalidValue;
-    if (p.Lk <= 128) return p.causal ? launch_mode<4, true>(p, idx_mode, st) : launch_mode<4, false>(p, idx_mode, st);
-    if (p.Lk <= 224) return p.causal ? launch_mode<7, true>(p, idx_mode, st) : launch_mode<7, false>(p, idx_mode, st);
-    return p.causal ? launch_mode<8, true>(p, idx_mode, st) : launch_mode<8, false>(p, idx_mode, st);
+    if (p.Lk <= 128) return p.causal ? launch_shape<4, true>(p, st) : launch_shape<4, false>(p, st);
+    if (p.Lk <= 224) return p.causal ? launch_shape<7, true>(p, st) : launch_shape<7, false>(p, st);
+    return p.causal ? launch_shape<8, true>(p, st) : launch_shape<8, false>(p, st);
 }
 
 } // namespace intattn

@@ -16,12 +16,10 @@
 // the 16 bytes of its key row that its MFMA operand holds; the next sub-tile is requested before this one is
 // computed), V sub-tiles go through a wave-private LDS buffer (direct global -> LDS loads, then the
 // transposing LDS read), and there is no workgroup barrier inside a sweep.
-//
-// Probabilities go to the signed MFMA as P - 128; the correction, 128 * (column sums of V over every key of
-// the processed sub-tiles), comes from one more MFMA per channel block and sub-tile against an operand of
-// all ones, which leaves the column sums in the accumulator layout of the outputs: one launch, no workspace.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "kernel_common.h"
 #include "params.h"
@@ -33,10 +31,10 @@ namespace {
 constexpr int WAVES = 4;
 constexpr int NT = WAVES * 64;
 
-// Waves a SIMD (and workgroups a compute unit): at d = 64 four, i.e. 128 registers (eight spill under the mask).  Row groups,
-// which hold constants per lane, spill 45 then, and run with three (32 heads of 1500 tokens: 51.8 -> 46.7 us; 512 tokens:
-// 20.2 -> 17.5); key groups hold yet more and run with two.
-constexpr int splitk_waves(int d, int mode) { return d != 64 || mode == IDX_KGROUP ? 2 : (mode == IDX_ROW64 ? 3 : 4); }
+// Waves a SIMD (and workgroups a compute unit): at d = 64 three, i.e. 168 registers (132 to 154 in use).  With four, 17 spill
+// inside the loops (2048 rows, 16 heads: 24.3 -> 31.8 us; 8 x 12 heads of 197 rows 8.2 -> 11.0); with four and the start values
+// added by the vector ALU instead of held for the MFMAs none does, at the same speed as three.  Key groups hold yet more.
+constexpr int splitk_waves(int d, int mode) { return d != 64 || mode == IDX_KGROUP ? 2 : 3; }
 
 template <int D, bool CAUSAL, int MODE>
 __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(const FwdParams p)
@@ -63,14 +61,17 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
     // asked for with the rest of the work item's parameters, not with vector loads through a selected pointer, whose wait is 0.1
     // to 0.2 us of a small launch
 #if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("" : "+s"(hp.c_int), "+s"(hp.idx_mul), "+s"(hp.idx_add), "+s"(hp.idx_shift), "+s"(hp.rq_mult), "+s"(hp.rq_shift), "+s"(hp.pad[0]));
+    asm volatile("" : "+s"(hp.c_int), "+s"(hp.idx_mul), "+s"(hp.idx_add), "+s"(hp.rq_mult), "+s"(hp.rq_shift), "+s"(hp.fma_r));
 #endif
     const WorkItem wi = fwd_work_item(p, (int)blockIdx.x);
     if (!wi.valid) return; // padding of the XCD-aware grid (uniform for the whole workgroup)
     const int b = wi.b, hq = wi.hq, kvh = wi.kvh, qt = wi.qt + p.row_lo / 32;
     const int bh = b * p.Hq + hq;
     if (p.hp_table) hp = p.hp_table[hq];
-    if (p.one_scheme && hp.pad[0] != MODE) return; // served by the other launch
+    // The rest with the index scheme M as a compile-time constant: MODE, or, under IDX_DEVICE, the one that the parameters
+    // derived on the device allow.
+    auto body = [&](auto mode_tag) __attribute__((always_inline)) {
+    constexpr int M = decltype(mode_tag)::value;
     const int L = p.Lk;
     const int rlo = p.row_lo, rhi = p.row_lo + p.L, LQ = p.L;
     const uint32_t top = (uint32_t)p.top;
@@ -78,7 +79,7 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
     // Finer quantization groups (Sec. 3.3).  RG: parameters per block of query rows, from the row table; KG: each key block
     // has a scale of its own too, so that the row maximum is taken over the dequantized logits (fp64) and a lane forms the
     // constants of its row for each key block (once per 32-key sub-tile where a sub-tile lies in one block).
-    constexpr bool KG = MODE == IDX_KGROUP, RG = KG || MODE == IDX_ROW64;
+    constexpr bool KG = M == IDX_KGROUP, RG = KG || M == IDX_ROW64;
     const float *skp = KG ? p.sk_blocks + (int64_t)(b * p.Hkv + kvh) * p.n_kblk : nullptr;
     const bool kg_blocks = KG && (p.k_block % 32) == 0; // uniform
     auto row_hp = [&](int r) __attribute__((always_inline)) {
@@ -99,7 +100,11 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
         return (sq_row * (double)skp[min(key, L - 1) / p.k_block]) / p.sqrt_d;
     };
 
-    if (tid < 16) lut_lds[tid] = p.lut[tid];
+    // LUT_hat by place (see ScoreIndex)
+    if (tid < 64) {
+        const int idx = ScoreIndex<M>::place(tid, (int)top);
+        ((uint8_t *)lut_lds)[tid] = idx >= 0 ? (uint8_t)(p.lut[idx / 4] >> (8 * (idx % 4))) : (uint8_t)0;
+    }
     for (int i = tid; i < 32 * (D + 1); i += NT) (&acc_lds[0][0])[i] = 0;
 
     // Q fragments: row q0 + n, bytes [32 kb + 16 h, +16)
@@ -124,8 +129,9 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
             for (int kb = 0; kb < KB; ++kb) kf[kb] = *(const v4i *)(Kp + (int64_t)key * p.ks[2] + kb * 32 + h * 16);
         }
     };
+    v16i start = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}; // what the scores are added to
     auto scores = [&](const v4i (&kf)[KB]) __attribute__((always_inline)) {
-        v16i s = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+        v16i s = start;
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) s = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf[kb], qf[kb], s, 0, 0, 0);
         return s;
@@ -204,9 +210,11 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
         }
     }
 
-    RowIndex<MODE> ri;
-    ri.init(MODE == IDX_ROW64 ? row_hp(row) : hp, KG ? 0 : mx, top);
-    if constexpr (KG) ri.shift = (int)top; // bound of the index (see RowIndex)
+    ScoreIndex<M> si;
+    si.init(M == IDX_ROW64 ? row_hp(row) : hp, KG ? 0 : mx, top);
+    [[maybe_unused]] RowIndex<M> &ri = si.ri;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) start[i] = si.start();
     // Group modes: where every lane's threshold is small enough, the index map runs in fp32 (see RowIndex32), the choice
     // uniform for the wave.
     RowIndex32 ri32;
@@ -214,7 +222,7 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
     auto pick_map = [&](int c_int) __attribute__((always_inline)) {
         single = __all(ri32.init(c_int, ri.mx, top));
     };
-    if constexpr (MODE == IDX_ROW64) pick_map(ri.mx - ri.bound);
+    if constexpr (M == IDX_ROW64) pick_map(ri.mx - ri.bound);
     // Key groups: the constants of the lane's row for the key block of `key`, as in the tiled kernel: c_int^(g) =
     // round(c / alpha^(g)) capped at 2^30, m^(g) = round(M / alpha^(g)) clamped to [-2^22, 2^30 + 2^22], which changes no
     // result (comparisons written so that a NaN from an unusable scale lands on a bound).
@@ -234,12 +242,16 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
             ri.negr = __longlong_as_double((long long)(bits ^ 0x8000000000000000ull));
         }
     };
-    // table indices of the sixteen scores of sub-tile j (in place); hidden keys and, with key groups, logits above their
-    // block's image of the maximum are brought to it
-    auto indices = [&](int j, v16i &s, bool clamp_max) __attribute__((always_inline)) {
+    // table places of the sixteen scores of sub-tile j (in place).  Hidden keys (masked: there may be some) take the last
+    // table entry, which is 0; with groups they and, with key groups, logits above their block's image of the maximum are
+    // brought to it, and the caller leaves them out.
+    const int last = CAUSAL ? min(L - 1, row) : L - 1; // last key the lane's row sees
+    auto indices = [&](int j, v16i &s, auto masked_tag) __attribute__((always_inline)) {
+        constexpr bool MASKED = decltype(masked_tag)::value;
         if constexpr (!RG) {
+            const int lim = last - 32 * j - 4 * h;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) s[i] = (int)ri(clamp_max ? min(max(s[i], ri.bound), ri.mx) : max(s[i], ri.bound));
+            for (int i = 0; i < 16; ++i) s[i] = (int)si.index(!MASKED || acc_key(i, 0) <= lim ? s[i] : si.hidden());
         } else if (KG && !kg_blocks) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
@@ -266,17 +278,17 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
         v16i s = scores(kf);
         if (sub_is_full(j)) {
             uint32_t e[16];
-            indices(j, s, false);
+            indices(j, s, std::false_type{});
 #pragma unroll
             for (int i = 0; i < 16; ++i) e[i] = lut_b[s[i]];
 #pragma unroll
             for (int i = 0; i < 16; ++i) sum += e[i];
         } else {
-            indices(j, s, true); // hidden keys may exceed the row max
+            indices(j, s, std::true_type{});
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const uint32_t e = lut_b[s[i]];
-                sum += visible(32 * j + acc_key(i, h)) ? e : 0u;
+                sum += !RG || visible(32 * j + acc_key(i, h)) ? e : 0u;
             }
         }
     });
@@ -284,18 +296,17 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
     if (h == 0) red[1][wave][n] = (int32_t)sum;
     __syncthreads();
     sum = (uint32_t)red[1][0][n] + (uint32_t)red[1][1][n] + (uint32_t)red[1][2][n] + (uint32_t)red[1][3][n];
-    if (sum == 0) sum = 1; // only rows outside [rlo, rhi); never stored
+    const bool big = __any(row_ok && sum <= BIG_ROW_SUM); // wave-uniform, and the same for the four waves
     if (wave == 0 && h == 0 && row_ok) {
         if (!KG && p.dbg_row_max) p.dbg_row_max[(int64_t)bh * LQ + (row - rlo)] = mx;
         if (p.dbg_row_sum) p.dbg_row_sum[(int64_t)bh * LQ + (row - rlo)] = (int32_t)sum;
     }
-    // per-row probability table, once per workgroup: PT[idx][row] = round(255 LUT_hat[idx] / S) - 128 as a byte
+    // per-row probability table, once per workgroup: PT[place of idx][row] = round(255 LUT_hat[idx] / S)
     for (int e = tid; e < NIDX * 32; e += NT) {
         const int idx = e >> 5, r = e & 31;
         const uint32_t S = (uint32_t)red[1][0][r] + (uint32_t)red[1][1][r] + (uint32_t)red[1][2][r] + (uint32_t)red[1][3][r];
-        const uint32_t Sd = S ? S : 1u;
-        const uint32_t ev = (uint32_t)idx <= top ? lut_b[idx] : 0u;
-        PT[e] = (prob_u8(ev, Sd, __builtin_amdgcn_rcpf((float)(2u * Sd))) ^ 0x80u) & 0xffu;
+        const uint32_t Sd = q0 + r >= rlo && q0 + r < rhi ? S : 1u << 24; // rows outside the problem: all probabilities 0
+        PT[e] = prob_u8(lut_b[idx], Sd, __builtin_amdgcn_rcpf((float)(2u * Sd))); // (LUT_hat is 0 past the table)
     }
     __syncthreads();
 
@@ -338,20 +349,20 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
         return a;
     };
 
-    v16i o[CB], ocs[CB]; // P_hat.V_hat with P - 128, and the column sums of V over the same keys
+    v16i o[CB];
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) o[cb][i] = 0, ocs[cb][i] = 0;
-    const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
+        for (int i = 0; i < 16; ++i) o[cb][i] = 0;
     const uint32_t *pt = PT + n;
     walk(stage_v, [&](int j, const v4i (&kf)[KB], int buf) __attribute__((always_inline)) {
         v16i s = scores(kf);
         const bool full = sub_is_full(j);
-        indices(j, s, !full);
+        if (full) indices(j, s, std::false_type{});
+        else indices(j, s, std::true_type{});
 #pragma unroll
         for (int i = 0; i < 16; ++i) s[i] = (int)pt[s[i] * 32];
-        v4i pf;
+        v4i pf, vf[CB];
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             uint32_t pb4[4];
@@ -359,25 +370,23 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
             for (int r = 0; r < 4; ++r) {
                 const int i = 4 * g + r;
                 pb4[r] = (uint32_t)s[i];
-                if (!full) pb4[r] = visible(32 * j + acc_key(i, h)) ? pb4[r] : 0x80u;
+                if (RG && !full) pb4[r] = visible(32 * j + acc_key(i, h)) ? pb4[r] : 0u;
             }
             pf[g] = (int)(((pb4[1] << 8) | pb4[0]) | (((pb4[3] << 8) | pb4[2]) << 16));
         }
         // (the compiler waits for this wave's direct-to-LDS loads into the buffer before the reads below)
         const int8_t *Vb = buf ? &Vw1[wave][0] : &Vw0[wave][0];
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) {
-            const v4i vf = vt_frag(Vb, cb);
-            o[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf, pf, o[cb], 0, 0, 0);
-            ocs[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf, ones, ocs[cb], 0, 0, 0);
-        }
+        for (int cb = 0; cb < CB; ++cb) vf[cb] = vt_frag(Vb, cb);
+        if (big) add_pv<true>(vf, pf, o);
+        else add_pv<false>(vf, pf, o);
     });
     // the accumulators of the four waves meet in LDS: register i of lane (n, h) in channel block cb is
     // row n, channel 32 cb + 8 (i / 4) + 4 h + (i % 4)
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) atomicAdd(&acc_lds[n][cb * 32 + 8 * (i >> 2) + 4 * h + (i & 3)], o[cb][i] + 128 * ocs[cb][i]);
+        for (int i = 0; i < 16; ++i) atomicAdd(&acc_lds[n][cb * 32 + 8 * (i >> 2) + 4 * h + (i & 3)], o[cb][i]);
     __syncthreads();
 
     // ================================================================= epilogue: 8 threads per row
@@ -400,6 +409,13 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
             *(uint32_t *)(Op + ec0 + c4) = packed;
         }
     }
+    };
+    if constexpr (MODE == IDX_DEVICE) {
+        if (hp.fma_r != 0) body(std::integral_constant<int, IDX_FMA>{}); // uniform for the workgroup
+        else body(std::integral_constant<int, IDX_FP64>{});
+    } else {
+        body(std::integral_constant<int, MODE>{});
+    }
 }
 
 // Slots of an XCD whose order is folded, or 0.  Where all workgroups of a causal launch are resident at once, a compute unit
@@ -420,20 +436,10 @@ int launch_mode(const FwdParams &p_in, int idx_mode, hipStream_t st)
     p.map.fold = fold_slots(n_wg, CAUSAL, splitk_waves(D, idx_mode));
     const dim3 grid((unsigned)n_wg), block(NT);
     const unsigned sh = (unsigned)((p.top < 32 ? 32 : 64) * 32 * sizeof(uint32_t)); // the per-row probability table
-    if (idx_mode == IDX_DEVICE) {
-        // the scheme is known on the device only: one launch per scheme, the other returns at once (a kernel that holds both
-        // took 6 % longer on host scales, 2048 x 2048, 16 heads, d 64, for the same registers)
-        p.one_scheme = 1;
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_MULHI24>), grid, block, sh, st, p);
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_FP64>), grid, block, sh, st, p);
-        return (int)hipGetLastError();
-    }
-    if (idx_mode == IDX_MAD24 || idx_mode == IDX_TOP24) // the top-byte scheme is the multiply-add with the shift at 24
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_MAD24>), grid, block, sh, st, p);
-    else if (idx_mode == IDX_MULHI24)
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_MULHI24>), grid, block, sh, st, p);
-    else if (idx_mode == IDX_FP32)
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_FP32>), grid, block, sh, st, p);
+    if (idx_mode == IDX_FMA)
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_FMA>), grid, block, sh, st, p);
+    else if (idx_mode == IDX_DEVICE)
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_DEVICE>), grid, block, sh, st, p);
     else if (idx_mode == IDX_ROW64)
         hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_ROW64>), grid, block, sh, st, p);
     else if (idx_mode == IDX_KGROUP)

@@ -20,90 +20,27 @@ __device__ __forceinline__ double idx_fp64_factor(const HeadParams &hp)
     return __builtin_bit_cast(double, ((uint64_t)hp.idx_add << 32) | (uint64_t)hp.idx_mul);
 }
 
-// t = -min(Delta, c_int) in [-c_int, 0]; returns round(-t * top / c_int).
-template <int MODE>
-__device__ __forceinline__ uint32_t index_map(int t, const HeadParams &hp, uint32_t top)
-{
-    if (MODE == IDX_MAD24) {
-        // (-t) * mul + add, 24-bit signed operands (idx_mul holds -mul)
-        return (uint32_t)(__mul24(t, (int)hp.idx_mul) + (int)hp.idx_add) >> hp.idx_shift;
-    } else if (MODE == IDX_TOP24) {
-        return (uint32_t)(__mul24(t, (int)hp.idx_mul) + (int)hp.idx_add) >> 24;
-    } else if (MODE == IDX_MULHI24) {
-        // high word of ((t << pre) - off) * (-mul): both factors negative 24-bit values
-        const int x = (int)(((uint32_t)t << hp.idx_shift) + hp.idx_add); // idx_add holds -off
-        int r;
-        // written as an instruction so that later address arithmetic is not folded back into a
-        // 64-bit product (which costs three more VALU operations per element)
-        asm("v_mul_hi_i32_i24 %0, %1, %2" : "=v"(r) : "v"(x), "v"((int)hp.idx_mul));
-        return (uint32_t)r;
-    } else if (MODE == IDX_FP32) {
-        // trunc(fma(t, -(top/c_int), 0.5)): t is exact in fp32, one rounding in the fma; the host
-        // proved the result exact on the whole range with the same IEEE operations
-        return (uint32_t)(int)__builtin_fmaf((float)t, __uint_as_float(hp.idx_mul), 0.5f);
-    } else {
-        // trunc(fma(t, -r, 0.5)) in IEEE fp64, r the double after top/c_int: exact for every c_int
-        return (uint32_t)(int)__builtin_fma((double)t, idx_fp64_factor(hp), 0.5);
-    }
-}
-
-// The map with the scheme named in the parameters themselves (pad[0]: chosen on the host, or by
-// the derivation kernel for device-resident scales), for kernels where the map is not the hot loop.
-__device__ __forceinline__ uint32_t index_any(const HeadParams &hp, int t, uint32_t top)
-{
-    switch (hp.pad[0]) {
-    case IDX_MAD24: return index_map<IDX_MAD24>(t, hp, top);
-    case IDX_TOP24: return index_map<IDX_TOP24>(t, hp, top);
-    case IDX_MULHI24: return index_map<IDX_MULHI24>(t, hp, top);
-    case IDX_FP32: return index_map<IDX_FP32>(t, hp, top);
-    default: return index_map<IDX_FP64>(t, hp, top);
-    }
-}
-
-// The same map applied to RAW scores of one query row (the lane's row): with the row maximum
-// mx, idx = round(min(mx - s, c_int) * top / c_int).  The subtraction of mx is folded into
-// per-row constants (all arithmetic is modulo 2^32 and the true values are small), so a
-// score costs: clip (max with `bound`), then the scheme's two operations.
-// Call with sc = max(s, bound), and additionally sc <= mx where hidden keys may exceed mx.
+// The fp64 map applied to RAW scores of one query row (the lane's row): with the row maximum mx,
+// idx = trunc(fma(-Delta', -r, 0.5)) in IEEE fp64, r the double after top/c_int: exact for every c_int.
+// Call with sc = max(s, bound), and additionally sc <= mx where logits may exceed mx.
 template <int MODE> struct RowIndex {
     int bound; // mx - c_int
     int mx;
-    uint32_t addc;
-    int mul;
-    int shift;
-    double negr; // fp64 schemes only (per lane when the parameters are per block of rows)
+    int top;     // key groups: 2^b - 1
+    double negr; // (per lane when the parameters are per block of rows)
 
     __device__ __forceinline__ void init(const HeadParams &hp, int row_max, uint32_t top_)
     {
         mx = row_max;
         bound = row_max - hp.c_int;
-        mul = (int)hp.idx_mul;
-        shift = hp.idx_shift;
-        negr = (MODE == IDX_FP64 || MODE == IDX_ROW64 || MODE == IDX_KGROUP) ? idx_fp64_factor(hp) : 0.0;
-        (void)top_;
-        if (MODE == IDX_MULHI24) addc = hp.idx_add - ((uint32_t)row_max << hp.idx_shift);
-        else if (MODE == IDX_MAD24 || MODE == IDX_TOP24) addc = hp.idx_add - (uint32_t)__mul24(row_max, (int)hp.idx_mul);
-        else addc = 0;
+        negr = idx_fp64_factor(hp);
+        top = (int)top_;
     }
     __device__ __forceinline__ uint32_t operator()(int sc) const
     {
-        if (MODE == IDX_MULHI24) {
-            const int x = (int)(((uint32_t)sc << shift) + addc);
-            int r;
-            asm("v_mul_hi_i32_i24 %0, %1, %2" : "=v"(r) : "v"(x), "v"(mul));
-            return (uint32_t)r;
-        } else if (MODE == IDX_MAD24) {
-            return ((uint32_t)__mul24(sc, mul) + addc) >> shift;
-        } else if (MODE == IDX_TOP24) {
-            return ((uint32_t)__mul24(sc, mul) + addc) >> 24;
-        } else if (MODE == IDX_FP32) {
-            return (uint32_t)(int)__builtin_fmaf((float)(sc - mx), __uint_as_float((uint32_t)mul), 0.5f);
-        } else if (MODE == IDX_KGROUP) {
-            // the fp64 map; the index is kept inside the table whatever an unusable scale produced
-            return min((uint32_t)(int)__builtin_fma((double)(sc - mx), negr, 0.5), (uint32_t)shift); // shift holds 2^b - 1 here
-        } else {
-            return (uint32_t)(int)__builtin_fma((double)(sc - mx), negr, 0.5);
-        }
+        const uint32_t idx = (uint32_t)(int)__builtin_fma((double)(sc - mx), negr, 0.5);
+        // key groups: the index is kept inside the table whatever an unusable scale produced
+        return MODE == IDX_KGROUP ? min(idx, (uint32_t)top) : idx;
     }
 };
 
@@ -168,6 +105,25 @@ template <int MODE> struct ScoreIndex {
     }
 };
 
+// The map with the scheme named in the parameters themselves (pad[0]: chosen on the host, or by the derivation kernel for
+// device-resident scales), for kernels where the map is not the hot loop: round(min(delta, c_int) * top / c_int) for
+// 0 <= delta < 2^23.
+struct AnyIndex {
+    const HeadParams &hp;
+    int c_int, add0, top;
+    float r, b;
+    bool fma;
+    __device__ __forceinline__ AnyIndex(const HeadParams &hp_, int top_)
+        : hp(hp_), c_int(hp_.c_int), add0(0x4b000000 + hp_.c_int), top(top_), r(__uint_as_float(hp_.fma_r)), b(r * -8388608.0f), fma(hp_.pad[0] == IDX_FMA)
+    {
+    }
+    __device__ __forceinline__ uint32_t operator()(int delta) const
+    {
+        if (fma) return (uint32_t)top - __builtin_amdgcn_cvt_pk_u8_f32(__builtin_fmaf(__uint_as_float((uint32_t)(add0 - delta)), r, b), 0, 0);
+        return (uint32_t)(int)__builtin_fma(-(double)min(delta, c_int), idx_fp64_factor(hp), 0.5);
+    }
+};
+
 // The barrier that publishes tiles filled by direct-to-LDS loads: a wave's own loads must have landed before
 // it signals, because the other waves read what it loaded.  (On this target the compiler also drains every
 // counter before s_barrier; the wait is spelled out so that correctness does not rest on that.)
@@ -191,6 +147,36 @@ __device__ __forceinline__ uint32_t prob_u8(uint32_t e, uint32_t S, float inv_2s
     if (q * den > num) --q;
     if ((q + 1u) * den <= num) ++q;
     return q;
+}
+
+// ------------------------------------------------------------------ P_hat.V_hat (Sec. 3, Eq. pv-link)
+// The int8 MFMA is signed x signed and P_hat unsigned.  P_hat = round(255 E / S) <= 127 wherever S > 510, so most rows feed
+// their bytes as they are.  The probabilities of a row add up to 255 or little more, so in any other row one or two keys may
+// have 128 or more.  The MFMA takes such a byte for P - 256, and where a sub-tile holds one, 256 = 2 + 127 + 127 in its
+// place are multiplied by V as well.  (Before, P - 128 went in for every key, and 128 times the column sums of V were added back: a launch of their
+// own, 4 to 5 us, or an MFMA more for each of P.V; and a masked key had to pass the matrix cores like any other.)
+constexpr uint32_t BIG_ROW_SUM = 510; // a row sum up to which a probability may exceed 127
+
+template <bool BIG, int CB> __device__ __forceinline__ void add_pv(const v4i (&vf)[CB], const v4i pf, v16i (&o)[CB])
+{
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) o[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf[cb], pf, o[cb], 0, 0, 0);
+    if constexpr (BIG) {
+        // (behind the MFMAs: with a branch ahead of them the compiler moves the accumulators, and spills 80 registers and more)
+        if (__any(((pf[0] | pf[1] | pf[2] | pf[3]) & (int)0x80808080u) != 0)) {
+            v4i part;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) part[g] = (int)(((uint32_t)pf[g] >> 6) & 0x02020202u);
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) o[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf[cb], part, o[cb], 0, 0, 0);
+#pragma unroll
+            for (int g = 0; g < 4; ++g) part[g] = (int)(((uint32_t)part[g] << 6) - ((uint32_t)part[g] >> 1)); // 127 in place of 2
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) o[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf[cb], part, o[cb], 0, 0, 0);
+        }
+    }
 }
 
 // Output requantization (Sec. 3.2): clamp(floor((acc * M + 2^(sh-1)) / 2^sh), -127, 127) with M < 2^31 and

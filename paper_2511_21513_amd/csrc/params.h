@@ -6,18 +6,19 @@
 namespace intattn {
 
 // How a kernel turns a clipped distance Delta' in [0, c_int] into the table index
-// idx = round(Delta' * top / c_int)  (Sec. 3.1 index map), exactly.
+// idx = round(Delta' * top / c_int)  (Sec. 3.1 index map), exactly.  (The numbers of MAD24 to FP32 and TOP24 are part of
+// intattn_derive_index_map, which searches constants for each of them.)
 enum IdxMode : int32_t {
     IDX_FP64 = 0,   // trunc(fma(Delta', r, 0.5)) in IEEE fp64, r = the double after top/c_int: exact for every c_int
                     // (idx_mul, idx_add hold the low and high word of the bits of -r)
     IDX_MAD24 = 1,  // (Delta' * mul + add) >> shift, 24-bit operands, 32-bit result
     IDX_MULHI24 = 2,// high 32 bits of the 48-bit product ((Delta' << pre) + add) * mul
     IDX_FP32 = 3,   // trunc(fma(Delta', top/c_int, 0.5)) in IEEE fp32 (idx_mul holds the bits of -top/c_int)
-    IDX_DEVICE = 4, // the scheme (MULHI24 or FP64, one for all heads of the call; FMA or FP64 in the kernels that take those) is in the HeadParams, written on the device
+    IDX_DEVICE = 4, // FMA or FP64, named by the HeadParams that a kernel derives
     IDX_ROW64 = 5,  // the fp64 scheme with parameters per block of query rows (FwdParams::row_table): finer
                     // quantization groups over the query rows, Sec. 3.3
+    IDX_TOP24 = 6,  // MAD24 with shift 24: the index is the top byte of Delta' * mul + add (IndexSoftmax on caller's logits)
     IDX_KGROUP = 7, // per-logit parameters: quantization groups over the key axis (Sec. 3.3), fp64 map per key block
-    IDX_TOP24 = 6,  // MAD24 with shift 24: the index is the top byte of Delta' * mul + add
     IDX_FMA = 9     // one fp32 fma on the accumulator read as a float and one conversion (ScoreIndex, kernel_common.h): every c_int up
                     // to about 130 000 and most up to 400 000; HeadParams::fma_r
 };
@@ -30,7 +31,7 @@ struct HeadParams {
     int32_t idx_shift; // MAD24: right shift; MULHI24: left pre-shift of Delta'
     int32_t rq_mult;   // output requantization multiplier M in [2^30, 2^31)
     int32_t rq_shift;  // output requantization shift sh in [1, 62]
-    int32_t pad[1];    // this head's IdxMode when the table was derived on the device
+    int32_t pad[1];    // this head's IdxMode, FMA or FP64, where a kernel asks for it (decode, device-resident scales)
     uint32_t fma_r;    // IDX_FMA: bits of the float factor r; 0: the head has none
 };
 
@@ -57,7 +58,6 @@ struct FwdParams {
     int32_t group_batch; // (batch, KV head) groups of an XCD whose query tiles are interleaved (at least 1)
     int32_t n_qtiles;    // tiles of (rows per workgroup) rows that [row_lo, row_lo + L) touches
     int32_t Hkv;
-    int32_t one_scheme;  // 1: a workgroup whose head's HeadParams name another index scheme than the kernel's returns at once
     const HeadParams *hp_table; // device [Hq] when per-head or derived on the device, else nullptr
     const int8_t *q, *k, *v;
     int8_t *out;
@@ -69,8 +69,6 @@ struct FwdParams {
                          // causal mask: Lk - L when causal, else 0; tiles are aligned to this numbering
     int32_t causal;
     int32_t top;         // 2^b - 1
-    int32_t n_chunks;    // ceil(Lk / rows per workgroup of sweep C): chunks of V the column sums are kept for
-    int32_t fma;         // host scales: every head has HeadParams::fma_r
     const HeadParams *row_table; // IDX_ROW64: device [B * Hq][n_rowblk], parameters of every block of q_block query rows
     int32_t q_block, n_rowblk;
     // IDX_KGROUP: scales per block of q_block query rows [B * Hq][n_rowblk] and per block of k_block keys
@@ -83,8 +81,8 @@ struct FwdParams {
     uint32_t lut[16];           // LUT_hat, up to 64 bytes packed little-endian (unused tail is 0)
     int32_t *dbg_row_max, *dbg_row_sum, *dbg_acc;
     // workspace: [B*Hq*L] row max and [B*Hq*L] row sum (handed from the first to the second launch
-    // of the two-launch variants), [B*Hkv*n_chunks*d] sums of V over each chunk of keys
-    int32_t *ws_row_max, *ws_row_sum, *ws_colsum;
+    // of the two-launch variants)
+    int32_t *ws_row_max, *ws_row_sum;
     // key-split tiled path: workgroups per query tile in sweeps A and B (split_ab) and in sweep C (split_c), each with a
     // range of the keys; ws_part: sweep C's partial accumulators [split_c][B * Hq * L][d].  0: keys not split
     int32_t split_ab, split_c;
@@ -163,7 +161,7 @@ struct DeriveParams {
 };
 
 // Launchers implemented in the .hip files.  Return a hipError_t cast to int.
-// stage 0: everything; 1: V column sums + sweeps A+B; 2: sweep C (two-launch variants only; else hipErrorNotSupported)
+// stage 0: everything; 1: sweeps A+B; 2: sweep C (two-launch variants only; else hipErrorNotSupported)
 int launch_fwd(const FwdParams &p, int d, int idx_mode, int variant, int stage, void *stream);
 int launch_fwd_splitk(const FwdParams &p, int d, int idx_mode, void *stream);
 int fwd_choose_variant(int variant, int B, int Hq, int L, int Lk, int d, int causal); // resolves 0 (automatic) to a concrete variant
@@ -186,7 +184,7 @@ constexpr int KEY_SPLIT_PIECES = 5;               // doublings of the context's 
 struct KeySplit {
     int ab, c; // workgroups per query tile; c == 0: this shape is better served by `variant`, the choice without a split
 };
-KeySplit fwd_key_split(int variant, int B, int Hq, int Hkv, int L, int Lk, int d, int causal);
+KeySplit fwd_key_split(int variant, int B, int Hq, int L, int Lk, int d, int causal);
 int quantize_partials_per_slice(int B, int H, int L, int d);
 int launch_quantize(const QuantParams *ps, int n, void *stream);
 int launch_decode(const FwdParams &p, int d, void *stream);

@@ -19,8 +19,6 @@
 // takes as long as the phases (271 us at two waves; three spill), tiles of 128 keys or workgroups of six or eight waves
 // longer (448, 315).
 //
-// A row whose keys are all hidden in a step adds P = 0, the byte -128, like any hidden key, and needs no scores.
-//
 // Tiles are two sub-tiles (64 keys), double buffered per operand; one barrier per tile.  K tiles are cut one sub-tile
 // earlier than V tiles (K tile t covers sub-tiles [2 t - 1, 2 t + 1)), so that iteration T reads exactly K tile T + 1 and
 // V tile T, and at its top requests K tile T + 2 and V tile T + 1 into the buffers that were read an iteration ago.
@@ -49,8 +47,7 @@ __global__ __launch_bounds__(NT, D == 128 ? 3 : 4) void sweep_c_kernel(const Fwd
     constexpr int CB = D / 32;       // 32-wide blocks of output channels
     constexpr int NSUB = 2;          // 32-key sub-tiles (steps) per tile
     constexpr int BK = 32 * NSUB;    // keys per tile
-    constexpr int BQ = WAVES * 32;   // query rows of the workgroup, and keys of a chunk of the column sums
-    constexpr int TPC = BQ / BK;     // tiles per chunk
+    constexpr int BQ = WAVES * 32;   // query rows of the workgroup
     constexpr int TILE = BK * D;     // bytes
     constexpr int SUB = 32 * D;      // bytes of a 32-key sub-tile
     constexpr int NBLK = TILE / 1024;
@@ -69,7 +66,6 @@ __global__ __launch_bounds__(NT, D == 128 ? 3 : 4) void sweep_c_kernel(const Fwd
     // share a query row (l and l + 32) each hold a copy of its table.
     __shared__ __attribute__((aligned(65536))) uint8_t PT[32 * 256];
     __shared__ uint32_t lut_lds[8];
-    __shared__ int32_t colsum[D];
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 31, h = lane >> 5;
     int bid = (int)blockIdx.x;
@@ -102,11 +98,10 @@ __global__ __launch_bounds__(NT, D == 128 ? 3 : 4) void sweep_c_kernel(const Fwd
     if (tid < 8) lut_lds[tid] = p.lut[tid];
 
     const int kmax = CAUSAL ? min(L, q0 + BQ) : L;
-    // chunks of BQ keys [clo, chi); iterations = V tiles [tlo, thi); K tiles tlo..thi are touched.  Key-split launches take
-    // a range of the chunks each and leave partial accumulators; otherwise the range is all of them.
-    const int call = (kmax + BQ - 1) / BQ;
-    const int clo = call * ksp / n_split, chi = call * (ksp + 1) / n_split;
-    const int tlo = clo * TPC, thi = chi * TPC;
+    // iterations = V tiles [tlo, thi); K tiles tlo..thi are touched.  Key-split launches take a range of the tiles each and
+    // leave partial accumulators; otherwise the range is all of them.
+    const int tall = (kmax + BK - 1) / BK;
+    const int tlo = tall * ksp / n_split, thi = tall * (ksp + 1) / n_split;
 
     // ---- staging: direct global -> LDS loads; the XOR swizzle is applied to the global address
     // (lane i of a wave-wide 16-byte load lands at byte 16 i of its 1 KiB block).
@@ -167,24 +162,16 @@ __global__ __launch_bounds__(NT, D == 128 ? 3 : 4) void sweep_c_kernel(const Fwd
     const HeadParams hrow = M == IDX_ROW64 ? row_hp(row) : hp;
     const int mx = valid ? p.ws_row_max[(int64_t)bh * LQ + (row - rlo)] : 0;
     uint32_t sum = valid ? (uint32_t)p.ws_row_sum[(int64_t)bh * LQ + (row - rlo)] : 0u;
-    if (sum == 0) sum = 1; // only rows outside [rlo, rhi); never stored
+    const bool big = __any(valid && sum <= BIG_ROW_SUM); // of any of the wave's rows: wave-uniform
+    if (!valid) sum = 1u << 24;                          // rows outside [rlo, rhi): all probabilities 0, never stored
     if (p.dbg_row_max && h == 0 && valid) p.dbg_row_max[(int64_t)bh * LQ + (row - rlo)] = mx;
     if (p.dbg_row_sum && h == 0 && valid) p.dbg_row_sum[(int64_t)bh * LQ + (row - rlo)] = (int32_t)sum;
     ScoreIndex<M> si;
     si.init(hrow, mx, top);
 
-    // Column sums of V over every key the steps below cover (the chunks of this range of tiles): the correction for
-    // feeding the probabilities to the signed MFMA as P - 128.  A small kernel ahead of this one left the sums of each chunk.
-    if (tid < D) {
-        const int32_t *cp = p.ws_colsum + (int64_t)(b * p.Hkv + kvh) * p.n_chunks * D + tid;
-        int32_t acc = 0;
-#pragma unroll 8
-        for (int c = clo; c < chi; ++c) acc += cp[(int64_t)c * D];
-        colsum[tid] = acc;
-    }
     publish_tiles_barrier(); // LUT_hat, K tiles tlo and tlo + 1, V tile tlo are in LDS
 
-    // per-row probability table: the byte at the place of idx = round(255 * LUT_hat[idx] / sum) - 128 as a byte; each lane of a row's pair
+    // per-row probability table: the byte at the place of idx is round(255 * LUT_hat[idx] / sum); each lane of a row's pair
     // computes half of the entries and stores them into both lanes' columns
     const uint32_t lane_base = (uint32_t)(4 * lane + wave);
     {
@@ -193,7 +180,7 @@ __global__ __launch_bounds__(NT, D == 128 ? 3 : 4) void sweep_c_kernel(const Fwd
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             const int kidx = 16 * h + j, at = ScoreIndex<M>::place(kidx, (int)top) & 31; // entries past the table go to rows nothing reads
-            const uint8_t byte = (uint8_t)((prob_u8(lut_b[kidx], sum, inv_2s) ^ 0x80u) & 0xffu);
+            const uint8_t byte = (uint8_t)prob_u8(lut_b[kidx], sum, inv_2s);
             PT[at * 256 + 4 * n + wave] = byte;
             PT[at * 256 + 4 * (n + 32) + wave] = byte;
         }
@@ -237,50 +224,47 @@ __global__ __launch_bounds__(NT, D == 128 ? 3 : 4) void sweep_c_kernel(const Fwd
 
     const int last = CAUSAL ? min(L - 1, row) : L - 1; // last key the lane's row sees
     // One step = sub-tile j: kf holds its K fragments and receives those of the next one.
-    auto step = [&](auto masked_tag, int j, const int8_t *Knext, const int8_t *Vcur) __attribute__((always_inline)) {
+    auto step = [&](auto masked_tag, auto big_tag, int j, const int8_t *Knext, const int8_t *Vcur) __attribute__((always_inline)) {
         constexpr bool MASKED = decltype(masked_tag)::value;
-        // no row of the wave sees a key of it: probability 0 (the column-sum correction counts every key of the tiles)
-        const bool hidden = MASKED && (32 * j >= L || (CAUSAL && 32 * j > qw0 + 31)); // wave-uniform
-        if (!hidden) {
-            v16i s = s0;
+        // no row of the wave sees a key of it, nor of any later one (wave-uniform)
+        if (MASKED && (32 * j >= L || (CAUSAL && 32 * j > qw0 + 31))) return;
+        v16i s = s0;
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb) s = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf[kb], qf[kb], s, 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            read_vf(Vcur, vf);
-            __builtin_amdgcn_sched_barrier(0);
-            const int lim = last - 32 * j - 4 * h;
-            uint32_t l[16];
+        for (int kb = 0; kb < KB; ++kb) s = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf[kb], qf[kb], s, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        read_vf(Vcur, vf);
+        __builtin_amdgcn_sched_barrier(0);
+        const int lim = last - 32 * j - 4 * h;
+        uint32_t l[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int sc = !MASKED || acc_key(i, 0) <= lim ? s[i] : si.hidden();
-                l[i] = PT[si.address(sc, lane_base)];
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const uint32_t a = __builtin_amdgcn_perm(l[4 * g + 1], l[4 * g], 0x0c0c0400u);
-                const uint32_t c = __builtin_amdgcn_perm(l[4 * g + 3], l[4 * g + 2], 0x0c0c0400u);
-                pf[g] = (int)__builtin_amdgcn_perm(c, a, 0x05040100u);
-            }
-        } else {
-            read_vf(Vcur, vf);
-            pf = v4i{(int)0x80808080, (int)0x80808080, (int)0x80808080, (int)0x80808080};
+        for (int i = 0; i < 16; ++i) {
+            const int sc = !MASKED || acc_key(i, 0) <= lim ? s[i] : si.hidden();
+            l[i] = PT[si.address(sc, lane_base)];
         }
         __builtin_amdgcn_sched_barrier(0);
-        read_kf(Knext, kf);
-        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) o[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(vf[cb], pf, o[cb], 0, 0, 0);
+        for (int g = 0; g < 4; ++g) {
+            const uint32_t a = __builtin_amdgcn_perm(l[4 * g + 1], l[4 * g], 0x0c0c0400u);
+            const uint32_t c = __builtin_amdgcn_perm(l[4 * g + 3], l[4 * g + 2], 0x0c0c0400u);
+            pf[g] = (int)__builtin_amdgcn_perm(c, a, 0x05040100u);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        constexpr bool BIG = decltype(big_tag)::value;
+        if (!BIG) read_kf(Knext, kf); // (ahead of P.V, which hides the latency; with BIG there are no registers for it)
+        __builtin_amdgcn_sched_barrier(0);
+        add_pv<BIG>(vf, pf, o);
+        __builtin_amdgcn_sched_barrier(0);
+        if (BIG) read_kf(Knext, kf);
         __builtin_amdgcn_sched_barrier(0);
     };
     // One iteration = V tile T and K tile T + 1.  With PAR = (T - tlo) & 1: K tile T + 2 replaces K tile T (read an
     // iteration ago) in Ks[PAR], V tile T + 1 replaces V tile T - 1 in Vs[PAR ^ 1].
-    auto iteration = [&](auto masked_tag, int T, int8_t *Kdma, int8_t *Vdma, const int8_t *Krd, const int8_t *Vrd)
+    auto iteration = [&](auto masked_tag, auto big_tag, int T, int8_t *Kdma, int8_t *Vdma, const int8_t *Krd, const int8_t *Vrd)
                          __attribute__((always_inline)) {
         if (T + 2 <= thi) dma_k(T + 2, Kdma);
         if (T + 1 < thi) dma_v(T + 1, Vdma);
 #pragma unroll
-        for (int u = 0; u < NSUB; ++u) step(masked_tag, NSUB * T + u, Krd + u * SUB, Vrd + u * SUB);
+        for (int u = 0; u < NSUB; ++u) step(masked_tag, big_tag, NSUB * T + u, Krd + u * SUB, Vrd + u * SUB);
         publish_tiles_barrier(); // K tile T + 2 and V tile T + 1 have landed; every wave is done with tile T
     };
 
@@ -295,18 +279,22 @@ __global__ __launch_bounds__(NT, D == 128 ? 3 : 4) void sweep_c_kernel(const Fwd
     const int nfull_sub = CAUSAL ? min(L / 32, (qw0 + 1) / 32) : L / 32;
     const int nhot = min(nfull_sub / NSUB, thi);
     int T = tlo;
+    auto hot = [&](auto big_tag) __attribute__((always_inline)) {
 #pragma unroll 1
-    for (; T + 2 <= nhot; T += 2) {
-        iteration(std::false_type{}, T, Ks0, Vs1, Ks1, Vs0);
-        iteration(std::false_type{}, T + 1, Ks1, Vs0, Ks0, Vs1);
-    }
+        for (; T + 2 <= nhot; T += 2) {
+            iteration(std::false_type{}, big_tag, T, Ks0, Vs1, Ks1, Vs0);
+            iteration(std::false_type{}, big_tag, T + 1, Ks1, Vs0, Ks0, Vs1);
+        }
+    };
+    if (big) hot(std::true_type{});
+    else hot(std::false_type{});
 #pragma unroll 1
     for (; T < thi; ++T) {
         const bool odd = (T - tlo) & 1;
-        iteration(std::true_type{}, T, odd ? Ks1 : Ks0, odd ? Vs0 : Vs1, odd ? Ks0 : Ks1, odd ? Vs1 : Vs0);
+        iteration(std::true_type{}, std::true_type{}, T, odd ? Ks1 : Ks0, odd ? Vs0 : Vs1, odd ? Ks0 : Ks1, odd ? Vs1 : Vs0);
     }
 
-    // Key-split launch: the accumulators of this range, corrected, for finish_split_kernel to add up
+    // Key-split launch: the accumulators of this range, for finish_split_kernel to add up
     if constexpr (SPLIT) {
         if (valid) {
             int32_t *Pp = p.ws_part + ((int64_t)ksp * p.B * p.Hq * LQ + (int64_t)bh * LQ + (row - rlo)) * D;
@@ -317,7 +305,7 @@ __global__ __launch_bounds__(NT, D == 128 ? 3 : 4) void sweep_c_kernel(const Fwd
                     const int ch0 = cb * 32 + 8 * g + 4 * h;
                     v4i a;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) a[r] = o[cb][4 * g + r] + 128 * colsum[ch0 + r];
+                    for (int r = 0; r < 4; ++r) a[r] = o[cb][4 * g + r];
                     *(v4i *)(Pp + ch0) = a;
                 }
             }
@@ -337,8 +325,7 @@ __global__ __launch_bounds__(NT, D == 128 ? 3 : 4) void sweep_c_kernel(const Fwd
                 uint32_t packed = 0;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    // the signed MFMA was fed P - 128: add 128 times the column sums of V back
-                    const int32_t acc = o[cb][4 * g + r] + 128 * colsum[ch0 + r];
+                    const int32_t acc = o[cb][4 * g + r];
                     if (DBG) p.dbg_acc[((int64_t)bh * LQ + (row - rlo)) * D + ch0 + r] = acc;
                     packed |= ((uint32_t)requant<FAST>(acc, hrow.rq_mult, hrow.rq_shift) & 0xffu) << (8 * r);
                 }
@@ -381,8 +368,7 @@ int launch_mode(const FwdParams &p_in, int idx_mode, hipStream_t st)
     return (int)hipGetLastError();
 }
 
-// p.n_qtiles must count tiles of 128 query rows, and the V chunk sums in p.ws_colsum must be over
-// chunks of as many keys; p.ws_row_max / ws_row_sum filled.  Instantiated in a source of its own for each D and SPLIT.
+// p.n_qtiles must count tiles of 128 query rows; p.ws_row_max / ws_row_sum filled.  Instantiated in a source of its own for each D and SPLIT.
 template <int D, bool SPLIT>
 int launch(const FwdParams &p, int idx_mode, hipStream_t st)
 {

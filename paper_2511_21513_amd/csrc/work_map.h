@@ -94,7 +94,7 @@ __host__ __device__ __forceinline__ WorkItem fwd_work_item(const FwdParams &p, i
     asm volatile("" ::"s"(m.groups), "s"(m.whole), "s"(m.left), "s"(m.units), "s"(m.dealt_mul), "s"(m.by_left.mul), "s"(m.by_left.shift),
                  "s"(m.by_group.mul), "s"(m.by_group.shift), "s"(m.by_hkv.mul), "s"(m.by_hkv.shift), "s"(m.by_batch.mul),
                  "s"(m.by_batch.shift), "s"(m.by_full.mul), "s"(m.by_full.shift), "s"(m.by_last.mul), "s"(m.by_last.shift),
-                 "s"(m.fold), "s"(g), "s"(gb), "s"(n_qtiles), "s"(hkv), "s"(p.one_scheme), "s"(p.hp_table));
+                 "s"(m.fold), "s"(g), "s"(gb), "s"(n_qtiles), "s"(hkv), "s"(p.hp_table));
 #endif
     const int xcd = bid & (NUM_XCD - 1), plain = bid >> 3, round = plain & ~31;
     // folded order: every other round of an XCD's 32 compute units in reverse
