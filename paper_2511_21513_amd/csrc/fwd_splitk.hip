@@ -54,7 +54,7 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
     __shared__ int32_t red[2][WAVES][32];                               // per-wave row max / row sum
     __shared__ double red_m[MODE == IDX_KGROUP ? WAVES : 1][32];        // per-wave maximum of the dequantized logits
     __shared__ uint32_t lut_lds[16];
-    extern __shared__ uint32_t PT[]; // [idx][row], NIDX * 32 words
+    extern __shared__ __attribute__((aligned(16))) uint32_t PT[]; // [idx][row], NIDX * 32 words; then, with p.kg_table, 8 bytes [key block][row]
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 31, h = lane >> 5;
     HeadParams hp = p.hp0;
@@ -94,7 +94,10 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
     const int8_t *Vp = p.v + (int64_t)b * p.vs[0] + (int64_t)kvh * p.vs[1];
 
     double sq_row = 0.0, Mreal = -__builtin_inf();
-    if constexpr (KG) sq_row = (double)p.sq_rows[(int64_t)bh * p.n_rowblk + (row_ok ? row - rlo : 0) / p.q_block];
+    auto scale_q = [&](int r) __attribute__((always_inline)) {
+        return (double)p.sq_rows[(int64_t)bh * p.n_rowblk + (r >= rlo && r < rhi ? r - rlo : 0) / p.q_block];
+    };
+    if constexpr (KG) sq_row = scale_q(row);
     // alpha^(g) of the logit (lane's row, key); keys past the end take the last block's scale
     auto kg_alpha = [&](int key) __attribute__((always_inline)) {
         return (sq_row * (double)skp[min(key, L - 1) / p.k_block]) / p.sqrt_d;
@@ -117,6 +120,24 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
 
     const int kmax = CAUSAL ? min(L, q0 + 32) : L; // keys any row of the block sees
     const int nsub = (kmax + 31) / 32;             // sub-tiles of the block; wave w takes w, w + 4, ...
+
+    // Key groups: the constants of each row for each block of keys, formed once by the workgroup instead of by every wave
+    // for every sub-tile and sweep (three double-precision divisions a lane): alpha^(g) for sweep A, then, in the same place,
+    // m^(g) and c_int^(g).  (1024 tokens, 32 / 8 heads, d 128, 128-row and 64-key groups: 61 -> KT us.)
+    const bool kg_table = KG && p.kg_table != 0; // uniform
+    double *const kt_alpha = (double *)(PT + NIDX * 32);
+    v2i *const kt = (v2i *)(PT + NIDX * 32);
+    auto kg_blk = [&](int j) __attribute__((always_inline)) { return quotient(j, p.by_k_subtiles); }; // of sub-tile j
+    auto each_group = [&](auto f) __attribute__((always_inline)) {
+        const int n_entries = (kg_blk(nsub - 1) + 1) * 32;
+        for (int e = tid; e < n_entries; e += NT) f(e);
+    };
+    if constexpr (KG) {
+        if (kg_table) {
+            each_group([&](int e) __attribute__((always_inline)) { kt_alpha[e] = (scale_q(q0 + (e & 31)) * (double)skp[e >> 5]) / p.sqrt_d; });
+            __syncthreads();
+        }
+    }
 
     // K fragments of sub-tile j straight from global memory: key row 32 j + n, bytes [32 kb + 16 h, +16)
     auto load_kf = [&](int j, v4i (&kf)[KB]) __attribute__((always_inline)) {
@@ -172,7 +193,8 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
                 for (int i = 0; i < 16; ++i)
                     if (full || visible(32 * j + acc_key(i, h))) lmax = max(lmax, s[i]);
                 if (lmax != INT32_MIN) {
-                    const double x = kg_alpha(32 * j) * (double)lmax; // alpha > 0: the block's largest logit
+                    const double al = kg_table ? kt_alpha[kg_blk(j) * 32 + n] : kg_alpha(32 * j);
+                    const double x = al * (double)lmax; // alpha > 0: the block's largest logit
                     Mreal = x > Mreal ? x : Mreal;
                 }
             } else {
@@ -226,19 +248,36 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
     // Key groups: the constants of the lane's row for the key block of `key`, as in the tiled kernel: c_int^(g) =
     // round(c / alpha^(g)) capped at 2^30, m^(g) = round(M / alpha^(g)) clamped to [-2^22, 2^30 + 2^22], which changes no
     // result (comparisons written so that a NaN from an unusable scale lands on a bound).
-    auto kg_index = [&](int key) __attribute__((always_inline)) {
-        const double al = kg_alpha(key);
+    auto kg_group = [&](double al, double M_row) __attribute__((always_inline)) {
         double cd = __builtin_floor(p.clip / al + 0.5);
         cd = cd >= 1.0 ? cd : 1.0;
         cd = cd < 1073741824.0 ? cd : 1073741824.0;
-        double md = __builtin_floor(Mreal / al + 0.5);
+        double md = __builtin_floor(M_row / al + 0.5);
         md = md < 1077936128.0 ? md : 1077936128.0;
         md = md > -4194304.0 ? md : -4194304.0;
-        ri.mx = (int)md;
-        ri.bound = ri.mx - (int)cd;
-        pick_map((int)cd);
+        return v2i{(int)md, (int)cd};
+    };
+    if constexpr (KG) {
+        if (kg_table) {
+            each_group([&](int e) __attribute__((always_inline)) { // (a thread meets the entries it wrote)
+                double M_row = red_m[0][e & 31];
+#pragma unroll
+                for (int w = 1; w < WAVES; ++w) {
+                    const double o = red_m[w][e & 31];
+                    M_row = o > M_row ? o : M_row;
+                }
+                kt[e] = kg_group(kt_alpha[e], M_row);
+            });
+            __syncthreads();
+        }
+    }
+    auto kg_index = [&](int key) __attribute__((always_inline)) {
+        const v2i g = kg_table ? kt[kg_blk(key >> 5) * 32 + n] : kg_group(kg_alpha(key), Mreal);
+        ri.mx = g[0];
+        ri.bound = g[0] - g[1];
+        pick_map(g[1]);
         if (!single) {
-            const uint64_t bits = (uint64_t)__double_as_longlong((double)top / cd) + 1ull; // the double after top / c_int
+            const uint64_t bits = (uint64_t)__double_as_longlong((double)top / (double)g[1]) + 1ull; // the double after top / c_int
             ri.negr = __longlong_as_double((long long)(bits ^ 0x8000000000000000ull));
         }
     };
@@ -435,7 +474,14 @@ int launch_mode(const FwdParams &p_in, int idx_mode, hipStream_t st)
     const int64_t n_wg = fwd_map_work(p);
     p.map.fold = fold_slots(n_wg, CAUSAL, splitk_waves(D, idx_mode));
     const dim3 grid((unsigned)n_wg), block(NT);
-    const unsigned sh = (unsigned)((p.top < 32 ? 32 : 64) * 32 * sizeof(uint32_t)); // the per-row probability table
+    unsigned sh = (unsigned)((p.top < 32 ? 32 : 64) * 32 * sizeof(uint32_t)); // the per-row probability table
+    p.kg_table = 0;
+    if (idx_mode == IDX_KGROUP && p.k_block % 32 == 0) {
+        p.by_k_subtiles = fast_div((uint32_t)(p.k_block / 32));
+        // up to 64 blocks of keys, 16 KiB, which leave two workgroups a compute unit at d = 128 (51 KiB without)
+        p.kg_table = p.n_kblk <= 64 ? 1 : 0;
+        if (p.kg_table) sh += (unsigned)p.n_kblk * 32u * 8u;
+    }
     if (idx_mode == IDX_FMA)
         hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_FMA>), grid, block, sh, st, p);
     else if (idx_mode == IDX_DEVICE)

@@ -75,6 +75,8 @@ struct FwdParams {
     // [B * Hkv][n_kblk] (device), the clip bound c and sqrt(d), and the per-head status words (non-zero: zeros out)
     const float *sq_rows, *sk_blocks;
     int32_t k_block, n_kblk;
+    FastDiv by_k_subtiles;      // by the 32-key sub-tiles of a block of keys (k_block a multiple of 32)
+    int32_t kg_table;           // fwd_splitk.hip: a workgroup keeps the constants of its rows for every block of keys in LDS
     double clip, sqrt_d;
     const int32_t *head_status;
     HeadParams hp0;             // the single parameter set when hp_table == nullptr
@@ -127,6 +129,7 @@ struct QuantBatch {
     int32_t n;
     uint32_t first[5];
     uint32_t gx[4];
+    int32_t loops;       // rounds of a workgroup in the second pass
 };
 
 // Arguments of IndexSoftmax as an operator on INT32 logits (Sec. 3.1-3.2).

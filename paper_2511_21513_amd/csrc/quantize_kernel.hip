@@ -12,6 +12,8 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <type_traits>
+
 #include "kernel_common.h"
 #include "params.h"
 
@@ -21,19 +23,32 @@ namespace {
 
 constexpr int QNT = 256;   // threads per workgroup
 constexpr int QITEMS = 4;  // 8-element items per thread in flight
-constexpr int QLOOP = 4;   // rounds of QITEMS items per thread in the second pass: the reduction of the partial
-                           // maxima at the start of a workgroup is paid once per 64 KiB of input
+constexpr int QLOOP_MAX = 4; // rounds of QITEMS items per thread in the second pass, which share one reduction of the partial maxima
+// Workgroups that the second pass is cut into where the tensors allow: six a compute unit.  (Always four rounds: Q, K, V of 2 x
+// 2048 tokens, 32 / 8 heads, fp16, 29.7 us for both passes, now 28.0; V of 1024 tokens, 8 heads, 14.7 -> 8.7; 3 x 100 tokens, 8
+// heads, 10.3 -> 7.7.  3072 workgroups: 29.7, 8.7, 7.8.)
+constexpr int64_t QWGS = 1536;
+constexpr int RHOLD = 8;   // items per thread that quantize_rows_kernel holds between its two passes
 
-// eight consecutive elements of a row as fp32 (widening fp16 / bf16 is exact)
-template <int DTYPE>
-__device__ __forceinline__ void load8(const uint8_t *p, float (&x)[8])
+// eight consecutive elements of a row as they are in memory, and as fp32 (widening fp16 / bf16 is exact)
+template <int DTYPE> struct Raw8 {
+    uint4 v[DTYPE == 0 ? 2 : 1];
+};
+template <int DTYPE> __device__ __forceinline__ Raw8<DTYPE> load_raw8(const uint8_t *p)
 {
-    if (DTYPE == 0) {
-        const float4 a = *(const float4 *)p, b = *(const float4 *)(p + 16);
-        x[0] = a.x, x[1] = a.y, x[2] = a.z, x[3] = a.w, x[4] = b.x, x[5] = b.y, x[6] = b.z, x[7] = b.w;
+    Raw8<DTYPE> r;
+    r.v[0] = *(const uint4 *)p;
+    if constexpr (DTYPE == 0) r.v[1] = *(const uint4 *)(p + 16);
+    return r;
+}
+template <int DTYPE> __device__ __forceinline__ void widen8(const Raw8<DTYPE> &raw, float (&x)[8])
+{
+    const uint32_t w[4] = {raw.v[0].x, raw.v[0].y, raw.v[0].z, raw.v[0].w};
+    if constexpr (DTYPE == 0) {
+        const uint32_t u[4] = {raw.v[1].x, raw.v[1].y, raw.v[1].z, raw.v[1].w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = __uint_as_float(w[i]), x[4 + i] = __uint_as_float(u[i]);
     } else {
-        const uint4 r = *(const uint4 *)p;
-        const uint32_t w[4] = {r.x, r.y, r.z, r.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if (DTYPE == 1) {
@@ -45,6 +60,10 @@ __device__ __forceinline__ void load8(const uint8_t *p, float (&x)[8])
             }
         }
     }
+}
+template <int DTYPE> __device__ __forceinline__ void load8(const uint8_t *p, float (&x)[8])
+{
+    widen8<DTYPE>(load_raw8<DTYPE>(p), x);
 }
 
 // Eight elements to INT8: q = clamp(rint(x / s), -127, 127) with x / s the IEEE fp32 quotient and rint to nearest,
@@ -162,7 +181,7 @@ __global__ __launch_bounds__(QNT) void absmax_kernel(const QuantBatch qb)
 }
 
 template <int DTYPE>
-__device__ __forceinline__ void quantize_body(const QuantParams &p, uint32_t bx, uint32_t by)
+__device__ __forceinline__ void quantize_body(const QuantParams &p, int loops, uint32_t bx, uint32_t by)
 {
     constexpr int ES = DTYPE == 0 ? 4 : 2;
     const int bh = (int)by, b = bh / p.H, h = bh % p.H;
@@ -190,14 +209,14 @@ __device__ __forceinline__ void quantize_body(const QuantParams &p, uint32_t bx,
     int8_t *dst = p.dst + (int64_t)b * p.ds[0] + (int64_t)h * p.ds[1];
     const int ipr = p.d / 8;
     const int64_t items = (int64_t)p.L * ipr;
-    for (int r = 0; r < QLOOP; ++r) {
+    for (int r = 0; r < loops; ++r) {
         // QITEMS loads in flight per thread, then the arithmetic and the stores
         float x[QITEMS][8];
         int64_t dofs[QITEMS];
         bool live[QITEMS];
 #pragma unroll
         for (int j = 0; j < QITEMS; ++j) {
-            const int64_t it = ((int64_t)(bx * QLOOP + r) * QITEMS + j) * QNT + threadIdx.x;
+            const int64_t it = ((int64_t)(bx * (uint32_t)loops + r) * QITEMS + j) * QNT + threadIdx.x;
             live[j] = it < items;
             dofs[j] = 0;
 #pragma unroll
@@ -224,56 +243,91 @@ __global__ __launch_bounds__(QNT) void quantize_kernel(const QuantBatch qb)
     for (int i = 0; i < 4; ++i) gx[i] = qb.gx[i];
     const BatchSlot sl = batch_slot(qb, qb.first[qb.n] - 1u - blockIdx.x, gx); // backwards through the grid
     const QuantParams &p = qb.t[sl.ti];
-    if (p.dtype == 0) quantize_body<0>(p, sl.bx, sl.by);
-    else if (p.dtype == 1) quantize_body<1>(p, sl.bx, sl.by);
-    else quantize_body<2>(p, sl.bx, sl.by);
+    if (p.dtype == 0) quantize_body<0>(p, qb.loops, sl.bx, sl.by);
+    else if (p.dtype == 1) quantize_body<1>(p, qb.loops, sl.bx, sl.by);
+    else quantize_body<2>(p, qb.loops, sl.bx, sl.by);
 }
 
 // One scale per block of q_block rows of a (b, h) slice (Sec. 3.3; per token at q_block = 1).  A
-// group is small, so one team (a wave, or the workgroup for groups above 4096 elements) takes it
-// whole: max|X| over the group, then the same arithmetic as above; the second read of the group
-// comes from the caches.
+// group is small, so one team (16 lanes up to 256 elements, a wave up to 4096, else the workgroup) takes it
+// whole: max|X| over the group, then the same arithmetic as above.
 template <int DTYPE, int NTHR>
 __global__ __launch_bounds__(QNT) void quantize_rows_kernel(const QuantParams p)
 {
     constexpr int ES = DTYPE == 0 ? 4 : 2;
     __shared__ float wmax[QNT / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int t = NTHR == 64 ? lane : tid;
+    const int t = tid % NTHR; // NTHR == QNT: the workgroup is the team; 64: a wave; 16: a quarter of a wave
     const int nblk = (p.L + p.q_block - 1) / p.q_block;
-    const int64_t gi = NTHR == 64 ? (int64_t)blockIdx.x * (QNT / 64) + wave : (int64_t)blockIdx.x;
-    if (gi >= (int64_t)p.B * p.H * nblk) return; // a whole wave of the four-group layout
+    const int64_t gi = (int64_t)blockIdx.x * (QNT / NTHR) + tid / NTHR;
+    if (gi >= (int64_t)p.B * p.H * nblk) return; // a whole team (of a wave or less: no barrier below)
     const int blk = (int)(gi % nblk), bh = (int)(gi / nblk), b = bh / p.H, h = bh % p.H;
     const int r0 = blk * p.q_block, r1 = min(p.L, r0 + p.q_block);
     const int ipr = p.d / 8, items = (r1 - r0) * ipr;
     const uint8_t *src = (const uint8_t *)p.src + (int64_t)b * p.ss[0] + (int64_t)h * p.ss[1] + (int64_t)r0 * p.ss[2];
     int8_t *dst = p.dst + (int64_t)b * p.ds[0] + (int64_t)h * p.ds[1] + (int64_t)r0 * p.ds[2];
+    auto offsets = [&](int it, int64_t &so, int64_t &dofs) __attribute__((always_inline)) {
+        item_offsets<ES>(p, (uint32_t)it, (uint32_t)ipr, so, dofs);
+    };
     float m = 0.0f;
-    for (int it = t; it < items; it += NTHR) {
-        const int row = it / ipr, c = it - row * ipr;
+    auto take = [&](const Raw8<DTYPE> &r) __attribute__((always_inline)) {
         float x[8];
-        load8<DTYPE>(src + (int64_t)row * p.ss[2] + (int64_t)c * 8 * ES, x);
+        widen8<DTYPE>(r, x);
 #pragma unroll
         for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(x[i]));
-    }
+    };
+    auto load = [&](int it) __attribute__((always_inline)) {
+        int64_t so, dofs;
+        offsets(it, so, dofs);
+        return load_raw8<DTYPE>(src + so);
+    };
+    float s = 0.0f, rs = 0.0f;
+    auto scale = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-    if (NTHR != 64) {
-        if (lane == 0) wmax[wave] = m;
-        __syncthreads();
+        for (int o = NTHR < 64 ? NTHR / 2 : 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+        if (NTHR == QNT) {
+            if (lane == 0) wmax[wave] = m;
+            __syncthreads();
 #pragma unroll
-        for (int w = 0; w < QNT / 64; ++w) m = fmaxf(m, wmax[w]);
-    }
-    const float s = fmaxf(m, 1e-12f) / 127.0f; // one IEEE fp32 division
-    const float rs = 1.0f / s;                 // and its reciprocal, for quantize8
-    if (t == 0) p.scales[gi] = s;
-    for (int it = t; it < items; it += NTHR) {
-        const int row = it / ipr, c = it - row * ipr;
+            for (int w = 0; w < QNT / 64; ++w) m = fmaxf(m, wmax[w]);
+        }
+        s = fmaxf(m, 1e-12f) / 127.0f; // one IEEE fp32 division
+        rs = 1.0f / s;                 // and its reciprocal, for quantize8
+        if (t == 0) p.scales[gi] = s;
+    };
+    auto put = [&](int it, const Raw8<DTYPE> &r) __attribute__((always_inline)) {
         float x[8];
-        load8<DTYPE>(src + (int64_t)row * p.ss[2] + (int64_t)c * 8 * ES, x);
+        widen8<DTYPE>(r, x);
         uint32_t w[2];
         quantize8(x, s, rs, w);
-        *(uint2 *)(dst + (int64_t)row * p.ds[2] + (int64_t)c * 8) = make_uint2(w[0], w[1]);
+        int64_t so, dofs;
+        offsets(it, so, dofs);
+        *(uint2 *)(dst + dofs) = make_uint2(w[0], w[1]);
+    };
+    // Groups of up to RHOLD items a thread are read once, all of them in flight, and held as they are; larger ones are read
+    // again, from the caches.  (With one load in flight and two reads: 32 x 1024 rows of 128 in blocks of 128 rows 9.6 us, now
+    // 7.0; with a test before each load 8.1.)
+    auto hold = [&](auto count) __attribute__((always_inline)) {
+        constexpr int N = decltype(count)::value;
+        Raw8<DTYPE> raw[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) raw[j] = load(min(t + j * NTHR, items - 1)); // past the end: the last item once more
+#pragma unroll
+        for (int j = 0; j < N; ++j) take(raw[j]);
+        scale();
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+            if (t + j * NTHR < items) put(t + j * NTHR, raw[j]);
+    };
+    if (items <= NTHR) hold(std::integral_constant<int, 1>{});
+    else if (items <= 2 * NTHR) hold(std::integral_constant<int, 2>{});
+    else if (items <= 4 * NTHR) hold(std::integral_constant<int, 4>{});
+    else if (items <= RHOLD * NTHR) hold(std::integral_constant<int, RHOLD>{});
+    else {
+#pragma unroll 4
+        for (int it = t; it < items; it += NTHR) take(load(it));
+        scale();
+        for (int it = t; it < items; it += NTHR) put(it, load(it));
     }
 }
 
@@ -281,7 +335,9 @@ template <int DTYPE>
 int launch_rows(const QuantParams &p, hipStream_t st)
 {
     const int64_t groups = (int64_t)p.B * p.H * ((p.L + p.q_block - 1) / p.q_block);
-    if ((int64_t)p.q_block * p.d <= 4096)
+    if ((int64_t)p.q_block * p.d <= 256) // one or two items a thread; per token most of a wave would idle (2048 tokens, 32 heads, d 128: 38 -> 11.7 us)
+        hipLaunchKernelGGL((quantize_rows_kernel<DTYPE, 16>), dim3((unsigned)((groups + 15) / 16)), dim3(QNT), 0, st, p);
+    else if ((int64_t)p.q_block * p.d <= 4096)
         hipLaunchKernelGGL((quantize_rows_kernel<DTYPE, 64>), dim3((unsigned)((groups + 3) / 4)), dim3(QNT), 0, st, p);
     else
         hipLaunchKernelGGL((quantize_rows_kernel<DTYPE, QNT>), dim3((unsigned)groups), dim3(QNT), 0, st, p);
@@ -316,6 +372,11 @@ int launch_quantize(const QuantParams *ps, int n, void *stream)
     QuantBatch qb;
     memset(&qb, 0, sizeof(qb));
     qb.n = n;
+    // Rounds of the second pass: as many as leave QWGS workgroups.
+    int64_t rounds = 0;
+    for (int i = 0; i < n; ++i)
+        rounds += (int64_t)ps[i].B * ps[i].H * (((int64_t)ps[i].L * (ps[i].d / 8) + QNT * QITEMS - 1) / (QNT * QITEMS));
+    qb.loops = (int)(rounds / QWGS < 1 ? 1 : (rounds / QWGS > QLOOP_MAX ? QLOOP_MAX : rounds / QWGS));
     uint64_t tot_a = 0, tot_q = 0;
     uint32_t first_a[5] = {0, 0, 0, 0, 0};
     for (int i = 0; i < n; ++i) {
@@ -323,7 +384,8 @@ int launch_quantize(const QuantParams *ps, int n, void *stream)
         if (p.per_head == 2 || p.dtype < 0 || p.dtype > 2) return (int)hipErrorInvalidValue;
         qb.t[i] = p;
         const int64_t items = (int64_t)p.L * (p.d / 8);
-        qb.gx[i] = (uint32_t)((items + QNT * QITEMS * QLOOP - 1) / (QNT * QITEMS * QLOOP));
+        const int64_t per_wg = (int64_t)QNT * QITEMS * qb.loops;
+        qb.gx[i] = (uint32_t)((items + per_wg - 1) / per_wg);
         first_a[i] = (uint32_t)tot_a;
         qb.first[i] = (uint32_t)tot_q;
         tot_a += (uint64_t)p.n_partial * (uint64_t)(p.B * p.H);
