@@ -545,13 +545,14 @@ struct Choice {
     int variant;
     bool decode; // the split-key kernels for few query rows
     KeySplit ks; // variant VARIANT_KEY_SPLIT: workgroups per query tile
+    bool in_split_room; // row maxima and sums in the key split's room (never moved), not in the workspace
 };
 
-// idx_mode: the index map of the call's scales; may_split: room for a key split can be had.
+// idx_mode: the index map of the call's scales; may_split: the key split's room can be had.
 Choice choose_kernels(const intattn_ctx *ctx, const intattn_args *a, const RunMode &rm, int idx_mode, bool may_split)
 {
     const int Lk = a->Lkv ? a->Lkv : a->L;
-    Choice ch = {fwd_choose_variant(ctx->variant, a->B, a->Hq, a->L, Lk, a->d, a->causal), false, {0, 0}};
+    Choice ch = {fwd_choose_variant(ctx->variant, a->B, a->Hq, a->L, Lk, a->d, a->causal), false, {0, 0}, false};
     if (ch.variant == 5 && ctx->lut_bits > 5) ch.variant = 4; // the pipelined sweep C holds 32-entry tables; same tiling otherwise
     const bool automatic = ctx->variant == 0 || ctx->variant == 9 || ctx->variant == 10;
     // Groups (scale modes 2 and 3): the keys split over the waves of a workgroup win up to 256 workgroups of 128 rows, up to
@@ -582,6 +583,16 @@ Choice choose_kernels(const intattn_ctx *ctx, const intattn_args *a, const RunMo
     // Short key sequences at d = 64 with the fma map: all scores in registers (fwd_short.hip)
     if (!rm.dynamic && idx_mode == IDX_FMA && a->scale_mode < 2 && fwd_short_serves(ch.variant, a->B, a->Hq, a->L, Lk, a->d, a->causal))
         ch.variant = VARIANT_SHORT;
+    // Square problems (measured with the fma map).  Variant 3 takes no memory, so what replaces it must not make the workspace
+    // grow, which frees memory that captured launches may still use.
+    const bool fma = idx_mode == IDX_FMA || idx_mode == IDX_DEVICE;
+    if (fma && a->scale_mode < 2 && a->L == Lk && !rm.no_alloc) {
+        const int v = fwd_refine_square(ch.variant, a->B, a->Hq, a->L, a->d, a->causal);
+        if (ch.variant != 3 || v == 3 || may_split) {
+            ch.in_split_room = ch.variant == 3 && v != 3;
+            ch.variant = v;
+        }
+    }
     return ch;
 }
 
@@ -698,10 +709,10 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
     p.group = a->Hq / a->Hkv;
     p.top = (1 << ctx->lut_bits) - 1;
     Choice ch = choose_kernels(ctx, a, rm, dv.idx_mode, !rm.reserve);
-    if (ch.ks.c > 0) {
+    if (ch.ks.c > 0 || ch.in_split_room) {
         bool room = true;
         if ((size_t)split_words(a, ch.ks.c) > ctx->split_cap) {
-            // a call that is being captured must not allocate: it runs as if the keys could not be split
+            // a call that is being captured must not allocate: it runs as if the room could not be had
             hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
             room = hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
             if (!room) (void)hipGetLastError();
@@ -909,6 +920,8 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
             p.split_ab = ch.ks.ab;
             p.split_c = ch.ks.c;
             base = p.ws_part + (size_t)ch.ks.c * rows * a->d;
+        } else if (ch.in_split_room) {
+            base = ctx->d_split;
         } else {
             rc = get_ws(2 * rows + kept);
             if (rc) return rc;

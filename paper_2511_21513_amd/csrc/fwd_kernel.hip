@@ -107,6 +107,33 @@ int fwd_choose_variant(int variant, int B, int Hq, int L, int Lk, int d, int cau
     if (workgroups <= 256) return 3;
     return (d == 64 && L >= 1024) ? 3 : 1;
 }
+// Square problems that neither split their keys nor hold all scores in registers: a second look at variants 1 and 3 around the
+// points where one of them starts a further round of workgroups (W = workgroups of 128 rows).  Rectangular ones, whose tiles
+// are as long as their keys and not as their rows, keep the choice above.  us, this choice against the one above:
+//   d 128: variant 3 holds 512 workgroups of 32 rows at a time and every one is as long without a mask: 1 past that (192 x 197:
+//     96 heads 16.2 against 20.0; 1024, 32 heads 38 against 58; at 504 workgroups, 384, 42 heads, 19.3 against 16.0 for 3).
+//     Variant 1 holds 512 workgroups: past that 5 with its finer launches (1024 masked, 120 heads 59.9 against 68.7; 197, 330
+//     heads 24.0 against 33.2; 4096 without a mask, 17 heads 211 against 259), but not under the mask beyond 2048 keys (4096, 24
+//     heads: 161 against 135), nor without one below 768 keys past 768 (384, 310 heads: 49 against 44; 250 heads: 37.7 against 40.0).  Under the mask 5 is
+//     ahead for 1025 to 2048 keys already from 257 (2048, 20 heads: 65.8 against 72.4; 1024, 60 heads: 42 both), and for short
+//     rows past 1023 too (640, 300 heads: 71 against 86).
+//   d 64: variant 3 where the chip is full of it loses to 5, past 640 under the mask (1024, 116 heads: 32.4 against 39.1; 4096, 19
+//     heads, W 608: 93.5 against 86.5 for 3) and past 400 without (2048, 28 heads: 60.6 against 72.3; 24 heads, W 384: 57 both).
+//     Rows below 1024: 3 up to 448 under the mask (640, 64 heads: 18.1 against 23.7; W 450: 23.2 against 23.8; W 540: 25.1 against 23.9), 5 past 800
+//     (640, 192 heads: 27.9 against 35.2; W 750: 25.7 against 25.9 for 1), short rows without a mask past 1023 excepted.
+int fwd_refine_square(int variant, int B, int Hq, int L, int d, int causal)
+{
+    if (variant != 1 && variant != 3) return variant;
+    const int64_t heads = (int64_t)B * Hq, w = heads * ((L + 127) / 128);
+    if (d == 128) {
+        if (variant == 3) return !causal && heads * ((L + 31) / 32) > 512 ? 1 : 3;
+        if (causal) return L <= 2048 && w > (L > 1024 ? 256 : 512) ? 5 : 1;
+        return w > 512 && w < 1024 && (L >= 768 || w <= 768) ? 5 : 1;
+    }
+    if (variant == 3) return w > (causal ? 640 : 400) ? 5 : 3;
+    if (causal && w <= 448) return 3;
+    return w > 800 && (causal || w < 1024) ? 5 : 1;
+}
 bool fwd_variant_known(int variant) { return variant == 0 || (variant >= 1 && variant <= 5) || variant == 9 || variant == 10; }
 
 // Workgroups per query tile for the key-split path, and whether it pays at all: a model of its time against one of the
