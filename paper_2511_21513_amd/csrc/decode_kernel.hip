@@ -581,15 +581,23 @@ __global__ __launch_bounds__(NT, 4) void decode_fused_kernel(const FwdParams p)
             const AnyIndex index(row_hp[nn], p.top);
             const bool full = key0 + 32 <= p.Lk && (!p.causal || key0 + 31 <= p.row_lo + ri);
             uint32_t w = 0, sum = 0;
+            if (__builtin_amdgcn_ballot_w64(!(full && index.fma)) == 0) { // every lane: no branch between the four
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                uint32_t idx = 64u; // hidden key: probability 0
-                if (full || key_visible(p, key0 + acc_key(4 * g + j, hh), ri)) {
-                    const int delta = WIDE ? base - (int)u[j] : base + (int)u[j]; // scores are below 2^22 in magnitude
-                    idx = index(delta);
-                    sum += lut_b[idx];
+                for (int j = 0; j < 4; ++j) w = index.place(WIDE ? base - (int)u[j] : base + (int)u[j], j, w);
+                w = (uint32_t)p.top * 0x01010101u - w; // (no borrow: a place is at most top)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) sum += lut_b[(w >> (8 * j)) & 0xffu];
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    uint32_t idx = 64u; // hidden key: probability 0
+                    if (full || key_visible(p, key0 + acc_key(4 * g + j, hh), ri)) {
+                        const int delta = WIDE ? base - (int)u[j] : base + (int)u[j]; // scores are below 2^22 in magnitude
+                        idx = index(delta);
+                        sum += lut_b[idx];
+                    }
+                    w |= idx << (8 * j);
                 }
-                w |= idx << (8 * j);
             }
             sc16[UW * q] = w; // the unit's first word now holds its four indices
             if (nn != acc_row) {

@@ -117,9 +117,14 @@ struct AnyIndex {
         : hp(hp_), c_int(hp_.c_int), add0(0x4b000000 + hp_.c_int), top(top_), r(__uint_as_float(hp_.fma_r)), b(r * -8388608.0f), fma(hp_.pad[0] == IDX_FMA)
     {
     }
+    // with the fma map: top minus the index, into byte j of w
+    __device__ __forceinline__ uint32_t place(int delta, int j, uint32_t w) const
+    {
+        return __builtin_amdgcn_cvt_pk_u8_f32(__builtin_fmaf(__uint_as_float((uint32_t)(add0 - delta)), r, b), j, w);
+    }
     __device__ __forceinline__ uint32_t operator()(int delta) const
     {
-        if (fma) return (uint32_t)top - __builtin_amdgcn_cvt_pk_u8_f32(__builtin_fmaf(__uint_as_float((uint32_t)(add0 - delta)), r, b), 0, 0);
+        if (fma) return (uint32_t)top - place(delta, 0, 0);
         return (uint32_t)(int)__builtin_fma(-(double)min(delta, c_int), idx_fp64_factor(hp), 0.5);
     }
 };
