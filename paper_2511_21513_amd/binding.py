@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 
 import numpy as np
 
@@ -69,6 +70,10 @@ class Args(ctypes.Structure):
     ]
 
 
+_ARGS = struct.Struct("@6i4P12q2i7P2i")  # the same, with the padding of the platform
+assert _ARGS.size == ctypes.sizeof(Args)
+
+
 class SoftmaxArgs(ctypes.Structure):
     _fields_ = [
         ("rows", ctypes.c_int64), ("cols", ctypes.c_int32), ("c_int", ctypes.c_int32),
@@ -90,6 +95,7 @@ class QuantArgs(ctypes.Structure):
 
 
 _lib = None
+_F32 = np.dtype(np.float32)
 
 
 def load() -> ctypes.CDLL:
@@ -148,9 +154,17 @@ def load() -> ctypes.CDLL:
 
 
 def _host_f32(x):
-    if x is None:
-        return None
+    if x is None or (type(x) is np.ndarray and x.dtype == _F32 and x.ndim and x.flags.c_contiguous):
+        return x
     return np.ascontiguousarray(np.atleast_1d(np.asarray(x, dtype=np.float32)))
+
+
+def _address(x):
+    """Address of a host array (``x.ctypes.data`` at half its time, for arrays that can be written to)."""
+    try:
+        return ctypes.addressof(ctypes.c_char.from_buffer(x))
+    except (TypeError, ValueError):
+        return x.ctypes.data
 
 
 class IntAttn:
@@ -223,21 +237,15 @@ class IntAttn:
         ``q_block`` query rows of every (batch, head), s_k and s_v one per KV head.  ``k_block`` > 0 as
         well: scale mode 3, s_k holds one value per block of ``k_block`` keys of every (batch, KV head)."""
         B, Hq, L, d = q.shape
-        Hkv = k.shape[1]
-        if k.shape != v.shape or k.shape[0] != B or k.shape[3] != d or out.shape != q.shape:
+        ks = k.shape
+        Hkv = ks[1]
+        if ks != v.shape or ks[0] != B or ks[3] != d or out.shape != q.shape:
             raise ValueError("q, out must be [B,Hq,L,d] and k, v [B,Hkv,Lkv,d]")
-        for t in (q, k, v, out):
-            if t.stride(-1) != 1:
+        strides = q.stride(), k.stride(), v.stride(), out.stride()
+        for st in strides:
+            if st[-1] != 1:
                 raise ValueError("the head dimension must be contiguous")
-        a = Args()
-        a.B, a.Hq, a.Hkv, a.L, a.d, a.causal = B, Hq, Hkv, L, d, int(bool(causal))
-        a.q, a.k, a.v, a.out = q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr()
-        a.q_stride = (ctypes.c_int64 * 3)(*q.stride()[:3])
-        a.k_stride = (ctypes.c_int64 * 3)(*k.stride()[:3])
-        a.v_stride = (ctypes.c_int64 * 3)(*v.stride()[:3])
-        a.out_stride = (ctypes.c_int64 * 3)(*out.stride()[:3])
-        a.scale_mode = int(bool(per_head))
-        a.Lkv = k.shape[2]
+        lkv = ks[2]
         if device_scales:
             import torch
 
@@ -246,20 +254,21 @@ class IntAttn:
                 if t is not None and (t.dtype != torch.float32 or not t.is_cuda or not t.is_contiguous()):
                     raise ValueError("device scales must be contiguous float32 tensors on the GPU")
             sizes = [t.numel() if t is not None else None for t in keep]
-            ptr = lambda t: t.data_ptr()  # noqa: E731
+            ptr = [t.data_ptr() for t in keep[:3]] + [s_o.data_ptr() if s_o is not None else 0]
         else:
             keep = [_host_f32(s_q), _host_f32(s_k), _host_f32(s_v), _host_f32(s_o)]
             sizes = [t.size if t is not None else None for t in keep]
-            ptr = lambda t: t.ctypes.data  # noqa: E731
+            ptr = [_address(t) for t in keep[:3]] + [_address(keep[3]) if keep[3] is not None else 0]
+        scale_mode = int(bool(per_head))
         if q_block:
             if not device_scales:
                 raise ValueError("q_block needs device_scales")
             n_grp = B * Hq * ((L + q_block - 1) // q_block)
-            a.scale_mode, a.q_block = 2, int(q_block)
+            scale_mode = 2
             want = [n_grp, Hkv, Hkv, n_grp]
             if k_block:
-                a.scale_mode, a.k_block = 3, int(k_block)
-                want[1] = B * Hkv * ((k.shape[2] + k_block - 1) // k_block)
+                scale_mode = 3
+                want[1] = B * Hkv * ((lkv + k_block - 1) // k_block)
         elif k_block:
             raise ValueError("k_block needs q_block (use q_block = L for one query scale per head)")
         else:
@@ -267,11 +276,15 @@ class IntAttn:
         for have, need in zip(sizes, want):
             if have is not None and (have != need if (per_head or q_block) else have < 1):
                 raise ValueError("scale arrays do not have the number of entries the scale mode needs")
-        a.scale_q, a.scale_k, a.scale_v = (ptr(x) for x in keep[:3])
-        a.scale_out = ptr(keep[3]) if keep[3] is not None else None
-        a.dbg_row_max = row_max.data_ptr() if row_max is not None else None
-        a.dbg_row_sum = row_sum.data_ptr() if row_sum is not None else None
-        a.dbg_acc = acc.data_ptr() if acc is not None else None
+        (q0, q1, q2), (k0, k1, k2), (v0, v1, v2), (o0, o1, o2) = (st[:3] for st in strides)
+        # one pack instead of an assignment for each field
+        a = Args.from_buffer_copy(_ARGS.pack(
+            B, Hq, Hkv, L, d, int(bool(causal)), q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
+            q0, q1, q2, k0, k1, k2, v0, v1, v2, o0, o1, o2, scale_mode, lkv, *ptr,
+            row_max.data_ptr() if row_max is not None else 0, row_sum.data_ptr() if row_sum is not None else 0,
+            acc.data_ptr() if acc is not None else 0, 0, 0))
+        if q_block:
+            a.q_block, a.k_block = int(q_block), int(k_block or 0)
         return a, keep
 
     def forward_args(self, args: Args, stream: int = 0, quantonly: bool = False):
@@ -400,7 +413,7 @@ class IntAttn:
         return outs, scales
 
     def forward_stage(self, args: Args, stage: int, stream: int = 0):
-        """intattn_forward_stage: 0 = everything, 1 = column sums and sweeps A+B, 2 = sweep C."""
+        """intattn_forward_stage: 0 = everything, 1 = sweeps A+B, 2 = sweep C."""
         rc = self._lib.intattn_forward_stage(self._ctx, ctypes.byref(args), ctypes.c_void_p(stream), stage)
         if rc != OK:
             raise IntAttnError(rc, self.last_error())
@@ -423,7 +436,8 @@ class IntAttn:
             }
         args, keep = self.make_args(q, k, v, out, s_q, s_k, s_v, s_o, causal=causal, per_head=per_head, **extra)
         if stream is None:
-            stream = torch.cuda.current_stream(q.device).cuda_stream
+            # the handle alone, without a Stream object around it
+            stream = torch._C._cuda_getCurrentRawStream(q.device.index) if q.is_cuda else torch.cuda.current_stream(q.device).cuda_stream
         self.forward_args(args, stream, quantonly)
         del keep
         if taps:
