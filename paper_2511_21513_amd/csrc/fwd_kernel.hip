@@ -90,7 +90,7 @@ int launch_neutral_rows(const FwdParams &p, hipStream_t st)
 //   4  two launches: sweeps A+B (32 or 64 rows per wave), then sweep C (32 rows per wave), phase-ordered kernels
 //   5  as 4 with sweep C's kernel of its own
 //   9, 10  the split-key kernels of decode_kernel.hip (one launch / four launches) whenever the shape allows them, else as 0
-// Automatic choice among the tiled kernels, by measurement on shapes from 8 x 12 x 197 to 2 x 32 x 4096 (W = workgroups
+// Automatic choice among the tiled kernels (square problems are looked at again by fwd_refine_square), by measurement on shapes from 8 x 12 x 197 to 2 x 32 x 4096 (W = workgroups
 // of 128 query rows): W >= 1024 fills the chip with the two-launch path (variant 5), short rows excepted; up to 256 the 128-row kernels
 // leave most SIMDs with one long-running wave and the split-key single launch (variant 3) is 1.1 to 2.3 times faster;
 // in between variant 3 still wins at d = 64 on long rows, otherwise variant 1 (at d = 128 the four waves of variant 3

@@ -335,7 +335,7 @@ template <int DTYPE>
 int launch_rows(const QuantParams &p, hipStream_t st)
 {
     const int64_t groups = (int64_t)p.B * p.H * ((p.L + p.q_block - 1) / p.q_block);
-    if ((int64_t)p.q_block * p.d <= 256) // one or two items a thread; per token most of a wave would idle (2048 tokens, 32 heads, d 128: 38 -> 11.7 us)
+    if ((int64_t)p.q_block * p.d <= 256) // one or two items a thread; per token most of a wave would idle (2048 tokens, 32 heads, d 128: 39 -> 11.5 us)
         hipLaunchKernelGGL((quantize_rows_kernel<DTYPE, 16>), dim3((unsigned)((groups + 15) / 16)), dim3(QNT), 0, st, p);
     else if ((int64_t)p.q_block * p.d <= 4096)
         hipLaunchKernelGGL((quantize_rows_kernel<DTYPE, 64>), dim3((unsigned)((groups + 3) / 4)), dim3(QNT), 0, st, p);

@@ -14,7 +14,7 @@
 // about 250.  No two of them overlap fully, so few instructions and many waves count: with the IDX_FMA map a score costs
 // two vector instructions, its share of the packing and one lookup, and the kernel fits three waves a SIMD (168
 // registers), four at d = 64, in place of two (232).  Measured against the kernel before it, which held a software pipeline
-// inside a wave and tables in registers (1 x 8192, 32 / 8 heads, d 128): 317 -> 270 us; 16 x 4096, 32 heads, a scale for each
+// inside a wave and tables in registers (1 x 8192, 32 / 8 heads, d 128): 317 -> 267 to 277 us with the card; 16 x 4096, 32 heads, a scale for each
 // head: 1545 -> 1162; without a mask, 2 x 2048: 102 -> 84; d 64, 4 x 4096, 16 heads: 121 -> 98.  With this map the pipeline
 // takes as long as the phases (271 us at two waves; three spill), tiles of 128 keys or workgroups of six or eight waves
 // longer (448, 315).
