@@ -3,13 +3,14 @@
 // 32 rows.
 //
 // All scores of a wave's rows fit its registers (16 per 32 keys), so Q.K^T is computed once and the three reductions of
-// IndexSoftmax (Sec. 3.1-3.2) run on registers: the score becomes its table index, then its probability, in place.  K and V of
-// the head are staged in LDS once, one barrier in all.  What bounds it is vector instructions per score: against the tiled
-// kernel it saves two of three score computations and one of two index computations, and pads rows and keys to 32 only
-// (197 x 197: 224 x 224 scores instead of 256 x 256).  Measured against them as they were: 128 x 12 heads of 197 x 197 75.1 -> 48.5 us, 256 x 32 heads
-// of 64 x 64 98 -> 46, 128 x 12 heads of 256 x 256 under the mask 78 -> 49.  Workgroups of up to eight waves, a whole head
-// each, took 60.5 us on the first: 148 to 167 registers (five to eight sub-tiles; 103 up to four) leave a compute unit 12
-// waves, so only one workgroup of seven.
+// IndexSoftmax (Sec. 3.1-3.2) run on registers: the score becomes its table index, then its probability, in place.  K and
+// V of the head are staged in LDS once; a barrier when they are, one when K is read.  What bounds it is vector
+// instructions per score: against the tiled kernel it saves two of three score computations and one of two index
+// computations, and pads rows and keys to 32 only (197 x 197: 224 x 224 scores instead of 256 x 256).  Measured against
+// them as they were: 128 x 12 heads of 197 x 197 75.1 -> 47.7 us, 256 x 32 heads of 64 x 64 98 -> 46, 128 x 12 heads of
+// 256 x 256 under the mask 78 -> 49.  Workgroups of up to eight waves, a whole head each, took 60.5 us on the first: 148
+// to 167 registers (five to eight sub-tiles; 103 up to four) leave a compute unit 12 waves, so only one workgroup of
+// seven.
 //
 // Hidden keys take the last table index, whose entry is 0 by Eq. lut16: no part in the sum, probability 0.
 #include <hip/hip_runtime.h>
@@ -34,8 +35,11 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
 {
     __shared__ __attribute__((aligned(1024))) int8_t Ks[NS * 32 * D];
     __shared__ __attribute__((aligned(1024))) int8_t Vs[NS * 32 * D];
-    __shared__ uint32_t lut_lds[8];
-    extern __shared__ __attribute__((aligned(16))) uint32_t PT_all[]; // a wave's probability table [idx][row], 32 x 32 words; then its output rows
+    // Tables by place, a row of 256 bytes for each: lane l of wave w reads byte 4 l + w, so the address is the conversion of the
+    // index map put into byte 1 of 4 l + w, with no instruction of its own, and no two lanes of a wave share a bank.  (With
+    // words [place][row], a table for each wave, and LUT_hat by byte: 48.5 us for 128 x 12 heads of 197 x 197, now 47.7.)
+    __shared__ __attribute__((aligned(256))) uint8_t LT[32 * 256]; // LUT_hat, the same for all
+    __shared__ __attribute__((aligned(256))) uint8_t PT[32 * 256]; // the probabilities of the lane's row
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 31, h = lane >> 5;
     [[maybe_unused]] const int n_waves = __builtin_amdgcn_readfirstlane((int)blockDim.x >> 6);
@@ -70,9 +74,11 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
     stage(p.k + (int64_t)b * p.ks[0] + (int64_t)kvh * p.ks[1], p.ks[2], Ks, wave, false);
     stage(p.v + (int64_t)b * p.vs[0] + (int64_t)kvh * p.vs[1], p.vs[2], Vs, wave, true);
     // LUT_hat by place (see ScoreIndex)
-    if (tid < 32) {
-        const int idx = ScoreIndex<IDX_FMA>::place(tid, (int)top);
-        ((uint8_t *)lut_lds)[tid] = idx >= 0 ? (uint8_t)(p.lut[idx / 4] >> (8 * (idx % 4))) : (uint8_t)0;
+    for (int t = tid; t < 256; t += 64 * n_waves) { // 32 bytes of a row each
+        const int idx = ScoreIndex<IDX_FMA>::place(t >> 3, (int)top);
+        const int v = (int)((idx >= 0 ? (p.lut[idx / 4] >> (8 * (idx % 4))) & 0xffu : 0u) * 0x01010101u);
+        *(v4i *)(LT + t * 32) = v4i{v, v, v, v};
+        *(v4i *)(LT + t * 32 + 16) = v4i{v, v, v, v};
     }
     v4i qf[KB];
 #pragma unroll
@@ -81,10 +87,9 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
         if (row_ok) qf[kb] = *(const v4i *)(Qp + (int64_t)lr * p.qs[2] + kb * 32 + h * 16);
     }
     publish_tiles_barrier();
-    if (l0 >= LQ) return; // no barrier below
 
     // wave-uniform: sub-tiles that hold keys some row of the wave sees, and whether every row sees all of a sub-tile
-    const int kmax = CAUSAL ? min(L, p.row_lo + l0 + 32) : L;
+    const int kmax = l0 >= LQ ? 0 : (CAUSAL ? min(L, p.row_lo + l0 + 32) : L);
     auto live = [&](int st) { return 32 * st < kmax; };
     auto full = [&](int st) { return 32 * st + 32 <= L && (!CAUSAL || 32 * st + 31 <= p.row_lo + l0); };
     auto visible = [&](int key) { return key < L && (!CAUSAL || key <= row); };
@@ -104,6 +109,8 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
             s[st] = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf, qf[kb], s[st], 0, 0, 0);
         }
     }
+    __syncthreads();      // K is read: the waves' output rows take its place
+    if (l0 >= LQ) return; // no barrier below
 #pragma unroll
     for (int st = 0; st < NS; ++st) {
         if (!live(st)) continue;
@@ -122,22 +129,22 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
     ScoreIndex<IDX_FMA> si;
     si.init(hp, mx, top);
     const int last = CAUSAL ? min(L - 1, row) : L - 1; // last key the lane's row sees
-    const uint8_t *lut_b = (const uint8_t *)lut_lds;
+    const uint32_t own = (uint32_t)(4 * lane + wave); // the lane's byte of a table row
     uint32_t sum = 0;
 #pragma unroll
     for (int st = 0; st < NS; ++st) {
         if (!live(st)) continue;
         if (full(st)) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) s[st][i] = (int)si.index(s[st][i] + si.start());
+            for (int i = 0; i < 16; ++i) s[st][i] = (int)si.address(s[st][i] + si.start(), own);
         } else {
             const int lim = last - 32 * st - 4 * h;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) s[st][i] = (int)si.index(acc_key(i, 0) <= lim ? s[st][i] + si.start() : si.hidden());
+            for (int i = 0; i < 16; ++i) s[st][i] = (int)si.address(acc_key(i, 0) <= lim ? s[st][i] + si.start() : si.hidden(), own);
         }
         uint32_t e[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) e[i] = lut_b[s[st][i]];
+        for (int i = 0; i < 16; ++i) e[i] = LT[(uint32_t)s[st][i]];
 #pragma unroll
         for (int i = 0; i < 16; ++i) sum += e[i];
     }
@@ -154,12 +161,13 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
     // all ones.  (Rows this short mostly have a key of that size in every sub-tile or none at all, so taking the top bits
     // apart as add_pv does costs more here: 128 x 12 heads of 197 x 197 with outlier channels 50.3 us.)
     const uint32_t flip = big ? 0x80u : 0u;
-    uint32_t *PT = PT_all + wave * 1024;
     const float inv_2s = __builtin_amdgcn_rcpf((float)(2u * sum));
 #pragma unroll 4
     for (int j = 0; j < 16; ++j) {
-        const int idx = 16 * h + j;
-        PT[idx * 32 + n] = prob_u8(lut_b[idx], sum, inv_2s) ^ flip; // lut is 0 past the table
+        const uint32_t row = (uint32_t)(16 * h + j) << 8;
+        const uint8_t pr = (uint8_t)(prob_u8(LT[row], sum, inv_2s) ^ flip); // LUT_hat is 0 past the table
+        PT[row + own] = pr; // half the places each: for this lane and for the other one of its row
+        PT[row + (own ^ 128u)] = pr;
     }
     v4i pf[NS];
 #pragma unroll
@@ -167,7 +175,7 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
         pf[st] = v4i{0, 0, 0, 0};
         if (!live(st)) continue;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) s[st][i] = (int)PT[s[st][i] * 32 + n];
+        for (int i = 0; i < 16; ++i) s[st][i] = (int)PT[(uint32_t)s[st][i]];
 #pragma unroll
         for (int g = 0; g < 4; ++g)
             pf[st][g] = (int)((((uint32_t)s[st][4 * g + 1] << 8) | (uint32_t)s[st][4 * g]) |
@@ -201,8 +209,9 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
         if (big) add_pv<false>(vf, ones, ocs);
     }
 
-    // ---- requantize (Sec. 3.2); the wave's 32 rows of 64 bytes meet in its LDS part, so that stores are 16 bytes a lane.
+    // ---- requantize (Sec. 3.2); the wave's 32 rows of 64 bytes meet in its part of what held K, so that stores are 16 bytes a lane.
     // Bits 2 and 3 of a word's number are XORed with bits 2 and 3 of the row's, which spreads the rows over the banks.
+    uint32_t *rows = (uint32_t *)Ks + wave * 512;
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
 #pragma unroll
@@ -215,14 +224,14 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
                 if (p.dbg_acc && row_ok) p.dbg_acc[((int64_t)bh * LQ + lr) * D + ch0 + r] = acc;
                 packed |= ((uint32_t)requant_any(acc, hp.rq_mult, hp.rq_shift) & 0xffu) << (8 * r);
             }
-            PT[n * 16 + ((ch0 / 4) ^ (((n >> 2) & 3) << 2))] = packed;
+            rows[n * 16 + ((ch0 / 4) ^ (((n >> 2) & 3) << 2))] = packed;
         }
     }
     int8_t *Op = p.out + (int64_t)b * p.os[0] + (int64_t)hq * p.os[1];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         const int r = q * 16 + lane / 4, c = lane % 4;
-        const v4i x = *(const v4i *)(PT + r * 16 + 4 * (c ^ ((r >> 2) & 3)));
+        const v4i x = *(const v4i *)(rows + r * 16 + 4 * (c ^ ((r >> 2) & 3)));
         if (l0 + r < LQ) *(v4i *)(Op + (int64_t)(l0 + r) * p.os[2] + c * 16) = x;
     }
 }
@@ -233,8 +242,7 @@ int launch_shape(const FwdParams &p_in, hipStream_t st)
     FwdParams p = p_in;
     const int waves = p.L >= MAX_WAVES * 32 ? MAX_WAVES : (p.L + 31) / 32;
     const dim3 grid((unsigned)fwd_map_work(p)), block((unsigned)(64 * waves));
-    const unsigned sh = (unsigned)waves * 4096u;
-    hipLaunchKernelGGL((fwd_short_kernel<NS, CAUSAL>), grid, block, sh, st, p);
+    hipLaunchKernelGGL((fwd_short_kernel<NS, CAUSAL>), grid, block, 0, st, p);
     return (int)hipGetLastError();
 }
 
