@@ -4,7 +4,7 @@
 //
 // All scores of a wave's rows fit its registers (16 per 32 keys), so Q.K^T is computed once and the three reductions of
 // IndexSoftmax (Sec. 3.1-3.2) run on registers: the score becomes its table index, then its probability, in place.  K and
-// V of the head are staged in LDS once; a barrier when they are, one when K is read.  What bounds it is vector
+// V of the head are staged in LDS once; a barrier when they are, and one when K is read where its room is used again.  What bounds it is vector
 // instructions per score: against the tiled kernel it saves two of three score computations and one of two index
 // computations, and pads rows and keys to 32 only (197 x 197: 224 x 224 scores instead of 256 x 256).  Measured against
 // them as they were: 128 x 12 heads of 197 x 197 75.1 -> 47.7 us, 256 x 32 heads of 64 x 64 98 -> 46, 128 x 12 heads of
@@ -30,16 +30,20 @@ constexpr int KB = D / 32, CB = D / 32;
 constexpr int RPB = 1024 / D; // key rows per 1 KiB block
 
 // NS: 32-key sub-tiles held (Lk <= 32 NS)
-template <int NS, bool CAUSAL>
+template <int NS, bool CAUSAL, bool BY_BYTE>
 __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdParams p)
 {
     __shared__ __attribute__((aligned(1024))) int8_t Ks[NS * 32 * D];
     __shared__ __attribute__((aligned(1024))) int8_t Vs[NS * 32 * D];
-    // Tables by place, a row of 256 bytes for each: lane l of wave w reads byte 4 l + w, so the address is the conversion of the
-    // index map put into byte 1 of 4 l + w, with no instruction of its own, and no two lanes of a wave share a bank.  (With
-    // words [place][row], a table for each wave, and LUT_hat by byte: 48.5 us for 128 x 12 heads of 197 x 197, now 47.7.)
-    __shared__ __attribute__((aligned(256))) uint8_t LT[32 * 256]; // LUT_hat, the same for all
-    __shared__ __attribute__((aligned(256))) uint8_t PT[32 * 256]; // the probabilities of the lane's row
+    // Tables by place.  BY_BYTE: a row of 256 bytes for each place; lane l of wave w reads byte 4 l + w, so the address is the
+    // conversion of the index map put into byte 1 of 4 l + w, with no instruction of its own, and no two lanes of a wave share
+    // a bank.  Else LUT_hat by byte and words [place][row], a table for each wave.  The first takes 8 KiB more of LDS where a
+    // workgroup has two waves, and a longer fill: 128 x 12 heads of 197 x 197 47.5 us against 48.5, but 256 x 32 heads of 64 x 64
+    // 59.4 against 44.5, and at 128 keys they are even (25.8, 26.1), so it serves more than 128
+    // keys, in workgroups of four waves, where the LDS is the same.
+    __shared__ __attribute__((aligned(256))) uint8_t LT[BY_BYTE ? 32 * 256 : 32];  // LUT_hat
+    __shared__ __attribute__((aligned(256))) uint8_t PT[BY_BYTE ? 32 * 256 : 256]; // the probabilities of the lane's row (BY_BYTE)
+    extern __shared__ __attribute__((aligned(16))) uint32_t PT_words[];            // else: 32 x 32 words a wave; then its output rows
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 31, h = lane >> 5;
     [[maybe_unused]] const int n_waves = __builtin_amdgcn_readfirstlane((int)blockDim.x >> 6);
@@ -74,7 +78,13 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
     stage(p.k + (int64_t)b * p.ks[0] + (int64_t)kvh * p.ks[1], p.ks[2], Ks, wave, false);
     stage(p.v + (int64_t)b * p.vs[0] + (int64_t)kvh * p.vs[1], p.vs[2], Vs, wave, true);
     // LUT_hat by place (see ScoreIndex)
-    for (int t = tid; t < 256; t += 64 * n_waves) { // 32 bytes of a row each
+    if constexpr (!BY_BYTE) {
+        if (tid < 32) {
+            const int idx = ScoreIndex<IDX_FMA>::place(tid, (int)top);
+            LT[tid] = idx >= 0 ? (uint8_t)(p.lut[idx / 4] >> (8 * (idx % 4))) : (uint8_t)0;
+        }
+    }
+    for (int t = tid; BY_BYTE && t < 256; t += 64 * n_waves) { // 32 bytes of a row each
         const int idx = ScoreIndex<IDX_FMA>::place(t >> 3, (int)top);
         const int v = (int)((idx >= 0 ? (p.lut[idx / 4] >> (8 * (idx % 4))) & 0xffu : 0u) * 0x01010101u);
         *(v4i *)(LT + t * 32) = v4i{v, v, v, v};
@@ -109,8 +119,8 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
             s[st] = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf, qf[kb], s[st], 0, 0, 0);
         }
     }
-    __syncthreads();      // K is read: the waves' output rows take its place
-    if (l0 >= LQ) return; // no barrier below
+    if constexpr (BY_BYTE) __syncthreads(); // K is read: the waves' output rows take its place
+    if (l0 >= LQ) return;                   // no barrier below
 #pragma unroll
     for (int st = 0; st < NS; ++st) {
         if (!live(st)) continue;
@@ -130,17 +140,19 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
     si.init(hp, mx, top);
     const int last = CAUSAL ? min(L - 1, row) : L - 1; // last key the lane's row sees
     const uint32_t own = (uint32_t)(4 * lane + wave); // the lane's byte of a table row
+    auto place = [&](int sc) __attribute__((always_inline)) { return (int)(BY_BYTE ? si.address(sc, own) : si.index(sc)); };
+    uint32_t *PTw = PT_words + wave * 1024;
     uint32_t sum = 0;
 #pragma unroll
     for (int st = 0; st < NS; ++st) {
         if (!live(st)) continue;
         if (full(st)) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) s[st][i] = (int)si.address(s[st][i] + si.start(), own);
+            for (int i = 0; i < 16; ++i) s[st][i] = place(s[st][i] + si.start());
         } else {
             const int lim = last - 32 * st - 4 * h;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) s[st][i] = (int)si.address(acc_key(i, 0) <= lim ? s[st][i] + si.start() : si.hidden(), own);
+            for (int i = 0; i < 16; ++i) s[st][i] = place(acc_key(i, 0) <= lim ? s[st][i] + si.start() : si.hidden());
         }
         uint32_t e[16];
 #pragma unroll
@@ -164,10 +176,14 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
     const float inv_2s = __builtin_amdgcn_rcpf((float)(2u * sum));
 #pragma unroll 4
     for (int j = 0; j < 16; ++j) {
-        const uint32_t row = (uint32_t)(16 * h + j) << 8;
-        const uint8_t pr = (uint8_t)(prob_u8(LT[row], sum, inv_2s) ^ flip); // LUT_hat is 0 past the table
-        PT[row + own] = pr; // half the places each: for this lane and for the other one of its row
-        PT[row + (own ^ 128u)] = pr;
+        const uint32_t pl = (uint32_t)(16 * h + j), row = BY_BYTE ? pl << 8 : pl;
+        const uint32_t pr = prob_u8(LT[row], sum, inv_2s) ^ flip; // LUT_hat is 0 past the table
+        if constexpr (BY_BYTE) { // half the places each: for this lane and for the other one of its row
+            PT[row + own] = (uint8_t)pr;
+            PT[row + (own ^ 128u)] = (uint8_t)pr;
+        } else {
+            PTw[row * 32 + n] = pr;
+        }
     }
     v4i pf[NS];
 #pragma unroll
@@ -175,7 +191,7 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
         pf[st] = v4i{0, 0, 0, 0};
         if (!live(st)) continue;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) s[st][i] = (int)PT[(uint32_t)s[st][i]];
+        for (int i = 0; i < 16; ++i) s[st][i] = BY_BYTE ? (int)PT[(uint32_t)s[st][i]] : (int)PTw[s[st][i] * 32 + n];
 #pragma unroll
         for (int g = 0; g < 4; ++g)
             pf[st][g] = (int)((((uint32_t)s[st][4 * g + 1] << 8) | (uint32_t)s[st][4 * g]) |
@@ -209,9 +225,9 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
         if (big) add_pv<false>(vf, ones, ocs);
     }
 
-    // ---- requantize (Sec. 3.2); the wave's 32 rows of 64 bytes meet in its part of what held K, so that stores are 16 bytes a lane.
+    // ---- requantize (Sec. 3.2); the wave's 32 rows of 64 bytes meet in what held K or its table, so that stores are 16 bytes a lane.
     // Bits 2 and 3 of a word's number are XORed with bits 2 and 3 of the row's, which spreads the rows over the banks.
-    uint32_t *rows = (uint32_t *)Ks + wave * 512;
+    uint32_t *rows = BY_BYTE ? (uint32_t *)Ks + wave * 512 : PTw;
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
 #pragma unroll
@@ -242,7 +258,13 @@ int launch_shape(const FwdParams &p_in, hipStream_t st)
     FwdParams p = p_in;
     const int waves = p.L >= MAX_WAVES * 32 ? MAX_WAVES : (p.L + 31) / 32;
     const dim3 grid((unsigned)fwd_map_work(p)), block((unsigned)(64 * waves));
-    hipLaunchKernelGGL((fwd_short_kernel<NS, CAUSAL>), grid, block, 0, st, p);
+    if constexpr (NS > 4) {
+        if (waves == MAX_WAVES) { // see BY_BYTE
+            hipLaunchKernelGGL((fwd_short_kernel<NS, CAUSAL, true>), grid, block, 0, st, p);
+            return (int)hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((fwd_short_kernel<NS, CAUSAL, false>), grid, block, (unsigned)waves * 4096u, st, p);
     return (int)hipGetLastError();
 }
 
