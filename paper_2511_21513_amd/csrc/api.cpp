@@ -447,8 +447,7 @@ int derive_all(intattn_ctx *ctx, const intattn_args *a, Derived *out)
     out->hp.assign((size_t)n, HeadParams{});
     out->alpha.assign((size_t)n, 0.f);
     out->svso.assign((size_t)n, 0.f);
-    // a launch uses one scheme for all heads
-    bool fma = true;
+    int n_fma = 0;
     for (int h = 0; h < n; ++h) {
         const int kv = a->scale_mode ? h / g : 0;
         const float sq = a->scale_q[h], sk = a->scale_k[kv], sv = a->scale_v[kv];
@@ -459,14 +458,17 @@ int derive_all(intattn_ctx *ctx, const intattn_args *a, Derived *out)
         hp.c_int = (int32_t)derive_c_int(ctx->clip, sq, sk, a->d);
         if (!derive_requant(sv, so, &hp.rq_mult, &hp.rq_shift))
             return fail(ctx, INTATTN_ERR_INVALID_ARG, "s_V / (255 s_O) is outside the representable range");
-        fma = fma && find_fma((uint32_t)hp.c_int, top, &hp);
+        if (find_fma((uint32_t)hp.c_int, top, &hp)) {
+            hp.pad[0] = IDX_FMA;
+            ++n_fma;
+        } else {
+            hp.pad[0] = IDX_FP64;
+            if (!find_fp64((uint32_t)hp.c_int, top, &hp)) return fail(ctx, INTATTN_ERR_UNSUPPORTED, "no exact index map for these scales");
+        }
         out->alpha[(size_t)h] = (float)(((double)sq * (double)sk) / std::sqrt((double)a->d));
         out->svso[(size_t)h] = (float)((double)sv / (double)so);
     }
-    out->idx_mode = fma ? IDX_FMA : IDX_FP64;
-    if (!fma)
-        for (HeadParams &hp : out->hp)
-            if (!find_fp64((uint32_t)hp.c_int, top, &hp)) return fail(ctx, INTATTN_ERR_UNSUPPORTED, "no exact index map for these scales");
+    out->idx_mode = n_fma == n ? IDX_FMA : (n_fma == 0 ? IDX_FP64 : IDX_DEVICE); // the last: every head its own
     return INTATTN_OK;
 }
 
@@ -821,10 +823,7 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
         if (rc) return rc;
         if (!rm.reserve) {
             std::vector<HeadParams> tab((size_t)a->Hq);
-            for (int h = 0; h < a->Hq; ++h) {
-                tab[(size_t)h] = dv.hp[a->scale_mode ? (size_t)h : 0];
-                tab[(size_t)h].pad[0] = dv.idx_mode;
-            }
+            for (int h = 0; h < a->Hq; ++h) tab[(size_t)h] = dv.hp[a->scale_mode ? (size_t)h : 0];
             rc = put_table(tab);
             if (rc) return rc;
             p.hp_table = d_hp;

@@ -14,7 +14,7 @@ enum IdxMode : int32_t {
     IDX_MAD24 = 1,  // (Delta' * mul + add) >> shift, 24-bit operands, 32-bit result
     IDX_MULHI24 = 2,// high 32 bits of the 48-bit product ((Delta' << pre) + add) * mul
     IDX_FP32 = 3,   // trunc(fma(Delta', top/c_int, 0.5)) in IEEE fp32 (idx_mul holds the bits of -top/c_int)
-    IDX_DEVICE = 4, // FMA or FP64, named by the HeadParams that a kernel derives
+    IDX_DEVICE = 4, // every head its own of FMA and FP64: parameters that a kernel derives, or host scales of which some have no factor
     IDX_ROW64 = 5,  // the fp64 scheme with parameters per block of query rows (FwdParams::row_table): finer
                     // quantization groups over the query rows, Sec. 3.3
     IDX_TOP24 = 6,  // MAD24 with shift 24: the index is the top byte of Delta' * mul + add (IndexSoftmax on caller's logits)
@@ -31,7 +31,7 @@ struct HeadParams {
     int32_t idx_shift; // MAD24: right shift; MULHI24: left pre-shift of Delta'
     int32_t rq_mult;   // output requantization multiplier M in [2^30, 2^31)
     int32_t rq_shift;  // output requantization shift sh in [1, 62]
-    int32_t pad[1];    // this head's IdxMode, FMA or FP64, where a kernel asks for it (decode, device-resident scales)
+    int32_t pad[1];    // this head's IdxMode, FMA or FP64
     uint32_t fma_r;    // IDX_FMA: bits of the float factor r; 0: the head has none
 };
 
