@@ -558,8 +558,8 @@ struct Choice {
     bool in_split_room; // row maxima and sums in the key split's room (never moved), not in the workspace
 };
 
-// idx_mode: the index map of the call's scales; may_split: the key split's room can be had.
-Choice choose_kernels(const intattn_ctx *ctx, const intattn_args *a, const RunMode &rm, int idx_mode, bool may_split)
+// dv: what was derived from the call's scales; may_split: the key split's room can be had.
+Choice choose_kernels(const intattn_ctx *ctx, const intattn_args *a, const RunMode &rm, const Derived &dv, bool may_split)
 {
     const int Lk = a->Lkv ? a->Lkv : a->L;
     Choice ch = {fwd_choose_variant(ctx->variant, a->B, a->Hq, a->L, Lk, a->d, a->causal), false, {0, 0}, false};
@@ -590,12 +590,15 @@ Choice choose_kernels(const intattn_ctx *ctx, const intattn_args *a, const RunMo
         ch.ks = fwd_key_split(ch.variant, a->B, a->Hq, a->L, Lk, a->d, a->causal);
         if (ch.ks.c > 0) ch.variant = VARIANT_KEY_SPLIT;
     }
-    // Short key sequences at d = 64 with the fma map: all scores in registers (fwd_short.hip)
-    if (!rm.dynamic && idx_mode == IDX_FMA && a->scale_mode < 2 && fwd_short_serves(ch.variant, a->B, a->Hq, a->L, Lk, a->d, a->causal))
+    // Short key sequences at d = 64 on host scales: all scores in registers (fwd_short.hip).  Thresholds past 2^24, of
+    // which no distance of two scores at d = 64 is more than an eighth, stay on the general kernels.
+    bool reachable = true;
+    for (const HeadParams &hp : dv.hp) reachable = reachable && hp.c_int <= (1 << 24);
+    if (!rm.dynamic && !rm.reserve && reachable && a->scale_mode < 2 && fwd_short_serves(ch.variant, a->B, a->Hq, a->L, Lk, a->d, a->causal))
         ch.variant = VARIANT_SHORT;
     // Square problems (measured with the fma map).  Variant 3 takes no memory, so what replaces it must not make the workspace
     // grow, which frees memory that captured launches may still use.
-    const bool fma = idx_mode == IDX_FMA || idx_mode == IDX_DEVICE;
+    const bool fma = dv.idx_mode == IDX_FMA || dv.idx_mode == IDX_DEVICE;
     if (fma && a->scale_mode < 2 && a->L == Lk && !rm.no_alloc) {
         const int v = fwd_refine_square(ch.variant, a->B, a->Hq, a->L, a->d, a->causal);
         if (ch.variant != 3 || v == 3 || may_split) {
@@ -718,7 +721,7 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
     p.causal = a->causal;
     p.group = a->Hq / a->Hkv;
     p.top = (1 << ctx->lut_bits) - 1;
-    Choice ch = choose_kernels(ctx, a, rm, dv.idx_mode, !rm.reserve);
+    Choice ch = choose_kernels(ctx, a, rm, dv, !rm.reserve);
     if (ch.ks.c > 0 || ch.in_split_room) {
         bool room = true;
         if ((size_t)split_words(a, ch.ks.c) > ctx->split_cap) {
@@ -728,7 +731,7 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
             if (!room) (void)hipGetLastError();
             else room = ensure_split(ctx, (size_t)split_words(a, ch.ks.c)) == INTATTN_OK;
         }
-        if (!room) ch = choose_kernels(ctx, a, rm, dv.idx_mode, false);
+        if (!room) ch = choose_kernels(ctx, a, rm, dv, false);
     }
     const int variant = ch.variant;
     const bool decode = ch.decode;
@@ -1241,7 +1244,7 @@ int intattn_kernel_choice(intattn_ctx *ctx, const intattn_args *a, int32_t dynam
         const int rd = derive_all(ctx, a, &dv);
         if (rd) return rd;
     }
-    const Choice ch = choose_kernels(ctx, a, rm, dv.idx_mode, true);
+    const Choice ch = choose_kernels(ctx, a, rm, dv, true);
     *kernel = ch.decode ? (ctx->variant == 10 ? 10 : 9) : ch.variant;
     *split_rows = ch.ks.ab;
     *split_pv = ch.ks.c;

@@ -99,7 +99,7 @@ __device__ __forceinline__ bool derive_head(const DeriveParams &dp, int h, int l
 #pragma unroll
     for (int q = 0; q < 2; ++q) want[q] = exact_index((double)at[q], cd, topd);
 
-    if (ok && c_int < (1u << 22)) { // wave-uniform
+    if (c_int < (1u << 22)) { // wave-uniform; also for unusable scales, whose c_int is 1
         const uint32_t quotient = __float_as_uint((float)(topd / cd));
 #pragma unroll 1
         for (int u = 0; u < 6 && hp.fma_r == 0; ++u) {

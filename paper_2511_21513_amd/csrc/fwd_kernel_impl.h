@@ -340,7 +340,8 @@ __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi,
         const int lr = (row >= rlo && row < rhi) ? row - rlo : 0;
         return p.row_table[(int64_t)bh * p.n_rowblk + lr / p.q_block];
     };
-    ScoreIndex<M> si[RB];
+    // (start values in double would leave the kernels with sweep C at d = 64 three waves a SIMD instead of four: 140 registers, 126 without)
+    ScoreIndex<M, PH == 0 || PH == 2> si[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) si[rb].init(M == IDX_ROW64 ? row_hp(qw0 + 32 * rb + n) : hp, KG ? 0 : mx[rb], top);
     // Key groups: the index constants of the lane's row for the key block of `key` (Sec. 3.3):
@@ -421,7 +422,7 @@ __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi,
                     const int key = klo + acc_key(i, h);
                     if constexpr (KG) {
                         if (!kg_blocks) kg_index(rb, key);
-                        const RowIndex<M> &ri = si[rb].ri;
+                        const RowIndex &ri = si[rb].ri;
                         const uint32_t e = lut_b[ri(min(max(s[st][rb][i], ri.bound), ri.mx))];
                         sum[rb] += (!MASKED || visible(key, row)) ? e : 0u;
                     } else {
@@ -517,7 +518,7 @@ __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi,
                     const int key = t * BK + 32 * (st0 + st) + acc_key(i, h);
                     if constexpr (KG) {
                         if (!kg_blocks) kg_index(rb, key);
-                        const RowIndex<M> &ri = si[rb].ri;
+                        const RowIndex &ri = si[rb].ri;
                         s[st][rb][i] = (int)pt[ri(min(max(s[st][rb][i], ri.bound), ri.mx)) * 32];
                         if (MASKED) s[st][rb][i] = visible(key, qw0 + 32 * rb + n) ? s[st][rb][i] : 0;
                     } else { // a hidden key takes the table's last entry, whose probability is 0

@@ -16,6 +16,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "kernel_common.h"
 #include "params.h"
 
@@ -29,8 +31,8 @@ constexpr int KB = D / 32, CB = D / 32;
 [[maybe_unused]] constexpr int CPR = D / 16; // 16-byte chunks per key row
 constexpr int RPB = 1024 / D; // key rows per 1 KiB block
 
-// NS: 32-key sub-tiles held (Lk <= 32 NS)
-template <int NS, bool CAUSAL, bool BY_BYTE>
+// NS: 32-key sub-tiles held (Lk <= 32 NS).  MODE: IDX_FMA, or IDX_DEVICE where every head has its own of IDX_FMA and IDX_FP64.
+template <int NS, bool CAUSAL, bool BY_BYTE, int MODE>
 __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdParams p)
 {
     __shared__ __attribute__((aligned(1024))) int8_t Ks[NS * 32 * D];
@@ -136,30 +138,39 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
     if (!row_ok) mx = 0; // rows outside the problem: zero scores, never stored
 
     // ---- table places and row sum; the row maximum is known only now, so the start value is added here
-    ScoreIndex<IDX_FMA> si;
-    si.init(hp, mx, top);
     const int last = CAUSAL ? min(L - 1, row) : L - 1; // last key the lane's row sees
     const uint32_t own = (uint32_t)(4 * lane + wave); // the lane's byte of a table row
-    auto place = [&](int sc) __attribute__((always_inline)) { return (int)(BY_BYTE ? si.address(sc, own) : si.index(sc)); };
     uint32_t *PTw = PT_words + wave * 1024;
     uint32_t sum = 0;
+    auto places = [&](auto mode_tag) __attribute__((always_inline)) {
+        constexpr int M = decltype(mode_tag)::value;
+        ScoreIndex<M> si;
+        si.init(hp, mx, top);
+        // (in double four scores at a time: sixteen hold 16 registers more, and 182 at 256 keys leave a SIMD two waves instead of three)
+        auto pause = [&](int i) __attribute__((always_inline)) {
+            if (M != IDX_FMA && i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        };
+        auto place = [&](int sc) __attribute__((always_inline)) { return (int)(BY_BYTE ? si.address(sc, own) : si.index(sc)); };
 #pragma unroll
-    for (int st = 0; st < NS; ++st) {
-        if (!live(st)) continue;
-        if (full(st)) {
+        for (int st = 0; st < NS; ++st) {
+            if (!live(st)) continue;
+            if (full(st)) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) s[st][i] = place(s[st][i] + si.start());
-        } else {
-            const int lim = last - 32 * st - 4 * h;
+                for (int i = 0; i < 16; ++i) s[st][i] = place(s[st][i] + si.start()), pause(i);
+            } else {
+                const int lim = last - 32 * st - 4 * h;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) s[st][i] = place(acc_key(i, 0) <= lim ? s[st][i] + si.start() : si.hidden());
+                for (int i = 0; i < 16; ++i) s[st][i] = place(acc_key(i, 0) <= lim ? s[st][i] + si.start() : si.hidden()), pause(i);
+            }
+            uint32_t e[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) e[i] = LT[(uint32_t)s[st][i]];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sum += e[i];
         }
-        uint32_t e[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) e[i] = LT[(uint32_t)s[st][i]];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) sum += e[i];
-    }
+    };
+    if (MODE == IDX_FMA || hp.fma_r != 0) places(std::integral_constant<int, IDX_FMA>{}); // uniform for the workgroup
+    else places(std::integral_constant<int, IDX_FP64>{});
     sum += __shfl_xor(sum, 32);
     const bool big = __any(row_ok && sum <= BIG_ROW_SUM); // wave-uniform
     if (!row_ok) sum = 1u << 24;                          // rows outside the problem: all probabilities 0
@@ -252,34 +263,40 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 2) void fwd_short_kernel(const FwdP
     }
 }
 
-template <int NS, bool CAUSAL>
-int launch_shape(const FwdParams &p_in, hipStream_t st)
+template <int NS, bool CAUSAL, int MODE>
+int launch_mode(const FwdParams &p_in, hipStream_t st)
 {
     FwdParams p = p_in;
     const int waves = p.L >= MAX_WAVES * 32 ? MAX_WAVES : (p.L + 31) / 32;
     const dim3 grid((unsigned)fwd_map_work(p)), block((unsigned)(64 * waves));
     if constexpr (NS > 4) {
         if (waves == MAX_WAVES) { // see BY_BYTE
-            hipLaunchKernelGGL((fwd_short_kernel<NS, CAUSAL, true>), grid, block, 0, st, p);
+            hipLaunchKernelGGL((fwd_short_kernel<NS, CAUSAL, true, MODE>), grid, block, 0, st, p);
             return (int)hipGetLastError();
         }
     }
-    hipLaunchKernelGGL((fwd_short_kernel<NS, CAUSAL, false>), grid, block, (unsigned)waves * 4096u, st, p);
+    hipLaunchKernelGGL((fwd_short_kernel<NS, CAUSAL, false, MODE>), grid, block, (unsigned)waves * 4096u, st, p);
     return (int)hipGetLastError();
+}
+
+template <int NS, bool CAUSAL>
+int launch_shape(const FwdParams &p, int idx_mode, hipStream_t st)
+{
+    return idx_mode == IDX_FMA ? launch_mode<NS, CAUSAL, IDX_FMA>(p, st) : launch_mode<NS, CAUSAL, IDX_DEVICE>(p, st);
 }
 
 } // namespace
 
-// d = 64, Lk <= 256, tables of at most 32 entries, host scales with the fma map, parameters per
+// d = 64, Lk <= 256, tables of at most 32 entries, host scales, parameters per
 // tensor or per head; p.n_qtiles counts tiles of 128 query rows from row 0; no workspace.
 int launch_fwd_short(const FwdParams &p, int d, int idx_mode, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
-    if (d != D || p.Lk > 256 || p.top > 31 || idx_mode != IDX_FMA)
+    if (d != D || p.Lk > 256 || p.top > 31 || (idx_mode != IDX_FMA && idx_mode != IDX_FP64 && idx_mode != IDX_DEVICE))
         return (int)hipErrorInvalidValue;
-    if (p.Lk <= 128) return p.causal ? launch_shape<4, true>(p, st) : launch_shape<4, false>(p, st);
-    if (p.Lk <= 224) return p.causal ? launch_shape<7, true>(p, st) : launch_shape<7, false>(p, st);
-    return p.causal ? launch_shape<8, true>(p, st) : launch_shape<8, false>(p, st);
+    if (p.Lk <= 128) return p.causal ? launch_shape<4, true>(p, idx_mode, st) : launch_shape<4, false>(p, idx_mode, st);
+    if (p.Lk <= 224) return p.causal ? launch_shape<7, true>(p, idx_mode, st) : launch_shape<7, false>(p, idx_mode, st);
+    return p.causal ? launch_shape<8, true>(p, idx_mode, st) : launch_shape<8, false>(p, idx_mode, st);
 }
 
 } // namespace intattn

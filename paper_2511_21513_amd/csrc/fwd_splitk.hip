@@ -76,10 +76,10 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
     const int rlo = p.row_lo, rhi = p.row_lo + p.L, LQ = p.L;
     const uint32_t top = (uint32_t)p.top;
     const int NIDX = top < 32 ? 32 : 64;
-    // Finer quantization groups (Sec. 3.3).  RG: parameters per block of query rows, from the row table; KG: each key block
+    // Finer quantization groups (Sec. 3.3): parameters per block of query rows, from the row table; KG: each key block
     // has a scale of its own too, so that the row maximum is taken over the dequantized logits (fp64) and a lane forms the
     // constants of its row for each key block (once per 32-key sub-tile where a sub-tile lies in one block).
-    constexpr bool KG = M == IDX_KGROUP, RG = KG || M == IDX_ROW64;
+    constexpr bool KG = M == IDX_KGROUP;
     const float *skp = KG ? p.sk_blocks + (int64_t)(b * p.Hkv + kvh) * p.n_kblk : nullptr;
     const bool kg_blocks = KG && (p.k_block % 32) == 0; // uniform
     auto row_hp = [&](int r) __attribute__((always_inline)) {
@@ -234,17 +234,16 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
 
     ScoreIndex<M> si;
     si.init(M == IDX_ROW64 ? row_hp(row) : hp, KG ? 0 : mx, top);
-    [[maybe_unused]] RowIndex<M> &ri = si.ri;
+    [[maybe_unused]] RowIndex &ri = si.ri;
 #pragma unroll
     for (int i = 0; i < 16; ++i) start[i] = si.start();
-    // Group modes: where every lane's threshold is small enough, the index map runs in fp32 (see RowIndex32), the choice
+    // Key groups: where every lane's threshold is small enough, the index map runs in fp32 (see RowIndex32), the choice
     // uniform for the wave.
     RowIndex32 ri32;
     bool single = false;
     auto pick_map = [&](int c_int) __attribute__((always_inline)) {
         single = __all(ri32.init(c_int, ri.mx, top));
     };
-    if constexpr (M == IDX_ROW64) pick_map(ri.mx - ri.bound);
     // Key groups: the constants of the lane's row for the key block of `key`, as in the tiled kernel: c_int^(g) =
     // round(c / alpha^(g)) capped at 2^30, m^(g) = round(M / alpha^(g)) clamped to [-2^22, 2^30 + 2^22], which changes no
     // result (comparisons written so that a NaN from an unusable scale lands on a bound).
@@ -282,16 +281,16 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
         }
     };
     // table places of the sixteen scores of sub-tile j (in place).  Hidden keys (masked: there may be some) take the last
-    // table entry, which is 0; with groups they and, with key groups, logits above their block's image of the maximum are
+    // table entry, which is 0; with key groups they and logits above their block's image of the maximum are
     // brought to it, and the caller leaves them out.
     const int last = CAUSAL ? min(L - 1, row) : L - 1; // last key the lane's row sees
     auto indices = [&](int j, v16i &s, auto masked_tag) __attribute__((always_inline)) {
         constexpr bool MASKED = decltype(masked_tag)::value;
-        if constexpr (!RG) {
+        if constexpr (!KG) {
             const int lim = last - 32 * j - 4 * h;
 #pragma unroll
             for (int i = 0; i < 16; ++i) s[i] = (int)si.index(!MASKED || acc_key(i, 0) <= lim ? s[i] : si.hidden());
-        } else if (KG && !kg_blocks) {
+        } else if (!kg_blocks) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 kg_index(32 * j + acc_key(i, h));
@@ -299,7 +298,7 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
                 s[i] = (int)(single ? ri32(sc) : ri(sc));
             }
         } else {
-            if (KG) kg_index(32 * j);
+            kg_index(32 * j);
             if (single) {
 #pragma unroll
                 for (int i = 0; i < 16; ++i) s[i] = (int)ri32(min(max(s[i], ri.bound), ri.mx));
@@ -327,7 +326,7 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const uint32_t e = lut_b[s[i]];
-                sum += !RG || visible(32 * j + acc_key(i, h)) ? e : 0u;
+                sum += !KG || visible(32 * j + acc_key(i, h)) ? e : 0u;
             }
         }
     });
@@ -409,7 +408,7 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
             for (int r = 0; r < 4; ++r) {
                 const int i = 4 * g + r;
                 pb4[r] = (uint32_t)s[i];
-                if (RG && !full) pb4[r] = visible(32 * j + acc_key(i, h)) ? pb4[r] : 0u;
+                if (KG && !full) pb4[r] = visible(32 * j + acc_key(i, h)) ? pb4[r] : 0u;
             }
             pf[g] = (int)(((pb4[1] << 8) | pb4[0]) | (((pb4[3] << 8) | pb4[2]) << 16));
         }
@@ -433,7 +432,7 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
     const int er = tid >> 3, ec0 = (tid & 7) * CPT, erow = q0 + er;
     if (erow >= rlo && erow < rhi) {
         int8_t *Op = p.out + (int64_t)b * p.os[0] + (int64_t)hq * p.os[1] + (int64_t)(erow - rlo) * p.os[2];
-        HeadParams he = RG ? row_hp(erow) : hp;
+        HeadParams he = KG || M == IDX_ROW64 ? row_hp(erow) : hp;
         if (KG && p.head_status[hq] != 0) he.rq_mult = 0; // an unusable scale somewhere in the head: all zeros
 #pragma unroll
         for (int c4 = 0; c4 < CPT; c4 += 4) {

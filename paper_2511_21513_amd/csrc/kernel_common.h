@@ -20,27 +20,18 @@ __device__ __forceinline__ double idx_fp64_factor(const HeadParams &hp)
     return __builtin_bit_cast(double, ((uint64_t)hp.idx_add << 32) | (uint64_t)hp.idx_mul);
 }
 
-// The fp64 map applied to RAW scores of one query row (the lane's row): with the row maximum mx,
-// idx = trunc(fma(-Delta', -r, 0.5)) in IEEE fp64, r the double after top/c_int: exact for every c_int.
-// Call with sc = max(s, bound), and additionally sc <= mx where logits may exceed mx.
-template <int MODE> struct RowIndex {
+// Key groups: the fp64 map applied to RAW scores of one query row (the lane's row), whose constants change from block to block
+// of keys: idx = trunc(fma(-Delta', -r, 0.5)) in IEEE fp64, r the double after top/c_int: exact for every c_int.  Call with sc =
+// min(max(s, bound), mx); the index is kept inside the table whatever an unusable scale produced.
+struct RowIndex {
     int bound; // mx - c_int
     int mx;
-    int top;     // key groups: 2^b - 1
-    double negr; // (per lane when the parameters are per block of rows)
+    int top;   // 2^b - 1
+    double negr;
 
-    __device__ __forceinline__ void init(const HeadParams &hp, int row_max, uint32_t top_)
-    {
-        mx = row_max;
-        bound = row_max - hp.c_int;
-        negr = idx_fp64_factor(hp);
-        top = (int)top_;
-    }
     __device__ __forceinline__ uint32_t operator()(int sc) const
     {
-        const uint32_t idx = (uint32_t)(int)__builtin_fma((double)(sc - mx), negr, 0.5);
-        // key groups: the index is kept inside the table whatever an unusable scale produced
-        return MODE == IDX_KGROUP ? min(idx, (uint32_t)top) : idx;
+        return min((uint32_t)(int)__builtin_fma((double)(sc - mx), negr, 0.5), (uint32_t)top);
     }
 };
 
@@ -62,46 +53,84 @@ struct RowIndex32 {
     __device__ __forceinline__ uint32_t operator()(int sc) const { return (uint32_t)(int)__builtin_fmaf((float)(sc - mx), negr, 0.5f); }
 };
 
-// The map of a score to its place in a table of 2^b entries, for kernels that start the score's MFMAs at start().
+// The map of a score to its place in a table of 2^b entries, for kernels that start the score's MFMAs at start().  Places count
+// entries from the end of the table (place = top - idx, 0 where a key is clipped or hidden), key groups apart, whose scores
+// are mapped with RowIndex.
 //
-// IDX_FMA counts entries from the end of the table (place = top - idx, 0 where a key is clipped or hidden) and needs neither the clip nor a conversion of the score.  The accumulators of the score's MFMAs start at the bits of
+// IDX_FMA needs neither a clip nor a conversion of the score.  The accumulators of the score's MFMAs start at the bits of
 // the float 2^23 + c_int - rowMax, so that a finished one, read as a float f, is 2^23 + x with x = c_int - Delta exactly
 // where x >= 0, and below 2^23 where the distance Delta exceeds c_int (|score - rowMax| <= 2^22, c_int < 2^22).  One fma gives
 // f r - 2^23 r = x r, rounded once (2^23 r is exact), and the conversion to a byte rounds it to the nearest integer and takes
 // negative values to 0.  r is a float just below top / c_int, so that ties (top x / c_int = k + 1/2) go down, as
 // top - round-half-up(top Delta / c_int) does; the host (find_fma) or the derivation kernel has proved it at both sides of
 // every step.  Rounding and saturation of v_cvt_pk_u8_f32: nearest even, [0, 255].
-template <int MODE> struct ScoreIndex {
-    RowIndex<MODE> ri;
+//
+// IDX_FP64 and IDX_ROW64 serve the thresholds c that have no such float, in double.  The accumulators start at c - rowMax, so
+// that x = max(accumulator, 0), and one fma gives y = x r + 2^20 + 1/2: 32 bits of y are a fraction, and the low byte of its
+// high word is the place, ceil(v) - 1 for v = top x / c + 1/2.  With r = (1 - e) top / c (to within 2^-51 of it) the sum
+// before its rounding, which is by at most 2^-33, is v - (v - 1/2) e.  An integer v, a tie, has to land below itself:
+// (v - 1/2) e > 2^-33.  Any other v lies at least 1 / (2 c) above the integer that it has to stay on or above: top e <= 1 / (2 c).
+//   c <= 2^24: e = 2^-31; a tie's (v - 1/2) e >= 2^-32, and top e < 2^-25.
+//   beyond, where no Delta passes 2^22, so that x >= 3/4 c or the key is hidden: e = 2^-31 / (top + 1); a tie has v - 1/2 >= 3/4 top,
+//   its (v - 1/2) e >= 3/4 2^-32, and top e < 2^-31 <= 1 / (2 c).
+// IDX_FP64 converts nothing: x is the low word of the double 2^52 + x, and 2^20 + 1/2 - 2^52 r is added, which is exact for r < 1.
+// A head that it serves has c > top (find_fma finds a float for every smaller one).  IDX_ROW64, whose rows may have any c, converts x.
+// (1 x 8192, 32 / 8 heads, d 128, whole calls: 683 us when a score took a clip, a subtraction, two conversions and the fma in double,
+// 568 now with IDX_FP64, about 600 with IDX_ROW64's form; IDX_FMA 533, and 640 the fp32 map that served such thresholds before it.  2048
+// rows, 16 heads, d 64: 31.9 -> 26.1, IDX_FMA 23.3, the fp32 map 29.9.  509 rows of 7001: 130 -> 112, IDX_FMA 105, the fp32 map 122.)
+//
+// LATE (in double only): the accumulators start at 0 and c - rowMax is added here, an instruction a score for 16 registers.
+template <int MODE, bool LATE = false> struct ScoreIndex {
+    static constexpr bool FMA = MODE == IDX_FMA, KG = MODE == IDX_KGROUP;
+    static constexpr uint32_t HIGH = 0x41300000u; // high word of 2^20
+    RowIndex ri;
     float r, b;
+    double r64, b64;
     int add0;
     // place of entry idx of the table, and the entry at a place (top = 2^b - 1)
-    static __device__ __forceinline__ int place(int idx, int top) { return MODE == IDX_FMA ? top - idx : idx; }
+    static __device__ __forceinline__ int place(int idx, int top) { return KG ? idx : top - idx; }
     __device__ __forceinline__ void init(const HeadParams &hp, int row_max, uint32_t top_)
     {
-        if constexpr (MODE == IDX_FMA) {
+        if constexpr (FMA) {
             r = __uint_as_float(hp.fma_r);
             b = r * -8388608.0f;
             add0 = 0x4b000000 + hp.c_int - row_max;
-        } else {
-            ri.init(hp, row_max, top_);
+        } else if constexpr (KG) {
+            ri.top = (int)top_;
             add0 = 0;
+        } else {
+            const double q = -idx_fp64_factor(hp); // the double after top / c
+            r64 = q - __builtin_ldexp(q, hp.c_int <= (1 << 24) ? -31 : -31 - (int)__builtin_popcount(top_));
+            if constexpr (MODE == IDX_FP64) { // (a head's: uniform, and so kept in scalar registers)
+                const uint64_t bits = __builtin_bit_cast(uint64_t, r64);
+                r64 = __builtin_bit_cast(double, ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(bits >> 32)) << 32) |
+                                                     (uint32_t)__builtin_amdgcn_readfirstlane((int)bits));
+            }
+            b64 = 1048576.5 - (MODE == IDX_FP64 ? 4503599627370496.0 * r64 : 0.0);
+            add0 = hp.c_int - row_max;
         }
     }
-    __device__ __forceinline__ int start() const { return add0; }                             // of the score's accumulator
-    __device__ __forceinline__ int hidden() const { return MODE == IDX_FMA ? 0 : INT32_MIN; } // the score of a hidden key
+    static constexpr bool ADD = LATE && !FMA && !KG;
+    __device__ __forceinline__ int start() const { return ADD ? 0 : add0; } // of the score's accumulator
+    __device__ __forceinline__ int hidden() const { return FMA ? 0 : -0x7f000000; } // the score of a hidden key (|c - rowMax| <= 2^30 + 2^21)
     __device__ __forceinline__ float steps(int sc) const { return __builtin_fmaf(__uint_as_float((uint32_t)sc), r, b); }
+    __device__ __forceinline__ uint32_t steps64(int sc) const // HIGH + place
+    {
+        const int x = max(ADD ? sc + add0 : sc, 0);
+        const double xd = MODE == IDX_FP64 ? __builtin_bit_cast(double, 0x4330000000000000ull | (uint64_t)(uint32_t)x) : (double)x;
+        return (uint32_t)(__builtin_bit_cast(uint64_t, __builtin_fma(xd, r64, b64)) >> 32);
+    }
     __device__ __forceinline__ uint32_t index(int sc) const
     {
-        if constexpr (MODE == IDX_FMA) return __builtin_amdgcn_cvt_pk_u8_f32(steps(sc), 0, 0);
-        else return ri(max(sc, ri.bound));
+        if constexpr (FMA) return __builtin_amdgcn_cvt_pk_u8_f32(steps(sc), 0, 0);
+        else return steps64(sc) - HIGH;
     }
     // Offset of the score's entry in a table whose rows (one per place) are 256 bytes apart; lane_base = the lane's offset
-    // (< 256) inside a row: the conversion writes the place into byte 1.
+    // (< 256) inside a row: the conversion, or a byte permute, writes the place into byte 1.
     __device__ __forceinline__ uint32_t address(int sc, uint32_t lane_base) const
     {
-        if constexpr (MODE == IDX_FMA) return __builtin_amdgcn_cvt_pk_u8_f32(steps(sc), 1, lane_base);
-        else return (index(sc) << 8) + lane_base;
+        if constexpr (FMA) return __builtin_amdgcn_cvt_pk_u8_f32(steps(sc), 1, lane_base);
+        else return __builtin_amdgcn_perm(steps64(sc), lane_base, 0x03020400u);
     }
 };
 

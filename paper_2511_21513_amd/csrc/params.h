@@ -10,7 +10,7 @@ namespace intattn {
 // intattn_derive_index_map, which searches constants for each of them.)
 enum IdxMode : int32_t {
     IDX_FP64 = 0,   // trunc(fma(Delta', r, 0.5)) in IEEE fp64, r = the double after top/c_int: exact for every c_int
-                    // (idx_mul, idx_add hold the low and high word of the bits of -r)
+                    // (idx_mul, idx_add hold the low and high word of the bits of -r; the tiled kernels: ScoreIndex, kernel_common.h)
     IDX_MAD24 = 1,  // (Delta' * mul + add) >> shift, 24-bit operands, 32-bit result
     IDX_MULHI24 = 2,// high 32 bits of the 48-bit product ((Delta' << pre) + add) * mul
     IDX_FP32 = 3,   // trunc(fma(Delta', top/c_int, 0.5)) in IEEE fp32 (idx_mul holds the bits of -top/c_int)
