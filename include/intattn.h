@@ -134,8 +134,8 @@ INTATTN_API int intattn_create(intattn_ctx **out, const intattn_config *cfg);
 
 /* Enqueues the fused IntAttention forward (Sec. 3) on hip_stream (a hipStream_t; NULL is
  * the default stream) and returns without waiting for it.  The context owns a device workspace
- * (8 bytes per query row) that the first call allocates and a
- * later, larger call re-allocates (hipMalloc / hipFree wait for the device and are not for use under
+ * (8 bytes per query row) that the first call whose kernels use it allocates and a
+ * later, larger such call re-allocates (hipMalloc / hipFree wait for the device and are not for use under
  * graph capture: call intattn_reserve first, or use intattn_forward_noalloc); the
  * kernels of a call pass intermediate results through it, so calls on ONE context must not
  * overlap in time (same stream, or ordered by the caller); use one context per concurrent stream.
@@ -143,8 +143,9 @@ INTATTN_API int intattn_create(intattn_ctx **out, const intattn_config *cfg);
  * take room of their own, at most 128 MiB a call.  It grows apart from the workspace and is never
  * given back or moved before intattn_destroy (what it outgrows, in all less than its last size, stays
  * too), so captured launches stay valid whatever is called later.  A captured call that lacks the room
- * allocates nothing for it and runs unsplit; what the unsplit kernels need of the workspace has to
- * be there, as for any captured call.
+ * allocates nothing for it and runs unsplit, and one that lacks the workspace for the two-launch kernels
+ * runs in one launch; what the split-key path (few query rows) and a variant chosen by hand need of the
+ * workspace has to be there.
  * The one-launch split-key path (few query rows; see intattn_config.variant) lets the workgroups of a
  * (batch, KV head) group wait for each other at a counter in device memory.  Alone on the GPU a group's
  * workgroups are always scheduled together (they have consecutive ids).  The wait is bounded (a few

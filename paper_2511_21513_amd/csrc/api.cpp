@@ -48,7 +48,7 @@ struct intattn_ctx {
     HeadParams *d_hp = nullptr;
     float *d_alpha = nullptr, *d_svso = nullptr;
     int table_cap = 0;
-    // kernel workspace (row max and row sum between the two launches, V chunk sums), grown on demand
+    // kernel workspace (row max and row sum between the two launches; partial results of the split-key kernels), grown on demand
     int32_t *d_ws = nullptr;
     size_t ws_cap = 0; // in int32 elements
     // room of the key-split launches, apart from the workspace: a smaller problem may need more of it than a larger one, and
@@ -596,13 +596,14 @@ Choice choose_kernels(const intattn_ctx *ctx, const intattn_args *a, const RunMo
     for (const HeadParams &hp : dv.hp) reachable = reachable && hp.c_int <= (1 << 24);
     if (!rm.dynamic && !rm.reserve && reachable && a->scale_mode < 2 && fwd_short_serves(ch.variant, a->B, a->Hq, a->L, Lk, a->d, a->causal))
         ch.variant = VARIANT_SHORT;
-    // Square problems (measured with the fma map).  Variant 3 takes no memory, so what replaces it must not make the workspace
-    // grow, which frees memory that captured launches may still use.
+    // Square problems (measured with the fma map).  Variants 1 and 3 take no memory, so where variant 5 replaces them it must not
+    // make the workspace grow, which frees memory that captured launches may still use.
     const bool fma = dv.idx_mode == IDX_FMA || dv.idx_mode == IDX_DEVICE;
     if (fma && a->scale_mode < 2 && a->L == Lk && !rm.no_alloc) {
         const int v = fwd_refine_square(ch.variant, a->B, a->Hq, a->L, a->d, a->causal);
-        if (ch.variant != 3 || v == 3 || may_split) {
-            ch.in_split_room = ch.variant == 3 && v != 3;
+        const bool takes_room = v == 5 && v != ch.variant;
+        if (may_split || !takes_room) {
+            ch.in_split_room = takes_room;
             ch.variant = v;
         }
     }
@@ -722,17 +723,25 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
     p.group = a->Hq / a->Hkv;
     p.top = (1 << ctx->lut_bits) - 1;
     Choice ch = choose_kernels(ctx, a, rm, dv, !rm.reserve);
+    // a call that is being captured must not allocate
+    auto capturing = [&]() {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        const bool none = hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+        if (!none) (void)hipGetLastError();
+        return !none;
+    };
     if (ch.ks.c > 0 || ch.in_split_room) {
         bool room = true;
-        if ((size_t)split_words(a, ch.ks.c) > ctx->split_cap) {
-            // a call that is being captured must not allocate: it runs as if the room could not be had
-            hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-            room = hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
-            if (!room) (void)hipGetLastError();
-            else room = ensure_split(ctx, (size_t)split_words(a, ch.ks.c)) == INTATTN_OK;
-        }
+        if ((size_t)split_words(a, ch.ks.c) > ctx->split_cap)
+            room = !capturing() && ensure_split(ctx, (size_t)split_words(a, ch.ks.c)) == INTATTN_OK;
         if (!room) ch = choose_kernels(ctx, a, rm, dv, false);
     }
+    // Two launches that were chosen automatically, without the workspace that passes their row maxima and sums: one launch instead
+    // (an earlier call on more rows may have been one launch itself, and have left no workspace).
+    const bool automatic = ctx->variant == 0 || ctx->variant == 9 || ctx->variant == 10;
+    if (automatic && (ch.variant == 4 || ch.variant == 5) && !ch.in_split_room && stage == 0 && !comparator && !rm.no_alloc && !rm.reserve &&
+        (size_t)split_words(a, 0) > ctx->ws_cap && capturing())
+        ch.variant = 1;
     const int variant = ch.variant;
     const bool decode = ch.decode;
     const int64_t packed_rows = (int64_t)p.group * p.L;
@@ -741,8 +750,7 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
     auto reserve_rest = [&]() -> int {
         const int r = get_ws((size_t)split_words(a, 0));
         if (r) return r;
-        if (ctx->variant != 0 && ctx->variant != 9 && ctx->variant != 10) return INTATTN_OK;
-        if (comparator || ctx->lut_bits > 5 || a->scale_mode > 2) return INTATTN_OK;
+        if (!automatic || comparator || ctx->lut_bits > 5 || a->scale_mode > 2) return INTATTN_OK;
         const int64_t most = std::min<int64_t>(KEY_SPLIT_MAX_WORDS, split_words(a, KEY_SPLIT_MAX_RANGES));
         if (ensure_split(ctx, (size_t)most) != INTATTN_OK) ctx->split_fixed = true; // later calls run unsplit rather than allocate
         return INTATTN_OK;
@@ -920,9 +928,11 @@ int run(intattn_ctx *ctx, const intattn_args *a, void *stream, const RunMode &rm
         ctx->err.clear();
         return INTATTN_OK;
     }
-    if (!comparator && variant != 3 && variant != VARIANT_SHORT) { // (those pass nothing through memory)
+    // (the single launches pass nothing through memory; what intattn_forward_noalloc takes of them is bounded all the same, below)
+    if (!comparator && (variant == 4 || variant == 5 || variant == VARIANT_KEY_SPLIT || (rm.no_alloc && variant != 3 && variant != VARIANT_SHORT))) {
         const size_t rows = (size_t)a->B * a->Hq * a->L;
-        // (the static array keeps the bound it has always had: d words per workgroup's worth of keys and KV head beside the rows)
+        // The bound of the static array is part of that entry's interface and counts d words per workgroup's worth of keys and KV
+        // head beside the rows, for kernels that wrote them there: what it refused then it refuses now.
         const size_t kept = rm.no_alloc ? (size_t)a->B * a->Hkv * ((p.Lk + rows_per_block - 1) / rows_per_block) * a->d : 0;
         int32_t *base = nullptr;
         if (variant == VARIANT_KEY_SPLIT) {
