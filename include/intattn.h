@@ -285,16 +285,18 @@ INTATTN_API int intattn_quantize_batch(intattn_ctx *ctx, const intattn_quant_arg
 INTATTN_API int intattn_derive_params(const intattn_ctx *ctx, float s_q, float s_k, float s_v, float s_o,
                           int32_t d, int64_t *c_int, int32_t *rq_mult, int32_t *rq_shift);
 
-/* Host-only, exposed for tests: how the kernels evaluate the index map of Sec. 3.1,
+/* Host-only, exposed for tests: ways to evaluate the index map of Sec. 3.1,
  * idx = round(x * (2^b - 1) / c_int) for x in [0, c_int], without dividing.  On entry *mode
  * names the scheme asked for; on return it is that scheme, or 0 if no constants exist for it
- * (the kernels then use scheme 0, which exists for every c_int).  Every scheme is checked
- * against the exact quotient at both sides of every index step before it is returned.
+ * (scheme 0 exists for every c_int).  Every scheme is checked
+ * against the exact quotient at both sides of every index step before it is returned.  The forward
+ * kernels use 9 where it exists, else 0; IndexSoftmax on logits uses 6, else 0.
  *   mode 0: idx = trunc(fma(x, r, 0.5)) in IEEE fp64, *mul / *add = low / high word of the bits of r
  *   mode 1: idx = (x * mul + add) >> shift                 (32-bit sum, 24-bit factors)
  *   mode 2: idx = (((x << shift) + add) * mul) >> 32       (48-bit product of 24-bit factors)
  *   mode 3: idx = trunc(fma(x, r, 0.5)) in IEEE fp32, *mul = the bits of r; add = shift = 0
- *   mode 6: mode 1 with shift = 24: the index is the top byte of x * mul + add */
+ *   mode 6: mode 1 with shift = 24: the index is the top byte of x * mul + add
+ *   mode 9: idx = 2^b - 1 - rint(fl32((c_int - x) * r)), rint to nearest even, *mul = the bits of the float r; add = shift = 0 */
 INTATTN_API int intattn_derive_index_map(const intattn_ctx *ctx, int64_t c_int, int32_t *mode, uint32_t *mul,
                                          uint32_t *add, int32_t *shift);
 

@@ -348,8 +348,8 @@ bool find_fp64(uint32_t c_int, uint32_t top, HeadParams *hp)
 // The factor of the IDX_FMA map (ScoreIndex, kernel_common.h): a float r near top / c_int for which x r, x = c_int - Delta',
 // rounded to a float and then to the nearest integer (ties to even) is top - round(Delta' top / c_int) for every integer x in
 // [0, c_int].  Ties of top x / c_int must go down, so r lies below the quotient: one unit in the last place serves 99 % of
-// thresholds up to 65 000, two nearly all others; some r exists for every threshold up to about 130 000 (b <= 5) and for
-// 95 % of those up to 400 000.  The accumulators that carry x hold thresholds below 2^22.
+// thresholds up to 65 000, two nearly all others; some r exists for every threshold up to 208 507 (b <= 5; b = 6: 104 203) and for
+// 95 % of those from 300 000 to 400 000.  The accumulators that carry x hold thresholds below 2^22.
 // A call with a scale for each head derives as many maps before its launch, so the check forms nothing in memory, divides
 // once for all steps and takes x r, of at most 46 bits, as a double where the kernels use an fma (32 heads: 21 -> 8 us of host time).
 bool find_fma(uint32_t c_int, uint32_t top, HeadParams *hp)
@@ -1216,8 +1216,16 @@ int intattn_derive_index_map(const intattn_ctx *ctx, int64_t c_int, int32_t *mod
         *mode = find_mulhi24((uint32_t)c_int, top, &hp) ? IDX_MULHI24 : IDX_FP64;
     } else if (*mode == IDX_TOP24) {
         *mode = find_top24((uint32_t)c_int, top, &hp) ? IDX_TOP24 : IDX_FP64;
+    } else if (*mode == IDX_FMA) {
+        *mode = find_fma((uint32_t)c_int, top, &hp) ? IDX_FMA : IDX_FP64;
     } else {
         *mode = IDX_FP64;
+    }
+    if (*mode == IDX_FMA) {
+        *mul = hp.fma_r;
+        *add = 0;
+        *shift = 0;
+        return INTATTN_OK;
     }
     if (*mode == IDX_FP64) {
         if (!find_fp64((uint32_t)c_int, top, &hp)) return INTATTN_ERR_UNSUPPORTED;

@@ -20,7 +20,7 @@ enum IdxMode : int32_t {
     IDX_TOP24 = 6,  // MAD24 with shift 24: the index is the top byte of Delta' * mul + add (IndexSoftmax on caller's logits)
     IDX_KGROUP = 7, // per-logit parameters: quantization groups over the key axis (Sec. 3.3), fp64 map per key block
     IDX_FMA = 9     // one fp32 fma on the accumulator read as a float and one conversion (ScoreIndex, kernel_common.h): every c_int up
-                    // to about 130 000 and most up to 400 000; HeadParams::fma_r
+                    // to 208 507 (tables of 64 entries: 104 203) and most up to 400 000; HeadParams::fma_r
 };
 
 // Per query head: everything the kernel needs that depends on the scales.

@@ -1,5 +1,5 @@
 """The index map of the tiled kernels as one single-precision fma on the score accumulator read as a float: thresholds at both
-ends of its range, around the table's steps, and past it (a head without a factor sends the call to the fp64 map), with
+ends of its range, around the table's steps, and past it (a head without a factor takes the map in double), with
 scores at the ends of theirs; bit-compared with the oracle."""
 import numpy as np
 import pytest
@@ -37,6 +37,31 @@ def test_small_and_usual_thresholds_have_a_factor(top):
     rng = np.random.default_rng(top)
     for c in [*range(1, 130), *(int(x) for x in np.exp(rng.uniform(np.log(130), np.log(60000), 300)))]:
         assert has_factor(c, top), c
+
+
+@pytest.mark.parametrize("lut_bits", [1, 3, 5, 6])
+def test_factors_of_the_library(lut_bits):
+    """The library reports a factor exactly where there is one (an exhaustive search of its first thresholds without one), and each
+    serves every distance in [0, c_int]."""
+    from paper_2511_21513_amd import binding
+
+    ia = binding.IntAttn(device=-1, lut_bits=lut_bits)
+    top = (1 << lut_bits) - 1
+    rng = np.random.default_rng(lut_bits)
+    cs = [*range(1, 130), 2 * top - 1, 2 * top, 445, 5203, 28794, 47011, 55064, 74999, 131071, 200003,
+          *(int(x) for x in np.exp(rng.uniform(np.log(130), np.log(2.0**22), 150))), (1 << 22) - 1, 1 << 22, (1 << 25) + 1]
+    for c in cs:
+        mode, bits, add, sh = ia.derive_index_map(c, 9)
+        assert mode == (9 if c < 1 << 22 and has_factor(c, top) else 0), c
+        if mode == 9:
+            assert add == 0 and sh == 0
+            x = np.arange(c + 1, dtype=np.int64)  # distances
+            products = ((c - x).astype(np.float64) * float(np.uint32(bits).view(np.float32))).astype(np.float32)
+            np.testing.assert_array_equal(top - np.rint(products).astype(np.int64), (2 * top * x + c) // (2 * c))
+    first = {5: 208508, 6: 104204}.get(lut_bits)
+    if first:
+        assert next(c for c in range(1, 300000) if ia.derive_index_map(c, 9)[0] != 9) == first
+        assert not has_factor(first, top)
 
 
 THRESHOLDS = {

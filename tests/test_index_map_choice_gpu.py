@@ -1,9 +1,10 @@
-"""The index map that the device picks for thresholds it learns from device-resident scales: the multiply-high and top-byte
-constants it searches, the fp64 map where a head has none, and the single-precision map of the group modes on both sides of
+"""The index map that the device picks for thresholds it learns from device-resident scales: the factor of the fma map that it
+searches, the map in double precision where a head has none, and the single-precision map of key groups on both sides of
 its limit; bit-compared with the oracle."""
 import numpy as np
 import pytest
 
+from test_fma_map_gpu import without_factor
 from test_parity_gpu import key_group_forward, torch_mod  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -24,24 +25,16 @@ def qkv(rng, B, H, L):
     return [rng.integers(-127, 128, (B, H, L, D), dtype=np.int8) for _ in range(3)]
 
 
-def without_multiply_high():
-    """A threshold that has no multiply-high constants at all (by the host's wider search)."""
-    from paper_2511_21513_amd import binding
-
-    host = binding.IntAttn(device=-1)
-    return next(c for c in range(70000, 90000) if host.derive_index_map(c, 2)[0] != 2)
-
-
 THRESHOLDS = [
     [5203],                          # per tensor: one wave derives for every head
     [47011],
-    [None],
-    [900, 5203, 33, 12000, 1],       # top byte for sweep C everywhere
-    [5203, 47011, 30011, 61, 55064], # some heads on multiply-high alone
-    [5203, None, 47011],             # one head without either: fp64 for all
-    [5203, 47011] * 9,               # a second round of the one workgroup
-    [5203, 47011] * 17,              # a workgroup per head
-    [5203] * 33 + [None],
+    [None],                          # no single-precision factor
+    [900, 5203, 33, 12000, 1],
+    [5203, 47011, 30011, 61, 55064],
+    [5203, None, 47011],             # one head without a factor: that one in double precision
+    [5203, 47011] * 9,
+    [5203, 47011] * 17,
+    [5203] * 33 + [None, 2**25 + 1],
 ]
 
 
@@ -51,7 +44,7 @@ def test_device_scales_bit_exact(torch_mod, oracle, which, variant):  # noqa: F8
     from paper_2511_21513_amd import binding
 
     torch = torch_mod
-    c_ints = [without_multiply_high() if c is None else c for c in THRESHOLDS[which]]
+    c_ints = [without_factor(31) if c is None else c for c in THRESHOLDS[which]]
     per_head = len(c_ints) > 1
     H, L, lq = (len(c_ints) if per_head else 2), 161, (1 if variant == 9 else 161)
     print(f"case {c_ints} variant {variant}", flush=True)

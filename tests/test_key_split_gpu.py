@@ -3,7 +3,7 @@ bit-compared with the CPU oracle; and the mapping of work to XCDs for group coun
 import numpy as np
 import pytest
 
-from test_index_map_choice_gpu import scales_for, without_multiply_high
+from test_fma_map_gpu import scales_for, without_factor
 from test_kernel_choice import SPLIT
 from test_parity_gpu import rect_forward, rect_problem, torch_mod  # noqa: F401
 
@@ -50,16 +50,15 @@ def test_key_split_bit_exact(torch_mod, oracle, shape):  # noqa: F811
     ia.close()
 
 
-@pytest.mark.parametrize("lut_bits, scheme", [(3, 6), (5, 2), (5, 3), (5, 0)], ids=["table of 8", "multiply-high", "fp32", "fp64"])
-def test_key_split_tables_and_index_maps_bit_exact(torch_mod, oracle, lut_bits, scheme):  # noqa: F811
-    """Tables of fewer than 32 entries, and every index map; the fp64 map also as the device picks it."""
+@pytest.mark.parametrize("lut_bits, c_int, scheme", [(3, 5203, 9), (5, 47011, 9), (5, None, 0), (5, 2**25 + 1, 0)],
+                         ids=["table of 8", "fma", "double", "double past 2^24"])
+def test_key_split_tables_and_index_maps_bit_exact(torch_mod, oracle, lut_bits, c_int, scheme):  # noqa: F811
+    """Tables of fewer than 32 entries, and both index maps; also as the device picks them."""
     from paper_2511_21513_amd import binding
 
     torch = torch_mod
-    host = binding.IntAttn(device=-1, lut_bits=lut_bits)
-    c_int = {6: 5203, 2: 47011, 3: without_multiply_high(), 0: 2**25 + 1}[scheme]
-    assert host.derive_index_map(c_int, scheme)[0] == scheme
-    assert scheme == 6 or host.derive_index_map(c_int, 6)[0] == 0
+    c_int = without_factor(31) if c_int is None else c_int
+    assert binding.IntAttn(device=-1, lut_bits=lut_bits).derive_index_map(c_int, 9)[0] == scheme
     base, q, k, v = rect_problem(77, 1, 2, 1, 129, 9001, 64, True)
     s_q, s_k = (np.array([x], dtype=np.float32) for x in scales_for(c_int))
     s_v, s_o = np.array([0.02], dtype=np.float32), np.array([0.004], dtype=np.float32)
