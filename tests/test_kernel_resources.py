@@ -63,16 +63,42 @@ def registers(kernels, pattern):
     return max(k[".vgpr_count"] for k in pick(kernels, pattern).values())
 
 
-@pytest.mark.parametrize("d, most", [(64, 140), (128, 224)])
-def test_tiled_kernels_with_sweep_c_on_known_schemes(kernels, d, most):
-    """All sweeps, and sweep C alone, of 32 rows a wave on host scales (index schemes 0 to 3)."""
+# Index schemes (the fifth template argument): 0 double, 4 every head its own, 5 row groups, 7 key groups, 9 fma.
+@pytest.mark.parametrize("d, schemes, most", [(64, "[49]", 144), (64, "[05]", 128), (128, "[0459]", 224)])
+def test_tiled_kernels_with_sweep_c(kernels, d, schemes, most):
+    """All sweeps, and sweep C alone, of 32 rows a wave.  A SIMD holds four waves up to 128 registers a lane, three up to 168,
+    two up to 256."""
     for phase in (0, 2):
-        assert registers(kernels, rf"fwd_kernelILi{d}ELi1ELi2ELb[01]ELi[0-3]ELi{phase}E") <= most
+        assert registers(kernels, rf"fwd_kernelILi{d}ELi1ELi2ELb[01]ELi{schemes}ELi{phase}E") <= most
 
 
-def test_sweep_c_at_head_dimension_64_runs_three_waves(kernels):
-    """168 registers a lane let three waves share a SIMD."""
-    assert registers(kernels, r"sweep_c_kernelILi64E") <= 168
+@pytest.mark.parametrize("d, most", [(64, 128), (128, 168)])
+def test_sweep_c_runs_three_or_four_waves(kernels, d, most):
+    """Spills, of two to four registers, only where the double map is held in sweep C of unsplit keys."""
+    assert registers(kernels, rf"sweep_c_kernelILi{d}E") <= most
+    for name, k in pick(kernels, rf"sweep_c_kernelILi{d}ELb[01]ELi[0459]ELb[01]E").items():
+        assert k[".vgpr_spill_count"] <= (4 if re.search(r"Li128ELb[01]ELi[04]ELb0E", name) else 0), name
+
+
+@pytest.mark.parametrize("d, rows, most, spilled", [(64, 1, 128, 0), (128, 1, 128, 0), (128, 2, 168, 14)])
+def test_sweeps_a_and_b_run_three_or_four_waves(kernels, d, rows, most, spilled):
+    """Two blocks of rows a wave hold three waves a SIMD at the price of 3 to 5 spilled registers with the fma map, up to 13
+    where the kernel holds both maps."""
+    found = pick(kernels, rf"fwd_kernelILi{d}ELi{rows}ELi2ELb[01]ELi[0459]ELi1E")
+    assert max(k[".vgpr_count"] for k in found.values()) <= most
+    assert max(k[".vgpr_spill_count"] for k in found.values()) <= spilled
+    assert all(k[".vgpr_spill_count"] <= 5 for n, k in found.items() if "ELi9E" in n)
+
+
+def test_sweep_b_over_a_range_of_keys(kernels):
+    assert registers(kernels, r"fwd_kernelILi\d+ELi2ELi2ELb[01]ELi[0459]ELi4E") <= 168
+    assert all(k[".vgpr_spill_count"] <= 8 for k in pick(kernels, r"fwd_kernelILi\d+ELi2ELi2ELb[01]ELi[0459]ELi4E").values())
+
+
+def test_short_sequences_run_three_waves(kernels):
+    """All scores in registers: 168 a lane for up to 256 keys, 128 for up to 128."""
+    assert registers(kernels, r"fwd_short_kernelILi[478]E") <= 168
+    assert registers(kernels, r"fwd_short_kernelILi4E") <= 128
 
 
 def test_derivation_kernels_use_no_scratch(kernels):
@@ -84,6 +110,8 @@ def test_row_maxima_alone_have_no_index_map(kernels):
     assert len(pick(kernels, r"fwd_kernelILi\d+ELi2ELi2ELb[01]ELi\d+ELi3E")) == 4
 
 
-def test_kernels_with_the_keys_split_over_waves_spill_little(kernels):
-    """Row groups and host scales (key groups at d = 128 are at the limit of 256 registers)."""
-    assert all(k[".vgpr_spill_count"] <= 10 for k in pick(kernels, r"fwd_splitk_kernelILi\d+ELb[01]ELi[0-6]E").values())
+def test_kernels_with_the_keys_split_over_waves_do_not_spill(kernels):
+    """Two waves a SIMD at d = 128, three at d = 64 (key groups: two)."""
+    found = pick(kernels, r"fwd_splitk_kernelILi\d+ELb[01]ELi[04579]E")
+    assert len(found) == 20 and all(k[".vgpr_spill_count"] == 0 for k in found.values())
+    assert registers(kernels, r"fwd_splitk_kernelILi64ELb[01]ELi[0459]E") <= 168
