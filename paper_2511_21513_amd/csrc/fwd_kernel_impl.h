@@ -333,15 +333,14 @@ __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi,
         return;
     }
 
-    // exact index map of each row block's lane row, applied to raw scores (no -rowMax start
-    // value in the accumulators, which saves 16 registers per row block)
+    // exact index map of each row block's lane row, applied to the accumulators of its scores
     // parameters of the block of query rows that `row` lies in (finer groups over query rows, Sec. 3.3)
     auto row_hp = [&](int row) __attribute__((always_inline)) {
         const int lr = (row >= rlo && row < rhi) ? row - rlo : 0;
         return p.row_table[(int64_t)bh * p.n_rowblk + lr / p.q_block];
     };
     // (start values in double would leave the kernels with sweep C at d = 64 three waves a SIMD instead of four: 140 registers, 126 without)
-    ScoreIndex<M, PH == 0 || PH == 2> si[RB];
+    ScoreIndex<M, PH == 0 || PH == 2, PH == 0 || M == IDX_ROW64> si[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) si[rb].init(M == IDX_ROW64 ? row_hp(qw0 + 32 * rb + n) : hp, KG ? 0 : mx[rb], top);
     // Key groups: the index constants of the lane's row for the key block of `key` (Sec. 3.3):

@@ -80,9 +80,14 @@ struct RowIndex32 {
 // rows, 16 heads, d 64: 31.9 -> 26.1, IDX_FMA 23.3, the fp32 map 29.9.  509 rows of 7001: 130 -> 112, IDX_FMA 105, the fp32 map 122.)
 //
 // LATE (in double only): the accumulators start at 0 and c - rowMax is added here, an instruction a score for 16 registers.
-template <int MODE, bool LATE = false> struct ScoreIndex {
+// SHIFTED (in double only): r and the addend are held 2^45 times as large, which moves the exponent alone.  The high word is then
+// 0x44000000 + place, of which a shift by 7 leaves the place, so the address of an entry in a table with rows of 128 bytes is one
+// shift-and-add and not four operations (128 x 12 heads of 197 rows, d 64, a scale for each 128 rows: 81.3 -> 74.7 us; IDX_FP64,
+// device scales, 76.8 -> 70.1).  It takes IDX_FP64 two registers more, and kernels that these cost a wave a SIMD, or a spill, go without.
+template <int MODE, bool LATE = false, bool SHIFTED = false> struct ScoreIndex {
     static constexpr bool FMA = MODE == IDX_FMA, KG = MODE == IDX_KGROUP;
-    static constexpr uint32_t HIGH = 0x41300000u; // high word of 2^20
+    static constexpr uint32_t HIGH = SHIFTED ? 0x44000000u : 0x41300000u; // high word of 2^65, of 2^20
+    static constexpr double UNIT = SHIFTED ? 35184372088832.0 : 1.0;      // 2^45
     RowIndex ri;
     float r, b;
     double r64, b64;
@@ -100,13 +105,13 @@ template <int MODE, bool LATE = false> struct ScoreIndex {
             add0 = 0;
         } else {
             const double q = -idx_fp64_factor(hp); // the double after top / c
-            r64 = q - __builtin_ldexp(q, hp.c_int <= (1 << 24) ? -31 : -31 - (int)__builtin_popcount(top_));
+            r64 = (q - __builtin_ldexp(q, hp.c_int <= (1 << 24) ? -31 : -31 - (int)__builtin_popcount(top_))) * UNIT;
             if constexpr (MODE == IDX_FP64) { // (a head's: uniform, and so kept in scalar registers)
                 const uint64_t bits = __builtin_bit_cast(uint64_t, r64);
                 r64 = __builtin_bit_cast(double, ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(bits >> 32)) << 32) |
                                                      (uint32_t)__builtin_amdgcn_readfirstlane((int)bits));
             }
-            b64 = 1048576.5 - (MODE == IDX_FP64 ? 4503599627370496.0 * r64 : 0.0);
+            b64 = 1048576.5 * UNIT - (MODE == IDX_FP64 ? 4503599627370496.0 * r64 : 0.0);
             add0 = hp.c_int - row_max;
         }
     }
@@ -118,7 +123,7 @@ template <int MODE, bool LATE = false> struct ScoreIndex {
     {
         const int x = max(ADD ? sc + add0 : sc, 0);
         const double xd = MODE == IDX_FP64 ? __builtin_bit_cast(double, 0x4330000000000000ull | (uint64_t)(uint32_t)x) : (double)x;
-        return (uint32_t)(__builtin_bit_cast(uint64_t, __builtin_fma(xd, r64, b64)) >> 32);
+        return (uint32_t)__builtin_bit_cast(v2i, __builtin_fma(xd, r64, b64))[1]; // (as a shift of 64 bits it would be joined with the address's)
     }
     __device__ __forceinline__ uint32_t index(int sc) const
     {

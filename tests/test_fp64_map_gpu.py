@@ -2,6 +2,7 @@
 of every step (host only); which kernels serve calls that need it, for all heads or for some; and on the GPU, with logits at the
 steps themselves and ties among them, against the oracle in every kernel that holds it."""
 import math
+import struct
 from fractions import Fraction
 
 import numpy as np
@@ -34,6 +35,9 @@ def test_form_is_exact(top):
         if c > top:  # the form without a conversion adds 2^20 + 1/2 - 2^52 r, which has to be a double
             b = 1048576.5 - 4503599627370496.0 * r
             assert Fraction(b) == Fraction(1048576.5) - 2**52 * Fraction(r)
+            scaled = 1048576.5 * 2.0**45 - 4503599627370496.0 * (r * 2.0**45)  # the same 2^45 times as large
+            assert Fraction(scaled) == 2**45 * Fraction(b)
+    assert struct.pack(">d", 2.0**65)[:4] == bytes.fromhex("44000000") and (0x44000000 << 7) % 2**32 == 0
 
 
 def test_small_thresholds_have_a_factor():
