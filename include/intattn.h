@@ -70,8 +70,8 @@ typedef struct {
     int32_t variant;  /* kernel variant: 0 = automatic choice.  Tuning knobs, all bit-identical: 1, 2 = one
                          launch with 32 / 64 query rows per wave; 3 = one launch, a workgroup per 32 query
                          rows with the keys split over its waves (small and mid-size problems); 4, 5 = two
-                         launches (row max and row sum, then P.V) with the phase-ordered / the
-                         software-pipelined second kernel;
+                         launches (row max and row sum, then P.V) with the common kernel / a
+                         kernel of its own for the second;
                          9 = the split-key path for few query rows wherever the shape allows (one launch
                          whose workgroups meet at counters in device memory; intattn_forward_noalloc
                          takes four launches);
@@ -168,13 +168,15 @@ INTATTN_API int intattn_reserve(intattn_ctx *ctx, const intattn_args *args, int3
 
 /* intattn_forward for callers that cannot allocate device memory (code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc): same arguments (host scales), same bytes out.  Same
- * kernels, except that tiled launches never split their keys over workgroups and that the split-key
+ * kernels, except that tiled launches never split their keys over workgroups, that square problems keep
+ * the choice of kernel that rectangular ones have (which may be slower), and that the split-key
  * path takes its four launches.  The workspace -- row maxima and row sums between the launches,
  * the partial results of the split-key path -- and the per-head parameter table live in a
  * static device array of INTATTN_NOALLOC_SCRATCH_BYTES that the library's image holds on every GPU it
  * runs on.  Calls no hipMalloc / hipFree.  A problem past the array's bound (8
- * bytes per query row of every (batch, head) plus 4 d bytes per 128 keys of every (batch, KV head),
- * or more than 512 query heads with per-head scales) is rejected with INTATTN_ERR_UNSUPPORTED and a
+ * bytes per query row of every (batch, head) plus 4 d bytes per 128 keys of every (batch, KV head);
+ * not asked of kernels that use none of it: variant 3, all scores in registers), or one of
+ * more than 512 query heads with per-head scales, is rejected with INTATTN_ERR_UNSUPPORTED and a
  * message naming both sizes.  The array is shared by every context on the GPU and keeps the last
  * call's contents (everything a call reads it has written first): calls that overlap in time on one
  * GPU race -- order them on one stream.

@@ -563,7 +563,7 @@ Choice choose_kernels(const intattn_ctx *ctx, const intattn_args *a, const RunMo
 {
     const int Lk = a->Lkv ? a->Lkv : a->L;
     Choice ch = {fwd_choose_variant(ctx->variant, a->B, a->Hq, a->L, Lk, a->d, a->causal), false, {0, 0}, false};
-    if (ch.variant == 5 && ctx->lut_bits > 5) ch.variant = 4; // the pipelined sweep C holds 32-entry tables; same tiling otherwise
+    if (ch.variant == 5 && ctx->lut_bits > 5) ch.variant = 4; // sweep C's own kernel holds 32-entry tables; same tiling otherwise
     const bool automatic = ctx->variant == 0 || ctx->variant == 9 || ctx->variant == 10;
     // Groups (scale modes 2 and 3): the keys split over the waves of a workgroup win up to 256 workgroups of 128 rows, up to
     // 512 with key groups and under the mask at d = 64 (1024 tokens, 32 / 8 heads, d 128: 64 against 112 us with key groups,

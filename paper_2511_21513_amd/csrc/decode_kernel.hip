@@ -533,7 +533,7 @@ __global__ __launch_bounds__(NT, 4) void decode_fused_kernel(const FwdParams p)
     lds_barrier();
     if (tid < R) atomicMax(state + 32 + tid, bias_i32(row_max[tid]));
 
-    // V of the first two sub-tiles is requested before the meetings: it travels while the group gathers
+    // V of the first two sub-tiles is requested between the two meetings: it travels while the table indices are formed
     struct Sub {
         v4i v[NBLK]; // block j: key row j * RPB + lane / CPR of the sub-tile, chunk lane % CPR
     };

@@ -1,5 +1,5 @@
-// Host side of the forward launches: the kernel variants, the small kernel that sums V over chunks
-// of keys, and the order of the launches of one forward.  The forward kernel template itself is in
+// Host side of the forward launches: the kernel variants, the small kernels ahead of and behind split
+// keys, and the order of the launches of one forward.  The forward kernel template itself is in
 // fwd_kernel_impl.h and is instantiated in fwd_single.hip (all three sweeps in one launch) and
 // fwd_split.hip (sweeps A+B, and sweep C, as launches of their own).
 #include <hip/hip_runtime.h>
@@ -142,12 +142,13 @@ bool fwd_variant_known(int variant) { return variant == 0 || (variant >= 1 && va
 // sweep C also writes and reads the partial accumulators of each range; 24 us for five launches.  The single launches are
 // bound by their longest chain of tiles or, once the chip is full, by a cost per 32 x 32 block (variant 3) or by rounds of
 // 380 workgroups (variant 1).  It is made to rank the two and errs where a launch is a little over a whole number of rounds
-// (509 x 7001, 32 / 8 heads, d 128: 544 workgroups of variant 3, two rounds of 512; it says 161 us, measured 247), for the
+// (509 x 7001, 32 / 8 heads, d 128: 544 workgroups of variant 3, two rounds of 512; it says 161 us, measured 238), for the
 // single launch then, as the margins below do.  KV heads do not enter: 32 / 32 and 32 / 8 heads
 // measure within 6 % of each other (one pair of 25: 11 %).  Timed on 286 shapes of 1 to 128 heads, 40
-// to 8192 rows and 600 to 16384 keys: the 105 that it splits take 0.23 to 0.94 of the time of the better of variants 1 and 3
-// (509 x 7001: 247 -> 120 us; 128 x 12000, 8 heads, d 64: 128 -> 47; 3000 square, 12 heads, d 128: 94.9 -> 88.8); what else a
-// split would serve was not timed.  Small problems lose by it (1024 square, 16 heads, d 128: 22 us unsplit, 49 split).
+// to 8192 rows and 600 to 16384 keys before the fma map: the 105 that it splits took 0.23 to 0.94 of the time of the better of
+// variants 1 and 3.  With the fma map, which made all sides faster: 509 x 7001 219 -> 111 us; 128 x 12000, 8 heads, d 64, 103 -> 37;
+// 3000 square, 12 heads, d 128, 93 -> 79.  What else a split would serve was not timed.  Small problems lose by it (1024 square, 16 heads,
+// d 128: 21 us unsplit, 49 split before the fma map).
 KeySplit fwd_key_split(int variant, int B, int Hq, int L, int Lk, int d, int causal)
 {
     const int row_lo = causal ? Lk - L : 0, tiles = (Lk + 127) / 128;

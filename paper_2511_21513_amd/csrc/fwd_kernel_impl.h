@@ -47,7 +47,7 @@ constexpr int NT = WAVES * 64;
 // The kernel for one work item with the index scheme M as a compile-time constant; the LDS arrays are the kernel's (see
 // there), ksp is the number of this workgroup's range of key tiles out of n_split.  A function rather than a lambda in the
 // kernel: as a lambda it cost the instantiations with sweep C 13 (d = 64) to 28 (d = 128) registers and 5 to 9 % more
-// vector instructions (135 and 217 registers as it is, causal, one launch).
+// vector instructions (139 and 221 registers as it is, causal, one launch, fma map).
 template <int D, int RB, int KT, bool CAUSAL, int M, int PH>
 __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi, const HeadParams &hp, const int ksp, const int n_split,
                                          int8_t *Ks0, int8_t *Ks1, int8_t *Vs0, int8_t *Vs1, uint32_t *PT, uint32_t *lut_lds)

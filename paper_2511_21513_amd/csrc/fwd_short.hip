@@ -7,8 +7,8 @@
 // V of the head are staged in LDS once; a barrier when they are, and one when K is read where its room is used again.  What bounds it is vector
 // instructions per score: against the tiled kernel it saves two of three score computations and one of two index
 // computations, and pads rows and keys to 32 only (197 x 197: 224 x 224 scores instead of 256 x 256).  Measured against
-// them as they were: 128 x 12 heads of 197 x 197 75.1 -> 47.7 us, 256 x 32 heads of 64 x 64 98 -> 46, 128 x 12 heads of
-// 256 x 256 under the mask 78 -> 49.  Workgroups of up to eight waves, a whole head each, took 60.5 us on the first: 148
+// them as they were: 128 x 12 heads of 197 x 197 75.1 -> 46.2 us, 256 x 32 heads of 64 x 64 98 -> 47, 128 x 12 heads of
+// 256 x 256 under the mask 78 -> 46.7.  Workgroups of up to eight waves, a whole head each, took 60.5 us on the first: 148
 // to 167 registers (five to eight sub-tiles; 103 up to four) leave a compute unit 12 waves, so only one workgroup of
 // seven.
 //

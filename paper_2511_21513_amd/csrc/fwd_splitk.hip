@@ -31,9 +31,10 @@ namespace {
 constexpr int WAVES = 4;
 constexpr int NT = WAVES * 64;
 
-// Waves a SIMD (and workgroups a compute unit): at d = 64 three, i.e. 168 registers (132 to 154 in use).  With four, 17 spill
+// Waves a SIMD (and workgroups a compute unit): at d = 64 three, i.e. 168 registers (143 to 150 in use).  With four, 17 spill
 // inside the loops (2048 rows, 16 heads: 24.3 -> 31.8 us; 8 x 12 heads of 197 rows 8.2 -> 11.0); with four and the start values
-// added by the vector ALU instead of held for the MFMAs none does, at the same speed as three.  Key groups hold yet more.
+// added by the vector ALU instead of held for the MFMAs none does, at the same speed as three.  Key groups hold yet
+// more (156 at d = 64, under the mask).
 constexpr int splitk_waves(int d, int mode) { return d != 64 || mode == IDX_KGROUP ? 2 : 3; }
 
 template <int D, bool CAUSAL, int MODE>

@@ -70,7 +70,7 @@ def test_forms_that_a_rule_does_not_take(ia):
     assert choice(ia, *chunk, scale_mode=3, dynamic=True, q_block=64, k_block=64)[0] == 3
     assert choice(ia, *short, scale_mode=1)[0] == SHORT
     assert choice(ia, *short, dynamic=True)[0] == 1  # device-resident scales
-    assert choice(ia, *short, c_int=2**25 + 1)[0] == 1  # no integer index map
+    assert choice(ia, *short, c_int=2**25 + 1)[0] == 1  # a threshold past 2^24
     wide = binding.IntAttn(device=-1, lut_bits=6)
     assert choice(wide, *chunk)[0] == 3 and choice(wide, *short)[0] == 1
     for variant in (1, 2, 3, 4, 5):

@@ -21,8 +21,7 @@ def torch_mod():
 
 
 # kernel variants: 0 = automatic choice; 1, 2 = one launch (32 / 64 query rows per wave); 4 = two
-# launches (sweeps A+B, then sweep C) with the phase-ordered kernels; 5 = the software-pipelined sweep C
-# with its short-table path; 9 = the split-key kernels (few query rows against many keys) wherever
+# launches (sweeps A+B, then sweep C) with the phase-ordered kernels; 5 = sweep C's own kernel; 9 = the split-key kernels (few query rows against many keys) wherever
 # (Hq / Hkv) * L <= 31, else as 0
 @pytest.fixture(scope="module", params=[0, 1, 2, 3, 4, 5, 9], ids=lambda v: f"variant{v}")
 def ia(torch_mod, request):
@@ -242,7 +241,7 @@ def test_quantonly_comparator_close_to_fp64(torch_mod, ia, shape):
 
 
 def test_stages_compose_to_the_forward(torch_mod, oracle):
-    """Stage 1 (column sums, sweeps A+B) followed by stage 2 (sweep C) gives the bytes of the
+    """Stage 1 (sweeps A+B) followed by stage 2 (sweep C) gives the bytes of the
     one-call forward; a single-launch variant refuses to be cut."""
     from paper_2511_21513_amd import binding
 
@@ -409,8 +408,7 @@ def test_dynamic_forward_mixed_schemes(torch_mod, ia, oracle):
 @pytest.mark.gpu
 @pytest.mark.parametrize("d,causal", [(64, True), (128, True), (128, False)], ids=lambda v: str(v))
 def test_host_scales_mixed_schemes_in_sweep_c(torch_mod, oracle, d, causal):
-    """Per-head host scales where most heads have top-byte index constants and some do not (thresholds below 62
-    and of tens of thousands): the two-launch path gives its second launch a table with each head's own scheme;
+    """Per-head host scales with thresholds below 62, of hundreds and of tens of thousands in one call of the two-launch path:
     every tap and the output equal the oracle's, also on a second call and after the scales change."""
     from paper_2511_21513_amd import binding
 
@@ -924,7 +922,7 @@ KEY_GROUP_SHAPES = [
     (1, 4, 4, 300, 300, 64, False, 300, 64, True),   # one query scale per head, 64-key blocks, no mask
     (1, 2, 2, 260, 260, 128, True, 64, 7, False),    # key blocks that straddle sub-tiles and tiles
     (2, 2, 1, 40, 333, 64, True, 8, 128, True),      # a chunk of queries against a longer key sequence
-    (1, 2, 1, 600, 600, 128, True, 600, 96, False),  # more than 512 keys: column sums from the small kernel
+    (1, 2, 1, 600, 600, 128, True, 600, 96, False),  # more than 512 keys
     (1, 1, 1, 130, 130, 64, False, 5, 1, True),
 ]
 
@@ -1196,16 +1194,15 @@ def test_parameter_cache_follows_the_scales(torch_mod, oracle):
     ia.close()
 
 
-# ---------------------------------------------------------------- short-table path of the pipelined sweep C
+# ---------------------------------------------------------------- sweep C on rows with large and small sums
 @pytest.mark.parametrize("case", [
     # L, d, causal, spread, per_head: flat logits make the row sums large, so that only the first eight table
-    # entries of a row can give a nonzero probability; the thresholds reach every index-map scheme
+    # entries of a row can give a nonzero probability
     (1500, 128, True, 0.6, False), (1500, 64, False, 0.6, True), (2048, 64, True, 1.0, False),
     (900, 128, True, 0.35, False), (700, 128, False, 2.0, False),
 ], ids=lambda c: "L{}d{}c{}s{}ph{}".format(c[0], c[1], int(c[2]), c[3], int(c[4])))
 def test_short_table_path_bit_exact(torch_mod, oracle, case):
-    """Rows whose sum of E_hat exceeds 510 * LUT_hat[8] (waves of such rows look probabilities up with a
-    byte permute and skip the offset of 128), rows below it, and waves and workgroups that mix both:
+    """Rows whose sum of E_hat exceeds 510 * LUT_hat[8], rows below it, and waves and workgroups that mix both:
     every tap and every output byte against the oracle, on diagonal (masked) and ragged tiles too."""
     from paper_2511_21513_amd import binding
 
@@ -1223,8 +1220,8 @@ def test_short_table_path_bit_exact(torch_mod, oracle, case):
 
 
 def test_short_table_path_on_the_headline_distribution(torch_mod, oracle):
-    """Four query heads of the long-context GQA workload at a ragged length: small threshold (the
-    24-bit index maps), late rows on the short-table path, early rows on the general one."""
+    """Four query heads of the long-context GQA workload at a ragged length: small threshold, late rows with large sums,
+    early rows with small ones."""
     from paper_2511_21513_amd import binding
 
     p = inputs.make_problem("c4_gqa_prefill_8k", Hq=4, Hkv=1, L=5000)
