@@ -468,6 +468,7 @@ __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi,
             const int row = qw0 + 32 * rb + n;
             sum[rb] = (row >= rlo && row < rhi) ? (uint32_t)p.ws_row_sum[(int64_t)bh * LQ + (row - rlo)] : 0u;
         }
+        __syncthreads(); // LUT_hat, which the first wave put into LDS, is visible (with sweeps ahead, their barriers do that)
     }
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {

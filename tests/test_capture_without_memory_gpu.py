@@ -59,3 +59,13 @@ def test_first_call(torch_mod, oracle, shape):  # noqa: F811
     if kernel in (1, 2):
         assert torch.cuda.mem_get_info()[0] == free
     ia.close()
+
+    ia, args, keep = fresh()  # a reservation has room for whichever kernels serve the call
+    ia.reserve(args)
+    free = torch.cuda.mem_get_info()[0]
+    out.fill_(55)
+    ia.forward_args(args, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.cuda.mem_get_info()[0] == free
+    assert int((out.cpu().numpy() != want).sum()) == 0
+    ia.close()
