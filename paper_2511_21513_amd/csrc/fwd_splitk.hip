@@ -37,7 +37,14 @@ constexpr int NT = WAVES * 64;
 // more (156 at d = 64, under the mask).
 constexpr int splitk_waves(int d, int mode) { return d != 64 || mode == IDX_KGROUP ? 2 : 3; }
 
-template <int D, bool CAUSAL, int MODE>
+// How key groups lie against the 32-key sub-tiles: a sub-tile may meet several blocks of keys (constants for each logit), or lies in
+// one, whose constants each wave forms, or the workgroup keeps in a table.  An instantiation each: in one kernel
+// that decided at run time the first took 5 % longer (24 heads of 700 under the mask, blocks of 7 keys: 92.2 us against 87.1 at d 64,
+// 101.7 against 96.7 at d 128; 87.7 and 97.7 before there was a table) and the second 4 % (200 rows of 4096 keys in blocks of
+// 32, 16 heads, d 64: 96.8 against 92.5).
+enum KeyBlocks { STRADDLING = 0, WHOLE = 1, WHOLE_TABLE = 2 };
+
+template <int D, bool CAUSAL, int MODE, int BLOCKS = STRADDLING>
 __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(const FwdParams p)
 {
     constexpr int KB = D / 32;  // 32-wide blocks of the head dimension
@@ -55,7 +62,7 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
     __shared__ int32_t red[2][WAVES][32];                               // per-wave row max / row sum
     __shared__ double red_m[MODE == IDX_KGROUP ? WAVES : 1][32];        // per-wave maximum of the dequantized logits
     __shared__ uint32_t lut_lds[16];
-    extern __shared__ __attribute__((aligned(16))) uint32_t PT[]; // [idx][row], NIDX * 32 words; then, with p.kg_table, 8 bytes [key block][row]
+    extern __shared__ __attribute__((aligned(16))) uint32_t PT[]; // [idx][row], NIDX * 32 words; then, under WHOLE_TABLE, 8 bytes [key block][row]
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 31, h = lane >> 5;
     HeadParams hp = p.hp0;
@@ -82,7 +89,7 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
     // constants of its row for each key block (once per 32-key sub-tile where a sub-tile lies in one block).
     constexpr bool KG = M == IDX_KGROUP;
     const float *skp = KG ? p.sk_blocks + (int64_t)(b * p.Hkv + kvh) * p.n_kblk : nullptr;
-    const bool kg_blocks = KG && (p.k_block % 32) == 0; // uniform
+    constexpr bool kg_blocks = KG && BLOCKS != STRADDLING, kg_table = KG && BLOCKS == WHOLE_TABLE;
     auto row_hp = [&](int r) __attribute__((always_inline)) {
         const int lr = (r >= p.row_lo && r < p.row_lo + p.L) ? r - p.row_lo : 0;
         return p.row_table[(int64_t)bh * p.n_rowblk + lr / p.q_block];
@@ -125,7 +132,6 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
     // Key groups: the constants of each row for each block of keys, formed once by the workgroup instead of by every wave
     // for every sub-tile and sweep (three double-precision divisions a lane): alpha^(g) for sweep A, then, in the same place,
     // m^(g) and c_int^(g).  (1024 tokens, 32 / 8 heads, d 128, 128-row and 64-key groups: 61 -> 54 us.)
-    const bool kg_table = KG && p.kg_table != 0; // uniform
     double *const kt_alpha = (double *)(PT + NIDX * 32);
     v2i *const kt = (v2i *)(PT + NIDX * 32);
     auto kg_blk = [&](int j) __attribute__((always_inline)) { return quotient(j, p.by_k_subtiles); }; // of sub-tile j
@@ -133,11 +139,9 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
         const int n_entries = (kg_blk(nsub - 1) + 1) * 32;
         for (int e = tid; e < n_entries; e += NT) f(e);
     };
-    if constexpr (KG) {
-        if (kg_table) {
-            each_group([&](int e) __attribute__((always_inline)) { kt_alpha[e] = (scale_q(q0 + (e & 31)) * (double)skp[e >> 5]) / p.sqrt_d; });
-            __syncthreads();
-        }
+    if constexpr (kg_table) {
+        each_group([&](int e) __attribute__((always_inline)) { kt_alpha[e] = (scale_q(q0 + (e & 31)) * (double)skp[e >> 5]) / p.sqrt_d; });
+        __syncthreads();
     }
 
     // K fragments of sub-tile j straight from global memory: key row 32 j + n, bytes [32 kb + 16 h, +16)
@@ -188,7 +192,7 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
         const v16i s = scores(kf);
         if constexpr (KG) {
             const bool full = sub_is_full(j);
-            if (kg_blocks) {
+            if constexpr (kg_blocks) {
                 int lmax = INT32_MIN; // no score is INT32_MIN
 #pragma unroll
                 for (int i = 0; i < 16; ++i)
@@ -242,9 +246,6 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
     // uniform for the wave.
     RowIndex32 ri32;
     bool single = false;
-    auto pick_map = [&](int c_int) __attribute__((always_inline)) {
-        single = __all(ri32.init(c_int, ri.mx, top));
-    };
     // Key groups: the constants of the lane's row for the key block of `key`, as in the tiled kernel: c_int^(g) =
     // round(c / alpha^(g)) capped at 2^30, m^(g) = round(M / alpha^(g)) clamped to [-2^22, 2^30 + 2^22], which changes no
     // result (comparisons written so that a NaN from an unusable scale lands on a bound).
@@ -257,29 +258,30 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
         md = md > -4194304.0 ? md : -4194304.0;
         return v2i{(int)md, (int)cd};
     };
-    if constexpr (KG) {
-        if (kg_table) {
-            each_group([&](int e) __attribute__((always_inline)) { // (a thread meets the entries it wrote)
-                double M_row = red_m[0][e & 31];
+    if constexpr (kg_table) {
+        each_group([&](int e) __attribute__((always_inline)) { // (a thread meets the entries it wrote)
+            double M_row = red_m[0][e & 31];
 #pragma unroll
-                for (int w = 1; w < WAVES; ++w) {
-                    const double o = red_m[w][e & 31];
-                    M_row = o > M_row ? o : M_row;
-                }
-                kt[e] = kg_group(kt_alpha[e], M_row);
-            });
-            __syncthreads();
-        }
+            for (int w = 1; w < WAVES; ++w) {
+                const double o = red_m[w][e & 31];
+                M_row = o > M_row ? o : M_row;
+            }
+            kt[e] = kg_group(kt_alpha[e], M_row);
+        });
+        __syncthreads();
     }
+    auto set_double = [&](v2i g) __attribute__((always_inline)) {
+        ri.mx = g[0];
+        ri.bound = g[0] - g[1];
+        const uint64_t bits = (uint64_t)__double_as_longlong((double)top / (double)g[1]) + 1ull; // the double after top / c_int
+        ri.negr = __longlong_as_double((long long)(bits ^ 0x8000000000000000ull));
+    };
     auto kg_index = [&](int key) __attribute__((always_inline)) {
         const v2i g = kg_table ? kt[kg_blk(key >> 5) * 32 + n] : kg_group(kg_alpha(key), Mreal);
         ri.mx = g[0];
         ri.bound = g[0] - g[1];
-        pick_map(g[1]);
-        if (!single) {
-            const uint64_t bits = (uint64_t)__double_as_longlong((double)top / (double)g[1]) + 1ull; // the double after top / c_int
-            ri.negr = __longlong_as_double((long long)(bits ^ 0x8000000000000000ull));
-        }
+        single = __all(ri32.init(g[1], g[0], top));
+        if (!single) set_double(g);
     };
     // table places of the sixteen scores of sub-tile j (in place).  Hidden keys (masked: there may be some) take the last
     // table entry, which is 0; with key groups they and logits above their block's image of the maximum are
@@ -291,12 +293,30 @@ __global__ __launch_bounds__(NT, splitk_waves(D, MODE)) void fwd_splitk_kernel(c
             const int lim = last - 32 * j - 4 * h;
 #pragma unroll
             for (int i = 0; i < 16; ++i) s[i] = (int)si.index(!MASKED || acc_key(i, 0) <= lim ? s[i] : si.hidden());
-        } else if (!kg_blocks) {
+        } else if constexpr (!kg_blocks) {
+            // Four logits at a time, whose divisions do not depend on each other, and one choice of map for them.  (One at a time: 87.1 us
+            // for 75.7 in the first case above, and 200 rows of 4096 keys, blocks of 48, 16 heads, d 64, where a wave has a SIMD to
+            // itself, 467 to 489 with the order that the compiler found, for 324.)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                kg_index(32 * j + acc_key(i, h));
-                const int sc = min(max(s[i], ri.bound), ri.mx);
-                s[i] = (int)(single ? ri32(sc) : ri(sc));
+            for (int i = 0; i < 16; i += 4) {
+                v2i g[4];
+                RowIndex32 m32[4];
+                bool fits = true;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    g[r] = kg_group(kg_alpha(32 * j + acc_key(i + r, h)), Mreal);
+                    fits = m32[r].init(g[r][1], g[r][0], top) && fits;
+                }
+                if (__all(fits)) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) s[i + r] = (int)m32[r](min(max(s[i + r], g[r][0] - g[r][1]), g[r][0]));
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        set_double(g[r]);
+                        s[i + r] = (int)ri(min(max(s[i + r], ri.bound), ri.mx));
+                    }
+                }
             }
         } else {
             kg_index(32 * j);
@@ -474,23 +494,23 @@ int launch_mode(const FwdParams &p_in, int idx_mode, hipStream_t st)
     const int64_t n_wg = fwd_map_work(p);
     p.map.fold = fold_slots(n_wg, CAUSAL, splitk_waves(D, idx_mode));
     const dim3 grid((unsigned)n_wg), block(NT);
-    unsigned sh = (unsigned)((p.top < 32 ? 32 : 64) * 32 * sizeof(uint32_t)); // the per-row probability table
-    p.kg_table = 0;
-    if (idx_mode == IDX_KGROUP && p.k_block % 32 == 0) {
-        p.by_k_subtiles = fast_div((uint32_t)(p.k_block / 32));
-        // up to 64 blocks of keys, 16 KiB, which leave two workgroups a compute unit at d = 128 (51 KiB without)
-        p.kg_table = p.n_kblk <= 64 ? 1 : 0;
-        if (p.kg_table) sh += (unsigned)p.n_kblk * 32u * 8u;
-    }
+    const unsigned sh = (unsigned)((p.top < 32 ? 32 : 64) * 32 * sizeof(uint32_t)); // the per-row probability table
     if (idx_mode == IDX_FMA)
         hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_FMA>), grid, block, sh, st, p);
     else if (idx_mode == IDX_DEVICE)
         hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_DEVICE>), grid, block, sh, st, p);
     else if (idx_mode == IDX_ROW64)
         hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_ROW64>), grid, block, sh, st, p);
-    else if (idx_mode == IDX_KGROUP)
-        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_KGROUP>), grid, block, sh, st, p);
-    else if (idx_mode == IDX_FP64)
+    else if (idx_mode == IDX_KGROUP && p.k_block % 32 != 0)
+        hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_KGROUP, STRADDLING>), grid, block, sh, st, p);
+    else if (idx_mode == IDX_KGROUP) {
+        p.by_k_subtiles = fast_div((uint32_t)(p.k_block / 32));
+        // a table of up to 64 blocks of keys, 16 KiB, which leave two workgroups a compute unit at d = 128 (51 KiB without)
+        if (p.n_kblk <= 64)
+            hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_KGROUP, WHOLE_TABLE>), grid, block, sh + (unsigned)p.n_kblk * 32u * 8u, st, p);
+        else
+            hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_KGROUP, WHOLE>), grid, block, sh, st, p);
+    } else if (idx_mode == IDX_FP64)
         hipLaunchKernelGGL((fwd_splitk_kernel<D, CAUSAL, IDX_FP64>), grid, block, sh, st, p);
     else
         return (int)hipErrorInvalidValue;

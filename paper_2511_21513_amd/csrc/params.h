@@ -76,7 +76,6 @@ struct FwdParams {
     const float *sq_rows, *sk_blocks;
     int32_t k_block, n_kblk;
     FastDiv by_k_subtiles;      // by the 32-key sub-tiles of a block of keys (k_block a multiple of 32)
-    int32_t kg_table;           // fwd_splitk.hip: a workgroup keeps the constants of its rows for every block of keys in LDS
     double clip, sqrt_d;
     const int32_t *head_status;
     HeadParams hp0;             // the single parameter set when hp_table == nullptr
