@@ -112,15 +112,25 @@ __device__ __forceinline__ void fwd_body(const FwdParams &p, const WorkItem &wi,
         return (sq_row[rb] * (double)skp[min(key, L - 1) / p.k_block]) / p.sqrt_d;
     };
 
-    // Q fragments: row block rb, row qw0 + 32 rb + n, bytes [32 kb + 16 h, +16).
+    // Q fragments: row block rb, row qw0 + 32 rb + n, bytes [32 kb + 16 h, +16); zeros for rows outside the problem.  With all sweeps and
+    // two row blocks a wave, where registers run past 256, lanes without a row load the first one and select: around a branch the
+    // compiler put a copy of a register that lives on (in the kernel of both index maps, d = 128) where those lanes were still
+    // switched off.
     v4i qf[RB][KB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
         const int row = qw0 + 32 * rb + n;
+        const bool row_ok = row >= rlo && row < rhi;
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) {
-            qf[rb][kb] = v4i{0, 0, 0, 0};
-            if (row >= rlo && row < rhi) qf[rb][kb] = *(const v4i *)(Qp + (int64_t)(row - rlo) * p.qs[2] + kb * 32 + h * 16);
+            if constexpr (RB == 2 && PH == 0) {
+                const v4i x = *(const v4i *)(Qp + (int64_t)(row_ok ? row - rlo : 0) * p.qs[2] + kb * 32 + h * 16);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) qf[rb][kb][i] = row_ok ? x[i] : 0;
+            } else {
+                qf[rb][kb] = v4i{0, 0, 0, 0};
+                if (row_ok) qf[rb][kb] = *(const v4i *)(Qp + (int64_t)(row - rlo) * p.qs[2] + kb * 32 + h * 16);
+            }
         }
     }
 

@@ -51,3 +51,31 @@ def test_bit_exact(torch_mod, oracle, variant, lq, lk, causal):  # noqa: F811
     torch.cuda.synchronize()
     assert int((got.cpu().numpy() != want).sum()) == 0
     ia.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("variant, lq, lk, causal", [(2, 12, 59, False), (2, 47, 3, False), (2, 150, 150, False), (2, 300, 333, True), (1, 47, 59, False), (4, 47, 159, False)])
+@pytest.mark.parametrize("which", [[None], [5203], [None, 26, 18295], [2, 764260, 2980995]], ids=str)
+def test_rows_that_fill_a_wave_in_part_at_head_dimension_128(torch_mod, oracle, which, variant, lq, lk, causal):  # noqa: F811
+    """Waves of which some rows lie outside the problem, thresholds of both maps, scales on the host and in device memory."""
+    from paper_2511_21513_amd import binding
+
+    torch = torch_mod
+    H, d = 12, 128
+    rng = np.random.default_rng(lk)
+    c_ints = [without_factor(31) if c is None else c for c in which]
+    q, k, v = (rng.integers(-128, 128, (1, H, n, d), dtype=np.int8) for n in (lq, lk, lk))
+    q[:, :, 1::3] //= 16
+    s_k = np.full(H, 0.0003, dtype=np.float32)
+    s_q = np.array([6.6 * d**0.5 / (0.0003 * c_ints[h % len(c_ints)]) for h in range(H)], dtype=np.float32)
+    s_v, s_o = np.full(H, 0.02, dtype=np.float32), np.full(H, 0.002, dtype=np.float32)
+    want = oracle.forward(q, k, v, s_q, s_k, s_v, s_o, causal=causal, per_head=True, threads=16)["out"]
+    ia = binding.IntAttn(device=0, variant=variant)
+    tq, tk, tv, *sc = (torch.from_numpy(x).cuda() for x in (q, k, v, s_q, s_k, s_v, s_o))
+    for device_scales in (False, True):
+        out = torch.full_like(tq, 99)
+        args, keep = ia.make_args(tq, tk, tv, out, *(sc if device_scales else (s_q, s_k, s_v, s_o)), causal=causal, per_head=True, device_scales=device_scales)
+        (ia.forward_dynamic_args if device_scales else ia.forward_args)(args, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert int((out.cpu().numpy() != want).sum()) == 0, device_scales
+    ia.close()
